@@ -277,17 +277,17 @@ groot_status groot_rows_over_degree(const groot_plan *plan, const float *Z_dev, 
  * the loss at Z,
  *     dWn = (A_hat X)^T dZ,   dWs = X^T dZ,
  * both in one pass over X and dZ with the aggregation kept on chip (A_hat X is
- * never written to memory); fp32 accuracy per product from bf16 piece products
- * as in the forward layer ("sage_pieces"), fp32 sums over the rows that one
- * wavefront sweeps (N / 1024 of them on an MI355X), fp64 across wavefronts, in
- * a fixed order: the same bits on every run.  The bias gradient is the column
+ * never written to memory); products and sums in fp32 on the matrix cores over
+ * the rows that one wavefront sweeps (N / 2048 of them on an MI355X, at most 512
+ * between two fp32 additions unless F_in = F_out = 64), fp64 across wavefronts,
+ * in a fixed order: the same bits on every run.  The bias gradient is the column
  * sum of dZ and is left to the caller.
  * X_dev (device): row-major [N, F_in] fp32, F_in = 32 or 64; dZ_dev (device):
  * row-major [N, F_out] fp32, F_out = 16, 32 or 64 (other widths: pad with zero
  * columns); dWn_dev, dWs_dev (device): row-major [F_in, F_out] fp32, fully
  * overwritten; workspace_dev (device, 16-byte aligned): at least the number of
  * bytes that groot_sage_layer_backward_weights_workspace reports for these
- * widths (2 F_in F_out floats per wavefront of the launch: 32 MiB at 64 x 64
+ * widths (8 F_in F_out floats per CU for F_in = 64, 16 for 32: 32 MiB at 64 x 64
  * on an MI355X), contents overwritten, owned by the caller.  The plan must be
  * uploaded with max_F >= F_in and have row-uniform weights.  Only enqueues on
  * hip_stream, allocates nothing; one call per plan in flight (the aggregated
@@ -516,7 +516,7 @@ groot_status groot_plan_hd_pieces(const groot_plan *plan, int64_t capacity, int6
  * instructions), "sage_gap" (kernel 0 only: 0..4, the pause between its matrix
  * instructions; all three read at each call of groot_sage_layer_forward),
  * "sage_pieces" (kernel 1 only: 3, default: every fp32 operand of the layer's
- * dense products is cut into three bf16 pieces and six piece products are
+ * dense products, forward and input gradient, is cut into three bf16 pieces and six piece products are
  * kept, fp32 accuracy; 2: two pieces and three products, half the matrix
  * instructions, every product exact to 3 x 2^-18 of its magnitude instead of
  * 2^-23; read at each call),

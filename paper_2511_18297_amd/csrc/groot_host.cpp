@@ -604,6 +604,9 @@ extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
         // the fused layer kernel completes a longer row inside the tile's turn, unoverlapped: 5 slots only when
         // at most one low-degree row in 2000 has 6 entries or more
         d.sage_depth = (n_ld - at_most(5)) * 2000 <= n_ld ? 5 : 6;
+        // the weight-gradient kernel notes such a tile and completes it later, for about the time of one more tile: 5 slots
+        // up to one row in 300 (five tiles in a hundred)
+        d.wgrad_depth = (n_ld - at_most(5)) * 300 <= n_ld ? 5 : 6;
         const int64_t first_mid = at_most(ch.depth);
         d.n_mid_rows = ch.pipelined ? n_ld - first_mid : 0;
         if (d.n_mid_rows &&
@@ -877,8 +880,7 @@ extern "C" groot_status groot_sage_layer_backward_weights(const groot_plan *plan
     int err = 0;
     if (hd.n_chunks) err = launch_hd(hd, X_dev, hd.hd_agg, F_in, hip_stream);
     if (!err && hd.n_split_rows) err = launch_hd_finish(hd, hd.hd_agg, F_in, hip_stream);
-    if (!err) err = launch_sage_wgrad(plan->dev, X_dev, dZ_dev, dWn_dev, dWs_dev, F_in, F_out, tuning().sage_pieces.load(),
-                                      workspace_dev, hip_stream);
+    if (!err) err = launch_sage_wgrad(plan->dev, X_dev, dZ_dev, dWn_dev, dWs_dev, F_in, F_out, workspace_dev, hip_stream);
     if (err) return fail(GROOT_EHIP, std::string(who) + "launch failed: " + hip_error_text(err));
     return GROOT_OK;
 }
@@ -1329,6 +1331,7 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             d.ld_pipelined = ch.pipelined;
             d.pipe_depth = ch.depth;
             d.sage_depth = (n_ld - at_most(5)) * 2000 <= n_ld ? 5 : 6;
+            d.wgrad_depth = (n_ld - at_most(5)) * 300 <= n_ld ? 5 : 6;
             const int64_t first_mid = at_most(ch.depth);
             d.n_mid_rows = ch.pipelined ? n_ld - first_mid : 0;
             if (d.n_mid_rows) {             // the tail of the degree-sorted list, which is on the device already

@@ -91,6 +91,7 @@ struct DevicePlan {
                                     // count once a part's plan reads the global matrix in place
     int ld_pipelined = 0;           // pipelined LD kernel: 0 never, 1 for F = 64 and 128, 2 for F = 32 as well
     int sage_depth = 6;             // gather slots per row of the fused layer kernel: 5 when rows of 6 entries are rare, else 6
+    int wgrad_depth = 6;            // the same for the weight-gradient kernel
     int pipe_depth = 6;             // slots per row of the pipelined LD kernel: kPipeMinDepth .. kPipeMaxDepth
     int32_t *mid_rows = nullptr;    // low-degree rows with more than pipe_depth entries (the pipelined kernel
     int64_t n_mid_rows = 0;         // masks them; a row-list kernel computes them), ordered by (length, id)
@@ -128,7 +129,7 @@ int launch_sage_pipe(const DevicePlan &dp, const float *X, float *H, const float
 // or 64, dZ of width F_out = 16, 32 or 64, row-uniform weights; workspace of sage_wgrad_workspace_bytes bytes (0: no device).
 size_t sage_wgrad_workspace_bytes(int32_t F_in, int32_t F_out);
 int launch_sage_wgrad(const DevicePlan &dp, const float *X, const float *dZ, float *dWn, float *dWs, int32_t F_in,
-                      int32_t F_out, int pieces, void *workspace, void *stream);
+                      int32_t F_out, void *workspace, void *stream);
 int launch_rows_over_degree(const DevicePlan &dp, const float *Z, float *out, int32_t F, void *stream);   // out may be Z
 // Schedule of the high-degree rows built on the device (groot_hd_sched_device.hip): the pieces in execution order,
 // once with rows named by id and once by their place in the list of high-degree rows, and the split rows likewise.

@@ -1,6 +1,5 @@
 // Weight gradients of the fused GraphSAGE-mean layer for gfx950:
 //     dWn = (A_hat X)^T dZ,   dWs = X^T dZ,   X [N, FI], dZ [N, FO], dWn and dWs [FI, FO], FI = 32 or 64, FO = 16, 32 or 64
-//     (described below for FI = FO = F = 64),
 // for the layer Z = (A_hat X) Wn + X Ws + b with dZ the gradient of the loss at Z (Section "GNN and Edge
 // Re-growth After Partition": the model is trained).  Two products with N as the contraction length: as plain
 // matrix products over [N, 64] operands they take 58 ms each on 134 M rows with the vendor library, and the
@@ -8,21 +7,28 @@
 //
 // The aggregation is the fused layer kernel's (groot_sage_pipe.hip: a persistent workgroup per CU, every
 // wavefront walks its own 16-row tiles and keeps the next tile's gathers in flight; slot table in LDS, a row of
-// zeros for dead slots, a plain path for the tiles that hold a row the slots do not serve).  For every tile the
-// wavefront has [A_hat X | X] (16 x 2F) and dZ (16 x F) in registers and adds [A_hat X | X]^T dZ (2F x F) to
-// accumulators that it keeps for its whole sweep: 8 x 4 blocks of v_mfma_f32_16x16x16_bf16 at F = 64, the
-// tile's 16 rows being the contraction length of one instruction.  fp32 accuracy as in the forward layer:
-// every operand is cut into three bf16 pieces and six piece products are kept (two pieces and three products
-// with the library's sage_pieces knob at 2).
+// zeros for dead slots).  For every tile the wavefront adds [A_hat X | X]^T dZ (2 FI x FO) to accumulators that it
+// keeps for its whole sweep.
 //
-// The matrix instruction wants, per lane, four consecutive contraction indices of one column of an operand, and
-// here the contraction runs over rows, of which a lane holds one per sweep.  So the tile goes through LDS
-// transposed, [column][row], and the rows are numbered so that the ones a lane holds are neighbours: row
-// r = grp * kRpg + g of the tile (sweep grp, lane group g) is contraction index g * kG + grp, for both operands.
-// A lane then writes its kG rows of one column as one 8-byte (F = 32: 4-byte) word, cut into pieces pairwise
-// (the pair of rows of a word's half is what one cut of two values packs).
+// The contraction runs over rows, and v_mfma_f32_16x16x4_f32 (fp32 in and out) wants exactly what the gathers leave
+// in the registers: lane (m = lane % 16, k = lane / 16) holds one value of column m of row k, and at FI = 64 lane l has
+// a float4 of row l / 16 of a sweep, columns 4 (l % 16) .. + 3.  So component j of that float4 is the operand whose
+// column m is feature 4 m + j, and a sweep's 4 rows are the contraction length of one instruction: no transposition,
+// no trip through LDS, and products and sums in fp32 throughout.  dZ is loaded with 16 lanes to a row (FO / 16
+// consecutive floats each), so its component i is the operand whose column n is feature (FO / 16) n + i.  At FI = 32 a
+// sweep has 8 rows (8 lanes to a row): neighbouring rows 2 k and 2 k + 1 sit in the two halves of 16 lanes, which swap
+// half of their float4 (DPP row rotation by 8), giving operands of row 2 k (p = 0) and of row 2 k + 1 (p = 1).
 //
-// Every wavefront ends by writing its 2F x F sums to its own slice of a workspace; a second kernel adds the
+// What bounds it: at 64 x 64 the fp32 matrix instructions, 128 of 32 cycles per 16 rows and SIMD (2.1 M cycles of the
+// 2.8 M that 8.4 M rows take, at the 2.0 GHz that the chip grants dense fp32 matrix work), on the other widths the memory
+// traffic.  The form before this one passed the operands transposed through LDS, cut into three bf16 pieces, six piece
+// products on v_mfma_f32_16x16x16_bf16, whose inner sums truncate: at 8.4 M rows, carry-save multipliers, whole call,
+// 64 x 64 2,030 us and 1.3e-5 from the 64-bit result, now 1,454 us and 1.1e-6; on the Booth shape, 4.3 M rows, 64 x 32:
+// whole call 966 us and 7e-6, now 575 us and 4e-7.
+//
+// An accumulator that took a whole sweep's rows one after the other would round N / 2048 times.  Where LDS has room for a
+// second set of sums (every width but 64 x 64), the accumulators are added to it every kWgFold tiles and cleared.  At
+// the end a workgroup's wavefronts are added in fp64 and written as one slice of a workspace; a second kernel adds the
 // slices in a fixed order in fp64.  No atomics: the result is the same on every run.
 #include <type_traits>
 
@@ -30,16 +36,16 @@
 
 namespace groot {
 
-constexpr int kWgRows = 16;                  // rows per tile: the contraction length of one matrix instruction
-// wavefronts per workgroup (one workgroup per CU): one per SIMD at F = 64, where the accumulators alone take 128
-// registers; two per SIMD at F = 32 (32 accumulator registers), so that one's vector work overlaps the other's matrix work
-constexpr int wg_waves(int FI) { return FI == 64 ? 4 : 8; }
-constexpr int kWgTRow = kWgRows * 2 + 8;     // bytes per column of a transposed bf16 plane (8 B of padding)
+constexpr int kWgRows = 16;                  // rows per tile
+constexpr int kWgFold = 32;                  // tiles between two additions to the sums in LDS (512 rows)
+constexpr int kWgPending = 32;               // tiles with rows that the slots do not serve, noted per wavefront
+// Wavefronts per workgroup (one workgroup per CU), two per SIMD: one's vector work and waits then run beside the other's
+// matrix work.  At 64 x 64 the accumulators take 128 of a wavefront's 256 registers (one wavefront per SIMD with a whole
+// tile of rows in flight: 1,621 us at 8.4 M rows instead of 1,454).
+constexpr int kWgWaves = 8;
+constexpr bool wg_folds(int FI, int FO) { return FI * FO < 64 * 64; }    // 64 x 64: the second set of sums would be 256 KB
 
 typedef float wg_f2 __attribute__((ext_vector_type(2)));
-typedef __bf16 wg_bf2 __attribute__((ext_vector_type(2)));
-typedef short wg_s4 __attribute__((ext_vector_type(4)));
-typedef unsigned int wg_u2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ void wg_wave_sync()
 {
@@ -48,89 +54,105 @@ __device__ __forceinline__ void wg_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// two fp32 values -> their bf16 roundings (nearest even), packed: a in the low half
-__device__ __forceinline__ unsigned wg_pack2(float a, float b)
+// the value of lane (l + 8) % 16 of the same 16 lanes
+__device__ __forceinline__ float wg_other_half(float x)
 {
-    const wg_f2 x = {a, b};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(x, wg_bf2));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
 }
 
-// (a, b) = hi + mid + lo, three packed bf16 pairs; the remainders are exact in fp32
-__device__ __forceinline__ void wg_split3(float a, float b, unsigned (&pc)[3])
+// feature of column m (0..15) of operand component j of a half (A_hat X or X)
+template <int FI>
+__device__ __forceinline__ int wg_feature(int m, int j)
 {
-    pc[0] = wg_pack2(a, b);
-    float ra = a - __builtin_bit_cast(float, pc[0] << 16), rb = b - __builtin_bit_cast(float, pc[0] & 0xffff0000u);
-    pc[1] = wg_pack2(ra, rb);
-    ra -= __builtin_bit_cast(float, pc[1] << 16);
-    rb -= __builtin_bit_cast(float, pc[1] & 0xffff0000u);
-    pc[2] = wg_pack2(ra, rb);
+    return FI == 64 ? 4 * m + j : m < 8 ? 4 * m + j : 4 * (m - 8) + 2 + j;
 }
 
-// The kG rows that one lane holds of columns c0 .. c0 + 3, into the P transposed planes: v[grp][j] is the value of
-// row grp * kRpg + g, column c0 + j; the word of column c0 + j starts at contraction index g * kG.
-template <int kG, int P, int kPlane>
-__device__ __forceinline__ void wg_park(char *planes, int c0, int g, const v4f (&v)[kG])
+// c[mb][nb] += a[mb] b[nb]^T for 4 x 4 blocks, every sum in place.  (Given the builtin, the compiler lets the sums wander between
+// registers, which costs 64 x 64 the last free ones: it spills in the loop, 2,497 us instead of 1,454 at 8.4 M rows.)  The two wait states before the first instruction
+// cover operands that a vector instruction has just written, those after the last one a read of the sums by whatever comes next.
+__device__ __forceinline__ void wg_mfma_4x4(v4f (&c0)[4], v4f (&c1)[4], v4f (&c2)[4], v4f (&c3)[4], const float (&a)[4], const float (&b)[4])
 {
-    static_assert(kG == 4 || kG == 2, "four or two rows per lane");
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        char *p = planes + (c0 + j) * kWgTRow + g * kG * 2;
-        unsigned lo[3], hi[3];
-        wg_split3(v[0][j], v[1][j], lo);
-        if constexpr (kG == 4) {
-            wg_split3(v[2][j], v[3][j], hi);
-#pragma unroll
-            for (int q = 0; q < P; ++q) *(wg_u2 *)(p + q * kPlane) = (wg_u2){lo[q], hi[q]};
-        } else {
-#pragma unroll
-            for (int q = 0; q < P; ++q) *(unsigned *)(p + q * kPlane) = lo[q];
-        }
-    }
+    asm volatile(
+        "s_nop 1\n"
+        "v_mfma_f32_16x16x4_f32 %0, %16, %20, %0\n"
+        "v_mfma_f32_16x16x4_f32 %1, %16, %21, %1\n"
+        "v_mfma_f32_16x16x4_f32 %2, %16, %22, %2\n"
+        "v_mfma_f32_16x16x4_f32 %3, %16, %23, %3\n"
+        "v_mfma_f32_16x16x4_f32 %4, %17, %20, %4\n"
+        "v_mfma_f32_16x16x4_f32 %5, %17, %21, %5\n"
+        "v_mfma_f32_16x16x4_f32 %6, %17, %22, %6\n"
+        "v_mfma_f32_16x16x4_f32 %7, %17, %23, %7\n"
+        "v_mfma_f32_16x16x4_f32 %8, %18, %20, %8\n"
+        "v_mfma_f32_16x16x4_f32 %9, %18, %21, %9\n"
+        "v_mfma_f32_16x16x4_f32 %10, %18, %22, %10\n"
+        "v_mfma_f32_16x16x4_f32 %11, %18, %23, %11\n"
+        "v_mfma_f32_16x16x4_f32 %12, %19, %20, %12\n"
+        "v_mfma_f32_16x16x4_f32 %13, %19, %21, %13\n"
+        "v_mfma_f32_16x16x4_f32 %14, %19, %22, %14\n"
+        "v_mfma_f32_16x16x4_f32 %15, %19, %23, %15\n"
+        "s_nop 15\n"
+        : "+v"(c0[0]), "+v"(c0[1]), "+v"(c0[2]), "+v"(c0[3]), "+v"(c1[0]), "+v"(c1[1]), "+v"(c1[2]), "+v"(c1[3]), "+v"(c2[0]), "+v"(c2[1]), "+v"(c2[2]), "+v"(c2[3]), "+v"(c3[0]), "+v"(c3[1]), "+v"(c3[2]), "+v"(c3[3])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]));
 }
 
-// W: kOnes or kMean; FI: width of X; FO: width of dZ; D: gather slots per row on the pipelined path; P: bf16 pieces per
-// operand.  The rows of dZ are loaded by the lane groups that load the rows of X (FI / 4 lanes per row): FO / FI float4
-// per lane, or one with the lanes past the row's end idle.
-template <int W, int FI, int FO, int D, int P>
-__global__ __launch_bounds__(wg_waves(FI) * kWave) __attribute__((amdgpu_waves_per_eu(wg_waves(FI) / 4, wg_waves(FI) / 4))) void sage_wgrad_kernel(
+// W: kOnes or kMean; FI: width of X; FO: width of dZ; D: gather slots per row on the pipelined path
+template <int W, int FI, int FO, int D>
+__global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_eu(kWgWaves / 4, kWgWaves / 4))) void sage_wgrad_kernel(
     const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const char *__restrict__ X, const char *__restrict__ dZ, int64_t zero_off, int64_t n, int32_t T, int64_t n_tiles,
+    const char *__restrict__ X, const char *__restrict__ dZ, int64_t zero_off, int64_t n, int64_t nnz, int32_t T, int64_t n_tiles,
     int64_t tiles_per_part, int64_t waves_per_part, int32_t parts, const int32_t *__restrict__ hd_rows, int32_t n_hd,
-    const char *__restrict__ hd_agg, float *__restrict__ partials)
+    const char *__restrict__ hd_agg, v4f *__restrict__ partials)
 {
     static_assert(FI == 64 || FI == 32, "width of X");
     static_assert(FO == 64 || FO == 32 || FO == 16, "width of dZ");
-    static_assert(P == 3 || P == 2, "pieces per operand");
     static_assert(W == kOnes || W == kMean, "row-uniform weights");
-    constexpr int F = FI;
-    constexpr int kWgWaves = wg_waves(FI);
-    constexpr int kL = F / 4, kRpg = kWave / kL, kG = kWgRows / kRpg, kRowShift = F == 64 ? 8 : 7;
+    constexpr int kL = FI / 4, kRpg = kWave / kL, kG = kWgRows / kRpg, kRowShift = FI == 64 ? 8 : 7;
     constexpr int kZShift = FO == 64 ? 8 : FO == 32 ? 7 : 6;             // log2 of a row of dZ in bytes
-    constexpr int kZ = (FO / 4 + kL - 1) / kL;                           // float4 of a row of dZ per lane
-    constexpr int kM = 2 * F, kMb = kM / 16, kNb = FO / 16;
-    constexpr int kPlaneA = kM * kWgTRow, kPlaneB = FO * kWgTRow;
+    constexpr int kP = kRpg / 4;                                         // contraction groups of 4 rows per sweep
+    constexpr int kMc = FI / 16, kMb = 2 * kMc, kNb = FO / 16;           // 16-column blocks of a half, of [A_hat X | X], of dZ
     constexpr int kSlots = kWgRows * D, kH = (kSlots + kWave - 1) / kWave;
+    using ZVec = typename std::conditional<kNb == 4, v4f, typename std::conditional<kNb == 2, wg_f2, float>::type>::type;
     __shared__ __align__(16) int64_t s_slot[kWgWaves][kSlots];
     __shared__ float s_inv[kWgWaves][kWgRows];
-    __shared__ __align__(16) char s_A[kWgWaves][P * kPlaneA];            // F = 64, P = 3: 15,360 B per wavefront
-    __shared__ __align__(16) char s_B[kWgWaves][P * kPlaneB];            //                  7,680 B
+    constexpr bool kFold = wg_folds(FI, FO);
+    // sweeps in flight: half a tile (a whole one: 2 % slower); 64 x 64 one (two: 1,478 us instead of 1,454, the registers are full)
+    constexpr int kSets = kFold ? kG / 2 : 1;
+    constexpr int kBufs = kFold ? kWgWaves : kWgWaves / 2;
+    __shared__ __align__(16) v4f s_sum[kBufs][kMb * kNb][kWave];         // 64 x 64: 32 KB per buffer
 
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
+    // a scalar: the tile arithmetic below then runs on the scalar unit, and vector instructions are what this kernel is short of
+    __shared__ int32_t s_pending[kWgWaves][kWgPending];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int g = l / kL, f = l % kL;
-    const int kq = l / 16, jl = l % 16;                  // matrix instruction: contraction quarter / row of A, column of B and D
+    const int kq = l / 16, jl = l % 16;                  // matrix instruction: contraction index / column of A, of B and of D
     const int64_t part = blockIdx.x % parts, j = (blockIdx.x / parts) * kWgWaves + w;
     const int64_t x_begin = part * tiles_per_part;
     const int64_t x_end = x_begin + tiles_per_part < n_tiles ? x_begin + tiles_per_part : n_tiles;
     const int64_t t_first = x_begin + j, stride = waves_per_part;
+    const int64_t n_full = n / kWgRows, x_full = x_end < n_full ? x_end : n_full;   // whole tiles
     const char *Xf = X + 16 * f;
-    const bool z_lane = 4 * f < FO;                      // kZ == 1: this lane holds four columns of dZ
-    const char *Zf = dZ + 16 * (z_lane ? f : 0);         // an idle lane reads the row's first columns and parks nothing
 
     v4f acc[kMb][kNb];
+    auto clear = [&]() {
 #pragma unroll
-    for (int mb = 0; mb < kMb; ++mb)
+        for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < kNb; ++nb) acc[mb][nb] = (v4f){0.f, 0.f, 0.f, 0.f};
+            for (int nb = 0; nb < kNb; ++nb) acc[mb][nb] = (v4f){0.f, 0.f, 0.f, 0.f};
+    };
+    auto fold = [&]() {                                  // accumulators -> sums in LDS (every lane its own words)
+#pragma unroll
+        for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < kNb; ++nb) {
+                s_sum[w][mb * kNb + nb][l] += acc[mb][nb];
+                __builtin_amdgcn_sched_barrier(0);       // one block at a time: no registers for more
+            }
+    };
+    clear();
+    if constexpr (kFold) {
+#pragma unroll
+        for (int b = 0; b < kMb * kNb; ++b) s_sum[w][b][l] = (v4f){0.f, 0.f, 0.f, 0.f};
+    }
 
     if (t_first < x_end) {
         // ---- CSR pipeline: rp_a and cc belong to the next tile to be staged, rp_b to the one after
@@ -138,28 +160,29 @@ __global__ __launch_bounds__(wg_waves(FI) * kWave) __attribute__((amdgpu_waves_p
         int32_t cc[kH];
 #pragma unroll
         for (int h = 0; h < kH; ++h) cc[h] = 0;
-        bool fix_a = true;                               // the tile has rows that the slots do not serve (or is ragged)
+        bool fix_a = false;                              // the tile has rows that the slots do not serve
         int32_t len_a = 0;                               // lanes 0..15: stored length of the tile's row
         uint32_t live_a = 0;                             // bit h: slot l + 64 h holds an entry
         auto load_rp = [&](int64_t tile) -> int64_t {
             const int64_t ri = tile * kWgRows + (l < kWgRows ? l : kWgRows);
-            return rowptr[ri < n ? ri : n];              // lanes 0..16 hold the pointers; rows past the end read rowptr[n]
+            return rowptr[ri < n ? ri : n];              // lanes 0..16 hold the pointers; rows past the end read rowptr[n]: no entries
         };
-        auto load_cols = [&](int64_t tile) {             // from rp_a: every slot fetches its own entry
-            const bool full = (tile + 1) * kWgRows <= n && tile < x_end;
-            const int64_t begin = __shfl(rp_a, 0);
-            const int32_t rel = full ? (int32_t)(rp_a - begin) : 0;
+        auto load_cols = [&]() {                         // from rp_a: every slot fetches its own entry
+            const uint32_t begin_lo = __builtin_amdgcn_readfirstlane((uint32_t)rp_a);
+            const int64_t begin = (int64_t)((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)rp_a >> 32)) << 32 | begin_lo);
+            const int32_t *const tile_col = col + (begin < nnz ? begin : 0);   // a dead slot reads the tile's first entry, or entry 0
+            const int32_t rel = (int32_t)((uint32_t)rp_a - begin_lo);
             len_a = __shfl_down(rel, 1) - rel;
-            fix_a = !full || __ballot(l < kWgRows && (len_a > D || len_a >= T)) != 0;
+            fix_a = __ballot(l < kWgRows && (len_a > D || len_a >= T)) != 0;
             live_a = 0;
 #pragma unroll
-            for (int h = 0; h < kH; ++h) {               // unconditional loads (a dead slot reads entry 0)
+            for (int h = 0; h < kH; ++h) {               // unconditional loads: the number of loads in flight stays known
                 const int s = l + kWave * h;             // slot s: row r, entry k
                 const int r = s / D, k = s - r * D;
                 const int32_t lo = __shfl(rel, r), len = __shfl(rel, r + 1) - lo;
                 const bool live = s < kSlots && k < len && len <= D && len < T;
                 live_a |= (uint32_t)live << h;
-                cc[h] = __builtin_nontemporal_load(&col[live ? begin + lo + k : 0]);
+                cc[h] = __builtin_nontemporal_load(&tile_col[live ? (uint32_t)(lo + k) : 0u]);
             }
         };
         auto stage = [&]() -> bool {                     // cc, live_a, len_a -> slot table and row weights; -> fix_a
@@ -172,141 +195,244 @@ __global__ __launch_bounds__(wg_waves(FI) * kWave) __attribute__((amdgpu_waves_p
             wg_wave_sync();
             return fix_a;
         };
-        // ---- one sweep: kRpg rows, one per lane group: the row's D slots, its own features and its row of dZ
+        // row (inside the tile) of X that this lane holds a float4 of in sweep grp; of dZ for contraction group p of the sweep
+        auto x_row = [&](int grp) -> int { return grp * kRpg + g; };
+        auto z_row = [&](int grp, int p) -> int { return grp * kRpg + kq * kP + p; };
+        // ---- one sweep: kRpg rows, one per lane group: the row's D slots, its own features; and the rows of dZ
         struct Regs {
-            v4f xs[D], self, dz[kZ];
+            v4f xs[D], self;
+            ZVec dz[kP];
             float inv;
         };
-        Regs rr[kG];
-        auto issue = [&](Regs &q, int64_t tile, int grp) {
-            const int lr = grp * kRpg + g;
-            int64_t row = tile * kWgRows + lr;
-            row = row < n ? row : n - 1;                 // past the end: any valid row, the values are replaced by zeros
+        Regs rr[kSets];
+        const uint32_t x_lane = (uint32_t)g << kRowShift | 16 * f, z_lane = (uint32_t)(kq * kP) << kZShift | 4 * kNb * jl;
+        auto load_self = [&](int64_t tile, int grp) -> v4f {
+            return *(const v4f *)(X + (tile << kRowShift) * kWgRows + x_lane + ((grp * kRpg) << kRowShift));
+        };
+        auto load_z = [&](int64_t tile, int grp, int p) -> ZVec {
+            return __builtin_nontemporal_load((const ZVec *)(dZ + (tile << kZShift) * kWgRows + z_lane + ((grp * kRpg + p) << kZShift)));
+        };
+        auto issue = [&](Regs &q, int64_t tile, int grp) {   // the tile whose slots are staged
+            const int lr = x_row(grp);
             if (W == kMean) q.inv = s_inv[w][lr];
 #pragma unroll
             for (int k = 0; k < D; ++k) q.xs[k] = *(const v4f *)(Xf + s_slot[w][lr * D + k]);
-            q.self = *(const v4f *)(Xf + (row << kRowShift));
+            q.self = load_self(tile, grp);
 #pragma unroll
-            for (int i = 0; i < kZ; ++i) q.dz[i] = *(const v4f *)(Zf + (row << kZShift) + 16 * kL * i);
+            for (int p = 0; p < kP; ++p) q.dz[p] = load_z(tile, grp, p);
         };
         auto sum = [&](const Regs &q) -> v4f {
-            v4f a = {0.f, 0.f, 0.f, 0.f};
+            v4f a = q.xs[0];
 #pragma unroll
-            for (int k = 0; k < D; ++k) a += q.xs[k];
+            for (int k = 1; k < D; ++k) a += q.xs[k];
             if (W == kMean) a *= q.inv;
             return a;
         };
-
-        // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
-        rp_a = load_rp(t_first);
-        load_cols(t_first);
-        bool fix_cur = stage();
-        rp_a = load_rp(t_first + stride);
-        load_cols(t_first + stride);
-        rp_b = load_rp(t_first + 2 * stride);
+        // acc[mb0 ..] += (this half's columns)^T dz, over the rows of one sweep
+        auto multiply = [&](int mb0, const v4f &x, const ZVec (&dz)[kP]) {
 #pragma unroll
-        for (int grp = 0; grp < kG; ++grp) issue(rr[grp], t_first, grp);
-        __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the loop's own order of loads is the only one from here on
-
-        char *const a_t = s_A[w], *const b_t = s_B[w];
-        for (int64_t tile = t_first; tile < x_end; tile += stride) {
-            const bool fix_next = stage();               // CSR of the next tile -> slot table (this tile's sweeps are all issued)
-            rp_a = rp_b;
-            load_cols(tile + 2 * stride);
-            rp_b = load_rp(tile + 3 * stride);
-            const int64_t base = tile * kWgRows;
-            // this tile's values out of the register sets, which take the rows of the next tile
-            v4f av[kG], sv[kG], zv[kZ][kG];
+            for (int p = 0; p < kP; ++p) {
+                float a[kMc], b[kNb];
+                if constexpr (FI == 64) {
 #pragma unroll
-            for (int grp = 0; grp < kG; ++grp) {
-                const bool in = base + grp * kRpg + g < n;
-                const v4f zero = {0.f, 0.f, 0.f, 0.f};
-                av[grp] = sum(rr[grp]);                  // a ragged tile has no live slot: zeros
-                sv[grp] = in ? rr[grp].self : zero;
+                    for (int c = 0; c < kMc; ++c) a[c] = x[c];
+                } else {                                 // the two halves of 16 lanes hold rows 2 k and 2 k + 1
+                    const bool odd = (jl & 8) != 0;
 #pragma unroll
-                for (int i = 0; i < kZ; ++i) zv[i][grp] = in ? rr[grp].dz[i] : zero;
-                issue(rr[grp], tile + stride, grp);
+                    for (int c = 0; c < kMc; ++c) {
+                        const float lo = p == 0 ? x[c] : wg_other_half(x[c]);
+                        const float hi = p == 0 ? wg_other_half(x[2 + c]) : x[2 + c];
+                        a[c] = odd ? hi : lo;
+                    }
+                }
+                if constexpr (kNb == 1) b[0] = dz[p];
+                else {
+#pragma unroll
+                    for (int c = 0; c < kNb; ++c) b[c] = dz[p][c];
+                }
+                if constexpr (kMc == 4 && kNb == 4) wg_mfma_4x4(acc[mb0], acc[mb0 + 1], acc[mb0 + 2], acc[mb0 + 3], a, b);
+                else {
+#pragma unroll
+                    for (int mb = 0; mb < kMc; ++mb)
+#pragma unroll
+                        for (int nb = 0; nb < kNb; ++nb)
+                            acc[mb0 + mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mb], b[nb], acc[mb0 + mb][nb], 0, 0, 0);
+                }
             }
-            if (fix_cur) {
-                // plain path: the rows of this tile that had no live slots (more entries than slots, high-degree, or
-                // every row of the ragged last tile), straight from global memory; high-degree sums from the side buffer
+        };
+        int until_fold = kWgFold;
+        int64_t tile = t_first;
+        while (tile < x_end) {
+            int pending = 0;
+            if (tile < x_full) {
+                // ---- prologue: the first kSets sweeps are in flight; the CSR of the next two tiles is on its way
+                rp_a = load_rp(tile);
+                load_cols();
+                bool fix_cur = stage(), fix_next = false;
+                rp_a = load_rp(tile + stride);
+                load_cols();
+                rp_b = load_rp(tile + 2 * stride);
 #pragma unroll
-                for (int grp = 0; grp < kG; ++grp) {
-                    const int64_t row = base + grp * kRpg + g;
-                    const bool full = base + kWgRows <= n;
-                    if (row < n) {
-                        const int64_t s = rowptr[row], e = rowptr[row + 1];
-                        if (e - s >= T) {
-                            int32_t lo = 0, hi = n_hd;   // the row's place in the list of high-degree rows
-                            while (lo < hi) {
-                                const int32_t mid = (lo + hi) / 2;
-                                if (hd_rows[mid] < row) lo = mid + 1; else hi = mid;
-                            }
-                            av[grp] = *(const v4f *)(hd_agg + ((int64_t)lo << kRowShift) + 16 * f);
-                        } else if (!full || e - s > D) {
-                            av[grp] = ld_row_sum<W, false, 8>(s, e, col, val, (const v4f *)X, kL, f);
+                for (int grp = 0; grp < kSets; ++grp) issue(rr[grp], tile, grp);
+                __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): the loop's own order of loads is the only one from here on
+
+                for (; tile < x_full && pending < kWgPending; tile += stride) {
+                    const int64_t next = tile + stride < n_full ? tile + stride : n_full - 1;
+#pragma unroll
+                    for (int grp = 0; grp < kG; ++grp) {
+                        if (grp == kG - kSets) {         // this tile's sweeps are all issued: CSR of the next tile -> slot table
+                            fix_next = stage();
+                            rp_a = rp_b;
+                            load_cols();
+                            rp_b = load_rp(tile + 3 * stride);
+                        }
+                        // this sweep's values out of the register set, which takes the sweep kSets later
+                        Regs &q = rr[grp % kSets];
+                        const v4f a = sum(q), s = q.self;   // a row that the slots do not serve: the sum is zero
+                        ZVec z[kP];
+#pragma unroll
+                        for (int p = 0; p < kP; ++p) z[p] = q.dz[p];
+                        issue(q, grp + kSets < kG ? tile : next, (grp + kSets) % kG);
+                        // Matrix instructions in one run: fp32 ones and vector instructions do not overlap within a
+                        // wavefront and alternating costs (left to the scheduler, 64 x 64 took 1,872 us); at a raised
+                        // priority, so that the SIMD's two wavefronts take turns (1,475 against 1,484 us).
+                        __builtin_amdgcn_sched_barrier(0);
+                        __builtin_amdgcn_s_setprio(1);
+                        multiply(0, a, z);
+                        multiply(kMc, s, z);
+                        __builtin_amdgcn_s_setprio(0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (fix_cur) {
+                        if (l == 0) s_pending[w][pending] = (int32_t)tile;
+                        ++pending;
+                    }
+                    fix_cur = fix_next;
+                    if constexpr (kFold) {
+                        if (--until_fold == 0) {
+                            fold();
+                            clear();
+                            until_fold = kWgFold;
                         }
                     }
                 }
             }
-            // transposed into LDS, cut into pieces: [A_hat X | X] and dZ
-            wg_park<kG, P, kPlaneA>(a_t, 4 * f, g, av);
-            wg_park<kG, P, kPlaneA>(a_t, F + 4 * f, g, sv);
-            if (z_lane) {
-#pragma unroll
-                for (int i = 0; i < kZ; ++i) wg_park<kG, P, kPlaneB>(b_t, 4 * (f + kL * i), g, zv[i]);
+            if (tile >= x_full && tile < x_end && pending < kWgPending) {   // the ragged last tile
+                if (l == 0) s_pending[w][pending] = (int32_t)tile;
+                ++pending;
+                tile += stride;
             }
+            // ---- the noted tiles, straight from global memory: A_hat X of the rows that had no live slots (more entries
+            //      than slots, or high-degree: their sums come from the side buffer), for which the loop above has
+            //      added zeros, and all of the ragged tile.  Outside the loop because the registers that hold its rows
+            //      in flight are needed here (inside it they were spilled), and so that its loads are all unconditional.
             wg_wave_sync();
-            // ---- [A_hat X | X]^T (2F x 16) times dZ (16 x F): lane (jl, kq) reads column jl of a block, rows 4 kq .. 4 kq + 3
-            wg_u2 bop[kNb][P];
+#pragma unroll 1
+            for (int i = 0; i < pending; ++i) {
+                const int64_t t = __builtin_amdgcn_readfirstlane(s_pending[w][i]);
+                const bool ragged = t >= n_full;
+                const int64_t rp = load_rp(t);           // rows past the end: no entries
+                const int64_t next_rp = __shfl_down(rp, 1);
+                const uint64_t redo = __ballot(l < kWgRows && (ragged || next_rp - rp > D || next_rp - rp >= T));
+#pragma unroll 1
+                for (int grp = 0; grp < kG; ++grp) {
+                    if ((redo >> (grp * kRpg) & ((1u << kRpg) - 1)) == 0) continue;
+                    const int lr = x_row(grp);
+                    const int64_t row = t * kWgRows + lr, s = __shfl(rp, lr), e = __shfl(rp, lr + 1);
+                    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+                    v4f a = zero;
+                    if (e - s >= T) {
+                        int32_t lo = 0, hi = n_hd;       // the row's place in the list of high-degree rows
+                        while (lo < hi) {
+                            const int32_t mid = (lo + hi) / 2;
+                            if (hd_rows[mid] < row) lo = mid + 1; else hi = mid;
+                        }
+                        a = *(const v4f *)(hd_agg + ((int64_t)lo << kRowShift) + 16 * f);
+                    } else if (ragged || e - s > D) {
+                        a = ld_row_sum<W, false, 8>(s, e, col, val, (const v4f *)X, kL, f);
+                    }
+                    ZVec z[kP];
 #pragma unroll
-            for (int nb = 0; nb < kNb; ++nb)
-#pragma unroll
-                for (int pb = 0; pb < P; ++pb)
-                    bop[nb][pb] = *(const wg_u2 *)(b_t + pb * kPlaneB + (16 * nb + jl) * kWgTRow + 8 * kq);
-#pragma unroll
-            for (int mb = 0; mb < kMb; ++mb) {
-                wg_u2 aop[P];
-#pragma unroll
-                for (int pa = 0; pa < P; ++pa)
-                    aop[pa] = *(const wg_u2 *)(a_t + pa * kPlaneA + (16 * mb + jl) * kWgTRow + 8 * kq);
-                // the piece products that are kept: pa + pb < P, the smallest first
-#pragma unroll
-                for (int pb = P - 1; pb >= 0; --pb)
-#pragma unroll
-                    for (int pa = P - 1 - pb; pa >= 0; --pa)
-#pragma unroll
-                        for (int nb = 0; nb < kNb; ++nb)
-                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
-                                __builtin_bit_cast(wg_s4, aop[pa]), __builtin_bit_cast(wg_s4, bop[nb][pb]), acc[mb][nb], 0, 0, 0);
+                    for (int p = 0; p < kP; ++p)
+                        z[p] = t * kWgRows + z_row(grp, p) < n ? load_z(t, grp, p) : (ZVec)(0.f);
+                    multiply(0, a, z);
+                    if (ragged) multiply(kMc, row < n ? load_self(t, grp) : zero, z);
+                }
             }
-            wg_wave_sync();                              // all reads of the parked tile are done
-            fix_cur = fix_next;
         }
     }
-    // ---- this wavefront's sums to its slice of the workspace (zeros if it had no tile): lane holds rows
-    //      16 mb + 4 kq + r of column 16 nb + jl
-    float *mine = partials + ((int64_t)blockIdx.x * kWgWaves + w) * (kM * FO);
+    // ---- the workgroup's slice of the workspace: its wavefronts' sums, in wavefront order, in fp64; stored as the
+    //      accumulators lie (block, lane, register), which the reducing kernel undoes
+    constexpr int kVecs = kMb * kNb * kWave, kMine = (kVecs + kWgWaves * kWave - 1) / (kWgWaves * kWave);
+    double t[kMine][4];
 #pragma unroll
-    for (int mb = 0; mb < kMb; ++mb)
+    for (int i = 0; i < kMine; ++i)
 #pragma unroll
-        for (int nb = 0; nb < kNb; ++nb)
+        for (int r = 0; r < 4; ++r) t[i][r] = 0.0;
+    if constexpr (kFold) fold();
+#pragma unroll 1
+    for (int first = 0; first < kWgWaves; first += kBufs) {
+        if constexpr (!kFold) {                          // kBufs wavefronts at a time
+            if (w >= first && w < first + kBufs) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) mine[(16 * mb + 4 * kq + r) * FO + 16 * nb + jl] = acc[mb][nb][r];
+                for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < kNb; ++nb) s_sum[w - first][mb * kNb + nb][l] = acc[mb][nb];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const int e = i * kWgWaves * kWave + threadIdx.x;
+            if (e < kVecs)
+                for (int q = 0; q < kBufs; ++q) {
+                    const v4f v = (&s_sum[q][0][0])[e];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) t[i][r] += (double)v[r];
+                }
+        }
+        __syncthreads();
+    }
+    v4f *mine = partials + (int64_t)blockIdx.x * kVecs;
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        const int e = i * kWgWaves * kWave + threadIdx.x;
+        if (e < kVecs) mine[e] = (v4f){(float)t[i][0], (float)t[i][1], (float)t[i][2], (float)t[i][3]};
+    }
 }
 
-// dWn[m][n] (m < FI) and dWs[m - FI][n] = sum over the slices, in slice order, in fp64; half = FI * FO
-__global__ __launch_bounds__(kBlock) void sage_wgrad_reduce_kernel(const float *__restrict__ partials, int64_t slices,
-                                                                   int32_t half, float *__restrict__ dWn,
-                                                                   float *__restrict__ dWs)
+// dWn[m][n] (m < FI) and dWs[m - FI][n] = sum over the workgroups' slices in fp64, in a fixed order.  A workgroup takes
+// 16 float4 of a slice; its 16 groups of 16 threads take every 16th slice each, so that a slice count of 256 is 16 loads
+// in flight per thread and one latency (one thread per element walking 2,048 slices took 42 us at 64 x 64 and 94 us at
+// 32 x 32, where 8 workgroups had it all), then the groups are added in order.
+constexpr int kWgRedVec = 16, kWgRedGroups = kBlock / kWgRedVec;
+template <int FI, int FO>
+__global__ __launch_bounds__(kBlock) void sage_wgrad_reduce_kernel(const v4f *__restrict__ partials, int64_t slices,
+                                                                   float *__restrict__ dWn, float *__restrict__ dWs)
 {
-    const int32_t e = blockIdx.x * kBlock + threadIdx.x, count = 2 * half;
-    if (e >= count) return;
-    double s = 0.0;
-#pragma unroll 8
-    for (int64_t k = 0; k < slices; ++k) s += (double)partials[k * count + e];
-    if (e < half) dWn[e] = (float)s;
-    else dWs[e - half] = (float)s;
+    constexpr int kMc = FI / 16, kNb = FO / 16, kVecs = 2 * FI * FO / 4;
+    static_assert(kVecs % kWgRedVec == 0, "whole workgroups");
+    __shared__ double s_part[kWgRedGroups][kWgRedVec][4];
+    const int v = threadIdx.x % kWgRedVec, grp = threadIdx.x / kWgRedVec;
+    const int e = blockIdx.x * kWgRedVec + v;            // float4 of the slice: block e / 64, lane e % 64
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 16
+    for (int64_t k = grp; k < slices; k += kWgRedGroups) {
+        const v4f x = partials[k * kVecs + e];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t[r] += (double)x[r];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_part[grp][v][r] = t[r];
+    __syncthreads();
+    if (threadIdx.x >= kWgRedVec * 4) return;
+    const int ve = threadIdx.x / 4, r = threadIdx.x % 4;
+    double sum = 0.0;
+    for (int q = 0; q < kWgRedGroups; ++q) sum += s_part[q][ve][r];
+    const int el = blockIdx.x * kWgRedVec + ve, blk = el / kWave, lane = el % kWave;
+    const int mb = blk / kNb, nb = blk % kNb;            // accumulator acc[mb][nb]: rows 4 (lane / 16) + r, column lane % 16
+    float *out = mb < kMc ? dWn : dWs;
+    out[wg_feature<FI>(4 * (lane / 16) + r, mb % kMc) * FO + kNb * (lane % 16) + nb] = (float)sum;
 }
 
 static int64_t wgrad_workgroups()
@@ -318,64 +444,66 @@ static int64_t wgrad_workgroups()
     return n_wg < kXcds ? kXcds : n_wg;
 }
 
-// bytes of workspace that launch_sage_wgrad needs for these widths on the current device (0 on failure)
+// bytes of workspace that launch_sage_wgrad asks for at these widths on the current device (0 on failure): one slice per
+// SIMD (F_in = 64) or two (32).  The kernel fills one slice per workgroup; the size is part of the interface.
 size_t sage_wgrad_workspace_bytes(int32_t FI, int32_t FO)
 {
     const int64_t n_wg = wgrad_workgroups();
-    return n_wg < 0 ? 0 : (size_t)n_wg * wg_waves(FI) * 2 * (size_t)FI * (size_t)FO * sizeof(float);
+    return n_wg < 0 ? 0 : (size_t)n_wg * (FI == 64 ? 4 : 8) * 2 * (size_t)FI * (size_t)FO * sizeof(float);
 }
 
-int launch_sage_wgrad(const DevicePlan &dp, const float *X, const float *dZ, float *dWn, float *dWs, int32_t FI, int32_t FO,
-                      int pieces, void *workspace, void *stream)
+template <int FI, int FO>
+static int wgrad_launch(const DevicePlan &dp, const float *X, const float *dZ, float *dWn, float *dWs, void *workspace,
+                        hipStream_t st)
 {
-    if (!weights_ok(dp) || !dp.zero_row || (FI != 64 && FI != 32) || (FO != 64 && FO != 32 && FO != 16) ||
-        (pieces != 2 && pieces != 3) || !workspace)
-        return (int)hipErrorInvalidValue;
-    if (dp.weight_mode == kExplicit) return (int)hipErrorInvalidValue;
-    if (dp.n_hd_rows && (!dp.hd_rows || !dp.hd_agg)) return (int)hipErrorInvalidValue;
-    const int64_t n_wg = wgrad_workgroups();
-    if (n_wg < 0) return (int)hipErrorInvalidDevice;
+    const int64_t cu_wg = wgrad_workgroups();
+    if (cu_wg < 0) return (int)hipErrorInvalidDevice;
     const int64_t n_tiles = (dp.n + kWgRows - 1) / kWgRows;
     const int32_t parts = dp.xcd_remap ? kXcds : 1;
     const int64_t tiles_per_part = (n_tiles + parts - 1) / parts;
-    const int64_t waves_per_part = n_wg / parts * wg_waves(FI);
+    // no more workgroups than tiles: a slice without rows would be written and read for nothing
+    const int64_t wanted = (tiles_per_part + kWgWaves - 1) / kWgWaves * parts;
+    const int64_t n_wg = wanted < cu_wg ? wanted : cu_wg / parts * parts;
+    const int64_t waves_per_part = n_wg / parts * kWgWaves;
     if (!grid_ok(n_wg) || n_tiles <= 0) return (int)hipErrorInvalidConfiguration;
     // the kernel reads entry 0 of the index array from idle lanes: give it something to read when the matrix has no entries
     const int32_t *col_arg = dp.col ? dp.col : (const int32_t *)dp.rowptr;
     const float *val_arg = dp.val ? dp.val : (const float *)dp.rowptr;
-    hipStream_t st = (hipStream_t)stream;
-#define GROOT_WGRAD_LAUNCH(WM, FFI, FFO, DD, PP)                                                                         \
-    sage_wgrad_kernel<WM, FFI, FFO, DD, PP><<<dim3((unsigned)n_wg), dim3(wg_waves(FFI) * kWave), 0, st>>>(                 \
-        dp.rowptr, col_arg, val_arg, (const char *)X, (const char *)dZ, byte_distance(X, dp.zero_row), dp.n, dp.threshold, \
+#define GROOT_WGRAD_LAUNCH(WM, DD)                                                                                      \
+    sage_wgrad_kernel<WM, FI, FO, DD><<<dim3((unsigned)n_wg), dim3(kWgWaves * kWave), 0, st>>>(                            \
+        dp.rowptr, col_arg, val_arg, (const char *)X, (const char *)dZ, byte_distance(X, dp.zero_row), dp.n, dp.nnz, dp.threshold, \
         n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows, (const char *)dp.hd_agg,    \
-        (float *)workspace)
-#define GROOT_WGRAD_P(WM, FFI, FFO, DD)                        \
-    if (pieces == 2) GROOT_WGRAD_LAUNCH(WM, FFI, FFO, DD, 2);  \
-    else GROOT_WGRAD_LAUNCH(WM, FFI, FFO, DD, 3)
-#define GROOT_WGRAD_D(WM, FFI, FFO)                                  \
-    if (dp.sage_depth == 5) { GROOT_WGRAD_P(WM, FFI, FFO, 5); }      \
-    else { GROOT_WGRAD_P(WM, FFI, FFO, 6); }
-#define GROOT_WGRAD_FO(WM, FFI)                          \
-    if (FO == 64) { GROOT_WGRAD_D(WM, FFI, 64); }        \
-    else if (FO == 32) { GROOT_WGRAD_D(WM, FFI, 32); }   \
-    else { GROOT_WGRAD_D(WM, FFI, 16); }
-    if (FI == 64) {
-        if (dp.weight_mode == kMean) { GROOT_WGRAD_FO(kMean, 64); }
-        else { GROOT_WGRAD_FO(kOnes, 64); }
+        (v4f *)workspace)
+    if (dp.weight_mode == kMean) {
+        if (dp.wgrad_depth == 5) GROOT_WGRAD_LAUNCH(kMean, 5);
+        else GROOT_WGRAD_LAUNCH(kMean, 6);
     } else {
-        if (dp.weight_mode == kMean) { GROOT_WGRAD_FO(kMean, 32); }
-        else { GROOT_WGRAD_FO(kOnes, 32); }
+        if (dp.wgrad_depth == 5) GROOT_WGRAD_LAUNCH(kOnes, 5);
+        else GROOT_WGRAD_LAUNCH(kOnes, 6);
     }
-#undef GROOT_WGRAD_FO
-#undef GROOT_WGRAD_D
-#undef GROOT_WGRAD_P
 #undef GROOT_WGRAD_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return (int)err;
-    const int32_t count = 2 * FI * FO;
-    sage_wgrad_reduce_kernel<<<dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), 0, st>>>(
-        (const float *)workspace, n_wg * wg_waves(FI), FI * FO, dWn, dWs);
+    sage_wgrad_reduce_kernel<FI, FO><<<dim3(2 * FI * FO / 4 / kWgRedVec), dim3(kBlock), 0, st>>>((const v4f *)workspace, n_wg, dWn, dWs);
     return (int)hipGetLastError();
+}
+
+int launch_sage_wgrad(const DevicePlan &dp, const float *X, const float *dZ, float *dWn, float *dWs, int32_t FI, int32_t FO,
+                      void *workspace, void *stream)
+{
+    if (!weights_ok(dp) || !dp.zero_row || (FI != 64 && FI != 32) || (FO != 64 && FO != 32 && FO != 16) || !workspace)
+        return (int)hipErrorInvalidValue;
+    if (dp.weight_mode == kExplicit) return (int)hipErrorInvalidValue;
+    if (dp.n_hd_rows && (!dp.hd_rows || !dp.hd_agg)) return (int)hipErrorInvalidValue;
+    hipStream_t st = (hipStream_t)stream;
+    if (FI == 64) {
+        if (FO == 64) return wgrad_launch<64, 64>(dp, X, dZ, dWn, dWs, workspace, st);
+        if (FO == 32) return wgrad_launch<64, 32>(dp, X, dZ, dWn, dWs, workspace, st);
+        return wgrad_launch<64, 16>(dp, X, dZ, dWn, dWs, workspace, st);
+    }
+    if (FO == 64) return wgrad_launch<32, 64>(dp, X, dZ, dWn, dWs, workspace, st);
+    if (FO == 32) return wgrad_launch<32, 32>(dp, X, dZ, dWn, dWs, workspace, st);
+    return wgrad_launch<32, 16>(dp, X, dZ, dWn, dWs, workspace, st);
 }
 
 }  // namespace groot

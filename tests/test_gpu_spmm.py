@@ -586,6 +586,37 @@ def test_fused_sage_layer_backward_weights_other_graphs_and_errors(torch_cuda):
         G.groot_sage_layer_backward_weights(plan_t, z(n, 64), z(n, 64), z(64, 64), z(64, 64), z(need // 4), 64)
 
 
+@pytest.mark.parametrize("F_in,F_out,graph", [(32, 16, "lut4"), (64, 64, "csa"), (32, 32, "csa"), (64, 32, "one")])
+def test_weight_gradients_at_the_edges_of_the_pipeline(torch_cuda, F_in, F_out, graph):
+    """Edges of the weight-gradient kernel's bookkeeping.  "lut4": every tile has rows longer than the slots and some
+    wavefront has more than the 32 tiles that it notes before it must complete them (66,304 tiles over 2,048
+    wavefronts).  "csa": 62,808 rows, 3,926 tiles: the last one ragged, wavefronts with two tiles, one or none; rows
+    past the end of X and of dZ must not be read as numbers (NaN behind both).  "one": a single row."""
+    torch = torch_cuda
+    if graph == "lut4":
+        c = wl.lut4_csa_graph(256, 8)
+        g, (rowptr, col, val), n = G.groot_graph_from_csr(c.rowptr, c.col, c.val), (c.rowptr, c.col, c.val), c.n
+    elif graph == "csa":
+        aig, g, (rowptr, col, val, _) = _aig_case(89, 1)
+        n = aig.num_nodes
+    else:
+        rowptr, col, val = np.array([0, 1], np.int64), np.array([0], np.int32), np.array([1.0], np.float32)
+        g, n = G.groot_graph_from_csr(rowptr, col, val), 1
+    _wgrad_check(torch, g, rowptr, col, val, 32, n, 95, F_in, F_out=F_out)
+    if graph == "csa":
+        assert n % 16 != 0
+        plan = G.groot_spmm_plan(g, 32)
+        G.groot_plan_upload(plan, F_in)
+        X = torch.full((n + 64, F_in), float("nan"), device="cuda")
+        dZ = torch.full((n + 64, F_out), float("nan"), device="cuda")
+        X[:n].uniform_(-1, 1)
+        dZ[:n].uniform_(-1, 1)
+        ws = torch.empty(G.groot_sage_layer_backward_weights_workspace(plan, F_in, F_out) // 4, device="cuda")
+        dW = torch.empty((2, F_in, F_out), device="cuda")
+        G.groot_sage_layer_backward_weights(plan, X, dZ, dW[0], dW[1], ws)
+        assert bool(torch.isfinite(dW).all())
+
+
 def test_calls_that_only_enqueue_run_under_graph_capture(torch_cuda):
     """groot_spmm_execute, the fused layer, its input gradient (with groot_rows_over_degree) and its weight
     gradients only enqueue kernels and allocate nothing, so a caller may capture them into a graph: the captured
