@@ -507,6 +507,18 @@ PipeChoice choose_ld_kernel(int knob, int64_t n_ld, AtMost at_most)
         if ((n_ld - at_most(d)) * 50 <= n_ld) return {2, d};
     return {knob > 0 ? 2 : 0, kPipeMaxDepth};
 }
+
+// Gather slots per row of the fused layer's kernels (5, 6 or 8).  A tile of 16 rows with a longer row is noted and completed
+// later, unoverlapped, for about the time of one more tile, so the line lies lower than for the aggregation alone: 5 slots up
+// to one longer row in 300, five tiles in a hundred (Booth multipliers, one row in 850: layer 64 -> 32 571 us with 5 slots,
+// 592 with 6; weight gradients 562 and 578), 6 or 8 up to one in 50 (4-LUT shape, rows of 7: layer 64 -> 64 583 us with 6
+// slots and every tile completed later, 266 with 8).
+template <class AtMost>
+int choose_layer_depth(int64_t n_ld, AtMost at_most)
+{
+    if ((n_ld - at_most(5)) * 300 <= n_ld) return 5;
+    return (n_ld - at_most(6)) * 50 > n_ld && (n_ld - at_most(8)) * 50 <= n_ld ? 8 : 6;
+}
 }  // namespace
 
 namespace {
@@ -601,12 +613,7 @@ extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
         const PipeChoice ch = choose_ld_kernel(tuning().ld_pipeline, n_ld, at_most);
         d.ld_pipelined = ch.pipelined;
         d.pipe_depth = ch.depth;
-        // the fused layer kernel completes a longer row inside the tile's turn, unoverlapped: 5 slots only when
-        // at most one low-degree row in 2000 has 6 entries or more
-        d.sage_depth = (n_ld - at_most(5)) * 2000 <= n_ld ? 5 : 6;
-        // the weight-gradient kernel notes such a tile and completes it later, for about the time of one more tile: 5 slots
-        // up to one row in 300 (five tiles in a hundred)
-        d.wgrad_depth = (n_ld - at_most(5)) * 300 <= n_ld ? 5 : 6;
+        d.sage_depth = choose_layer_depth(n_ld, at_most);
         const int64_t first_mid = at_most(ch.depth);
         d.n_mid_rows = ch.pipelined ? n_ld - first_mid : 0;
         if (d.n_mid_rows &&
@@ -1330,8 +1337,7 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             const PipeChoice ch = choose_ld_kernel(tuning().ld_pipeline, n_ld, at_most);
             d.ld_pipelined = ch.pipelined;
             d.pipe_depth = ch.depth;
-            d.sage_depth = (n_ld - at_most(5)) * 2000 <= n_ld ? 5 : 6;
-            d.wgrad_depth = (n_ld - at_most(5)) * 300 <= n_ld ? 5 : 6;
+            d.sage_depth = choose_layer_depth(n_ld, at_most);
             const int64_t first_mid = at_most(ch.depth);
             d.n_mid_rows = ch.pipelined ? n_ld - first_mid : 0;
             if (d.n_mid_rows) {             // the tail of the degree-sorted list, which is on the device already

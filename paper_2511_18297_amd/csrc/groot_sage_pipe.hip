@@ -6,8 +6,8 @@
 // its own tiles and keeps a whole tile of gathers in flight; slot table in LDS, zero row for dead slots, no
 // workgroup barrier after the start).  A tile here is 16 rows, the height of a matrix instruction.  Instead
 // of storing the 16 sums, the wavefront parks [A_hat X | X] of its tile in its own LDS region, multiplies it
-// with the stacked weights [Wn; Ws] (128 x 64) on the matrix cores, passes the 16 x 64 result through LDS once
-// more to get whole rows per lane group, and stores them.  Nothing is shared between wavefronts, so nothing
+// with the stacked weights [Wn; Ws] (128 x 64) on the matrix cores and stores the result from the accumulators, whole
+// 128-byte lines per instruction.  Nothing is shared between wavefronts, so nothing
 // waits for another wavefront; while a wavefront multiplies, the gathers of its next tile are in flight, and
 // the second wavefront of its SIMD issues whenever the first one waits (with one wavefront per SIMD, which
 // could keep the weights in registers, every wait of that wavefront idles the SIMD: 25.9 against 24.5 ms of
@@ -30,9 +30,15 @@
 // again.  So SD is the layer with unit weights whose own-row operand is scaled by the row's stored length.
 //
 // High-degree rows are aggregated beforehand by the HD kernel into a side buffer of the plan, one row per
-// high-degree row in ascending order of their ids; a tile that contains one (or a row with more than kSpD entries,
-// or the ragged end) is redone by a plain path that picks those sums up (the row's place in the buffer by binary
-// search in the list of high-degree rows).
+// high-degree row in ascending order of their ids.  A tile that contains one (or a row with more than D entries) is
+// noted, its result goes to the trash area, and it is computed by a plain path outside the loop, which picks those
+// sums up (the row's place in the buffer by binary search in the list of high-degree rows); so is the ragged last
+// tile.  The loop itself has no conditional load or store.
+//
+// What bounds it: at 64 x 64 the power the chip grants dense bf16 matrix work beside the memory traffic (it runs at
+// 1.4 to 1.7 GHz).  Scalar tile arithmetic, the result stored from the accumulators, whole tiles only in the loop
+// (390 instead of 500 vector instructions per tile): 8.4 M rows of carry-save multipliers, 64 -> 64: 1,288 -> 1,214 us,
+// 32 -> 32: 630 -> 594 us (lines stored by halves instead: 1,364 and 675 us, 9 % more bytes written).
 #include <type_traits>
 
 #include "groot_device.h"
@@ -40,7 +46,8 @@
 namespace groot {
 
 constexpr int kSpRows = 16;                  // rows per tile: the height of a matrix instruction
-static_assert(kSpRows * 64 <= kTrashFloats, "rows past the end of the matrix are stored to the trash area");
+constexpr int kSpPending = 16;               // tiles noted per wavefront for the plain path
+static_assert(kSpRows * 64 <= kTrashFloats, "a tile that the plain path computes is stored to the trash area");
 
 // Shapes for FI input and FO output features and NW wavefronts per workgroup (one workgroup per CU).
 template <int FI, int FO, int NW>
@@ -55,14 +62,9 @@ struct SpCfg {
     static constexpr int kNb = FO / 16;              // blocks of 16 output columns
     static constexpr int kBRow = kK * 2 + 16;        // bytes per LDS row of one bf16 plane (16 B of padding: conflict-free)
     static constexpr int kPlane = kSpRows * kBRow;
-    static constexpr int kOStride = FO + 4;          // floats per LDS row of the result tile
-    static constexpr int kLo = FO / 4;               // lanes per output row
-    static constexpr int kRo = kWave / kLo;          // output rows per store instruction
-    static constexpr int kGo = kSpRows / kRo;        // store sweeps per tile
     static constexpr int kORowShift = FO == 64 ? 8 : FO == 32 ? 7 : 6;   // log2 of an output row's bytes
     static_assert(FI == 64 || FI == 32, "input width");
     static_assert(FO == 64 || FO == 32 || FO == 16, "output width");
-    static_assert(kSpRows * kOStride * 4 <= 2 * kPlane, "the result tile fits the parked tile's space (two planes at least)");
 };
 
 typedef __bf16 sp_bf2 __attribute__((ext_vector_type(2)));
@@ -114,35 +116,38 @@ template <int W, int FI, int FO, int NW, int D, int P, bool SD = false>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void sage_pipe_kernel(
     const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
     const char *__restrict__ X, char *H, int64_t zero_off, char *trash,
-    const float *__restrict__ Wn, const float *__restrict__ Ws, const float *__restrict__ bias, int relu, int64_t n,
+    const float *__restrict__ Wn, const float *__restrict__ Ws, const float *__restrict__ bias, int relu, int64_t n, int64_t nnz,
     int32_t T, int64_t n_tiles, int64_t tiles_per_part, int64_t waves_per_part, int32_t parts,
     const int32_t *__restrict__ hd_rows, int32_t n_hd, const char *__restrict__ hd_agg)
 {
     static_assert(P == 3 || P == 2, "pieces per operand");
     static_assert(!SD || W == kOnes, "the own-row operand is scaled by the row length in the unit-weight form only");
+    static_assert(W == kOnes || W == kMean, "row-uniform weights");
     using C = SpCfg<FI, FO, NW>;
     constexpr int F = FI;
     constexpr int kSpD = D, kSpSlots = kSpRows * kSpD, kSpH = (kSpSlots + kWave - 1) / kWave;
     constexpr int kSpWaves = C::kWaves, kSpL = C::kL, kSpRpg = C::kRpg, kSpG = C::kG, kRowShift = C::kRowShift;
-    constexpr int kKs = C::kKs, kNb = C::kNb, kSpBRow = C::kBRow, kSpPlane = C::kPlane, kSpOStride = C::kOStride;
-    struct SlotW { int64_t off; float w; float pad; };
-    using Slot = typename std::conditional<W == kExplicit, SlotW, int64_t>::type;
-    __shared__ __align__(16) Slot s_slot[kSpWaves][kSpSlots];
+    constexpr int kKs = C::kKs, kNb = C::kNb, kSpBRow = C::kBRow, kSpPlane = C::kPlane;
+    __shared__ __align__(16) int64_t s_slot[kSpWaves][kSpSlots];
     __shared__ float s_inv[kSpWaves][kSpRows];
-    __shared__ __align__(16) char s_A[kSpWaves][P * kSpPlane];           // F = 64, P = 3: 13,056 B per wavefront; the result tile reuses it
-    __shared__ __align__(16) sp_u4 s_W[kNb][kKs][P][kWave];              // F = 64, P = 3: 49,152 B: [nb][ks][piece][lane] B operands
-    __shared__ float s_bias[FO];
+    __shared__ __align__(16) char s_A[kSpWaves][P * kSpPlane];           // F = 64, P = 3: 13,056 B per wavefront
+    __shared__ __align__(16) sp_u4 s_W[kNb][kKs][P][kWave];              // F = 64, P = 3: 49,152 B: [nb][ks][piece][lane] weight operands
+    __shared__ __align__(16) float s_bias[FO];
+    __shared__ int32_t s_pending[kSpWaves][kSpPending];
 
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
+    // the wavefront's number as a scalar: the tile arithmetic below then runs on the scalar unit, and vector instructions
+    // are what this kernel is short of
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = threadIdx.x % kWave;
     const int g = l / kSpL, f = l % kSpL;
-    const int kq = l / 16, jl = l % 16;                  // matrix instruction: k block / row (A), column (B, D)
+    const int kq = l / 16, jl = l % 16;                  // matrix instruction: k block / weight column (A), tile row (B, D)
     const int64_t part = blockIdx.x % parts, j = (blockIdx.x / parts) * kSpWaves + w;
     const int64_t x_begin = part * tiles_per_part;
     const int64_t x_end = x_begin + tiles_per_part < n_tiles ? x_begin + tiles_per_part : n_tiles;
     const int64_t t_first = x_begin + j, stride = waves_per_part;
+    const int64_t n_full = n / kSpRows, x_full = x_end < n_full ? x_end : n_full;   // whole tiles
     const char *Xf = X + 16 * f;
 
-    // ---- the weights, cut once per workgroup: s_W[nb][ks][piece][lane] is the B operand of output columns
+    // ---- the weights, cut once per workgroup: s_W[nb][ks][piece][lane] is the operand of output columns
     //      16 nb .. 16 nb + 15 for k = 32 ks + 8 kq + e, e = 0..7.  The wavefronts share the (nb, ks) pairs.
     //      Every wavefront reaches this barrier (none has left yet, nothing is in flight).
     {
@@ -168,29 +173,28 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
     __syncthreads();
     if (t_first >= x_end) return;
 
-    // ---- CSR pipeline: rp_a and cc/vv belong to the next tile to be staged, rp_b to the one after
+    // ---- CSR pipeline: rp_a and cc belong to the next tile to be staged, rp_b to the one after
     int64_t rp_a = 0, rp_b = 0;
     int32_t cc[kSpH];
-    float vv[kSpH];
 #pragma unroll
-    for (int h = 0; h < kSpH; ++h) { cc[h] = 0; vv[h] = 0.f; }
-    bool fix_a = true;                                   // the tile has rows that the slots do not serve (or is ragged)
+    for (int h = 0; h < kSpH; ++h) cc[h] = 0;
+    bool fix_a = false;                                  // the tile has rows that the slots do not serve
     int32_t len_a = 0;                                   // lanes 0..kSpRows-1: stored length of the tile's row
     uint32_t live_a = 0;                                 // bit h: slot l + 64 h holds an entry
     auto load_rp = [&](int64_t tile) -> int64_t {
         const int64_t ri = tile * kSpRows + (l < kSpRows ? l : kSpRows);
-        return rowptr[ri < n ? ri : n];                  // lanes 0..kSpRows hold the pointers; rows past the end read rowptr[n]
+        return rowptr[ri < n ? ri : n];                  // lanes 0..kSpRows hold the pointers; rows past the end read rowptr[n]: no entries
     };
-    auto load_cols = [&](int64_t tile) {                 // from rp_a: every slot fetches its own entry
-        const bool full = (tile + 1) * kSpRows <= n && tile < x_end;
-        const int64_t begin = __shfl(rp_a, 0);
-        const int32_t rel = full ? (int32_t)(rp_a - begin) : 0;
+    auto load_cols = [&]() {                             // from rp_a: every slot fetches its own entry
+        const uint32_t begin_lo = __builtin_amdgcn_readfirstlane((uint32_t)rp_a);
+        const int64_t begin = (int64_t)((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)rp_a >> 32)) << 32 | begin_lo);
+        const int32_t *const tile_col = col + (begin < nnz ? begin : 0);   // a dead slot reads the tile's first entry, or entry 0
+        const int32_t rel = (int32_t)((uint32_t)rp_a - begin_lo);
         len_a = __shfl_down(rel, 1) - rel;
-        // a row with more entries than slots, or a high-degree row, has no live slot: the tile is completed by the
-        // plain path below, row by row
-        fix_a = !full || __ballot(l < kSpRows && (len_a > kSpD || len_a >= T)) != 0;
+        // a row with more entries than slots, or a high-degree row, has no live slot: the tile is left to the plain path
+        fix_a = __ballot(l < kSpRows && (len_a > kSpD || len_a >= T)) != 0;
         live_a = 0;
-        // unconditional loads (a dead slot reads entry 0): the number of loads in flight stays known
+        // unconditional loads: the number of loads in flight stays known
 #pragma unroll
         for (int h = 0; h < kSpH; ++h) {
             const int s = l + kWave * h;                 // slot s: row r, entry k
@@ -198,25 +202,17 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
             const int32_t lo = __shfl(rel, r), len = __shfl(rel, r + 1) - lo;
             const bool live = s < kSpSlots && k < len && len <= kSpD && len < T;
             live_a |= (uint32_t)live << h;
-            const int64_t i = live ? begin + lo + k : 0;
-            cc[h] = __builtin_nontemporal_load(&col[i]);
-            if (W == kExplicit) vv[h] = __builtin_nontemporal_load(&val[i]);
+            cc[h] = __builtin_nontemporal_load(&tile_col[live ? (uint32_t)(lo + k) : 0u]);
         }
     };
-    auto stage = [&]() -> bool {                         // cc, vv, live_a, len_a -> slot table and row weights; -> fix_a
+    auto stage = [&]() -> bool {                         // cc, live_a, len_a -> slot table and row weights; -> fix_a
 #pragma unroll
         for (int h = 0; h < kSpH; ++h) {
             const int s = l + kWave * h;
-            const bool live = (live_a >> h) & 1;
-            if (s < kSpSlots) {
-                const int64_t off = live ? ((int64_t)cc[h] << kRowShift) : zero_off;
-                if constexpr (W == kExplicit) s_slot[w][s] = SlotW{off, live ? vv[h] : 0.f, 0.f};
-                else s_slot[w][s] = off;
-            }
+            if (s < kSpSlots) s_slot[w][s] = ((live_a >> h) & 1) ? ((int64_t)cc[h] << kRowShift) : zero_off;
         }
         if (W == kMean && l < kSpRows) s_inv[w][l] = row_weight<kMean>(len_a);
-        if (SD && l < kSpRows) s_inv[w][l] = (float)len_a;   // exact: a row that the slots serve has few entries, and
-                                                             // a longer one has fewer than 2^24 (the plain path redoes ragged tiles)
+        if (SD && l < kSpRows) s_inv[w][l] = (float)len_a;   // exact: a row that the slots serve has few entries
         sp_wave_sync();
         return fix_a;
     };
@@ -224,104 +220,34 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
     // ---- one group: kSpRpg rows, one per lane group: the row's own features and its kSpD slots
     struct Regs {
         v4f xs[kSpD], self;
-        float ws[W == kExplicit ? kSpD : 1];
         float inv;
     };
-    Regs rr[kSpG];
-    auto issue = [&](Regs &q, int64_t tile, int grp) {
+    constexpr int kSets = D <= 6 ? kSpG : kSpG / 2;      // sweeps in flight: a whole tile (half of it: 2 % slower), or what registers allow
+    Regs rr[kSets];
+    const uint32_t x_lane = (uint32_t)g << kRowShift | 16 * f;
+    auto issue = [&](Regs &q, int64_t tile, int grp) {   // the tile whose slots are staged, a whole one
         const int lr = grp * kSpRpg + g;
-        int64_t row = tile * kSpRows + lr;
-        row = row < n ? row : n - 1;                     // past the end: any valid row, the result is not kept
         if (W == kMean || SD) q.inv = s_inv[w][lr];
 #pragma unroll
-        for (int k = 0; k < kSpD; ++k) {
-            if constexpr (W == kExplicit) {
-                const SlotW sl = s_slot[w][lr * kSpD + k];
-                q.xs[k] = *(const v4f *)(Xf + sl.off);
-                q.ws[k] = sl.w;
-            } else {
-                q.xs[k] = *(const v4f *)(Xf + s_slot[w][lr * kSpD + k]);
-            }
-        }
-        q.self = *(const v4f *)(Xf + (row << kRowShift));
+        for (int k = 0; k < kSpD; ++k) q.xs[k] = *(const v4f *)(Xf + s_slot[w][lr * kSpD + k]);
+        q.self = *(const v4f *)(X + (tile << kRowShift) * kSpRows + x_lane + ((grp * kSpRpg) << kRowShift));
     };
     auto sum = [&](const Regs &q) -> v4f {
-        v4f a = {0.f, 0.f, 0.f, 0.f};
+        v4f a = q.xs[0];
 #pragma unroll
-        for (int k = 0; k < kSpD; ++k) {
-            if (W == kExplicit) a += q.ws[k] * q.xs[k];
-            else a += q.xs[k];
-        }
+        for (int k = 1; k < kSpD; ++k) a += q.xs[k];
         if (W == kMean) a *= q.inv;
         return a;
     };
-
-    // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
-    rp_a = load_rp(t_first);
-    load_cols(t_first);
-    bool fix_cur = stage();
-    rp_a = load_rp(t_first + stride);
-    load_cols(t_first + stride);
-    rp_b = load_rp(t_first + 2 * stride);
-#pragma unroll
-    for (int grp = 0; grp < kSpG; ++grp) issue(rr[grp], t_first, grp);
-    __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): the loop's own order of loads is the only one from here on
-
     char *const a_tile = s_A[w];
-    float *const o_tile = (float *)s_A[w];               // after the products the parked tile is dead
-    for (int64_t tile = t_first; tile < x_end; tile += stride) {
-        const bool fix_next = stage();                   // CSR of the next tile -> slot table (this tile's groups are all issued)
-        rp_a = rp_b;
-        load_cols(tile + 2 * stride);
-        rp_b = load_rp(tile + 3 * stride);
-        const int64_t base = tile * kSpRows;
-        // sums of this tile -> LDS, cut into bf16 pieces; the same register set takes the rows of the next tile
+    v4f bias4[kNb];                                      // this lane's output features 16 nb + 4 kq .. + 3
 #pragma unroll
-        for (int grp = 0; grp < kSpG; ++grp) {
-            const v4f a = sum(rr[grp]);
-            sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, 4 * f, a);
-            sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, F + 4 * f, SD ? rr[grp].self * rr[grp].inv : rr[grp].self);
-            issue(rr[grp], tile + stride, grp);
-        }
-        if (fix_cur) {
-            // plain path: the rows of this tile that had no live slots (more entries than slots, high-degree, or
-            // every row of the ragged last tile), straight from global memory; high-degree sums from the side buffer
-#pragma unroll 1
-            for (int grp = 0; grp < kSpG; ++grp) {
-                const int64_t row = base + grp * kSpRpg + g;
-                const bool full = base + kSpRows <= n;
-                v4f a = {0.f, 0.f, 0.f, 0.f};
-                bool redo = false;
-                if (row < n) {
-                    const int64_t s = rowptr[row], e = rowptr[row + 1];
-                    redo = !full || e - s > kSpD || e - s >= T;
-                    if (e - s >= T) {
-                        int32_t lo = 0, hi = n_hd;       // the row's place in the list of high-degree rows
-                        while (lo < hi) {
-                            const int32_t mid = (lo + hi) / 2;
-                            if (hd_rows[mid] < row) lo = mid + 1; else hi = mid;
-                        }
-                        a = *(const v4f *)(hd_agg + ((int64_t)lo << kRowShift) + 16 * f);
-                    } else if (redo) {
-                        a = ld_row_sum<W, false, 8>(s, e, col, val, (const v4f *)X, kSpL, f);
-                    }
-                }
-                if (redo) sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, 4 * f, a);
-                if (SD && !full && row < n) {            // a ragged tile carries no row lengths: the own-row operand again
-                    const v4f own = *(const v4f *)(Xf + (row << kRowShift));
-                    sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, F + 4 * f,
-                                                  own * (float)(rowptr[row + 1] - rowptr[row]));
-                }
-            }
-        }
-        sp_wave_sync();
-        // ---- [agg | self] (16 x 2F) times [Wn; Ws] (2F x F): lane (jl, kq) reads row jl, k = 32 ks + 8 kq + 0..7
-        v4f acc[kNb];
-#pragma unroll
-        for (int nb = 0; nb < kNb; ++nb) {
-            const float bv = s_bias[16 * nb + jl];
-            acc[nb] = (v4f){bv, bv, bv, bv};
-        }
+    for (int nb = 0; nb < kNb; ++nb) bias4[nb] = *(const v4f *)&s_bias[16 * nb + 4 * kq];
+    // ---- [Wn; Ws]^T (FO x 2F) times the parked tile [agg | self]^T (2F x 16), + bias: the weights are the instruction's
+    //      first operand, so that lane (jl, kq) ends with features 16 nb + 4 kq .. + 3 of tile row jl and stores them as
+    //      they are.  (With the tile as first operand a lane holds one feature of four rows, and the result went through
+    //      LDS once more.)
+    auto multiply = [&](v4f (&acc)[kNb]) {
         const char *a_lane = a_tile + jl * kSpBRow + 16 * kq;
         // P kKs steps (ks, weight piece pb = hi, mid, lo), each against the tile pieces whose product is kept
         // (P = 3: hi with lo, mid, hi; mid with mid, hi; lo with hi.  P = 2: hi with mid, hi; mid with hi), on kNb
@@ -349,33 +275,129 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
             for (int pa = P - 1 - pb; pa >= 0; --pa)
 #pragma unroll
                 for (int nb = 0; nb < kNb; ++nb)
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(sp_bf8, aop[pa]),
-                                                                      __builtin_bit_cast(sp_bf8, bop[s_ & 1][nb]),
-                                                                      acc[nb], 0, 0, 0);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(sp_bf8, bop[s_ & 1][nb]),
+                                                                      __builtin_bit_cast(sp_bf8, aop[pa]),
+                                                                      s_ == 0 && pa == P - 1 ? bias4[nb] : acc[nb], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if (ks + 1 < kKs && pb == P - 1) read_a(ks + 1, 0);      // hi after the last step
         }
-        sp_wave_sync();                                  // all reads of the parked tile are done: its space takes the result
-        // ---- result: lane holds rows 4 kq + r of column 16 nb + jl; through LDS to whole rows per lane group
+        if (relu) {
 #pragma unroll
-        for (int nb = 0; nb < kNb; ++nb)
+            for (int nb = 0; nb < kNb; ++nb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float v = acc[nb][r];
-                if (relu) v = v > 0.0f ? v : 0.0f;
-                o_tile[(4 * kq + r) * kSpOStride + 16 * nb + jl] = v;
-            }
-        sp_wave_sync();
-#pragma unroll
-        for (int go = 0; go < C::kGo; ++go) {
-            const int lr = go * C::kRo + l / C::kLo, fo = l % C::kLo;
-            const int64_t row = base + lr;
-            const v4f v = *(const v4f *)&o_tile[lr * kSpOStride + 4 * fo];
-            char *dst = row < n ? H + (row << C::kORowShift) : trash + (lr << C::kORowShift);
-            __builtin_nontemporal_store(v, (v4f *)(dst + 16 * fo));
+                for (int r = 0; r < 4; ++r) acc[nb][r] = acc[nb][r] > 0.0f ? acc[nb][r] : 0.0f;
         }
-        sp_wave_sync();                                  // the tiles in LDS are free for the next round
-        fix_cur = fix_next;
+    };
+    // whole 128-byte lines per store instruction: neighbouring lanes (tile rows 2 i and 2 i + 1) swap half of their blocks
+    const bool odd = (jl & 1) != 0;
+    const uint32_t h_lane = (uint32_t)(kNb > 1 ? jl & ~1 : jl) << C::kORowShift | (kNb > 1 && odd ? 64 : 0) | 16 * kq;
+    auto swap1 = [](float x) -> float {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false));
+    };
+    auto store = [&](char *rows, const v4f (&acc)[kNb], int live) {   // live: rows of the tile that exist
+        if constexpr (kNb == 1) {
+            if (jl < live) __builtin_nontemporal_store(acc[0], (v4f *)(rows + h_lane));
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < kNb; nb += 2) {
+                v4f x, y;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float got = swap1(odd ? acc[nb][r] : acc[nb + 1][r]);
+                    x[r] = odd ? got : acc[nb][r];
+                    y[r] = odd ? acc[nb + 1][r] : got;
+                }
+                if ((jl & ~1) < live) __builtin_nontemporal_store(x, (v4f *)(rows + h_lane + 64 * nb));
+                if ((jl | 1) < live) __builtin_nontemporal_store(y, (v4f *)(rows + h_lane + 64 * nb + (1 << C::kORowShift)));
+            }
+        }
+    };
+
+    int64_t tile = t_first;
+    while (tile < x_end) {
+        int pending = 0;
+        if (tile < x_full) {
+            // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
+            rp_a = load_rp(tile);
+            load_cols();
+            bool fix_cur = stage();
+            rp_a = load_rp(tile + stride);
+            load_cols();
+            rp_b = load_rp(tile + 2 * stride);
+#pragma unroll
+            for (int grp = 0; grp < kSets; ++grp) issue(rr[grp], tile, grp);
+            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the loop's own order of loads is the only one from here on
+
+            for (; tile < x_full && pending < kSpPending; tile += stride) {
+                const int64_t next = tile + stride < n_full ? tile + stride : n_full - 1;
+                bool fix_next = false;
+                // sums of this tile -> LDS, cut into bf16 pieces; a register set then takes the sweep kSets later
+#pragma unroll
+                for (int grp = 0; grp < kSpG; ++grp) {
+                    if (grp == kSpG - kSets) {           // this tile's sweeps are all issued: CSR of the next tile -> slot table
+                        fix_next = stage();
+                        rp_a = rp_b;
+                        load_cols();
+                        rp_b = load_rp(tile + 3 * stride);
+                    }
+                    Regs &q = rr[grp % kSets];
+                    const v4f a = sum(q);
+                    sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, 4 * f, a);
+                    sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, F + 4 * f, SD ? q.self * q.inv : q.self);
+                    issue(q, grp + kSets < kSpG ? tile : next, (grp + kSets) % kSpG);
+                }
+                sp_wave_sync();
+                v4f acc[kNb];
+#pragma unroll
+                for (int nb = 0; nb < kNb; ++nb) acc[nb] = bias4[nb];
+                // A tile with a row that the slots do not serve is noted and stored to the trash area (a scalar select: the
+                // number of stores in flight stays known).
+                if (!fix_cur) multiply(acc);
+                store(fix_cur ? trash : H + (tile << C::kORowShift) * kSpRows, acc, kSpRows);
+                sp_wave_sync();                          // the tile in LDS is free for the next round
+                if (fix_cur) {
+                    if (l == 0) s_pending[w][pending] = (int32_t)tile;
+                    ++pending;
+                }
+                fix_cur = fix_next;
+            }
+        }
+        if (tile >= x_full && tile < x_end && pending < kSpPending) {   // the ragged last tile
+            if (l == 0) s_pending[w][pending] = (int32_t)tile;
+            ++pending;
+            tile += stride;
+        }
+        // ---- plain path: the noted tiles, every row straight from global memory, high-degree sums from the side buffer
+        sp_wave_sync();
+#pragma unroll 1
+        for (int i = 0; i < pending; ++i) {
+            const int64_t t = __builtin_amdgcn_readfirstlane(s_pending[w][i]);
+            const int64_t rp = load_rp(t);               // rows past the end: no entries
+#pragma unroll 1
+            for (int grp = 0; grp < kSpG; ++grp) {
+                const int lr = grp * kSpRpg + g;
+                const int64_t row = t * kSpRows + lr, s = __shfl(rp, lr), e = __shfl(rp, lr + 1);
+                v4f a, own = *(const v4f *)(Xf + ((row < n ? row : n - 1) << kRowShift));   // past the end: not stored
+                if (e - s >= T) {
+                    int32_t lo = 0, hi = n_hd;           // the row's place in the list of high-degree rows
+                    while (lo < hi) {
+                        const int32_t mid = (lo + hi) / 2;
+                        if (hd_rows[mid] < row) lo = mid + 1; else hi = mid;
+                    }
+                    a = *(const v4f *)(hd_agg + ((int64_t)lo << kRowShift) + 16 * f);
+                } else {
+                    a = ld_row_sum<W, false, 8>(s, e, col, val, (const v4f *)X, kSpL, f);
+                }
+                if (SD) own *= (float)(e - s);
+                sp_park<kSpBRow, kSpPlane, P>(a_tile, lr, 4 * f, a);
+                sp_park<kSpBRow, kSpPlane, P>(a_tile, lr, F + 4 * f, own);
+            }
+            sp_wave_sync();
+            v4f acc[kNb];
+            multiply(acc);
+            store(H + (t << C::kORowShift) * kSpRows, acc, n - t * kSpRows < kSpRows ? (int)(n - t * kSpRows) : kSpRows);
+            sp_wave_sync();
+        }
     }
 }
 
@@ -435,14 +457,15 @@ int launch_sage_pipe(const DevicePlan &dp, const float *X, float *H, const float
 #define GROOT_SAGE_PIPE_LAUNCH(WM, FFI, FFO, DD, PP)                                                                   \
     sage_pipe_kernel<WM, FFI, FFO, kNwRun, DD, PP, SDV><<<dim3((unsigned)n_wg), dim3(kNwRun * kWave), 0, st>>>(        \
         dp.rowptr, col_arg, val_arg, (const char *)X, (char *)H, byte_distance(X, dp.zero_row), trash, Wn, Ws, bias, relu, \
-        dp.n, dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows,         \
+        dp.n, dp.nnz, dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows,         \
         (const char *)dp.hd_agg)
 #define GROOT_SAGE_PIPE_P(WM, FFI, FFO, DD)                               \
     if (pieces == 2) GROOT_SAGE_PIPE_LAUNCH(WM, FFI, FFO, DD, 2);         \
     else GROOT_SAGE_PIPE_LAUNCH(WM, FFI, FFO, DD, 3)
 #define GROOT_SAGE_PIPE_D(WM, FFI, FFO)                                   \
     if (dp.sage_depth == 5) { GROOT_SAGE_PIPE_P(WM, FFI, FFO, 5); }       \
-    else { GROOT_SAGE_PIPE_P(WM, FFI, FFO, 6); }
+    else if (dp.sage_depth == 6) { GROOT_SAGE_PIPE_P(WM, FFI, FFO, 6); }  \
+    else { GROOT_SAGE_PIPE_P(WM, FFI, FFO, 8); }
 #define GROOT_SAGE_PIPE_FO(WM, FFI)                            \
     if (FO == 64) { GROOT_SAGE_PIPE_D(WM, FFI, 64); }          \
     else if (FO == 32) { GROOT_SAGE_PIPE_D(WM, FFI, 32); }     \

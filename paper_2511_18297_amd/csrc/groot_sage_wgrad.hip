@@ -95,7 +95,7 @@ __device__ __forceinline__ void wg_mfma_4x4(v4f (&c0)[4], v4f (&c1)[4], v4f (&c2
         : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]));
 }
 
-// W: kOnes or kMean; FI: width of X; FO: width of dZ; D: gather slots per row on the pipelined path
+// W: kOnes or kMean; FI: width of X; FO: width of dZ; D: gather slots per row on the pipelined path (5, 6 or 8)
 template <int W, int FI, int FO, int D>
 __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_eu(kWgWaves / 4, kWgWaves / 4))) void sage_wgrad_kernel(
     const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
@@ -475,11 +475,13 @@ static int wgrad_launch(const DevicePlan &dp, const float *X, const float *dZ, f
         n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows, (const char *)dp.hd_agg,    \
         (v4f *)workspace)
     if (dp.weight_mode == kMean) {
-        if (dp.wgrad_depth == 5) GROOT_WGRAD_LAUNCH(kMean, 5);
-        else GROOT_WGRAD_LAUNCH(kMean, 6);
+        if (dp.sage_depth == 5) GROOT_WGRAD_LAUNCH(kMean, 5);
+        else if (dp.sage_depth == 6) GROOT_WGRAD_LAUNCH(kMean, 6);
+        else GROOT_WGRAD_LAUNCH(kMean, 8);
     } else {
-        if (dp.wgrad_depth == 5) GROOT_WGRAD_LAUNCH(kOnes, 5);
-        else GROOT_WGRAD_LAUNCH(kOnes, 6);
+        if (dp.sage_depth == 5) GROOT_WGRAD_LAUNCH(kOnes, 5);
+        else if (dp.sage_depth == 6) GROOT_WGRAD_LAUNCH(kOnes, 6);
+        else GROOT_WGRAD_LAUNCH(kOnes, 8);
     }
 #undef GROOT_WGRAD_LAUNCH
     hipError_t err = hipGetLastError();

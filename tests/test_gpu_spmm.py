@@ -617,6 +617,33 @@ def test_weight_gradients_at_the_edges_of_the_pipeline(torch_cuda, F_in, F_out, 
         assert bool(torch.isfinite(dW).all())
 
 
+@pytest.mark.parametrize("case", ["all_noted", "lut4", "cells", "ragged"])
+def test_fused_layer_at_the_edges_of_the_pipeline(torch_cuda, case):
+    """Edges of the layer kernel's bookkeeping.  "all_noted": T = 4 makes nearly every row high-degree, so every tile is
+    noted and wavefronts have more of them (717,900 rows, 44,869 tiles over 2,048 wavefronts) than the 16 they note
+    before they must complete them.  "lut4": rows of 7 entries, 8 slots per row and half a tile in flight; "cells":
+    rows of 6.  "ragged": a last tile of 1 row, and of 15; forward layer, input gradient and weight gradients."""
+    torch = torch_cuda
+    if case == "all_noted":
+        aig, g, (rowptr, col, val, pol) = _aig_case(300, 1)
+        _sage_check(torch, g, rowptr, col, val, 4, aig.num_nodes, 41, True, True, case, F=32, F_out=16)
+    elif case in ("lut4", "cells"):
+        c = (wl.lut4_csa_graph if case == "lut4" else wl.cellmap_csa_graph)(40, 2)
+        g = G.groot_graph_from_csr(c.rowptr, c.col, c.val)
+        for F, FO in ((64, 64), (64, 16), (32, 32), (32, 64)):
+            _sage_check(torch, g, c.rowptr, c.col, c.val, 32, c.n, 42 + F, FO != 32, True, case, F=F, F_out=FO)
+            _wgrad_check(torch, g, c.rowptr, c.col, c.val, 32, c.n, 43 + F, F, F_out=FO)
+    else:
+        for n_bits, batch, left in ((15, 1, 15), (17, 1, 1)):
+            aig, g, (rowptr, col, val, pol) = _aig_case(n_bits, batch)
+            n = batch * aig.num_nodes
+            assert n % 16 == left
+            for F, FO in ((64, 64), (32, 16), (32, 32)):
+                _sage_check(torch, g, rowptr, col, val, 32, n, 44 + F, False, True, case, F=F, F_out=FO)
+                _backward_data_check(torch, g, rowptr, col, val, 32, n, 45 + F, F, FO)
+                _wgrad_check(torch, g, rowptr, col, val, 32, n, 46 + F, F, F_out=FO)
+
+
 def test_calls_that_only_enqueue_run_under_graph_capture(torch_cuda):
     """groot_spmm_execute, the fused layer, its input gradient (with groot_rows_over_degree) and its weight
     gradients only enqueue kernels and allocate nothing, so a caller may capture them into a graph: the captured
