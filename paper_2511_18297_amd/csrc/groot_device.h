@@ -68,6 +68,66 @@ __device__ __forceinline__ v4f ld_row_sum(int64_t s, int64_t e, const int32_t *_
     return acc;
 }
 
+// ---------------------------------------------------------------------------
+// HD part.  One workgroup per piece of a high-degree row (the plan cuts a row
+// into balanced pieces).  The 256/L lane groups of the workgroup stride over
+// the piece's non-zeros, each keeping a register accumulator for its float4
+// slice; the group sums meet in LDS and are added by a tree.  The result goes
+// to Y (single-piece rows) or to the row's slot of partial sums.
+// ---------------------------------------------------------------------------
+template <int L, int W>
+__device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int32_t *__restrict__ col,
+                                         const float *__restrict__ val, const v4f *__restrict__ X,
+                                         v4f *__restrict__ Y, v4f *__restrict__ partials, int32_t F4,
+                                         const int64_t *__restrict__ out_ids)
+{
+    constexpr int G = kBlock / L;
+    v4f(*s_red)[L] = (v4f(*)[L])smem;                    // [G][L]
+    const int g = threadIdx.x / L, f = threadIdx.x % L;
+    const int64_t end = ch.begin + ch.len;
+    const float rw = row_weight<W>(ch.row_nnz);
+
+    for (int32_t fb = 0; fb < F4; fb += L) {
+        const int32_t ff = fb + f;
+        const bool live = ff < F4;
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        if (live) {
+            int64_t p = ch.begin + g;
+            for (; p + 3 * G < end; p += 4 * G) {
+                int32_t c0 = col[p], c1 = col[p + G], c2 = col[p + 2 * G], c3 = col[p + 3 * G];
+                v4f x0 = X[(int64_t)c0 * F4 + ff], x1 = X[(int64_t)c1 * F4 + ff];
+                v4f x2 = X[(int64_t)c2 * F4 + ff], x3 = X[(int64_t)c3 * F4 + ff];
+                if (W == kExplicit) {
+                    acc += val[p] * x0;
+                    acc += val[p + G] * x1;
+                    acc += val[p + 2 * G] * x2;
+                    acc += val[p + 3 * G] * x3;
+                } else {
+                    acc += (x0 + x1) + (x2 + x3);
+                }
+            }
+            for (; p < end; p += G) {
+                v4f x = X[(int64_t)col[p] * F4 + ff];
+                if (W == kExplicit) acc += val[p] * x;
+                else acc += x;
+            }
+            if (W != kExplicit) acc *= rw;
+        }
+        s_red[g][f] = acc;
+        __syncthreads();
+#pragma unroll
+        for (int stride = G / 2; stride > 0; stride /= 2) {
+            if (g < stride) s_red[g][f] += s_red[g + stride][f];
+            __syncthreads();
+        }
+        if (g == 0 && live) {
+            v4f sum = s_red[0][f];
+            if (ch.slot < 0) Y[(out_ids ? out_ids[ch.row] : (int64_t)ch.row) * F4 + ff] = sum;
+            else partials[(int64_t)ch.slot * F4 + ff] = sum;
+        }
+        __syncthreads();
+    }
+}
 
 #define GROOT_DISPATCH_L(L, CALL)        \
     switch (L) {                         \

@@ -681,8 +681,9 @@ extern "C" groot_status groot_spmm_execute_phases(const groot_plan *plan, const 
     const int64_t x_bytes = plan->dev.n_cols * (int64_t)F * 4, y_bytes = plan->dev.n * (int64_t)F * 4;
     if (a < b + y_bytes && b < a + x_bytes) return fail(GROOT_EINVAL, "groot_spmm_execute: X and Y overlap");
     int err = 0;
-    if (!err && (phases & GROOT_PHASE_LD)) err = launch_ld(plan->dev, X_dev, Y_dev, F, hip_stream);
-    if (!err && (phases & GROOT_PHASE_HD) && plan->dev.n_chunks) err = launch_hd(plan->dev, X_dev, Y_dev, F, hip_stream);
+    const bool together = (phases & GROOT_PHASE_LD) && (phases & GROOT_PHASE_HD) && ld_takes_hd(plan->dev, F);
+    if (!err && (phases & GROOT_PHASE_LD)) err = launch_ld(plan->dev, X_dev, Y_dev, F, hip_stream, nullptr, together);
+    if (!err && !together && (phases & GROOT_PHASE_HD) && plan->dev.n_chunks) err = launch_hd(plan->dev, X_dev, Y_dev, F, hip_stream);
     if (!err && (phases & GROOT_PHASE_FINISH) && plan->dev.n_split_rows) err = launch_hd_finish(plan->dev, Y_dev, F, hip_stream);
     if (err) return fail(GROOT_EHIP, std::string("groot_spmm_execute: launch failed: ") + hip_error_text(err));
     return GROOT_OK;
@@ -699,8 +700,9 @@ extern "C" groot_status groot_spmm_execute_rows(const groot_plan *plan, const fl
     if (n_rows < 0 || n_rows > plan->dev.n) return fail(GROOT_EINVAL, "groot_spmm_execute_rows: n_rows outside [0, N]");
     if (n_rows == 0) return GROOT_OK;
     const RowOut out{out_ids_dev, n_rows};
-    int err = launch_ld(plan->dev, X_dev, Y_dev, F, hip_stream, &out);
-    if (!err && plan->dev.n_chunks) err = launch_hd(plan->dev, X_dev, Y_dev, F, hip_stream, &out);
+    const bool together = ld_takes_hd(plan->dev, F, &out);
+    int err = launch_ld(plan->dev, X_dev, Y_dev, F, hip_stream, &out, together);
+    if (!err && !together && plan->dev.n_chunks) err = launch_hd(plan->dev, X_dev, Y_dev, F, hip_stream, &out);
     if (!err && plan->dev.n_split_rows) err = launch_hd_finish(plan->dev, Y_dev, F, hip_stream, &out);
     if (err) return fail(GROOT_EHIP, std::string("groot_spmm_execute_rows: launch failed: ") + hip_error_text(err));
     return GROOT_OK;

@@ -100,8 +100,9 @@ constexpr int kCodeNear = 0x4000;     // column codes below kCodeHot: row + code
 constexpr int kCodeHot = 0x8000;      // codes from here on: index into the hot list
 constexpr int kCodeBad = 0xFFFF;      // an entry that no code can express: its row is not served in compact form
 constexpr int kCodeMaxHot = 0x7FFF;
+constexpr int kHdBesideLd = 1024;     // pieces of high-degree rows up to which they join the low-degree rows' launch
 constexpr int kPipeMinDepth = 5, kPipeMaxDepth = 8;   // gather slots per row the pipelined LD kernel is built for
-constexpr int kZeroRowFloats = 128;
+constexpr int kZeroRowFloats = 256;     // a row of the widest matrix that the pipelined kernels serve
 constexpr int kTrashFloats = 2048;
 constexpr int kRowsPerLdTile = 256;   // rows of one LD block (4 wavefronts x 64 rows)
 
@@ -113,9 +114,12 @@ struct RowOut {
 };
 
 // Kernel launchers (groot_kernels.hip).  Return hipError_t as int (0 = success).
-int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out = nullptr);
+// with_hd: the pieces of the high-degree rows in the same launch (only where ld_takes_hd says so), launch_hd is then not called
+int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out = nullptr,
+              bool with_hd = false);
+bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out = nullptr);
 int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream,
-                        const RowOut *out = nullptr);   // F = 32, 64, 128
+                        const RowOut *out, bool with_hd);   // F up to 256; with out F = 32, 64, 128
 int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out = nullptr);
 int launch_hd_finish(const DevicePlan &dp, float *Y, int32_t F, void *stream, const RowOut *out = nullptr);
 int launch_sage(const DevicePlan &dp, const float *X, float *H, const float *Wn, const float *Ws, const float *bias,

@@ -77,67 +77,6 @@ __device__ __forceinline__ void ld_tile(char *smem, int64_t tile, const int64_t 
     }
 }
 
-// ---------------------------------------------------------------------------
-// HD part.  One workgroup per piece of a high-degree row (the plan cuts a row
-// into balanced pieces).  The 256/L lane groups of the workgroup stride over
-// the piece's non-zeros, each keeping a register accumulator for its float4
-// slice; the group sums meet in LDS and are added by a tree.  The result goes
-// to Y (single-piece rows) or to the row's slot of partial sums.
-// ---------------------------------------------------------------------------
-template <int L, int W>
-__device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int32_t *__restrict__ col,
-                                         const float *__restrict__ val, const v4f *__restrict__ X,
-                                         v4f *__restrict__ Y, v4f *__restrict__ partials, int32_t F4,
-                                         const int64_t *__restrict__ out_ids)
-{
-    constexpr int G = kBlock / L;
-    v4f(*s_red)[L] = (v4f(*)[L])smem;                    // [G][L]
-    const int g = threadIdx.x / L, f = threadIdx.x % L;
-    const int64_t end = ch.begin + ch.len;
-    const float rw = row_weight<W>(ch.row_nnz);
-
-    for (int32_t fb = 0; fb < F4; fb += L) {
-        const int32_t ff = fb + f;
-        const bool live = ff < F4;
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        if (live) {
-            int64_t p = ch.begin + g;
-            for (; p + 3 * G < end; p += 4 * G) {
-                int32_t c0 = col[p], c1 = col[p + G], c2 = col[p + 2 * G], c3 = col[p + 3 * G];
-                v4f x0 = X[(int64_t)c0 * F4 + ff], x1 = X[(int64_t)c1 * F4 + ff];
-                v4f x2 = X[(int64_t)c2 * F4 + ff], x3 = X[(int64_t)c3 * F4 + ff];
-                if (W == kExplicit) {
-                    acc += val[p] * x0;
-                    acc += val[p + G] * x1;
-                    acc += val[p + 2 * G] * x2;
-                    acc += val[p + 3 * G] * x3;
-                } else {
-                    acc += (x0 + x1) + (x2 + x3);
-                }
-            }
-            for (; p < end; p += G) {
-                v4f x = X[(int64_t)col[p] * F4 + ff];
-                if (W == kExplicit) acc += val[p] * x;
-                else acc += x;
-            }
-            if (W != kExplicit) acc *= rw;
-        }
-        s_red[g][f] = acc;
-        __syncthreads();
-#pragma unroll
-        for (int stride = G / 2; stride > 0; stride /= 2) {
-            if (g < stride) s_red[g][f] += s_red[g + stride][f];
-            __syncthreads();
-        }
-        if (g == 0 && live) {
-            v4f sum = s_red[0][f];
-            if (ch.slot < 0) Y[(out_ids ? out_ids[ch.row] : (int64_t)ch.row) * F4 + ff] = sum;
-            else partials[(int64_t)ch.slot * F4 + ff] = sum;
-        }
-        __syncthreads();
-    }
-}
-
 // Block t of the LD launch computes the tile of rows [256 t, 256 t + 256).
 template <int L, int W>
 __global__ __launch_bounds__(kBlock) void ld_kernel(const int64_t *__restrict__ rowptr,
@@ -231,14 +170,28 @@ static int lanes_for(int32_t F4)
     default: { constexpr int kW = kExplicit; GROOT_DISPATCH_L(L, CALL) } break; \
     }
 
-int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out)
+// The pipelined kernel serves the leading rows of a graph at F = 32, 64 and 128, whole graphs also at the widths between:
+// from 20 on with 5 or 6 slots per row (512-bit multiplier, plain against pipelined kernel: F = 16 107 and 105 us with more than
+// twice the time at 8, F = 20 145 and 122, F = 100 ... 200 a quarter less), from 36 on with 7 or 8 (4-LUT shape: F = 20 55 and
+// 62 us, F = 36 88 and 88, F = 124 257 and 233), up to 256 (64 lanes of one float4).
+static bool ld_pipelined(const DevicePlan &dp, int32_t F4, const RowOut *out)
+{
+    if (!dp.zero_row || !dp.ld_pipelined) return false;
+    return F4 == 8 || F4 == 16 || F4 == 32 || (!out && F4 <= kWave && F4 > (dp.pipe_depth <= 6 ? 4 : 8));
+}
+
+bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out)
+{
+    return ld_pipelined(dp, F / 4, out) && dp.n_chunks > 0 && dp.n_chunks <= kHdBesideLd;
+}
+
+int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out, bool with_hd)
 {
     const int32_t F4 = F / 4;
     const int64_t *out_ids = out ? out->ids : nullptr;
     const int64_t n_out = out ? out->n_out : dp.n;
-    // the pipelined kernel serves whole graphs at F = 32, 64 and 128 (ld_pipelined: 2 all three widths, 1 only the two wider)
-    if (dp.zero_row && ((dp.ld_pipelined == 2 && F4 == 8) || (dp.ld_pipelined && (F4 == 16 || F4 == 32))))
-        return launch_ld_pipelined(dp, X, Y, F, stream, out);
+    if (ld_pipelined(dp, F4, out)) return launch_ld_pipelined(dp, X, Y, F, stream, out, with_hd);
+    if (with_hd) return (int)hipErrorInvalidValue;
     const int64_t n_tiles = (n_out + kRowsPerLdTile - 1) / kRowsPerLdTile;
     if (n_tiles == 0) return 0;
     const int64_t per_xcd = (n_tiles + kXcds - 1) / kXcds;

@@ -36,7 +36,7 @@ constexpr int kPipeWaves = 4;                // wavefronts per workgroup, one wo
 // 4 / 5 / 6 / 7 / 8 (with both matrices in one class of address ranges 5 was the best: 16.9 / 14.4 / 14.2 / 13.7 /
 // 14.0 / 13.8 / 13.9 ms for 2..8); 8 lanes (F = 32): 6.46 / 6.36 ms for 5 / 7; 32 lanes (F = 128): 31.0 / 30.5 /
 // 31.3 ms per step for 5 / 7 / 8
-constexpr int pipe_groups(int) { return 7; }
+constexpr int pipe_groups(int L) { return L == 4 ? 3 : 7; }   // 4 lanes per row: as many as row pointers fit one wavefront
 
 __device__ __forceinline__ void pipe_wave_sync()
 {
@@ -48,6 +48,19 @@ __device__ __forceinline__ void pipe_wave_sync()
 // The compact form of the CSR (C = true: 4-byte row pointers, 2-byte column codes, the list of high-degree
 // rows that a code can name; see groot_compress.hip) replaces the loads of the pipeline; the plain path and the
 // row-list kernel keep reading the full arrays.
+// What a launch does beside the sweep, in workgroups of their own behind it: the low-degree rows that the pipeline masks,
+// one lane group per row, and, where the plan has few of them (kHdBesideLd), the pieces of the high-degree rows.  On small
+// graphs the launches were most of the time: 32-bit multiplier, F = 32, three kernels of 10 + 3.5 + 3.4 us, now one of 8.0;
+// 256-bit, F = 64, 48 + 7.6 + 5 and the gaps (75 us), now one of 48 (65 us).  A graph of many pieces keeps the kernel of
+// their own: it wants all wavefronts of a CU, this one has registers for one or two per SIMD.
+struct SideWork {
+    int64_t n_ld;                            // workgroups of the sweep
+    const int32_t *rows;                     // the row list
+    int64_t n_rows, n_row_wg;
+    const HdChunk *chunks;                   // one workgroup per piece
+    float *partials;
+};
+
 struct CompactCsr {
     const uint32_t *rp32;
     const uint16_t *col16;
@@ -57,31 +70,56 @@ struct CompactCsr {
 
 // M: the sum of row r goes to row out_ids[r] of Y (the owned rows of a part written into place in the matrix of
 // the whole graph); n is then the number of leading rows that are wanted.  Only without the compact matrix.
-template <int L, int W, int G, int D, bool C, bool M = false>
+// S: rows of F4 float4, any number up to L (otherwise F4 = L): the lanes past a row's end do what the lane of its last
+// float4 does, and store the same value to the same place (a trash area for them made a hot spot of it: 4-LUT shape,
+// 0.5 M rows, F = 124: 574 us, now 233).
+// The workgroups behind the first n_ld of the grid compute the rows of the row list, then (n_hd of them) the pieces of the
+// high-degree rows: see SideWork.
+template <int L, int W, int G, int D, bool C, bool M = false, bool S = false>
 __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per_eu(1, 2))) void ld_pipe_kernel(
     const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
     const CompactCsr cz, const char *__restrict__ X, char *__restrict__ Y, int64_t zero_off, char *trash, int64_t n,
     int32_t T, int64_t n_tiles, int64_t tiles_per_part, int64_t waves_per_part, int32_t parts,
-    const int64_t *__restrict__ out_ids)
+    const int64_t *__restrict__ out_ids, int32_t F4, const SideWork side)
 {
-    static_assert(!(C && M), "the row-mapped form reads the plain arrays");
+    static_assert(!(C && M) && !(S && M), "the row-mapped form reads the plain arrays and has rows of L float4");
     constexpr int kRpg = kWave / L;                      // rows per lane group sweep
     constexpr int kTileRows = G * kRpg;
     constexpr int kPipeD = D;                            // slots per row
     constexpr int kSlots = kTileRows * kPipeD, kH = (kSlots + kWave - 1) / kWave;
-    constexpr int kRowShift = L == 8 ? 7 : L == 16 ? 8 : 9;   // log2 of a feature row's bytes
-    static_assert(L == 8 || L == 16 || L == 32, "one float4 per lane");
+    constexpr int kRowShift = L == 4 ? 6 : L == 8 ? 7 : L == 16 ? 8 : L == 32 ? 9 : 10;   // log2 of a feature row's bytes
+    static_assert(L == 4 || L == 8 || L == 16 || L == 32 || L == 64, "one float4 per lane");
+    auto row_bytes = [&](int64_t row) -> int64_t { return S ? row * (F4 * 16) : row << kRowShift; };
     static_assert(kTileRows + 1 <= kWave, "row pointers of a tile fit one wavefront");
     // a slot: byte offset of the gathered row from X; with explicit weights the entry's weight rides in the
     // same 16-byte slot, so that one LDS read per slot serves both
     struct SlotW { int64_t off; float w; float pad; };
     using Slot = typename std::conditional<W == kExplicit, SlotW, int64_t>::type;
-    __shared__ __align__(16) Slot s_slot[kPipeWaves][kSlots];
+    constexpr int kSlotBytes = kPipeWaves * kSlots * (int)sizeof(Slot), kRedBytes = kBlock * (int)sizeof(v4f);
+    __shared__ __align__(16) char s_buf[kSlotBytes > kRedBytes ? kSlotBytes : kRedBytes];
+    Slot (*const s_slot)[kSlots] = (Slot(*)[kSlots])s_buf;
     __shared__ float s_inv[kPipeWaves][kTileRows];       // row weight (1 unless W == kMean), or -1: the row is masked
     __shared__ int64_t s_oid[M ? kPipeWaves : 1][M ? kTileRows : 1];   // M: byte offset of the row's place in Y
 
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
-    const int g = l / L, f = l % L;
+    if (blockIdx.x >= side.n_ld) {
+        const int64_t b = blockIdx.x - side.n_ld;
+        if (b < side.n_row_wg) {
+            const int64_t k = b * (kBlock / L) + threadIdx.x / L;
+            const int ff = threadIdx.x % L;
+            if (k >= side.n_rows || ff >= F4) return;
+            const int64_t row = side.rows[k];
+            if (row >= n) return;                        // a row that is not wanted (row-mapped calls: boundary rows)
+            __builtin_nontemporal_store(ld_row_sum<W, false>(rowptr[row], rowptr[row + 1], col, val, (const v4f *)X, F4, ff),
+                                        (v4f *)Y + (M ? out_ids[row] : row) * F4 + ff);
+        } else {
+            const HdChunk ch = side.chunks[b - side.n_row_wg];
+            if (ch.row >= n) return;                     // the whole workgroup
+            hd_piece<L, W>(s_buf, ch, col, val, (const v4f *)X, (v4f *)Y, (v4f *)side.partials, F4, M ? out_ids : nullptr);
+        }
+        return;
+    }
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = threadIdx.x % kWave;
+    const int g = l / L, f = S ? (l % L < F4 ? l % L : F4 - 1) : l % L;
     // Part x (an XCD) owns tiles [x TP, (x+1) TP); its wavefronts take them round-robin, so that the
     // part sweeps a narrow window of rows at any time.
     const int64_t part = blockIdx.x % parts, j = (blockIdx.x / parts) * kPipeWaves + w;
@@ -89,12 +127,6 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     const int64_t x_end = x_begin + tiles_per_part < n_tiles ? x_begin + tiles_per_part : n_tiles;
     const int64_t t_first = x_begin + j, stride = waves_per_part;
     extern __shared__ int32_t s_hot[];                   // C: the hot list (at least one element)
-    if constexpr (C) {
-        for (int i = threadIdx.x; i < cz.n_hot; i += kPipeWaves * kWave) s_hot[i] = cz.hot[i];
-        if (threadIdx.x == 0 && cz.n_hot == 0) s_hot[0] = 0;
-        __syncthreads();                                 // every wavefront gets here: none has left, nothing is in flight
-    }
-    if (t_first >= x_end) return;
     const char *Xf = X + 16 * f;
 
     // ---- CSR pipeline: rp_a and cc/vv belong to the next tile to be staged, rp_b to the one after
@@ -159,7 +191,7 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
                 c = c >= kCodeHot ? hot_c : base_a + s / kPipeD + c - kCodeNear;
             }
             if (s < kSlots) {
-                const int64_t off = live ? ((int64_t)c << kRowShift) : zero_off;
+                const int64_t off = live ? row_bytes(c) : zero_off;
                 if constexpr (W == kExplicit) s_slot[w][s] = SlotW{off, live ? vv[h] : 0.f, 0.f};
                 else s_slot[w][s] = off;
             }
@@ -219,18 +251,28 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     };
 
     char *const tbase = trash + 16 * f;
+    int64_t rp_first = 0;
+    if (t_first < x_end) rp_first = load_rp(t_first);    // on its way while the hot list is copied
+    if constexpr (C) {
+        for (int i = threadIdx.x; i < cz.n_hot; i += kPipeWaves * kWave) s_hot[i] = cz.hot[i];
+        if (threadIdx.x == 0 && cz.n_hot == 0) s_hot[0] = 0;
+        __syncthreads();                                 // every wavefront of the sweep gets here: none has left
+    }
+    if (t_first >= x_end) return;
     // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
-    rp_a = load_rp(t_first);
+    rp_a = rp_first;
     oid_a = load_oid(t_first);
     load_cols(t_first);
+    rp_b = load_rp(t_first + stride);                    // arrives with the columns
+    oid_b = load_oid(t_first + stride);
     bool ok_cur = stage();
-    rp_a = load_rp(t_first + stride);
-    oid_a = load_oid(t_first + stride);
+#pragma unroll
+    for (int grp = 0; grp < G; ++grp) issue(rr[grp], grp);
+    rp_a = rp_b;
+    oid_a = oid_b;
     load_cols(t_first + stride);
     rp_b = load_rp(t_first + 2 * stride);
     oid_b = load_oid(t_first + 2 * stride);
-#pragma unroll
-    for (int grp = 0; grp < G; ++grp) issue(rr[grp], grp);
     // Everything above has arrived before the loop starts: the loop's own order of loads is then the
     // only one the compiler has to account for at the loop head, and its waits stay exact.
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
@@ -243,14 +285,14 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
         rp_b = load_rp(tile + 3 * stride);
         oid_b = load_oid(tile + 3 * stride);
         const int64_t base = tile * kTileRows;
-        char *const ybase = Y + (base << kRowShift) + 16 * f;
+        char *const ybase = Y + row_bytes(base) + 16 * f;
 #pragma unroll
         for (int grp = 0; grp < G; ++grp) {
             const v4f a = sum(rr[grp]);
-            const int roff = (grp * kRpg + g) << kRowShift;
+            const int lr = grp * kRpg + g;
             // a masked row (every row of a tile that is not ok) goes to the trash area: a select, no branch
-            char *const yrow = M ? Y + rr[grp].oid + 16 * f : ybase + roff;
-            char *const dst = rr[grp].inv >= 0.f ? yrow : tbase + roff;
+            char *const yrow = M ? Y + rr[grp].oid + 16 * f : ybase + (int)row_bytes(lr);
+            char *const dst = rr[grp].inv >= 0.f ? yrow : tbase + (lr << kRowShift);
             __builtin_nontemporal_store(a, (v4f *)dst);
             issue(rr[grp], grp);                         // the same rows of the next tile
         }
@@ -262,32 +304,13 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
                 if (row < n) {
                     const int64_t s = rowptr[row], e = rowptr[row + 1];
                     if (e - s < T && e - s <= kPipeD)
-                        __builtin_nontemporal_store(ld_row_sum<W, false>(s, e, col, val, (const v4f *)X, L, f),
-                                                    (v4f *)(Y + ((M ? out_ids[row] : row) << kRowShift) + 16 * f));
+                        __builtin_nontemporal_store(ld_row_sum<W, false>(s, e, col, val, (const v4f *)X, S ? F4 : L, f),
+                                                    (v4f *)(Y + row_bytes(M ? out_ids[row] : row) + 16 * f));
                 }
             }
         }
         ok_cur = ok_next;
     }
-}
-
-// Low-degree rows that are longer than the pipeline's slots, by list: one lane group per row.
-template <int L, int W>
-__global__ __launch_bounds__(kBlock) void ld_rows_kernel(const int32_t *__restrict__ rows, int64_t n_rows,
-                                                         const int64_t *__restrict__ rowptr,
-                                                         const int32_t *__restrict__ col, const float *__restrict__ val,
-                                                         const v4f *__restrict__ X, v4f *__restrict__ Y, int32_t F4,
-                                                         const int64_t *__restrict__ out_ids, int64_t n_out)
-{
-    constexpr int G = kBlock / L;
-    const int64_t k = (int64_t)blockIdx.x * G + threadIdx.x / L;
-    if (k >= n_rows) return;
-    const int64_t row = rows[k];
-    if (row >= n_out) return;                            // a row that is not wanted (row-mapped calls: boundary rows)
-    const int64_t s = rowptr[row], e = rowptr[row + 1];
-    const int64_t orow = out_ids ? out_ids[row] : row;
-    for (int32_t ff = threadIdx.x % L; ff < F4; ff += L)
-        __builtin_nontemporal_store(ld_row_sum<W, false>(s, e, col, val, X, F4, ff), &Y[orow * F4 + ff]);
 }
 
 struct PipeArgs {
@@ -307,24 +330,44 @@ struct PipeArgs {
     int64_t n_wg;
     hipStream_t st;
     const int64_t *out_ids;                  // row-mapped form, else NULL
+    int32_t F4;                              // float4 per row
+    SideWork side;
+    int64_t n_hd;                            // pieces of high-degree rows in this launch
 };
 
 template <int L, int W, int G, int D>
 static void pipe_launch(const PipeArgs &a)
 {
+    const dim3 grid((unsigned)(a.n_wg + a.side.n_row_wg + a.n_hd));
     if (a.out_ids) {
-        ld_pipe_kernel<L, W, G, D, false, true><<<dim3((unsigned)a.n_wg), dim3(kPipeWaves * kWave), 0, a.st>>>(
+        ld_pipe_kernel<L, W, G, D, false, true><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, a.out_ids);
+            a.waves_per_part, a.parts, a.out_ids, a.F4, a.side);
     } else if (a.compact) {
         const size_t lds = (size_t)(a.cz.n_hot ? a.cz.n_hot : 1) * sizeof(int32_t);
-        ld_pipe_kernel<L, W, G, D, true><<<dim3((unsigned)a.n_wg), dim3(kPipeWaves * kWave), lds, a.st>>>(
+        ld_pipe_kernel<L, W, G, D, true><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, nullptr);
+            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
     } else {
-        ld_pipe_kernel<L, W, G, D, false><<<dim3((unsigned)a.n_wg), dim3(kPipeWaves * kWave), 0, a.st>>>(
+        ld_pipe_kernel<L, W, G, D, false><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, nullptr);
+            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
+    }
+}
+
+template <int L, int W, int G, int D>
+static void pipe_launch_any(const PipeArgs &a)
+{
+    const dim3 grid((unsigned)(a.n_wg + a.side.n_row_wg + a.n_hd));
+    if (a.compact) {
+        const size_t lds = (size_t)(a.cz.n_hot ? a.cz.n_hot : 1) * sizeof(int32_t);
+        ld_pipe_kernel<L, W, G, D, true, false, true><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
+            a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
+            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
+    } else {
+        ld_pipe_kernel<L, W, G, D, false, false, true><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
+            a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
+            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
     }
 }
 
@@ -333,7 +376,12 @@ static void pipe_dispatch_l(int32_t F4, const PipeArgs &a)
 {
     if (F4 == 8) pipe_launch<8, W, pipe_groups(8), D>(a);
     else if (F4 == 16) pipe_launch<16, W, pipe_groups(16), D>(a);
-    else pipe_launch<32, W, pipe_groups(32), D>(a);
+    else if (F4 == 32) pipe_launch<32, W, pipe_groups(32), D>(a);
+    else if (F4 <= 4) pipe_launch_any<4, W, pipe_groups(4), D>(a);
+    else if (F4 < 8) pipe_launch_any<8, W, pipe_groups(8), D>(a);
+    else if (F4 < 16) pipe_launch_any<16, W, pipe_groups(16), D>(a);
+    else if (F4 < 32) pipe_launch_any<32, W, pipe_groups(32), D>(a);
+    else pipe_launch_any<64, W, pipe_groups(64), D>(a);
 }
 
 template <int W>
@@ -350,18 +398,23 @@ static void pipe_dispatch_d(int depth, int32_t F4, const PipeArgs &a)
 // The compact form keeps the hot list in dynamic LDS, up to 128 KB: the runtime wants to be told once per
 // kernel that more than its default limit may be asked for.  Called when a plan gets its compact CSR (not at
 // launch, which may be under stream capture).
-template <int L, int W, int D>
+template <int L, int W, int D, bool S>
 static int pipe_allow_lds()
 {
-    return (int)hipFuncSetAttribute((const void *)&ld_pipe_kernel<L, W, pipe_groups(L), D, true>,
+    return (int)hipFuncSetAttribute((const void *)&ld_pipe_kernel<L, W, pipe_groups(L), D, true, false, S>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kCodeMaxHot * (int)sizeof(int32_t));
 }
 template <int W, int D>
 static int pipe_allow_lds_l()
 {
-    int err = pipe_allow_lds<8, W, D>();
-    if (!err) err = pipe_allow_lds<16, W, D>();
-    if (!err) err = pipe_allow_lds<32, W, D>();
+    int err = pipe_allow_lds<8, W, D, false>();
+    if (!err) err = pipe_allow_lds<16, W, D, false>();
+    if (!err) err = pipe_allow_lds<32, W, D, false>();
+    if (!err) err = pipe_allow_lds<4, W, D, true>();
+    if (!err) err = pipe_allow_lds<8, W, D, true>();
+    if (!err) err = pipe_allow_lds<16, W, D, true>();
+    if (!err) err = pipe_allow_lds<32, W, D, true>();
+    if (!err) err = pipe_allow_lds<64, W, D, true>();
     return err;
 }
 template <int W>
@@ -386,14 +439,14 @@ int pipe_compact_prepare()
 }
 
 // out: the leading out->n_out rows only, row r written to row out->ids[r] of Y (ids NULL: to row r)
-int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out)
+int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out, bool with_hd)
 {
     const int64_t n_rows = out ? out->n_out : dp.n;
     const int64_t *out_ids = out ? out->ids : nullptr;
     if (n_rows < 0 || n_rows > dp.n) return (int)hipErrorInvalidValue;
     if (n_rows == 0) return 0;
     const int32_t F4 = F / 4;
-    if (F4 != 8 && F4 != 16 && F4 != 32) return (int)hipErrorInvalidValue;
+    if (F4 < 1 || F4 > kWave || (out && F4 != 8 && F4 != 16 && F4 != 32)) return (int)hipErrorInvalidValue;
     if (!weights_ok(dp) || !dp.zero_row) return (int)hipErrorInvalidValue;
     if (dp.pipe_depth < kPipeMinDepth || dp.pipe_depth > kPipeMaxDepth) return (int)hipErrorInvalidValue;
     if (dp.n_mid_rows && !dp.mid_rows) return (int)hipErrorInvalidValue;
@@ -402,13 +455,17 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     if (e != hipSuccess) return (int)e;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return (int)e;
-    const int tile_rows = pipe_groups(F4) * (kWave / F4);
+    int L = 4;                                           // lanes per row
+    while (L < F4) L *= 2;
+    const int tile_rows = pipe_groups(L) * (kWave / L);
     const int64_t n_tiles = (n_rows + tile_rows - 1) / tile_rows;
     // one workgroup per CU; consecutive workgroup ids land on different XCDs
     int64_t n_wg = cus / kXcds * kXcds;
     if (n_wg < kXcds) n_wg = kXcds;
     const int32_t parts = dp.xcd_remap ? kXcds : 1;
     const int64_t tiles_per_part = (n_tiles + parts - 1) / parts;
+    const int64_t wanted = (tiles_per_part + kPipeWaves - 1) / kPipeWaves * parts;   // a small graph: a wavefront per tile
+    n_wg = wanted < n_wg ? wanted : n_wg / parts * parts;
     const int64_t waves_per_part = n_wg / parts * kPipeWaves;
     if (!grid_ok(n_wg) || n_tiles <= 0) return (int)hipErrorInvalidConfiguration;
     // the kernel reads entry 0 of the index (and weight) array from idle lanes: give it something to read
@@ -421,24 +478,17 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     hipStream_t st = (hipStream_t)stream;
     // the compact matrix codes rows that the row list serves as uncoded, which only holds for whole-graph calls
     const bool compact = !out && dp.compressed && dp.rp32 && dp.col16 && dp.hot_cols;
-    const PipeArgs a{dp.rowptr, col_arg, val_arg, CompactCsr{dp.rp32, dp.col16, dp.hot_cols, dp.n_hot}, compact,
-                     (const char *)X, (char *)Y, byte_distance(X, dp.zero_row), trash, n_rows,
-                     dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, n_wg, st, out_ids};
-    GROOT_DISPATCH_W(dp.weight_mode, (pipe_dispatch_d<kW>(dp.pipe_depth, F4, a)));
-    hipError_t err = hipGetLastError();
     // the low-degree rows with more entries than the pipeline has slots; the rows that the compact matrix cannot
     // code stand at the end of the list and are the pipeline's own whenever it reads the plain arrays
     const int64_t n_mid = compact ? dp.n_mid_rows : dp.n_mid_rows - dp.n_bad_rows;
-    if (err != hipSuccess || n_mid <= 0) return (int)err;
-    const int64_t grid = (n_mid + kBlock / F4 - 1) / (kBlock / F4);
-    if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
-    GROOT_DISPATCH_W(dp.weight_mode,
-                     (F4 == 8 ? ld_rows_kernel<8, kW><<<dim3((unsigned)grid), dim3(kBlock), 0, st>>>(
-                                    dp.mid_rows, n_mid, dp.rowptr, col_arg, val_arg, (const v4f *)X, (v4f *)Y, F4, out_ids, n_rows)
-                      : F4 == 16 ? ld_rows_kernel<16, kW><<<dim3((unsigned)grid), dim3(kBlock), 0, st>>>(
-                                       dp.mid_rows, n_mid, dp.rowptr, col_arg, val_arg, (const v4f *)X, (v4f *)Y, F4, out_ids, n_rows)
-                                 : ld_rows_kernel<32, kW><<<dim3((unsigned)grid), dim3(kBlock), 0, st>>>(
-                                       dp.mid_rows, n_mid, dp.rowptr, col_arg, val_arg, (const v4f *)X, (v4f *)Y, F4, out_ids, n_rows)));
+    const int64_t n_row_wg = n_mid > 0 ? (n_mid + kBlock / L - 1) / (kBlock / L) : 0;
+    const int64_t n_hd = with_hd ? dp.n_chunks : 0;
+    if (!grid_ok(n_wg + n_row_wg + n_hd)) return (int)hipErrorInvalidConfiguration;
+    const PipeArgs a{dp.rowptr, col_arg, val_arg, CompactCsr{dp.rp32, dp.col16, dp.hot_cols, dp.n_hot}, compact,
+                     (const char *)X, (char *)Y, byte_distance(X, dp.zero_row), trash, n_rows,
+                     dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, n_wg, st, out_ids, F4,
+                     SideWork{n_wg, dp.mid_rows, n_mid, n_row_wg, dp.chunks, dp.partials}, n_hd};
+    GROOT_DISPATCH_W(dp.weight_mode, (pipe_dispatch_d<kW>(dp.pipe_depth, F4, a)));
     return (int)hipGetLastError();
 }
 

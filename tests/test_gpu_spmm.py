@@ -239,6 +239,40 @@ def test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit):
     assert_close_to_oracle(Y, Y64, S, f"mixed rows max_len={max_len} T={T} F={F}")
 
 
+@pytest.mark.parametrize("max_len,T,F,explicit", [(5, 32, 20, False), (6, 9, 28, True), (8, 32, 36, False), (8, 32, 60, True),
+                                                   (7, 32, 124, False), (5, 6, 132, True), (5, 32, 252, False),
+                                                   (8, 4, 256, True), (40, 16, 100, False), (4, 4, 48, False)])
+def test_mixed_row_lengths_at_other_widths(torch_cuda, max_len, T, F, explicit):
+    """The same at widths that fill no power of two of lanes (the lanes past a row's end double its last one), with 5 to 8
+    slots per row, and with the high-degree rows in the low-degree launch (T = 9 with rows up to 6: none at all) or in
+    one of their own (thousands of pieces)."""
+    test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit)
+
+
+@pytest.mark.parametrize("pieces", [1023, 1024, 1025])
+def test_high_degree_rows_beside_the_low_degree_ones(torch_cuda, pieces):
+    """Around the number of pieces up to which the high-degree rows ride in the low-degree rows' launch: 600 rows of two
+    pieces and the rest of one, the first row and the last among them, next to rows of 1 to 4 entries."""
+    n, T = 9000, 32
+    split = pieces - 600
+    rng = np.random.default_rng(pieces)
+    deg = rng.integers(1, 5, size=n)
+    heavy = np.unique(np.concatenate([[0, n - 1], rng.permutation(np.arange(1, n - 1))[:598]]))
+    deg[heavy] = 40
+    deg[heavy[:split]] = 600                              # two pieces of 300
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    col = np.concatenate([np.sort((i + 13 * np.arange(d)) % n) for i, d in enumerate(deg)]).astype(np.int32)
+    val = np.repeat(np.float32(1.0) / deg.astype(np.float32), deg).astype(np.float32)
+    g = G.groot_graph_from_csr(rowptr, col, val)
+    for F in (32, 100):
+        X = wl.uniform_features_numpy(45, 0, n, F)
+        Y, plan, _, _ = _run(torch_cuda, g, T, X)
+        assert G.groot_plan_query(plan, "hd_pieces") == pieces
+        Y64, S = oracle.spmm_f64(rowptr, col, val, X)
+        assert_close_to_oracle(Y, Y64, S, f"{pieces} pieces F={F}")
+
+
 @pytest.mark.parametrize("case", ["aig", "stress"])
 def test_transposed_spmm(torch_cuda, case):
     """dX = A_hat^T dY through groot_graph_transpose + the ordinary plan/execute, against the oracle's
