@@ -70,16 +70,16 @@ int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd
     const int32_t bad_cap = (int32_t)(dp.n / 50 + 1024);
     int32_t *n_bad = nullptr, *bad_rows = nullptr, *merged = nullptr;
     auto give_up = [&](int err) {
-        (void)hipFree(dp.rp32); (void)hipFree(dp.col16); (void)hipFree(dp.hot_cols); (void)hipFree(n_bad);
-        (void)hipFree(bad_rows); (void)hipFree(merged);
+        dev_free(dp.rp32); dev_free(dp.col16); dev_free(dp.hot_cols); dev_free(n_bad);
+        dev_free(bad_rows); dev_free(merged);
         dp.rp32 = nullptr; dp.col16 = nullptr; dp.hot_cols = nullptr; dp.n_hot = 0;
         return err;
     };
-    if (hipMalloc((void **)&dp.rp32, (size_t)(dp.n + 1) * 4) != hipSuccess ||
-        hipMalloc((void **)&dp.col16, (size_t)dp.nnz * 2) != hipSuccess ||
-        hipMalloc((void **)&dp.hot_cols, (size_t)(n_hot ? n_hot : 1) * 4) != hipSuccess ||
-        hipMalloc((void **)&bad_rows, (size_t)bad_cap * 4) != hipSuccess ||
-        hipMalloc((void **)&n_bad, 4) != hipSuccess) {
+    if (dev_alloc((void **)&dp.rp32, (size_t)(dp.n + 1) * 4) != 0 ||
+        dev_alloc((void **)&dp.col16, (size_t)dp.nnz * 2) != 0 ||
+        dev_alloc((void **)&dp.hot_cols, (size_t)(n_hot ? n_hot : 1) * 4) != 0 ||
+        dev_alloc((void **)&bad_rows, (size_t)bad_cap * 4) != 0 ||
+        dev_alloc((void **)&n_bad, 4) != 0) {
         (void)hipGetLastError();
         return give_up(0);                                           // out of device memory: not an error, the plain arrays serve
     }
@@ -100,7 +100,7 @@ int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd
     if (h_bad > bad_cap || (int64_t)h_bad * 50 > dp.n) return give_up(0);
     if (h_bad > 0) {
         // the rows that could not be encoded join the list of rows that the row-list kernel computes
-        if (hipMalloc((void **)&merged, (size_t)(dp.n_mid_rows + h_bad) * 4) != hipSuccess) {
+        if (dev_alloc((void **)&merged, (size_t)(dp.n_mid_rows + h_bad) * 4) != 0) {
             (void)hipGetLastError();
             return give_up(0);
         }
@@ -109,13 +109,13 @@ int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd
         if (e == hipSuccess) e = hipMemcpyAsync(merged + dp.n_mid_rows, bad_rows, (size_t)h_bad * 4, hipMemcpyDeviceToDevice, st);
         e2 = hipStreamSynchronize(st);
         if (e != hipSuccess || e2 != hipSuccess) return give_up((int)(e != hipSuccess ? e : e2));
-        (void)hipFree(dp.mid_rows);
+        dev_free(dp.mid_rows);
         dp.mid_rows = merged;
         merged = nullptr;
         dp.n_mid_rows += h_bad;
     }
-    (void)hipFree(n_bad);
-    (void)hipFree(bad_rows);
+    dev_free(n_bad);
+    dev_free(bad_rows);
     dp.n_hot = n_hot;
     dp.n_bad_rows = h_bad;
     dp.compressed = 1;

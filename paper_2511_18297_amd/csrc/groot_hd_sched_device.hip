@@ -157,12 +157,12 @@ __global__ __launch_bounds__(kBlock) void hs_permute(const HdChunk *__restrict__
 struct Tmp {                                             // device memory freed on scope exit
     void *p[12] = {};
     int used = 0;
-    ~Tmp() { for (int i = 0; i < used; ++i) (void)hipFree(p[i]); }
+    ~Tmp() { for (int i = 0; i < used; ++i) dev_free(p[i]); }
     template <class T>
     bool get(T **out, size_t count)
     {
         void *q = nullptr;
-        if (used >= 12 || hipMalloc(&q, (count ? count : 1) * sizeof(T)) != hipSuccess) { (void)hipGetLastError(); return false; }
+        if (used >= 12 || dev_alloc(&q, (count ? count : 1) * sizeof(T)) != 0) return false;
         p[used++] = q;
         *out = (T *)q;
         return true;
@@ -173,7 +173,7 @@ struct Tmp {                                             // device memory freed 
 
 void free_device_hd_schedule(DeviceHdSchedule &s)
 {
-    (void)hipFree(s.chunks); (void)hipFree(s.chunks_rank); (void)hipFree(s.split_rows); (void)hipFree(s.split_rows_rank);
+    dev_free(s.chunks); dev_free(s.chunks_rank); dev_free(s.split_rows); dev_free(s.split_rows_rank);
     s = DeviceHdSchedule{};
 }
 
@@ -210,7 +210,7 @@ int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev,
         !tmp.get(&keys_sorted, (size_t)n_chunks) || !tmp.get(&order, (size_t)n_chunks) || !tmp.get(&order_sorted, (size_t)n_chunks))
         return kErrOutOfDeviceMemory;
     auto own = [&](auto **p, size_t count) {
-        return hipMalloc((void **)p, (count ? count : 1) * sizeof(**p)) == hipSuccess;
+        return dev_alloc((void **)p, (count ? count : 1) * sizeof(**p)) == 0;
     };
     if (!own(&s.chunks, (size_t)n_chunks) || !own(&s.chunks_rank, (size_t)n_chunks) || !own(&s.split_rows, (size_t)n_split) ||
         !own(&s.split_rows_rank, (size_t)n_split)) {

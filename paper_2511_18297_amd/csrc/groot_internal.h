@@ -185,9 +185,12 @@ int device_download(void *dst_host, const void *src_dev, size_t bytes, void *str
 int device_copy(void *dst_dev, const void *src_dev, size_t bytes, void *stream);   // device to device, synchronous
 const char *hip_error_text(int err);
 
-// Device memory helpers (groot_kernels.hip, so that the host file needs no HIP headers).
+// Device memory of the library (groot_pool.hip): every allocation that it makes.  dev_alloc returns a hipError_t as int and
+// leaves no HIP error behind; dev_free takes NULL, may be called while the block is still in use by running kernels, and waits
+// for nothing.
 int dev_alloc(void **p, size_t bytes);
 void dev_free(void *p);
+// (groot_kernels.hip, so that the host file needs no HIP headers)
 int dev_upload(void *dst, const void *src, size_t bytes);
 
 }  // namespace groot

@@ -270,13 +270,6 @@ int launch_rows_scatter(const int64_t *ids, int64_t n, const float *in, float *Y
 
 const char *hip_error_text(int err) { return hipGetErrorString((hipError_t)err); }
 
-int dev_alloc(void **p, size_t bytes) { return (int)hipMalloc(p, bytes); }
-
-void dev_free(void *p)
-{
-    if (p) (void)hipFree(p);
-}
-
 int dev_upload(void *dst, const void *src, size_t bytes)
 {
     return (int)hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);

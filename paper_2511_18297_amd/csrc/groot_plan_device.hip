@@ -217,15 +217,13 @@ int launch_plan_device(const int64_t *rowptr_dev, int64_t n, int32_t T, uint8_t 
     if (T < 1 || cols > kPlanMaxCols || n < 0 || n > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     int32_t *hist = nullptr;
     int64_t *total = nullptr;
-    hipError_t e = hipMalloc((void **)&hist, (size_t)(n_blocks ? n_blocks : 1) * cols * sizeof(int32_t));
-    if (e != hipSuccess) return (int)hipErrorOutOfMemory;
-    e = hipMalloc((void **)&total, (size_t)cols * sizeof(int64_t));
-    if (e != hipSuccess) { (void)hipFree(hist); return (int)hipErrorOutOfMemory; }
+    if (dev_alloc((void **)&hist, (size_t)(n_blocks ? n_blocks : 1) * cols * sizeof(int32_t))) return (int)hipErrorOutOfMemory;
+    if (dev_alloc((void **)&total, (size_t)cols * sizeof(int64_t))) { dev_free(hist); return (int)hipErrorOutOfMemory; }
     const int err = plan_launches(rowptr_dev, n, T, cols, n_blocks, hist, total, row_class, hd_rows, ld_rows, by_degree,
                                   deg_offsets, counts, st);
     hipError_t e2 = hipStreamSynchronize(st);               // the scratch is freed below
-    (void)hipFree(hist);
-    (void)hipFree(total);
+    dev_free(hist);
+    dev_free(total);
     return err ? err : (int)e2;
 }
 

@@ -477,12 +477,12 @@ inline unsigned rg_grid(int64_t items, int per_block) { return (unsigned)((items
 struct Scratch {
     void *p[8] = {};
     int used = 0;
-    ~Scratch() { for (int i = 0; i < used; ++i) (void)hipFree(p[i]); }
+    ~Scratch() { for (int i = 0; i < used; ++i) dev_free(p[i]); }
     template <class T>
     bool get(T **out, size_t count)
     {
         void *q = nullptr;
-        if (used >= 8 || hipMalloc(&q, (count ? count : 1) * sizeof(T)) != hipSuccess) return false;
+        if (used >= 8 || dev_alloc(&q, (count ? count : 1) * sizeof(T)) != 0) return false;
         p[used++] = q;
         *out = (T *)q;
         return true;
@@ -493,10 +493,10 @@ struct Scratch {
 
 void free_device_part(DevicePart &part)
 {
-    (void)hipFree(part.global_id);
-    (void)hipFree(part.rowptr);
-    (void)hipFree(part.col);
-    (void)hipFree(part.val);
+    dev_free(part.global_id);
+    dev_free(part.rowptr);
+    dev_free(part.col);
+    dev_free(part.val);
     part = DevicePart{};
 }
 
@@ -549,8 +549,8 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
     const int64_t n_loc = part.n_owned + part.n_halo;
     if (part.n_owned < 0 || part.n_halo < 0 || n_loc > n) return done((int)hipErrorUnknown);
 
-    if (hipMalloc((void **)&part.global_id, (size_t)(n_loc ? n_loc : 1) * sizeof(int64_t)) != hipSuccess ||
-        hipMalloc((void **)&part.rowptr, (size_t)(n_loc + 1) * sizeof(int64_t)) != hipSuccess)
+    if (dev_alloc((void **)&part.global_id, (size_t)(n_loc ? n_loc : 1) * sizeof(int64_t)) != 0 ||
+        dev_alloc((void **)&part.rowptr, (size_t)(n_loc + 1) * sizeof(int64_t)) != 0)
         return done(kErrOutOfDeviceMemory);
     const int64_t loc_blocks = (n_loc + kRgRowsPerBlock - 1) / kRgRowsPerBlock;
     if (!scratch.get(&len, (size_t)n_loc) || !scratch.get(&sums, (size_t)loc_blocks) ||
@@ -576,9 +576,9 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
     part.nnz = h_total[3];
     if (part.nnz < 0 || part.nnz > dp.nnz) return done((int)hipErrorUnknown);
 
-    if (hipMalloc((void **)&part.col, (size_t)(part.nnz ? part.nnz : 1) * sizeof(int32_t)) != hipSuccess)
+    if (dev_alloc((void **)&part.col, (size_t)(part.nnz ? part.nnz : 1) * sizeof(int32_t)) != 0)
         return done(kErrOutOfDeviceMemory);
-    if (g.val && hipMalloc((void **)&part.val, (size_t)(part.nnz ? part.nnz : 1) * sizeof(float)) != hipSuccess)
+    if (g.val && dev_alloc((void **)&part.val, (size_t)(part.nnz ? part.nnz : 1) * sizeof(float)) != 0)
         return done(kErrOutOfDeviceMemory);
     if (n_loc) {
         rg_fill<<<dim3(rg_grid(n_loc, kBlock)), dim3(kBlock), 0, st>>>(g, local_of, part.global_id, part.n_owned, n_loc,

@@ -98,3 +98,60 @@ def test_threshold_above_the_device_limit(torch_cuda):
     with pytest.raises(G.GrootError) as e:
         G.groot_plan_lists_device(plan, *bufs)
     assert e.value.status == G.GROOT_ERANGE
+
+
+def test_plan_freed_while_its_kernels_run(torch_cuda):
+    """A plan may be freed right after its last call: its device memory goes to the next plan only once the kernels
+    that read it have ended, on whatever stream they run.  The second plan is of the same size, so it would take
+    the first one's blocks; repeated, so that blocks are handed back and forth."""
+    torch = torch_cuda
+    aig = wl.csa_multiplier_aig(256)
+    g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 2)
+    gt = G.groot_graph_transpose(g)
+    n, F = 2 * aig.num_nodes, 64
+    X = wl.uniform_features(3, 0, n, F, device="cuda")
+    want = torch.empty_like(X)
+    plan = G.groot_spmm_plan(g, 32)
+    G.groot_plan_upload(plan, F)
+    G.groot_spmm_execute(plan, X, want)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    outs = [torch.full_like(X, float("nan")) for _ in range(12)]
+    side.wait_stream(torch.cuda.current_stream())
+    for k in range(3):
+        for y in outs[4 * k:4 * k + 4]:
+            G.groot_spmm_execute(plan, X, y, stream=side)
+        del plan                                          # the kernels above are still queued
+        other = G.groot_spmm_plan(gt, 32)                 # takes the memory and writes another matrix to it
+        G.groot_plan_upload(other, F)
+        del other
+        plan = G.groot_spmm_plan(g, 32)
+        G.groot_plan_upload(plan, F)
+    torch.cuda.synchronize()
+    for k, y in enumerate(outs):
+        assert torch.equal(y, want), f"pass {k}"
+
+
+def test_device_memory_is_given_back(torch_cuda):
+    """Blocks that the library keeps between objects go back to the device with its last object."""
+    import gc
+
+    torch = torch_cuda
+    gc.collect()
+    torch.cuda.synchronize()
+    aig = wl.csa_multiplier_aig(192)
+
+    def one():
+        g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 4)
+        plan = G.groot_spmm_plan(g, 32)
+        G.groot_plan_upload(plan, 64)
+        part = G.groot_partition_regrow_device(plan, 4, 1)
+        sub = G.groot_dev_part_plan(part, 32, 64)
+        del sub, part, plan
+        gc.collect()
+    one()                                                 # code objects, the runtime's own allocations
+    before = torch.cuda.mem_get_info()[0]
+    for _ in range(3):
+        one()
+    after = torch.cuda.mem_get_info()[0]
+    assert before - after < 16 << 20, f"{(before - after) >> 20} MiB of device memory did not come back"
