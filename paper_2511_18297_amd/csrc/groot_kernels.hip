@@ -93,17 +93,26 @@ __global__ __launch_bounds__(kBlock) void ld_kernel(const int64_t *__restrict__ 
     ld_tile<L, W>(smem, tile, rowptr, col, val, X, Y, n, F4, T, out_ids, n_out);
 }
 
-// Block k of the HD launch computes piece k.
+// One workgroup per piece.  The pieces stand in the order of their first column, so neighbours in the list gather from the
+// same stretch of X; consecutive workgroups land on different XCDs, each with an L2 of its own.  run > 1: the list is dealt
+// to the XCDs in runs of that many pieces.
 template <int L, int W>
 __global__ __launch_bounds__(kBlock) void hd_kernel(const HdChunk *__restrict__ chunks,
                                                     const int32_t *__restrict__ col,
                                                     const float *__restrict__ val,
                                                     const v4f *__restrict__ X, v4f *__restrict__ Y,
                                                     v4f *__restrict__ partials, int32_t F4,
-                                                    const int64_t *__restrict__ out_ids, int64_t n_out)
+                                                    const int64_t *__restrict__ out_ids, int64_t n_out, int64_t n_chunks,
+                                                    int32_t run)
 {
     __shared__ __align__(16) char smem[kBlock * sizeof(v4f)];
-    const HdChunk ch = chunks[blockIdx.x];
+    int64_t piece = blockIdx.x;
+    if (run > 1) {
+        const int64_t k = blockIdx.x / kXcds;            // the XCD's k-th workgroup
+        piece = (k / run * kXcds + blockIdx.x % kXcds) * run + k % run;
+        if (piece >= n_chunks) return;                   // the whole workgroup
+    }
+    const HdChunk ch = chunks[piece];
     if (ch.row >= n_out) return;                         // the whole workgroup: a row that is not wanted
     hd_piece<L, W>(smem, ch, col, val, X, Y, partials, F4, out_ids);
 }
@@ -124,7 +133,16 @@ __global__ __launch_bounds__(kBlock) void hd_finish_kernel(const HdSplitRow *__r
     const int64_t orow = out_ids ? out_ids[sr.row] : (int64_t)sr.row;
     for (int32_t ff = threadIdx.x % L; ff < F4; ff += L) {
         v4f acc = {0.f, 0.f, 0.f, 0.f};
-        for (int32_t c = 0; c < sr.count; ++c) acc += partials[(int64_t)(sr.first + c) * F4 + ff];
+        const v4f *p = partials + (int64_t)sr.first * F4 + ff;
+        int32_t c = 0;
+        for (; c + 8 <= sr.count; c += 8, p += 8 * (int64_t)F4) {   // eight loads in flight: a row may have hundreds of pieces
+            v4f x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = p[i * (int64_t)F4];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc += x[i];
+        }
+        for (; c < sr.count; ++c, p += F4) acc += *p;
         Y[orow * F4 + ff] = acc;
     }
 }
@@ -212,12 +230,19 @@ int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
     const int32_t F4 = F / 4;
     const int64_t *out_ids = out ? out->ids : nullptr;
     const int64_t n_out = out ? out->n_out : dp.n;
-    if (!grid_ok(dp.n_chunks)) return (int)hipErrorInvalidConfiguration;
     if (!weights_ok(dp)) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
+    // Runs of 64 pieces from F = 64 on, where a stretch of X is large beside an L2 (polarized graphs, every row of X gathered
+    // 70 times: 65,536 rows F = 128 90 -> 64 us, 262,144 rows F = 128 571 -> 550, F = 256 1,517 -> 1,030; multipliers, whose rows
+    // are gathered once or twice, the same; runs of 16: 566 and 1,335, of 1,024: 582 and 1,073; cutting rows into slices by XCD:
+    // 594 and 1,181).  At F = 32 it costs 2 %.  Below 2,048 pieces all of them are in flight anyway.
+    const int32_t run = F4 >= 16 && dp.n_chunks >= 2048 ? 64 : 1;
+    const int64_t grid = run > 1 ? (dp.n_chunks + kXcds * run - 1) / (kXcds * run) * (kXcds * run) : dp.n_chunks;
+    if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
     GROOT_DISPATCH_LW(lanes_for(F4), dp.weight_mode,
-                      (hd_kernel<kL, kW><<<dim3((unsigned)dp.n_chunks), dim3(kBlock), 0, st>>>(
-                          dp.chunks, dp.col, dp.val, (const v4f *)X, (v4f *)Y, (v4f *)dp.partials, F4, out_ids, n_out)));
+                      (hd_kernel<kL, kW><<<dim3((unsigned)grid), dim3(kBlock), 0, st>>>(
+                          dp.chunks, dp.col, dp.val, (const v4f *)X, (v4f *)Y, (v4f *)dp.partials, F4, out_ids, n_out, dp.n_chunks,
+                          run)));
     return (int)hipGetLastError();
 }
 

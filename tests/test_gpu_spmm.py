@@ -249,15 +249,17 @@ def test_mixed_row_lengths_at_other_widths(torch_cuda, max_len, T, F, explicit):
     test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit)
 
 
-@pytest.mark.parametrize("pieces", [1023, 1024, 1025])
+@pytest.mark.parametrize("pieces", [1023, 1024, 1025, 2047, 2048, 2600])
 def test_high_degree_rows_beside_the_low_degree_ones(torch_cuda, pieces):
-    """Around the number of pieces up to which the high-degree rows ride in the low-degree rows' launch: 600 rows of two
-    pieces and the rest of one, the first row and the last among them, next to rows of 1 to 4 entries."""
+    """Around the number of pieces up to which the high-degree rows ride in the low-degree rows' launch, and around the one
+    from which the list is dealt to the XCDs in runs of 64 (2600: the last runs are short or empty): rows of two pieces
+    and of one, the first row and the last among them, next to rows of 1 to 4 entries."""
     n, T = 9000, 32
-    split = pieces - 600
+    heavies = 600 if pieces < 1200 else 1500
+    split = pieces - heavies
     rng = np.random.default_rng(pieces)
     deg = rng.integers(1, 5, size=n)
-    heavy = np.unique(np.concatenate([[0, n - 1], rng.permutation(np.arange(1, n - 1))[:598]]))
+    heavy = np.unique(np.concatenate([[0, n - 1], rng.permutation(np.arange(1, n - 1))[:heavies - 2]]))
     deg[heavy] = 40
     deg[heavy[:split]] = 600                              # two pieces of 300
     rowptr = np.zeros(n + 1, dtype=np.int64)
