@@ -177,8 +177,8 @@ void free_device_hd_schedule(DeviceHdSchedule &s)
     s = DeviceHdSchedule{};
 }
 
-// hd_rows_dev: the n_hd high-degree rows, ascending.  Synchronises the stream (sizes are read back between the
-// passes).  kErrOutOfDeviceMemory when an allocation fails, kErrTooManyPieces when the slots do not fit 31 bits.
+// hd_rows_dev: the n_hd high-degree rows, ascending.  Waits for the stream once (sizes are read back between the
+// passes); the schedule itself is complete when the stream has reached the end of what is enqueued here.  kErrOutOfDeviceMemory when an allocation fails, kErrTooManyPieces when the slots do not fit 31 bits.
 int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev, const int32_t *hd_rows_dev, int64_t n_hd,
                               int32_t hd_chunk, void *stream, DeviceHdSchedule *out)
 {
@@ -237,10 +237,9 @@ int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev,
                                                                                             n_chunks, s.chunks, s.chunks_rank);
         e = hipGetLastError();
     }
-    e2 = hipStreamSynchronize(st);                       // the temporaries are freed on return
-    if (e != hipSuccess || e2 != hipSuccess) {
+    if (e != hipSuccess) {
         free_device_hd_schedule(s);
-        return (int)(e != hipSuccess ? e : e2);
+        return (int)e;
     }
     s.n_chunks = n_chunks;
     s.n_split_rows = n_split;

@@ -1279,21 +1279,20 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
     try {
         std::unique_ptr<groot_plan> pl(new groot_plan);
         // lists on the device; only the high-degree rows and the degree offsets are needed here
-        DevBuf row_class, hd_rows, ld_rows, by_degree, deg_offsets, counts;
+        DevBuf row_class, hd_rows, ld_rows, by_degree, sizes;   // sizes: the two counts, then the T + 1 degree offsets
         if (row_class.alloc((size_t)n) || hd_rows.alloc((size_t)n * 4) || ld_rows.alloc((size_t)n * 4) ||
-            by_degree.alloc((size_t)n * 4) || deg_offsets.alloc((size_t)(T + 1) * 8) || counts.alloc(16))
+            by_degree.alloc((size_t)n * 4) || sizes.alloc((size_t)(T + 3) * 8))
             return fail(GROOT_ENOMEM, std::string(who) + "device allocation of the plan lists failed");
         int err = launch_plan_device(part->d.rowptr, n, T, row_class.as<uint8_t>(), hd_rows.as<int32_t>(),
-                                     ld_rows.as<int32_t>(), by_degree.as<int32_t>(), deg_offsets.as<int64_t>(),
-                                     counts.as<int64_t>(), hip_stream);
+                                     ld_rows.as<int32_t>(), by_degree.as<int32_t>(), sizes.as<int64_t>() + 2,
+                                     sizes.as<int64_t>(), hip_stream, false);
         if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, std::string(who) + "scratch allocation failed");
         if (err) return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
-        int64_t h_counts[2] = {0, 0};
-        std::vector<int64_t> offs(T + 1, 0);
-        if ((err = device_download(h_counts, counts.p, sizeof h_counts, hip_stream)) ||
-            (err = device_download(offs.data(), deg_offsets.p, offs.size() * 8, hip_stream)))
+        std::vector<int64_t> h_sizes(T + 3, 0);
+        if ((err = device_download(h_sizes.data(), sizes.p, h_sizes.size() * 8, hip_stream)))
             return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
-        const int64_t n_hd = h_counts[0], n_ld = h_counts[1];
+        const int64_t n_hd = h_sizes[0], n_ld = h_sizes[1];
+        const int64_t *const offs = h_sizes.data() + 2;
         if (n_hd < 0 || n_ld < 0 || n_hd + n_ld != n) return fail(GROOT_EHIP, std::string(who) + "inconsistent row counts from the device");
         // the schedule of the high-degree rows, cut and ordered on the device too: only four sizes come back
         DeviceHdSchedule sched;
@@ -1308,9 +1307,8 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         d.split_rows = sched.split_rows;
         d.split_rows_rank = sched.split_rows_rank;
         pl->n_partials = sched.n_partials;
-        const std::vector<float> zeros(kZeroRowFloats + kTrashFloats, 0.0f);
         groot_status st;
-        if ((st = to_device(&d.zero_row, zeros.data(), zeros.size(), "zero row")) != GROOT_OK ||
+        if ((st = to_device<float>(&d.zero_row, nullptr, kZeroRowFloats + kTrashFloats, "zero row")) != GROOT_OK ||
             (st = to_device<float>(&d.partials, nullptr, (size_t)sched.n_partials * max_F, "HD partial sums")) != GROOT_OK ||
             (st = to_device<float>(&d.hd_agg, nullptr, (size_t)n_hd * max_F, "high-degree sums of the fused layer")) != GROOT_OK ||
             (st = to_device<int32_t>(&d.hd_rows, nullptr, (size_t)n_hd, "high-degree row list")) != GROOT_OK) {
@@ -1319,7 +1317,8 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             set_error(keep);
             return st;
         }
-        if (n_hd && (err = device_copy(d.hd_rows, hd_rows.p, (size_t)n_hd * 4, hip_stream))) {
+        if ((err = device_zero(d.zero_row, (kZeroRowFloats + kTrashFloats) * sizeof(float), hip_stream)) ||
+            (n_hd && (err = device_copy(d.hd_rows, hd_rows.p, (size_t)n_hd * 4, hip_stream)))) {
             release_device(pl.get());
             return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
         }
@@ -1367,6 +1366,10 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
                 release_device(pl.get());               // the sub-graph's arrays are the plan's by now
                 return fail(GROOT_EHIP, std::string(who) + "compact CSR: " + hip_error_text(err));
             }
+        }
+        if ((err = device_wait(hip_stream))) {           // the plan may be used on any stream from here on
+            release_device(pl.get());
+            return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
         }
         pl->g = nullptr;
         pl->threshold = T;

@@ -143,7 +143,7 @@ struct DeviceHdSchedule {
 };
 constexpr int kErrTooManyPieces = -3;
 int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev, const int32_t *hd_rows_dev, int64_t n_hd,
-                              int32_t hd_chunk, void *stream, DeviceHdSchedule *out);   // synchronises the stream
+                              int32_t hd_chunk, void *stream, DeviceHdSchedule *out);   // complete in stream order
 void free_device_hd_schedule(DeviceHdSchedule &s);
 // Compact CSR for the pipelined LD kernel, built on the device (groot_compress.hip); synchronises the stream.
 int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, void *stream);
@@ -152,12 +152,13 @@ int pipe_compact_prepare();   // once per process, before the first launch with 
 int launch_col_map(int32_t *col, int64_t nnz, const int64_t *ids, void *stream);
 int launch_rows_gather(const int64_t *ids, int64_t n, const float *X, float *out, int32_t F, void *stream);
 int launch_rows_scatter(const int64_t *ids, int64_t n, const float *in, float *Y, int32_t F, void *stream);
-// Device-side plan lists (groot_plan_device.hip).  Synchronises the stream; kErrOutOfDeviceMemory when its
+// Device-side plan lists (groot_plan_device.hip).  Synchronises the stream unless wait is false; kErrOutOfDeviceMemory when its
 // scratch cannot be allocated.
 constexpr int kPlanDeviceMaxThreshold = 1024;
 constexpr int kErrOutOfDeviceMemory = 2;   // hipErrorOutOfMemory
 int launch_plan_device(const int64_t *rowptr_dev, int64_t n, int32_t T, uint8_t *row_class, int32_t *hd_rows,
-                       int32_t *ld_rows, int32_t *by_degree, int64_t *deg_offsets, int64_t *counts, void *stream);
+                       int32_t *ld_rows, int32_t *by_degree, int64_t *deg_offsets, int64_t *counts, void *stream,
+                       bool wait = true);
 // The same lists with the block table in a fixed array inside the library instead of allocated memory: no
 // allocation, no synchronisation; hipErrorInvalidValue when plan_static_scratch_needed exceeds the array.
 constexpr size_t kPlanStaticScratchBytes = (size_t)8 << 20;
@@ -182,7 +183,9 @@ void free_device_part(DevicePart &part);
 // Small synchronous device reads and copies (sizes and lists of a plan built from device arrays).
 int device_time_ms(void *stream, int reps, int (*fn)(void *ctx), void *ctx, float *ms);
 int device_download(void *dst_host, const void *src_dev, size_t bytes, void *stream);
-int device_copy(void *dst_dev, const void *src_dev, size_t bytes, void *stream);   // device to device, synchronous
+int device_copy(void *dst_dev, const void *src_dev, size_t bytes, void *stream);   // device to device, in stream order
+int device_zero(void *dst_dev, size_t bytes, void *stream);                        // in stream order; bytes a multiple of 4
+int device_wait(void *stream);
 const char *hip_error_text(int err);
 
 // Device memory of the library (groot_pool.hip): every allocation that it makes.  dev_alloc returns a hipError_t as int and

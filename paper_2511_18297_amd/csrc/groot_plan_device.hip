@@ -209,7 +209,7 @@ constexpr size_t plan_totals_bytes(int32_t cols) { return ((size_t)cols * sizeof
 }  // namespace
 
 int launch_plan_device(const int64_t *rowptr_dev, int64_t n, int32_t T, uint8_t *row_class, int32_t *hd_rows,
-                       int32_t *ld_rows, int32_t *by_degree, int64_t *deg_offsets, int64_t *counts, void *stream)
+                       int32_t *ld_rows, int32_t *by_degree, int64_t *deg_offsets, int64_t *counts, void *stream, bool wait)
 {
     hipStream_t st = (hipStream_t)stream;
     const int32_t cols = T + 2;
@@ -221,8 +221,8 @@ int launch_plan_device(const int64_t *rowptr_dev, int64_t n, int32_t T, uint8_t 
     if (dev_alloc((void **)&total, (size_t)cols * sizeof(int64_t))) { dev_free(hist); return (int)hipErrorOutOfMemory; }
     const int err = plan_launches(rowptr_dev, n, T, cols, n_blocks, hist, total, row_class, hd_rows, ld_rows, by_degree,
                                   deg_offsets, counts, st);
-    hipError_t e2 = hipStreamSynchronize(st);               // the scratch is freed below
-    dev_free(hist);
+    const hipError_t e2 = wait ? hipStreamSynchronize(st) : hipSuccess;
+    dev_free(hist);                                          // may still be in use (see dev_free)
     dev_free(total);
     return err ? err : (int)e2;
 }

@@ -516,9 +516,10 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
     Scratch scratch;
     int32_t *local_of = nullptr, *cnt = nullptr, *flag = nullptr, *len = nullptr, *long_list = nullptr;
     int64_t *total = nullptr, *sums = nullptr;
-    if (!scratch.get(&local_of, (size_t)n) || !scratch.get(&cnt, (size_t)n_blocks * 2) || !scratch.get(&flag, 2) ||
-        !scratch.get(&total, 4 + kRgCrossSlots))
+    // total[0 .. 3], the crossing-pair counters, two 32-bit flags
+    if (!scratch.get(&local_of, (size_t)n) || !scratch.get(&cnt, (size_t)n_blocks * 2) || !scratch.get(&total, 5 + kRgCrossSlots))
         return kErrOutOfDeviceMemory;
+    flag = (int32_t *)(total + 4 + kRgCrossSlots);
 
     DevicePart part;
     hipError_t e = hipSuccess;
@@ -528,8 +529,7 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
         return code;
     };
 
-    rg_fill_i32<<<dim3(1), dim3(kBlock), 0, st>>>(flag, 2, 0);
-    rg_fill_i32<<<dim3(1), dim3(kBlock), 0, st>>>((int32_t *)total, 2 * (4 + kRgCrossSlots), 0);
+    rg_fill_i32<<<dim3(1), dim3(kBlock), 0, st>>>((int32_t *)total, 2 * (5 + kRgCrossSlots), 0);
     unsigned long long *cross_slots = (unsigned long long *)(total + 4);
     rg_fill_i32<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, st>>>(local_of, n, kRgNone);
     if (part_of_dev) rg_check_parts<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, st>>>(part_of_dev, n, P, flag);
@@ -537,13 +537,11 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
     rg_count<<<dim3((unsigned)n_blocks), dim3(kBlock), 0, st>>>(g, local_of, cnt);
     rg_scan_counts<<<dim3(2), dim3(kBlock), 0, st>>>(cnt, n_blocks, 2, total);
     if ((e = hipGetLastError()) != hipSuccess) return done((int)e);
-    int64_t h_total[4] = {0, 0, 0, 0};
-    int32_t h_flag = 0;
-    if ((e = hipMemcpyAsync(h_total, total, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipMemcpyAsync(&h_flag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+    int64_t h_total[5 + kRgCrossSlots] = {};
+    if ((e = hipMemcpyAsync(h_total, total, sizeof h_total, hipMemcpyDeviceToHost, st)) != hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
         return done((int)e);
-    if (h_flag) return done(kErrBadPartId);
+    if ((int32_t)h_total[4 + kRgCrossSlots]) return done(kErrBadPartId);
     part.n_owned = h_total[0];
     part.n_halo = h_total[1];
     const int64_t n_loc = part.n_owned + part.n_halo;
@@ -628,9 +626,16 @@ int device_copy(void *dst_dev, const void *src_dev, size_t bytes, void *stream)
 {
     if (!bytes) return 0;
     hipStream_t st = (hipStream_t)stream;
-    hipError_t err = hipMemcpyAsync(dst_dev, src_dev, bytes, hipMemcpyDeviceToDevice, st);
-    hipError_t err2 = hipStreamSynchronize(st);
-    return (int)(err != hipSuccess ? err : err2);
+    return (int)hipMemcpyAsync(dst_dev, src_dev, bytes, hipMemcpyDeviceToDevice, st);
 }
+
+int device_zero(void *dst_dev, size_t bytes, void *stream)
+{
+    const int64_t n = (int64_t)(bytes / 4);
+    if (n) rg_fill_i32<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, (hipStream_t)stream>>>((int32_t *)dst_dev, n, 0);
+    return (int)hipGetLastError();
+}
+
+int device_wait(void *stream) { return (int)hipStreamSynchronize((hipStream_t)stream); }
 
 }  // namespace groot
