@@ -6,8 +6,8 @@
 // at one of the few high-degree rows (the primary inputs), which is what the two code ranges cover:
 //     code <  0x8000:  column = row + code - 0x4000          (within -16384 .. +16383 rows)
 //     code >= 0x8000:  column = hot[code - 0x8000]           (one of up to 32767 high-degree rows)
-//     code == 0xFFFF:  neither (a primary output and its driver, say): the whole row is left to the row-list
-//                      kernel, which reads the plain arrays
+//     code == 0xFFFF:  neither (a primary output and its driver, say): the whole row joins the
+//                      list of rows that are computed one by one, from the plain arrays
 // Only rows that the pipelined kernel can serve are encoded (no more entries than it has slots, not
 // high-degree); if more than one row in 50 cannot be encoded the plan keeps using the plain arrays.
 #include "groot_device.h"
@@ -23,7 +23,7 @@ __global__ __launch_bounds__(kBlock) void rp32_kernel(const int64_t *__restrict_
 }
 
 // One thread per row.  An entry that fits neither range gets kCodeBad and its row is appended to bad_rows (in no
-// particular order): the pipelined kernel masks such a row and the row-list kernel computes it.
+// particular order): the pipelined kernel masks such a row, which is then computed by list.
 __global__ __launch_bounds__(kBlock) void col16_kernel(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                                        int64_t n, int32_t T, int32_t depth, const int32_t *__restrict__ hot,
                                                        int32_t n_hot, uint16_t *__restrict__ out, int32_t *__restrict__ bad_rows,
@@ -99,7 +99,7 @@ int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd
     if (e != hipSuccess || e2 != hipSuccess) return give_up((int)(e != hipSuccess ? e : e2));
     if (h_bad > bad_cap || (int64_t)h_bad * 50 > dp.n) return give_up(0);
     if (h_bad > 0) {
-        // the rows that could not be encoded join the list of rows that the row-list kernel computes
+        // the rows that could not be encoded join the list of rows that are computed one by one
         if (dev_alloc((void **)&merged, (size_t)(dp.n_mid_rows + h_bad) * 4) != 0) {
             (void)hipGetLastError();
             return give_up(0);

@@ -488,7 +488,7 @@ namespace {
 // Which LD kernel an uploaded plan uses.  The pipelined kernel gives every row D gather slots and always issues
 // all D (a slot past the row's end reads a row of zeros), and a gather costs the same whether it hits a cache or
 // not (it is the per-CU return path of the vector memory unit that it occupies): so D should be as small as the
-// rows allow.  A low-degree row with more than D entries is masked there and computed by a row-list kernel (one
+// rows allow.  A low-degree row with more than D entries is masked there and computed from a list (one
 // lane group per row, nothing overlapped), which is fine as long as such rows are few.  Rule: the smallest D in
 // kPipeMinDepth .. kPipeMaxDepth that leaves at most 2 low-degree rows in 100 to the row list; none does: the
 // plain kernel (or D = kPipeMaxDepth when the knob insists).  at_most(d) = low-degree rows with at most d entries.
@@ -1465,7 +1465,7 @@ extern "C" groot_status groot_plan_query(const groot_plan *plan, const char *wha
         const DevicePlan &d = plan->dev;
         const int64_t w_bytes = d.weight_mode == (int)WeightMode::Explicit ? 4 : 0;
         const int64_t per_entry = 4 + w_bytes;
-        // the pipelined LD kernel (feature widths 32, 64, 128) reads the compact form when the plan has one
+        // the pipelined LD kernel reads the compact form when the plan has one
         const bool compact = d.ld_pipelined && d.compressed;
         const int64_t ld = compact ? 4 * (d.n + 1) + (2 + w_bytes) * (d.nnz - d.nnz_hd)
                                    : 8 * (d.n + 1) + per_entry * (d.nnz - d.nnz_hd);

@@ -89,11 +89,11 @@ struct DevicePlan {
     int compressed = 0;
     int64_t n_cols = 0;             // rows of the feature matrix the columns index: n, or the whole graph's row
                                     // count once a part's plan reads the global matrix in place
-    int ld_pipelined = 0;           // pipelined LD kernel: 0 never, 1 for F = 64 and 128, 2 for F = 32 as well
+    int ld_pipelined = 0;           // pipelined LD kernel: 0 never, 2 at the widths that it serves
     int sage_depth = 6;             // gather slots per row of the fused layer's kernels: 5, 6 or 8 (choose_layer_depth)
     int pipe_depth = 6;             // slots per row of the pipelined LD kernel: kPipeMinDepth .. kPipeMaxDepth
     int32_t *mid_rows = nullptr;    // low-degree rows with more than pipe_depth entries (the pipelined kernel
-    int64_t n_mid_rows = 0;         // masks them; a row-list kernel computes them), ordered by (length, id)
+    int64_t n_mid_rows = 0;         // masks them; they are computed by list), ordered by (length, id)
 };
 
 constexpr int kCodeNear = 0x4000;     // column codes below kCodeHot: row + code - kCodeNear

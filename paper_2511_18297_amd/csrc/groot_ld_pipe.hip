@@ -1,5 +1,6 @@
 // Software-pipelined LD kernel for gfx950: the low-degree rows of graphs whose rows are short (an AIG
-// with self-loops has 2 to 6 entries per low-degree row), F = 32, 64 or 128.
+// with self-loops has 2 to 6 entries per low-degree row), F = 20 to 256 (32, 64 and 128 without
+// idle lanes).
 //
 // One persistent workgroup of four wavefronts per CU, i.e. one wavefront per SIMD.  Every wavefront walks
 // its own tiles of G lane groups x (64 / L) rows (L = F / 4 lanes per row) and keeps a whole tile in
@@ -20,7 +21,7 @@
 //    exact: the wait before a group's sum leaves the G-1 younger groups in flight.  A row that does not
 //    fit (more than D entries, or a high-degree row) is masked: all its slots point at the zero row and
 //    its sum is stored to a trash area instead of Y (an address select, not a branch); the high-degree
-//    kernel, or the row-list kernel below for low-degree rows longer than D, computes it.  Only the ragged
+//    kernel, or a workgroup behind the sweep for low-degree rows longer than D, computes it.  Only the ragged
 //    last tile is masked as a whole and redone by a plain, unoverlapped path.
 //  * No workgroup barrier after the start (the list of hot rows is copied to LDS once): wavefronts share
 //    nothing else.
@@ -45,9 +46,6 @@ __device__ __forceinline__ void pipe_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The compact form of the CSR (C = true: 4-byte row pointers, 2-byte column codes, the list of high-degree
-// rows that a code can name; see groot_compress.hip) replaces the loads of the pipeline; the plain path and the
-// row-list kernel keep reading the full arrays.
 // What a launch does beside the sweep, in workgroups of their own behind it: the low-degree rows that the pipeline masks,
 // one lane group per row, and, where the plan has few of them (kHdBesideLd), the pieces of the high-degree rows.  On small
 // graphs the launches were most of the time: 32-bit multiplier, F = 32, three kernels of 10 + 3.5 + 3.4 us, now one of 8.0;
@@ -61,6 +59,9 @@ struct SideWork {
     float *partials;
 };
 
+// The compact form of the CSR (C = true: 4-byte row pointers, 2-byte column codes, the list of high-degree
+// rows that a code can name; see groot_compress.hip) replaces the loads of the pipeline; the plain path and the
+// side work keep reading the full arrays.
 struct CompactCsr {
     const uint32_t *rp32;
     const uint16_t *col16;
