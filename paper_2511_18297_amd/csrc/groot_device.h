@@ -68,6 +68,46 @@ __device__ __forceinline__ v4f ld_row_sum(int64_t s, int64_t e, const int32_t *_
     return acc;
 }
 
+// Rows before `row` in the ascending list of high-degree rows, found by the whole wavefront: 64 samples of what is left of
+// the list per step, so two or three loads one after the other where a binary search has a dozen (at about 0.8 us each).
+__device__ __forceinline__ int32_t hd_place(const int32_t *__restrict__ hd_rows, int32_t n_hd, int64_t row)
+{
+    const int lane = threadIdx.x % kWave;
+    int32_t place = 0;
+    for (int32_t len = n_hd; len > 0;) {                 // the answer lies in [place, place + len]
+        const int32_t step = (len + kWave - 1) / kWave, at = lane * step;
+        const int below = __popcll(__ballot(at < len && hd_rows[place + (at < len ? at : 0)] < row));
+        if (below == 0) break;
+        const int32_t cut = (below - 1) * step + 1;
+        place += cut;
+        len = step - 1 < len - cut ? step - 1 : len - cut;
+    }
+    return place;
+}
+
+// Sum of one row for one float4 slice with row-uniform weights, in CSR order, eight gathers in flight without a branch between
+// them (an entry past the row's end reads the row of zeros).  Xf: the lane's slice of row 0; zero_off: byte distance to its
+// slice of the row of zeros.
+template <int W>
+__device__ __forceinline__ v4f row_sum_ahead(int64_t s, int64_t e, const int32_t *__restrict__ cols, const char *__restrict__ Xf,
+                                             int row_shift, int64_t zero_off)
+{
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int64_t p = s; p < e; p += 8) {
+        int64_t c[8];
+        v4f x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = cols[p + k < e ? p + k : e - 1];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = *(const v4f *)(Xf + (p + k < e ? c[k] << row_shift : zero_off));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc += x[k];
+    }
+    if (W == kMean) acc *= row_weight<kMean>(e - s);
+    return acc;
+}
+
 // ---------------------------------------------------------------------------
 // HD part.  One workgroup per piece of a high-degree row (the plan cuts a row
 // into balanced pieces).  The 256/L lane groups of the workgroup stride over

@@ -508,11 +508,12 @@ PipeChoice choose_ld_kernel(int knob, int64_t n_ld, AtMost at_most)
     return {knob > 0 ? 2 : 0, kPipeMaxDepth};
 }
 
-// Gather slots per row of the fused layer's kernels (5, 6 or 8).  A tile of 16 rows with a longer row is noted and completed
-// later, unoverlapped, for about the time of one more tile, so the line lies lower than for the aggregation alone: 5 slots up
-// to one longer row in 300, five tiles in a hundred (Booth multipliers, one row in 850: layer 64 -> 32 571 us with 5 slots,
-// 592 with 6; weight gradients 562 and 578), 6 or 8 up to one in 50 (4-LUT shape, rows of 7: layer 64 -> 64 583 us with 6
-// slots and every tile completed later, 266 with 8).
+// Gather slots per row of the fused layer's kernels (5, 6 or 8).  A tile of 16 rows with a longer row costs the layer that
+// row's sum, unoverlapped, and the weight gradients most of one more tile, so the line lies lower than for the aggregation
+// alone: 5 slots up to one longer row in 300, five tiles in a hundred (Booth multipliers, one row in 1,700: layer 64 -> 32
+// 532 us with 5 slots, 561 with 6, weight gradients 584 and 599; rows of 6 spread at random, one in 500: layer 139 and 137,
+// weight gradients 148 and 138), 6 or 8 up to one in 50 (4-LUT shape, rows of 7: layer 64 -> 64 424 us with 6 slots, 256 with 8;
+// one row of 7 or 8 in 50: 206 and 189).
 template <class AtMost>
 int choose_layer_depth(int64_t n_ld, AtMost at_most)
 {

@@ -30,15 +30,18 @@
 // again.  So SD is the layer with unit weights whose own-row operand is scaled by the row's stored length.
 //
 // High-degree rows are aggregated beforehand by the HD kernel into a side buffer of the plan, one row per
-// high-degree row in ascending order of their ids.  A tile that contains one (or a row with more than D entries) is
-// noted, its result goes to the trash area, and it is computed by a plain path outside the loop, which picks those
-// sums up (the row's place in the buffer by binary search in the list of high-degree rows); so is the ragged last
-// tile.  The loop itself has no conditional load or store.
+// high-degree row in ascending order of their ids.  Such a row, and one with more than D entries, has no live slot: the
+// loop's own sum of it is zero, and before the tile is multiplied a branch parks the right one over it, straight from
+// global memory or from the side buffer (the row's place in it by a search over the list of high-degree rows).  The same
+// path computes the ragged last tile behind the loop.  All other loads and stores of the loop are unconditional.
+// A tile that was dropped, noted and computed as a whole behind the loop, high-degree rows by binary search, instead:
+// 1 M rows, 1 in 100 of 9 to 12 entries, 64 -> 64 309 us, now 209; 1 in 25 474, now 230; polarized degrees, 1 M rows 635,
+// now 483; multipliers, where one tile in 600 has such a row, the same to 2 % better.
 //
 // What bounds it: at 64 x 64 the power the chip grants dense bf16 matrix work beside the memory traffic (it runs at
 // 1.4 to 1.7 GHz).  Scalar tile arithmetic, the result stored from the accumulators, whole tiles only in the loop
-// (390 instead of 500 vector instructions per tile): 8.4 M rows of carry-save multipliers, 64 -> 64: 1,288 -> 1,214 us,
-// 32 -> 32: 630 -> 594 us (lines stored by halves instead: 1,364 and 675 us, 9 % more bytes written).
+// (390 instead of 500 vector instructions per tile): 8.4 M rows of carry-save multipliers, 64 -> 64: 1,285 -> 1,215 us,
+// 32 -> 32: 617 -> 580 us (lines stored by halves instead: 1,364 and 675 us, 9 % more bytes written).
 #include <type_traits>
 
 #include "groot_device.h"
@@ -46,8 +49,6 @@
 namespace groot {
 
 constexpr int kSpRows = 16;                  // rows per tile: the height of a matrix instruction
-constexpr int kSpPending = 16;               // tiles noted per wavefront for the plain path
-static_assert(kSpRows * 64 <= kTrashFloats, "a tile that the plain path computes is stored to the trash area");
 
 // Shapes for FI input and FO output features and NW wavefronts per workgroup (one workgroup per CU).
 template <int FI, int FO, int NW>
@@ -114,8 +115,7 @@ __device__ __forceinline__ void sp_park(char *tile, int row, int k, v4f x)
 // W: kOnes or kMean; D: gather slots per row on the pipelined path; P: bf16 pieces per fp32 operand, 3 or 2
 template <int W, int FI, int FO, int NW, int D, int P, bool SD = false>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void sage_pipe_kernel(
-    const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const char *__restrict__ X, char *H, int64_t zero_off, char *trash,
+    const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const char *__restrict__ X, char *H, int64_t zero_off,
     const float *__restrict__ Wn, const float *__restrict__ Ws, const float *__restrict__ bias, int relu, int64_t n, int64_t nnz,
     int32_t T, int64_t n_tiles, int64_t tiles_per_part, int64_t waves_per_part, int32_t parts,
     const int32_t *__restrict__ hd_rows, int32_t n_hd, const char *__restrict__ hd_agg)
@@ -133,7 +133,6 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
     __shared__ __align__(16) char s_A[kSpWaves][P * kSpPlane];           // F = 64, P = 3: 13,056 B per wavefront
     __shared__ __align__(16) sp_u4 s_W[kNb][kKs][P][kWave];              // F = 64, P = 3: 49,152 B: [nb][ks][piece][lane] weight operands
     __shared__ __align__(16) float s_bias[FO];
-    __shared__ int32_t s_pending[kSpWaves][kSpPending];
 
     // the wavefront's number as a scalar: the tile arithmetic below then runs on the scalar unit, and vector instructions
     // are what this kernel is short of
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
         const int32_t *const tile_col = col + (begin < nnz ? begin : 0);   // a dead slot reads the tile's first entry, or entry 0
         const int32_t rel = (int32_t)((uint32_t)rp_a - begin_lo);
         len_a = __shfl_down(rel, 1) - rel;
-        // a row with more entries than slots, or a high-degree row, has no live slot: the tile is left to the plain path
+        // a row with more entries than slots, or a high-degree row, has no live slot: patch() serves it
         fix_a = __ballot(l < kSpRows && (len_a > kSpD || len_a >= T)) != 0;
         live_a = 0;
         // unconditional loads: the number of loads in flight stays known
@@ -224,8 +223,14 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
     };
     constexpr int kSets = D <= 6 ? kSpG : kSpG / 2;      // sweeps in flight: a whole tile (half of it: 2 % slower), or what registers allow
     Regs rr[kSets];
+    // Whether the next tile's gathers arrive before this tile is multiplied.  Where the matrix instructions bound the kernel
+    // they are left in flight; on the other widths the memory system does better with fewer requests (8.4 M rows of
+    // carry-save multipliers, left in flight and drained: 64 -> 64 1,215 and 1,212 us, on 4.3 M rows of the Booth shape 682 and
+    // 691; 64 -> 16 868 and 828, 32 -> 64 804 and 782, 32 -> 16 506 and 484; two pieces per operand, 64 -> 64 1,125 and 1,109,
+    // 32 -> 32 576 and 552).  With 8 slots only half a tile is in flight: 4-LUT shape, 64 -> 64 254 and 260 us.
+    constexpr bool kDrain = D <= 6 && !(FI == 64 && FO == 64 && P == 3);
     const uint32_t x_lane = (uint32_t)g << kRowShift | 16 * f;
-    auto issue = [&](Regs &q, int64_t tile, int grp) {   // the tile whose slots are staged, a whole one
+    auto issue = [&](Regs &q, int64_t tile, int grp) {   // the tile whose slots are staged; a whole one
         const int lr = grp * kSpRpg + g;
         if (W == kMean || SD) q.inv = s_inv[w][lr];
 #pragma unroll
@@ -313,91 +318,89 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
         }
     };
 
-    int64_t tile = t_first;
-    while (tile < x_end) {
-        int pending = 0;
-        if (tile < x_full) {
-            // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
-            rp_a = load_rp(tile);
-            load_cols();
-            bool fix_cur = stage();
-            rp_a = load_rp(tile + stride);
-            load_cols();
-            rp_b = load_rp(tile + 2 * stride);
+    // ---- rows of a tile straight from global memory into the parked tile (A_hat X only), one per lane group: rows with more
+    //      entries than slots are summed here, high-degree rows come from the side buffer
+    auto patch = [&](int64_t t, bool all) {
+        const int64_t rp = load_rp(t), next_rp = __shfl_down(rp, 1);
+        const int64_t mine = l < kSpRows ? next_rp - rp : 0;
+        const uint32_t hd = (uint32_t)__ballot(l < kSpRows && mine >= T);
+        const int32_t place = hd ? hd_place(hd_rows, n_hd, t * kSpRows) : 0;   // of the tile's first high-degree row
+        uint32_t rows = (uint32_t)__ballot(l < kSpRows && (all || mine > kSpD || mine >= T));
+#pragma unroll 1
+        while (rows) {
+            uint32_t left = rows;                        // lane group g takes the g-th row that is left
 #pragma unroll
-            for (int grp = 0; grp < kSets; ++grp) issue(rr[grp], tile, grp);
-            __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the loop's own order of loads is the only one from here on
-
-            for (; tile < x_full && pending < kSpPending; tile += stride) {
-                const int64_t next = tile + stride < n_full ? tile + stride : n_full - 1;
-                bool fix_next = false;
-                // sums of this tile -> LDS, cut into bf16 pieces; a register set then takes the sweep kSets later
-#pragma unroll
-                for (int grp = 0; grp < kSpG; ++grp) {
-                    if (grp == kSpG - kSets) {           // this tile's sweeps are all issued: CSR of the next tile -> slot table
-                        fix_next = stage();
-                        rp_a = rp_b;
-                        load_cols();
-                        rp_b = load_rp(tile + 3 * stride);
-                    }
-                    Regs &q = rr[grp % kSets];
-                    const v4f a = sum(q);
-                    sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, 4 * f, a);
-                    sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, F + 4 * f, SD ? q.self * q.inv : q.self);
-                    issue(q, grp + kSets < kSpG ? tile : next, (grp + kSets) % kSpG);
-                }
-                sp_wave_sync();
-                v4f acc[kNb];
-#pragma unroll
-                for (int nb = 0; nb < kNb; ++nb) acc[nb] = bias4[nb];
-                // A tile with a row that the slots do not serve is noted and stored to the trash area (a scalar select: the
-                // number of stores in flight stays known).
-                if (!fix_cur) multiply(acc);
-                store(fix_cur ? trash : H + (tile << C::kORowShift) * kSpRows, acc, kSpRows);
-                sp_wave_sync();                          // the tile in LDS is free for the next round
-                if (fix_cur) {
-                    if (l == 0) s_pending[w][pending] = (int32_t)tile;
-                    ++pending;
-                }
-                fix_cur = fix_next;
+            for (int i = 0; i < kSpRpg; ++i) {
+                if (i < g) left &= left - 1;
+                rows &= rows - 1;
             }
-        }
-        if (tile >= x_full && tile < x_end && pending < kSpPending) {   // the ragged last tile
-            if (l == 0) s_pending[w][pending] = (int32_t)tile;
-            ++pending;
-            tile += stride;
-        }
-        // ---- plain path: the noted tiles, every row straight from global memory, high-degree sums from the side buffer
-        sp_wave_sync();
-#pragma unroll 1
-        for (int i = 0; i < pending; ++i) {
-            const int64_t t = __builtin_amdgcn_readfirstlane(s_pending[w][i]);
-            const int64_t rp = load_rp(t);               // rows past the end: no entries
-#pragma unroll 1
-            for (int grp = 0; grp < kSpG; ++grp) {
-                const int lr = grp * kSpRpg + g;
-                const int64_t row = t * kSpRows + lr, s = __shfl(rp, lr), e = __shfl(rp, lr + 1);
-                v4f a, own = *(const v4f *)(Xf + ((row < n ? row : n - 1) << kRowShift));   // past the end: not stored
-                if (e - s >= T) {
-                    int32_t lo = 0, hi = n_hd;           // the row's place in the list of high-degree rows
-                    while (lo < hi) {
-                        const int32_t mid = (lo + hi) / 2;
-                        if (hd_rows[mid] < row) lo = mid + 1; else hi = mid;
-                    }
-                    a = *(const v4f *)(hd_agg + ((int64_t)lo << kRowShift) + 16 * f);
-                } else {
-                    a = ld_row_sum<W, false, 8>(s, e, col, val, (const v4f *)X, kSpL, f);
-                }
-                if (SD) own *= (float)(e - s);
+            const int lr = left ? __builtin_ctz(left) : 0;
+            const int64_t s = __shfl(rp, lr), e = __shfl(rp, lr + 1);
+            if (left) {
+                const v4f a = (hd >> lr) & 1
+                    ? *(const v4f *)(hd_agg + ((int64_t)(place + __popc(hd & ((1u << lr) - 1))) << kRowShift) + 16 * f)
+                    : row_sum_ahead<W>(s, e, col, Xf, kRowShift, zero_off);
                 sp_park<kSpBRow, kSpPlane, P>(a_tile, lr, 4 * f, a);
-                sp_park<kSpBRow, kSpPlane, P>(a_tile, lr, F + 4 * f, own);
             }
+        }
+    };
+
+    int64_t tile = t_first;
+    if (tile < x_full) {
+        // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
+        rp_a = load_rp(tile);
+        load_cols();
+        bool fix_cur = stage();
+        rp_a = load_rp(tile + stride);
+        load_cols();
+        rp_b = load_rp(tile + 2 * stride);
+#pragma unroll
+        for (int grp = 0; grp < kSets; ++grp) issue(rr[grp], tile, grp);
+        __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): the loop's own order of loads is the only one from here on
+
+        for (; tile < x_full; tile += stride) {
+            const int64_t next = tile + stride < n_full ? tile + stride : n_full - 1;
+            bool fix_next = false;
+            // sums of this tile -> LDS, cut into bf16 pieces; a register set then takes the sweep kSets later
+#pragma unroll
+            for (int grp = 0; grp < kSpG; ++grp) {
+                if (grp == kSpG - kSets) {               // this tile's sweeps are all issued: CSR of the next tile -> slot table
+                    fix_next = stage();
+                    rp_a = rp_b;
+                    load_cols();
+                    rp_b = load_rp(tile + 3 * stride);
+                }
+                Regs &q = rr[grp % kSets];
+                const v4f a = sum(q);
+                sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, 4 * f, a);
+                sp_park<kSpBRow, kSpPlane, P>(a_tile, grp * kSpRpg + g, F + 4 * f, SD ? q.self * q.inv : q.self);
+                issue(q, grp + kSets < kSpG ? tile : next, (grp + kSets) % kSpG);
+            }
+            if (fix_cur) patch(tile, false);             // the rows that had no live slots, parked again
+            if constexpr (kDrain) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
             sp_wave_sync();
             v4f acc[kNb];
             multiply(acc);
-            store(H + (t << C::kORowShift) * kSpRows, acc, n - t * kSpRows < kSpRows ? (int)(n - t * kSpRows) : kSpRows);
-            sp_wave_sync();
+            store(H + (tile << C::kORowShift) * kSpRows, acc, kSpRows);
+            sp_wave_sync();                              // the tile in LDS is free for the next round
+            fix_cur = fix_next;
         }
+    }
+    if (tile < x_end) {                                  // the ragged last tile
+        const int64_t rp = load_rp(tile), next_rp = __shfl_down(rp, 1);
+#pragma unroll 1
+        for (int grp = 0; grp < kSpG; ++grp) {
+            const int lr = grp * kSpRpg + g;
+            const int64_t row = tile * kSpRows + lr;
+            v4f own = *(const v4f *)(Xf + ((row < n ? row : n - 1) << kRowShift));   // past the end: not stored
+            if (SD) own *= (float)__shfl(next_rp - rp, lr);
+            sp_park<kSpBRow, kSpPlane, P>(a_tile, lr, F + 4 * f, own);
+        }
+        patch(tile, true);                               // rows past the end: no entries
+        sp_wave_sync();
+        v4f acc[kNb];
+        multiply(acc);
+        store(H + (tile << C::kORowShift) * kSpRows, acc, (int)(n - tile * kSpRows));
     }
 }
 
@@ -448,15 +451,12 @@ int launch_sage_pipe(const DevicePlan &dp, const float *X, float *H, const float
     const int64_t tiles_per_part = (n_tiles + parts - 1) / parts;
     const int64_t waves_per_part = n_wg / parts * kNwRun;
     if (!grid_ok(n_wg) || n_tiles <= 0) return (int)hipErrorInvalidConfiguration;
-    // the kernel reads entry 0 of the index (and weight) array from idle lanes: give it something to read
-    // when the matrix has no entries, or no weight array
+    // the kernel reads entry 0 of the index array from idle lanes: give it something to read when the matrix has no entries
     const int32_t *col_arg = dp.col ? dp.col : (const int32_t *)dp.rowptr;
-    const float *val_arg = dp.val ? dp.val : (const float *)dp.rowptr;
-    char *trash = (char *)(dp.zero_row + kZeroRowFloats);
     hipStream_t st = (hipStream_t)stream;
 #define GROOT_SAGE_PIPE_LAUNCH(WM, FFI, FFO, DD, PP)                                                                   \
     sage_pipe_kernel<WM, FFI, FFO, kNwRun, DD, PP, SDV><<<dim3((unsigned)n_wg), dim3(kNwRun * kWave), 0, st>>>(        \
-        dp.rowptr, col_arg, val_arg, (const char *)X, (char *)H, byte_distance(X, dp.zero_row), trash, Wn, Ws, bias, relu, \
+        dp.rowptr, col_arg, (const char *)X, (char *)H, byte_distance(X, dp.zero_row), Wn, Ws, bias, relu, \
         dp.n, dp.nnz, dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows,         \
         (const char *)dp.hd_agg)
 #define GROOT_SAGE_PIPE_P(WM, FFI, FFO, DD)                               \

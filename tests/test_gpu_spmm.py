@@ -655,9 +655,8 @@ def test_weight_gradients_at_the_edges_of_the_pipeline(torch_cuda, F_in, F_out, 
 
 @pytest.mark.parametrize("case", ["all_noted", "lut4", "cells", "ragged"])
 def test_fused_layer_at_the_edges_of_the_pipeline(torch_cuda, case):
-    """Edges of the layer kernel's bookkeeping.  "all_noted": T = 4 makes nearly every row high-degree, so every tile is
-    noted and wavefronts have more of them (717,900 rows, 44,869 tiles over 2,048 wavefronts) than the 16 they note
-    before they must complete them.  "lut4": rows of 7 entries, 8 slots per row and half a tile in flight; "cells":
+    """Edges of the layer kernel's pipeline.  "all_noted": T = 4 makes nearly every row high-degree, so every tile of every
+    wavefront (717,900 rows, 44,869 tiles over 2,048 wavefronts) has rows that its slots do not serve.  "lut4": rows of 7 entries, 8 slots per row and half a tile in flight; "cells":
     rows of 6.  "ragged": a last tile of 1 row, and of 15; forward layer, input gradient and weight gradients."""
     torch = torch_cuda
     if case == "all_noted":
@@ -678,6 +677,74 @@ def test_fused_layer_at_the_edges_of_the_pipeline(torch_cuda, case):
                 _sage_check(torch, g, rowptr, col, val, 32, n, 44 + F, False, True, case, F=F, F_out=FO)
                 _backward_data_check(torch, g, rowptr, col, val, 32, n, 45 + F, F, FO)
                 _wgrad_check(torch, g, rowptr, col, val, 32, n, 46 + F, F, F_out=FO)
+
+
+def _graph_of_row_lengths(lens, seed):
+    """CSR arrays with these row lengths: consecutive columns from a random one within 1,000 of the row, mean weights"""
+    rng = np.random.default_rng(seed)
+    n = lens.shape[0]
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    first = np.clip(np.arange(n) + rng.integers(-1000, 1000, n), 0, n - lens)
+    row = np.repeat(np.arange(n), lens)
+    col = (first[row] + np.arange(rowptr[-1]) - rowptr[row]).astype(np.int32)
+    val = np.repeat(np.float32(1) / np.maximum(lens, 1).astype(np.float32), lens).astype(np.float32)
+    return rowptr, col, val
+
+
+@pytest.mark.parametrize("n_hd", [0, 1, 64, 65, 4096, 4097])
+def test_fused_layer_rows_that_the_slots_do_not_serve(torch_cuda, n_hd):
+    """Rows of every length from 0 to 31 among short ones, and n_hd high-degree rows: the sums that are parked over a tile's
+    own (eight entries at a time: 8, 9, 16, 17, 24, 25), the search for a row's place in the list of high-degree rows (64
+    samples a step: one step up to 64 rows, two up to 4,096), first and last row of the graph among them, a ragged last
+    tile with long rows."""
+    rng = np.random.default_rng(60 + n_hd)
+    n = 16 * 640 + 11
+    lens = rng.integers(3, 6, n)
+    odd = rng.permutation(n)[:3200]
+    lens[odd] = np.arange(3200) % 32
+    heavy = np.concatenate([[0, n - 1], 1 + rng.permutation(n - 2)])[:n_hd]
+    lens[heavy] = rng.integers(32, 40, n_hd)
+    rowptr, col, val = _graph_of_row_lengths(lens, 61)
+    g = G.groot_graph_from_csr(rowptr, col, val)
+    assert G.groot_plan_view(G.groot_spmm_plan(g, 32))["n_hd"] == n_hd
+    for F, FO in ((64, 64), (32, 16)):
+        _sage_check(torch_cuda, g, rowptr, col, val, 32, n, 62 + F, False, True, f"{n_hd} heavy", F=F, F_out=FO)
+        _wgrad_check(torch_cuda, g, rowptr, col, val, 32, n, 63 + F, F, F_out=FO)
+
+
+def _best_time(torch, fn, reps=8, inner=4):
+    """milliseconds of a call among others, the best of some"""
+    best = float("inf")
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(inner):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / inner)
+    return best
+
+
+def test_a_few_long_rows_do_not_slow_the_layer_down(torch_cuda):
+    """One row in 50 with 9 to 12 entries, so that one tile in four has one: the layer takes what these rows' own entries
+    take (1.15 times the layer without them, measured), not the time of computing such tiles twice (2.0 times)."""
+    torch = torch_cuda
+    n, times = 1 << 20, []
+    for frac in (0.0, 0.02):
+        rng = np.random.default_rng(8)
+        lens = rng.integers(4, 6, n)
+        long = rng.random(n) < frac
+        lens[long] = rng.integers(9, 13, int(long.sum()))
+        g = G.groot_graph_from_csr(*_graph_of_row_lengths(lens, 9))
+        plan = G.groot_spmm_plan(g, 32)
+        G.groot_plan_upload(plan, 64)
+        X, H = torch.rand((n, 64), device="cuda"), torch.empty((n, 64), device="cuda")
+        W = torch.rand((2, 64, 64), device="cuda")
+        call = lambda: G.groot_sage_layer_forward(plan, X, W[0], W[1], None, False, H, 64)
+        call()
+        times.append(_best_time(torch, call))
+    assert times[1] < 1.4 * times[0], f"{times[0]:.3f} ms without long rows, {times[1]:.3f} ms with"
 
 
 def test_calls_that_only_enqueue_run_under_graph_capture(torch_cuda):
