@@ -98,8 +98,7 @@ __device__ __forceinline__ void wg_mfma_4x4(v4f (&c0)[4], v4f (&c1)[4], v4f (&c2
 // W: kOnes or kMean; FI: width of X; FO: width of dZ; D: gather slots per row on the pipelined path (5, 6 or 8)
 template <int W, int FI, int FO, int D>
 __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_eu(kWgWaves / 4, kWgWaves / 4))) void sage_wgrad_kernel(
-    const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
-    const char *__restrict__ X, const char *__restrict__ dZ, int64_t zero_off, int64_t n, int64_t nnz, int32_t T, int64_t n_tiles,
+    const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const char *__restrict__ X, const char *__restrict__ dZ, int64_t zero_off, int64_t n, int64_t nnz, int32_t T, int64_t n_tiles,
     int64_t tiles_per_part, int64_t waves_per_part, int32_t parts, const int32_t *__restrict__ hd_rows, int32_t n_hd,
     const char *__restrict__ hd_agg, v4f *__restrict__ partials)
 {
@@ -334,6 +333,8 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                 const int64_t rp = load_rp(t);           // rows past the end: no entries
                 const int64_t next_rp = __shfl_down(rp, 1);
                 const uint64_t redo = __ballot(l < kWgRows && (ragged || next_rp - rp > D || next_rp - rp >= T));
+                const uint32_t hd = (uint32_t)__ballot(l < kWgRows && next_rp - rp >= T);
+                const int32_t place = hd ? hd_place(hd_rows, n_hd, t * kWgRows) : 0;   // of the tile's first high-degree row
 #pragma unroll 1
                 for (int grp = 0; grp < kG; ++grp) {
                     if ((redo >> (grp * kRpg) & ((1u << kRpg) - 1)) == 0) continue;
@@ -341,16 +342,10 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                     const int64_t row = t * kWgRows + lr, s = __shfl(rp, lr), e = __shfl(rp, lr + 1);
                     const v4f zero = {0.f, 0.f, 0.f, 0.f};
                     v4f a = zero;
-                    if (e - s >= T) {
-                        int32_t lo = 0, hi = n_hd;       // the row's place in the list of high-degree rows
-                        while (lo < hi) {
-                            const int32_t mid = (lo + hi) / 2;
-                            if (hd_rows[mid] < row) lo = mid + 1; else hi = mid;
-                        }
-                        a = *(const v4f *)(hd_agg + ((int64_t)lo << kRowShift) + 16 * f);
-                    } else if (ragged || e - s > D) {
-                        a = ld_row_sum<W, false, 8>(s, e, col, val, (const v4f *)X, kL, f);
-                    }
+                    if ((hd >> lr) & 1)
+                        a = *(const v4f *)(hd_agg + ((int64_t)(place + __popc(hd & ((1u << lr) - 1))) << kRowShift) + 16 * f);
+                    else if (ragged || e - s > D)
+                        a = row_sum_ahead<W>(s, e, col, Xf, kRowShift, zero_off);
                     ZVec z[kP];
 #pragma unroll
                     for (int p = 0; p < kP; ++p)
@@ -468,10 +463,9 @@ static int wgrad_launch(const DevicePlan &dp, const float *X, const float *dZ, f
     if (!grid_ok(n_wg) || n_tiles <= 0) return (int)hipErrorInvalidConfiguration;
     // the kernel reads entry 0 of the index array from idle lanes: give it something to read when the matrix has no entries
     const int32_t *col_arg = dp.col ? dp.col : (const int32_t *)dp.rowptr;
-    const float *val_arg = dp.val ? dp.val : (const float *)dp.rowptr;
 #define GROOT_WGRAD_LAUNCH(WM, DD)                                                                                      \
     sage_wgrad_kernel<WM, FI, FO, DD><<<dim3((unsigned)n_wg), dim3(kWgWaves * kWave), 0, st>>>(                            \
-        dp.rowptr, col_arg, val_arg, (const char *)X, (const char *)dZ, byte_distance(X, dp.zero_row), dp.n, dp.nnz, dp.threshold, \
+        dp.rowptr, col_arg, (const char *)X, (const char *)dZ, byte_distance(X, dp.zero_row), dp.n, dp.nnz, dp.threshold, \
         n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows, (const char *)dp.hd_agg,    \
         (v4f *)workspace)
     if (dp.weight_mode == kMean) {
