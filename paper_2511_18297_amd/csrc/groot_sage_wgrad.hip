@@ -259,7 +259,12 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                 }
             }
         };
-        int until_fold = kWgFold;
+        int until_fold = kWgFold;                        // tiles that may still be added before the next fold
+        auto fold_now = [&]() {
+            fold();
+            clear();
+            until_fold = kWgFold;
+        };
         int64_t tile = t_first;
         while (tile < x_end) {
             int pending = 0;
@@ -308,11 +313,7 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                     }
                     fix_cur = fix_next;
                     if constexpr (kFold) {
-                        if (--until_fold == 0) {
-                            fold();
-                            clear();
-                            until_fold = kWgFold;
-                        }
+                        if (--until_fold == 0) fold_now();
                     }
                 }
             }
@@ -326,6 +327,10 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
             //      added zeros, and all of the ragged tile.  Outside the loop because the registers that hold its rows
             //      in flight are needed here (inside it they were spilled), and so that its loads are all unconditional.
             wg_wave_sync();
+            static_assert(kWgPending <= kWgFold, "the noted tiles fit between two folds");
+            if constexpr (kFold) {
+                if (pending > until_fold) fold_now();
+            }
 #pragma unroll 1
             for (int i = 0; i < pending; ++i) {
                 const int64_t t = __builtin_amdgcn_readfirstlane(s_pending[w][i]);
@@ -353,6 +358,10 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                     multiply(0, a, z);
                     if (ragged) multiply(kMc, row < n ? load_self(t, grp) : zero, z);
                 }
+            }
+            if constexpr (kFold) {
+                until_fold -= pending;
+                if (until_fold == 0) fold_now();
             }
         }
     }

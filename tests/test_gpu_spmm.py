@@ -712,6 +712,33 @@ def test_fused_layer_rows_that_the_slots_do_not_serve(torch_cuda, n_hd):
         _wgrad_check(torch_cuda, g, rowptr, col, val, 32, n, 63 + F, F, F_out=FO)
 
 
+def test_weight_gradients_noted_tiles_count_towards_a_fold(torch_cuda):
+    """A wavefront's accumulators take at most 512 rows between two additions to its second set of sums, the tiles that it
+    notes and completes later among them.  The first wavefront's first 32 tiles have a row of 8 entries each, so they are
+    noted, and the first of these rows adds 2^27 to every sum; its next 32 tiles add 512 rows of ones, every four of which
+    would be lost beside 2^27 (spacing 16) but not as 512."""
+    torch = torch_cuda
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    stride = cus // 8 * 8                                    # wavefronts that share an eighth of the tiles
+    n = 16 * 8 * 64 * stride
+    tile_row = 16 * stride * np.arange(64)                   # first rows of the first wavefront's tiles
+    lens = np.ones(n, np.int64)
+    lens[tile_row[:32]] = 8
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = np.repeat(np.arange(n), lens).astype(np.int32)
+    col += (np.arange(rowptr[-1]) - rowptr[col]).astype(np.int32)
+    val = np.repeat(np.float32(1) / lens.astype(np.float32), lens).astype(np.float32)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, 32)
+    X, dZ = torch.ones((n, 32), device="cuda"), torch.zeros((n, 16), device="cuda")
+    dZ[0] = 2.0 ** 27
+    dZ[torch.from_numpy((tile_row[32:, None] + np.arange(16)).ravel()).cuda()] = 1.0
+    ws = torch.empty(G.groot_sage_layer_backward_weights_workspace(plan, 32, 16) // 4, device="cuda")
+    dW = torch.empty((2, 32, 16), device="cuda")
+    G.groot_sage_layer_backward_weights(plan, X, dZ, dW[0], dW[1], ws)
+    assert bool((dW == 2.0 ** 27 + 512).all()), (dW - 2.0 ** 27).unique()
+
+
 def _best_time(torch, fn, reps=8, inner=4):
     """milliseconds of a call among others, the best of some"""
     best = float("inf")
