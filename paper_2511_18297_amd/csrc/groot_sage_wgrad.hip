@@ -28,8 +28,8 @@
 //
 // An accumulator that took a whole sweep's rows one after the other would round N / 2048 times.  Where LDS has room for a
 // second set of sums (every width but 64 x 64), the accumulators are added to it every kWgFold tiles and cleared.  At
-// the end a workgroup's wavefronts are added in fp64 and written as one slice of a workspace; a second kernel adds the
-// slices in a fixed order in fp64.  No atomics: the result is the same on every run.
+// the end a workgroup's wavefronts are added in fp64 and written, in fp64, as one slice of a workspace; a second kernel adds the
+// slices in a fixed order.  No atomics: the result is the same on every run.
 #include <type_traits>
 
 #include "groot_device.h"
@@ -46,6 +46,7 @@ constexpr int kWgWaves = 8;
 constexpr bool wg_folds(int FI, int FO) { return FI * FO < 64 * 64; }    // 64 x 64: the second set of sums would be 256 KB
 
 typedef float wg_f2 __attribute__((ext_vector_type(2)));
+typedef double wg_d2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ void wg_wave_sync()
 {
@@ -100,7 +101,7 @@ template <int W, int FI, int FO, int D>
 __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_eu(kWgWaves / 4, kWgWaves / 4))) void sage_wgrad_kernel(
     const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const char *__restrict__ X, const char *__restrict__ dZ, int64_t zero_off, int64_t n, int64_t nnz, int32_t T, int64_t n_tiles,
     int64_t tiles_per_part, int64_t waves_per_part, int32_t parts, const int32_t *__restrict__ hd_rows, int32_t n_hd,
-    const char *__restrict__ hd_agg, v4f *__restrict__ partials)
+    const char *__restrict__ hd_agg, wg_d2 *__restrict__ partials)
 {
     static_assert(FI == 64 || FI == 32, "width of X");
     static_assert(FO == 64 || FO == 32 || FO == 16, "width of dZ");
@@ -397,43 +398,42 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
         }
         __syncthreads();
     }
-    v4f *mine = partials + (int64_t)blockIdx.x * kVecs;
+    wg_d2 *mine = partials + (int64_t)blockIdx.x * kVecs * 2;
 #pragma unroll
     for (int i = 0; i < kMine; ++i) {
         const int e = i * kWgWaves * kWave + threadIdx.x;
-        if (e < kVecs) mine[e] = (v4f){(float)t[i][0], (float)t[i][1], (float)t[i][2], (float)t[i][3]};
+        if (e < kVecs) {
+            mine[e] = (wg_d2){t[i][0], t[i][1]};         // registers 0 and 1 of all lanes, then 2 and 3: whole lines per store
+            mine[kVecs + e] = (wg_d2){t[i][2], t[i][3]};
+        }
     }
 }
 
 // dWn[m][n] (m < FI) and dWs[m - FI][n] = sum over the workgroups' slices in fp64, in a fixed order.  A workgroup takes
-// 16 float4 of a slice; its 16 groups of 16 threads take every 16th slice each, so that a slice count of 256 is 16 loads
-// in flight per thread and one latency (one thread per element walking 2,048 slices took 42 us at 64 x 64 and 94 us at
+// 16 pairs of a slice's numbers; its 16 groups of 16 threads take every 16th slice each, so that a slice count of 256 is 16
+// loads in flight per thread and one latency (one thread per element walking 2,048 slices took 42 us at 64 x 64 and 94 us at
 // 32 x 32, where 8 workgroups had it all), then the groups are added in order.
 constexpr int kWgRedVec = 16, kWgRedGroups = kBlock / kWgRedVec;
 template <int FI, int FO>
-__global__ __launch_bounds__(kBlock) void sage_wgrad_reduce_kernel(const v4f *__restrict__ partials, int64_t slices,
+__global__ __launch_bounds__(kBlock) void sage_wgrad_reduce_kernel(const wg_d2 *__restrict__ partials, int64_t slices,
                                                                    float *__restrict__ dWn, float *__restrict__ dWs)
 {
-    constexpr int kMc = FI / 16, kNb = FO / 16, kVecs = 2 * FI * FO / 4;
-    static_assert(kVecs % kWgRedVec == 0, "whole workgroups");
-    __shared__ double s_part[kWgRedGroups][kWgRedVec][4];
+    constexpr int kMc = FI / 16, kNb = FO / 16, kPairs = 2 * FI * FO / 2;
+    static_assert(kPairs % kWgRedVec == 0, "whole workgroups");
+    __shared__ double s_part[kWgRedGroups][kWgRedVec][2];
     const int v = threadIdx.x % kWgRedVec, grp = threadIdx.x / kWgRedVec;
-    const int e = blockIdx.x * kWgRedVec + v;            // float4 of the slice: block e / 64, lane e % 64
-    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    wg_d2 t = {0.0, 0.0};
 #pragma unroll 16
-    for (int64_t k = grp; k < slices; k += kWgRedGroups) {
-        const v4f x = partials[k * kVecs + e];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) t[r] += (double)x[r];
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) s_part[grp][v][r] = t[r];
+    for (int64_t k = grp; k < slices; k += kWgRedGroups) t += partials[k * kPairs + blockIdx.x * kWgRedVec + v];
+    s_part[grp][v][0] = t[0];
+    s_part[grp][v][1] = t[1];
     __syncthreads();
-    if (threadIdx.x >= kWgRedVec * 4) return;
-    const int ve = threadIdx.x / 4, r = threadIdx.x % 4;
+    if (threadIdx.x >= kWgRedVec * 2) return;
     double sum = 0.0;
-    for (int q = 0; q < kWgRedGroups; ++q) sum += s_part[q][ve][r];
-    const int el = blockIdx.x * kWgRedVec + ve, blk = el / kWave, lane = el % kWave;
+    for (int q = 0; q < kWgRedGroups; ++q) sum += (&s_part[q][0][0])[threadIdx.x];
+    // pair of the slice: registers 0 and 1 of every block and lane, then registers 2 and 3
+    const int at = blockIdx.x * kWgRedVec + threadIdx.x / 2, half = at / (kPairs / 2), e = at % (kPairs / 2);
+    const int blk = e / kWave, lane = e % kWave, r = 2 * half + threadIdx.x % 2;
     const int mb = blk / kNb, nb = blk % kNb;            // accumulator acc[mb][nb]: rows 4 (lane / 16) + r, column lane % 16
     float *out = mb < kMc ? dWn : dWs;
     out[wg_feature<FI>(4 * (lane / 16) + r, mb % kMc) * FO + kNb * (lane % 16) + nb] = (float)sum;
@@ -448,8 +448,9 @@ static int64_t wgrad_workgroups()
     return n_wg < kXcds ? kXcds : n_wg;
 }
 
-// bytes of workspace that launch_sage_wgrad asks for at these widths on the current device (0 on failure): one slice per
-// SIMD (F_in = 64) or two (32).  The kernel fills one slice per workgroup; the size is part of the interface.
+// bytes of workspace that launch_sage_wgrad asks for at these widths on the current device (0 on failure): 2 F_in F_out
+// floats per SIMD (F_in = 64) or twice that (32).  The kernel fills 2 F_in F_out doubles per workgroup, a half or a quarter of
+// it; the size is part of the interface.
 size_t sage_wgrad_workspace_bytes(int32_t FI, int32_t FO)
 {
     const int64_t n_wg = wgrad_workgroups();
@@ -476,7 +477,7 @@ static int wgrad_launch(const DevicePlan &dp, const float *X, const float *dZ, f
     sage_wgrad_kernel<WM, FI, FO, DD><<<dim3((unsigned)n_wg), dim3(kWgWaves * kWave), 0, st>>>(                            \
         dp.rowptr, col_arg, (const char *)X, (const char *)dZ, byte_distance(X, dp.zero_row), dp.n, dp.nnz, dp.threshold, \
         n_tiles, tiles_per_part, waves_per_part, parts, dp.hd_rows, (int32_t)dp.n_hd_rows, (const char *)dp.hd_agg,    \
-        (v4f *)workspace)
+        (wg_d2 *)workspace)
     if (dp.weight_mode == kMean) {
         if (dp.sage_depth == 5) GROOT_WGRAD_LAUNCH(kMean, 5);
         else if (dp.sage_depth == 6) GROOT_WGRAD_LAUNCH(kMean, 6);
@@ -489,7 +490,7 @@ static int wgrad_launch(const DevicePlan &dp, const float *X, const float *dZ, f
 #undef GROOT_WGRAD_LAUNCH
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return (int)err;
-    sage_wgrad_reduce_kernel<FI, FO><<<dim3(2 * FI * FO / 4 / kWgRedVec), dim3(kBlock), 0, st>>>((const v4f *)workspace, n_wg, dWn, dWs);
+    sage_wgrad_reduce_kernel<FI, FO><<<dim3(2 * FI * FO / 2 / kWgRedVec), dim3(kBlock), 0, st>>>((const wg_d2 *)workspace, n_wg, dWn, dWs);
     return (int)hipGetLastError();
 }
 

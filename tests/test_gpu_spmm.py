@@ -739,6 +739,23 @@ def test_weight_gradients_noted_tiles_count_towards_a_fold(torch_cuda):
     assert bool((dW == 2.0 ** 27 + 512).all()), (dW - 2.0 ** 27).unique()
 
 
+@pytest.mark.parametrize("F_in,F_out", [(64, 64), (64, 16), (32, 32)])
+def test_weight_gradients_of_the_wavefronts_meet_in_fp64(torch_cuda, F_in, F_out):
+    """2,048 rows, one tile per wavefront: two wavefronts of a workgroup add 2^24 and 1, one of another workgroup -2^24.  No
+    fp32 rounding on the way between them: the sum is 1."""
+    torch = torch_cuda
+    n = 2048
+    rowptr, col, val = np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32), np.ones(n, np.float32)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F_in)
+    X, dZ = torch.ones((n, F_in), device="cuda"), torch.zeros((n, F_out), device="cuda")
+    dZ[0], dZ[16], dZ[8 * 16] = 2.0 ** 24, 1.0, -2.0 ** 24
+    ws = torch.empty(G.groot_sage_layer_backward_weights_workspace(plan, F_in, F_out) // 4, device="cuda")
+    dW = torch.empty((2, F_in, F_out), device="cuda")
+    G.groot_sage_layer_backward_weights(plan, X, dZ, dW[0], dW[1], ws)
+    assert bool((dW == 1.0).all()), dW.unique()
+
+
 def _best_time(torch, fn, reps=8, inner=4):
     """milliseconds of a call among others, the best of some"""
     best = float("inf")
