@@ -189,13 +189,14 @@ static int lanes_for(int32_t F4)
     }
 
 // The pipelined kernel serves the leading rows of a graph at F = 32, 64 and 128, whole graphs also at the widths between:
-// from 20 on with 5 or 6 slots per row (512-bit multiplier, plain against pipelined kernel: F = 16 107 and 105 us with more than
-// twice the time at 8, F = 20 145 and 122, F = 100 ... 200 a quarter less), from 36 on with 7 or 8 (4-LUT shape: F = 20 55 and
-// 62 us, F = 36 88 and 88, F = 124 257 and 233), up to 256 (64 lanes of one float4).
+// from 20 on with 5 slots per row (512-bit multiplier, plain against pipelined kernel: F = 16 107 and 105 us with more than
+// twice the time at 8, F = 20 145 and 122, F = 100 ... 200 a quarter less), from 36 on with 6 to 8 (shape mapped to cells, rows
+// of 6: F = 20 50 and 56 us, F = 28 54 and 60; 4-LUT shape: F = 20 55 and 62, F = 36 88 and 88, F = 124 257 and 233), up to 256
+// (64 lanes of one float4).
 static bool ld_pipelined(const DevicePlan &dp, int32_t F4, const RowOut *out)
 {
     if (!dp.zero_row || !dp.ld_pipelined) return false;
-    return F4 == 8 || F4 == 16 || F4 == 32 || (!out && F4 <= kWave && F4 > (dp.pipe_depth <= 6 ? 4 : 8));
+    return F4 == 8 || F4 == 16 || F4 == 32 || (!out && F4 <= kWave && F4 > (dp.pipe_depth <= 5 ? 4 : 8));
 }
 
 bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out)
