@@ -20,8 +20,8 @@
 //  * The steady state has no branch and no conditional load or store, so the compiler's vmcnt waits are
 //    exact: the wait before a group's sum leaves the G-1 younger groups in flight.  A row that does not
 //    fit (more than D entries, or a high-degree row) is masked: all its slots point at the zero row and
-//    its sum is stored to a trash area instead of Y (an address select, not a branch); the high-degree
-//    kernel, or a workgroup behind the sweep for low-degree rows longer than D, computes it.  Only the ragged
+//    its sum is stored to a trash area instead of Y, or past the end of a buffer descriptor, where the
+//    hardware drops it (an address select, not a branch); the high-degree kernel, or a workgroup behind the sweep for low-degree rows longer than D, computes it.  Only the ragged
 //    last tile is masked as a whole and redone by a plain, unoverlapped path.
 //  * No workgroup barrier after the start (the list of hot rows is copied to LDS once): wavefronts share
 //    nothing else.
@@ -38,6 +38,11 @@ constexpr int kPipeWaves = 4;                // wavefronts per workgroup, one wo
 // 14.0 / 13.8 / 13.9 ms for 2..8); 8 lanes (F = 32): 6.46 / 6.36 ms for 5 / 7; 32 lanes (F = 128): 31.0 / 30.5 /
 // 31.3 ms per step for 5 / 7 / 8
 constexpr int pipe_groups(int L) { return L == 4 ? 3 : 7; }   // 4 lanes per row: as many as row pointers fit one wavefront
+
+typedef unsigned int pipe_u4 __attribute__((ext_vector_type(4)));
+constexpr int kPipeRawBuffer = 0x00027000;   // last word of a buffer descriptor: raw 32-bit data, offsets checked against the size
+constexpr int kPipeNontemporal = 2;
+constexpr uint32_t kPipeDropped = 0x40000000;
 
 __device__ __forceinline__ void pipe_wave_sync()
 {
@@ -72,8 +77,10 @@ struct CompactCsr {
 // M: the sum of row r goes to row out_ids[r] of Y (the owned rows of a part written into place in the matrix of
 // the whole graph); n is then the number of leading rows that are wanted.  Only without the compact matrix.
 // S: rows of F4 float4, any number up to L (otherwise F4 = L): the lanes past a row's end do what the lane of its last
-// float4 does, and store the same value to the same place (a trash area for them made a hot spot of it: 4-LUT shape,
-// 0.5 M rows, F = 124: 574 us, now 233).
+// float4 does, and store the same value to the same place.  No trash area here: parts of a line written to one place by all
+// wavefronts wait for one another (lanes past the end, 4-LUT shape, 0.5 M rows, F = 124: 574 us, now 233; masked rows, 4 M
+// rows, one in 27 masked, F = 100: 2,140 us, now 1,095).  With whole lines it costs next to nothing and the plain store is
+// the faster one (8.4 M rows of carry-save multipliers, F = 32: 491 us, through the descriptor 502; F = 64 942 and 951).
 // The workgroups behind the first n_ld of the grid compute the rows of the row list, then (n_hd of them) the pieces of the
 // high-degree rows: see SideWork.
 template <int L, int W, int G, int D, bool C, bool M = false, bool S = false>
@@ -287,14 +294,21 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
         oid_b = load_oid(tile + 3 * stride);
         const int64_t base = tile * kTileRows;
         char *const ybase = Y + row_bytes(base) + 16 * f;
+        const __amdgpu_buffer_rsrc_t ytile =             // S: the tile's rows of Y; a store past their end is dropped
+            __builtin_amdgcn_make_buffer_rsrc(Y + row_bytes(base), 0, (int)row_bytes(kTileRows), kPipeRawBuffer);
 #pragma unroll
         for (int grp = 0; grp < G; ++grp) {
             const v4f a = sum(rr[grp]);
             const int lr = grp * kRpg + g;
-            // a masked row (every row of a tile that is not ok) goes to the trash area: a select, no branch
-            char *const yrow = M ? Y + rr[grp].oid + 16 * f : ybase + (int)row_bytes(lr);
-            char *const dst = rr[grp].inv >= 0.f ? yrow : tbase + (lr << kRowShift);
-            __builtin_nontemporal_store(a, (v4f *)dst);
+            // a masked row (every row of a tile that is not ok) is not stored: a select of the address, no branch
+            if constexpr (S) {
+                const uint32_t off = rr[grp].inv >= 0.f ? (uint32_t)row_bytes(lr) + 16 * f : kPipeDropped;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(pipe_u4, a), ytile, (int)off, 0, kPipeNontemporal);
+            } else {
+                char *const yrow = M ? Y + rr[grp].oid + 16 * f : ybase + (int)row_bytes(lr);
+                char *const dst = rr[grp].inv >= 0.f ? yrow : tbase + (lr << kRowShift);
+                __builtin_nontemporal_store(a, (v4f *)dst);
+            }
             issue(rr[grp], grp);                         // the same rows of the next tile
         }
         if (!ok_cur) {

@@ -275,6 +275,32 @@ def test_high_degree_rows_beside_the_low_degree_ones(torch_cuda, pieces):
         assert_close_to_oracle(Y, Y64, S, f"{pieces} pieces F={F}")
 
 
+def _long_row_list(n_long, base, seed):
+    """A graph with n_long rows of 9 to 12 entries among rows of base - 1 and base: as many rows as the list of those may be"""
+    rng = np.random.default_rng(seed)
+    n = 52 * n_long + 17
+    lens = rng.integers(base - 1, base + 1, n)
+    lens[rng.permutation(n)[:n_long]] = 9 + np.arange(n_long) % 4
+    return n, _graph_of_row_lengths(lens, seed + 1)
+
+
+def test_masked_rows_do_not_slow_the_sweep_down(torch_cuda):
+    """One row in 52 with 9 to 12 entries at a width that fills no power of two of lanes: the call takes what these rows' own
+    entries take (measured 1.05 to 1.1 times the call without them), not 1.6 times as when the masked rows' sums all went
+    to one place."""
+    torch = torch_cuda
+    n, long_rows = _long_row_list(20000, 5, 71)
+    times = []
+    for rowptr, col, val in (_graph_of_row_lengths(np.random.default_rng(72).integers(4, 6, n), 72), long_rows):
+        plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+        G.groot_plan_upload(plan, 100)
+        X, Y = torch.rand((n, 100), device="cuda"), torch.empty((n, 100), device="cuda")
+        call = lambda: G.groot_spmm_execute(plan, X, Y)
+        call()
+        times.append(_best_time(torch, call))
+    assert times[1] < 1.35 * times[0], f"{times[0]:.3f} ms without long rows, {times[1]:.3f} ms with"
+
+
 @pytest.mark.parametrize("case", ["aig", "stress"])
 def test_transposed_spmm(torch_cuda, case):
     """dX = A_hat^T dY through groot_graph_transpose + the ordinary plan/execute, against the oracle's
