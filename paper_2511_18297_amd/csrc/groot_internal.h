@@ -100,7 +100,6 @@ constexpr int kCodeNear = 0x4000;     // column codes below kCodeHot: row + code
 constexpr int kCodeHot = 0x8000;      // codes from here on: index into the hot list
 constexpr int kCodeBad = 0xFFFF;      // an entry that no code can express: its row is not served in compact form
 constexpr int kCodeMaxHot = 0x7FFF;
-constexpr int kHdBesideLd = 1024;     // pieces of high-degree rows up to which they join the low-degree rows' launch
 constexpr int kPipeMinDepth = 5, kPipeMaxDepth = 8;   // gather slots per row the pipelined LD kernel is built for
 constexpr int kZeroRowFloats = 256;     // a row of the widest matrix that the pipelined kernels serve
 constexpr int kTrashFloats = 2048;

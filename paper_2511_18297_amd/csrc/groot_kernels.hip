@@ -199,9 +199,15 @@ static bool ld_pipelined(const DevicePlan &dp, int32_t F4, const RowOut *out)
     return F4 == 8 || F4 == 16 || F4 == 32 || (!out && F4 <= kWave && F4 > (dp.pipe_depth <= 5 ? 4 : 8));
 }
 
+// Whether the pieces of the high-degree rows join the low-degree rows' launch.  In the same launch / in one of their own, us:
+// 374 pieces (polarized degrees) F = 32 15.4 / 19.7, F = 64 13.8 / 18.5; 512 (256-bit multiplier) F = 32 42.2 / 42.7, F = 64
+// 54.3 / 60.2, F = 100 89.5 / 88.5; 512 (4-LUT shape) F = 32 17.6 / 22.2; 771 (Booth) F = 32 50.0 / 48.0, F = 64 61.6 / 69.0;
+// F = 136 183 / 209; 949 (polarized) F = 32 30.3 / 26.1, F = 64 32.2 / 34.0, F = 128 45.0 / 48.4, F = 100 61.1 / 46.9, F = 200
+// 63.7 / 60.2; 1,024 (shape mapped to cells) F = 136 78 / 94; 2,905 (polarized) F = 64 62.2 / 51.5, F = 128 94.8 / 68.1.
 bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out)
 {
-    return ld_pipelined(dp, F / 4, out) && dp.n_chunks > 0 && dp.n_chunks <= kHdBesideLd;
+    const int64_t few = F == 64 || F >= 128 ? 1024 : 512;
+    return ld_pipelined(dp, F / 4, out) && dp.n_chunks > 0 && dp.n_chunks <= few;
 }
 
 int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out, bool with_hd)

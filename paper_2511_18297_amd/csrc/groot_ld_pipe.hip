@@ -52,7 +52,8 @@ __device__ __forceinline__ void pipe_wave_sync()
 }
 
 // What a launch does beside the sweep, in workgroups of their own behind it: the low-degree rows that the pipeline masks,
-// one lane group per row, and, where the plan has few of them (kHdBesideLd), the pieces of the high-degree rows.  On small
+// one lane group per row, where they are few (rows_beside_sweep), and, where those are few (ld_takes_hd), the pieces of the
+// high-degree rows.  On small
 // graphs the launches were most of the time: 32-bit multiplier, F = 32, three kernels of 10 + 3.5 + 3.4 us, now one of 8.0;
 // 256-bit, F = 64, 48 + 7.6 + 5 and the gaps (75 us), now one of 48 (65 us).  A graph of many pieces keeps the kernel of
 // their own: it wants all wavefronts of a CU, this one has registers for one or two per SIMD.
@@ -328,6 +329,23 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     }
 }
 
+// A long row list in a launch of its own, at full occupancy: one lane group per row.
+template <int L, int W>
+__global__ __launch_bounds__(kBlock) void ld_rows_kernel(const int32_t *__restrict__ rows, int64_t n_rows,
+                                                         const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                                                         const float *__restrict__ val, const v4f *__restrict__ X,
+                                                         v4f *__restrict__ Y, int32_t F4, const int64_t *__restrict__ out_ids,
+                                                         int64_t n)
+{
+    const int64_t k = (int64_t)blockIdx.x * (kBlock / L) + threadIdx.x / L;
+    const int ff = threadIdx.x % L;
+    if (k >= n_rows || ff >= F4) return;
+    const int64_t row = rows[k];
+    if (row >= n) return;                                // a row that is not wanted (row-mapped calls: boundary rows)
+    __builtin_nontemporal_store(ld_row_sum<W, false>(rowptr[row], rowptr[row + 1], col, val, X, F4, ff),
+                                Y + (out_ids ? out_ids[row] : row) * F4 + ff);
+}
+
 struct PipeArgs {
     const int64_t *rowptr;
     const int32_t *col;
@@ -384,6 +402,19 @@ static void pipe_launch_any(const PipeArgs &a)
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
             a.waves_per_part, a.parts, nullptr, a.F4, a.side);
     }
+}
+
+template <int W>
+static void rows_dispatch_l(int L, int64_t n_wg, int64_t n_rows, const PipeArgs &a)
+{
+    auto launch = [&](auto kernel) {
+        kernel<<<dim3((unsigned)n_wg), dim3(kBlock), 0, a.st>>>(a.side.rows, n_rows, a.rowptr, a.col, a.val, (const v4f *)a.X,
+                                                                (v4f *)a.Y, a.F4, a.out_ids, a.n);
+    };
+    if (L == 8) launch(ld_rows_kernel<8, W>);
+    else if (L == 16) launch(ld_rows_kernel<16, W>);
+    else if (L == 32) launch(ld_rows_kernel<32, W>);
+    else launch(ld_rows_kernel<64, W>);
 }
 
 template <int W, int D>
@@ -453,6 +484,26 @@ int pipe_compact_prepare()
     return err;
 }
 
+// Rows of the list that the sweep's launch takes along.  They run there at the sweep's occupancy, so a long list wants a launch
+// of its own.  Rows of 9 to 14 entries, beside the sweep / in a launch of their own, us:
+//   5 slots, F = 24    155,625 of 4 M rows     315 / 333
+//   5 slots, F = 32     11,001 of 0.5 M       43.6 / 44.5    21,332 of 1 M     71.7 / 69.7    155,625 of 4 M  392 / 325
+//   5 slots, F = 64      2,861 of 0.5 M       55.9 / 60.3    11,001 of 0.5 M   68.6 / 61.9    155,625 of 4 M  618 / 645
+//   5 slots, F = 100     3,238 of 0.1 M       33.3 / 36.9    11,001 of 0.5 M   99.1 / 86.5    155,625 of 4 M  1,095 / 1,117
+//   5 slots, F = 128     5,043 of 1 M          276 / 285     155,625 of 4 M   1,206 / 1,244
+//   8 slots, F = 32      5,043 of 1 M         72.7 / 83.1    21,332 of 1 M     86.1 / 87.0
+//   8 slots, F = 100     5,043 of 1 M          343 / 339     21,332 of 1 M      392 / 349
+// From F = 36 on with 5 slots it depends on whether X stays in the last-level cache (F = 64, 0.5 M rows): a sweep that
+// waits for the memory has room for any list.
+static int64_t rows_beside_sweep(int depth, int32_t F4, int64_t n_rows)
+{
+    constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+    if (depth == 5 && F4 < 8) return n_rows;
+    if (F4 <= 8) return 16384;
+    if (depth > 5) return 8192;
+    return n_rows * F4 * 16 < kCacheBytes ? 4096 : n_rows;
+}
+
 // out: the leading out->n_out rows only, row r written to row out->ids[r] of Y (ids NULL: to row r)
 int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out, bool with_hd)
 {
@@ -496,7 +547,9 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     // the low-degree rows with more entries than the pipeline has slots; the rows that the compact matrix cannot
     // code stand at the end of the list and are the pipeline's own whenever it reads the plain arrays
     const int64_t n_mid = compact ? dp.n_mid_rows : dp.n_mid_rows - dp.n_bad_rows;
-    const int64_t n_row_wg = n_mid > 0 ? (n_mid + kBlock / L - 1) / (kBlock / L) : 0;
+    const int64_t list_wg = n_mid > 0 ? (n_mid + kBlock / L - 1) / (kBlock / L) : 0;
+    const bool own_list = n_mid > rows_beside_sweep(dp.pipe_depth, F4, n_rows);
+    const int64_t n_row_wg = own_list ? 0 : list_wg;
     const int64_t n_hd = with_hd ? dp.n_chunks : 0;
     if (!grid_ok(n_wg + n_row_wg + n_hd)) return (int)hipErrorInvalidConfiguration;
     const PipeArgs a{dp.rowptr, col_arg, val_arg, CompactCsr{dp.rp32, dp.col16, dp.hot_cols, dp.n_hot}, compact,
@@ -504,6 +557,9 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
                      dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, n_wg, st, out_ids, F4,
                      SideWork{n_wg, dp.mid_rows, n_mid, n_row_wg, dp.chunks, dp.partials}, n_hd};
     GROOT_DISPATCH_W(dp.weight_mode, (pipe_dispatch_d<kW>(dp.pipe_depth, F4, a)));
+    e = hipGetLastError();
+    if (e != hipSuccess || !own_list) return (int)e;
+    GROOT_DISPATCH_W(dp.weight_mode, (rows_dispatch_l<kW>(L, list_wg, n_mid, a)));
     return (int)hipGetLastError();
 }
 

@@ -249,13 +249,14 @@ def test_mixed_row_lengths_at_other_widths(torch_cuda, max_len, T, F, explicit):
     test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit)
 
 
-@pytest.mark.parametrize("pieces", [1023, 1024, 1025, 2047, 2048, 2600])
+@pytest.mark.parametrize("pieces", [512, 513, 1023, 1024, 1025, 2047, 2048, 2600])
 def test_high_degree_rows_beside_the_low_degree_ones(torch_cuda, pieces):
-    """Around the number of pieces up to which the high-degree rows ride in the low-degree rows' launch, and around the one
+    """Around the numbers of pieces up to which the high-degree rows ride in the low-degree rows' launch (1,024 at F = 64 and from
+    128 on, 512 at other widths), and around the one
     from which the list is dealt to the XCDs in runs of 64 (2600: the last runs are short or empty): rows of two pieces
     and of one, the first row and the last among them, next to rows of 1 to 4 entries."""
     n, T = 9000, 32
-    heavies = 600 if pieces < 1200 else 1500
+    heavies = 300 if pieces < 600 else 600 if pieces < 1200 else 1500
     split = pieces - heavies
     rng = np.random.default_rng(pieces)
     deg = rng.integers(1, 5, size=n)
@@ -267,7 +268,7 @@ def test_high_degree_rows_beside_the_low_degree_ones(torch_cuda, pieces):
     col = np.concatenate([np.sort((i + 13 * np.arange(d)) % n) for i, d in enumerate(deg)]).astype(np.int32)
     val = np.repeat(np.float32(1.0) / deg.astype(np.float32), deg).astype(np.float32)
     g = G.groot_graph_from_csr(rowptr, col, val)
-    for F in (32, 100):
+    for F in (32, 64, 100, 136):
         X = wl.uniform_features_numpy(45, 0, n, F)
         Y, plan, _, _ = _run(torch_cuda, g, T, X)
         assert G.groot_plan_query(plan, "hd_pieces") == pieces
@@ -282,6 +283,21 @@ def _long_row_list(n_long, base, seed):
     lens = rng.integers(base - 1, base + 1, n)
     lens[rng.permutation(n)[:n_long]] = 9 + np.arange(n_long) % 4
     return n, _graph_of_row_lengths(lens, seed + 1)
+
+
+@pytest.mark.parametrize("F,base,n_long", [(100, 5, 4096), (100, 5, 4097), (64, 8, 8192), (64, 8, 8193), (36, 6, 8193),
+                                           (32, 5, 16384), (32, 5, 16385), (24, 5, 16385)])
+def test_long_rows_beside_the_sweep_and_in_a_launch_of_their_own(torch_cuda, F, base, n_long):
+    """Around the lengths up to which the list of longer low-degree rows rides in the sweep's launch: 4,096 rows where X fits
+    the last-level cache, 8,192 with 6 to 8 slots per row, 16,384 at F = 32; at F = 24 it always does."""
+    n, (rowptr, col, val) = _long_row_list(n_long, base, 70)
+    X = wl.uniform_features_numpy(46, 0, n, F)
+    Y, plan, _, _ = _run(torch_cuda, G.groot_graph_from_csr(rowptr, col, val), 32, X)
+    if G.groot_plan_query(plan, "ld_pipelined"):
+        assert G.groot_plan_query(plan, "pipe_depth") == base
+        assert G.groot_plan_query(plan, "mid_rows") - G.groot_plan_query(plan, "uncoded_rows") == n_long
+    Y64, S = oracle.spmm_f64(rowptr, col, val, X)
+    assert_close_to_oracle(Y, Y64, S, f"{n_long} long rows F={F}")
 
 
 def test_masked_rows_do_not_slow_the_sweep_down(torch_cuda):
