@@ -37,7 +37,7 @@ constexpr int kPipeWaves = 4;                // wavefronts per workgroup, one wo
 // 4 / 5 / 6 / 7 / 8 (with both matrices in one class of address ranges 5 was the best: 16.9 / 14.4 / 14.2 / 13.7 /
 // 14.0 / 13.8 / 13.9 ms for 2..8); 8 lanes (F = 32): 6.46 / 6.36 ms for 5 / 7; 32 lanes (F = 128): 31.0 / 30.5 /
 // 31.3 ms per step for 5 / 7 / 8
-constexpr int pipe_groups(int L) { return L == 4 ? 3 : 7; }   // 4 lanes per row: as many as row pointers fit one wavefront
+constexpr int pipe_groups(int) { return 7; }
 
 typedef unsigned int pipe_u4 __attribute__((ext_vector_type(4)));
 constexpr int kPipeRawBuffer = 0x00027000;   // last word of a buffer descriptor: raw 32-bit data, offsets checked against the size
@@ -96,8 +96,8 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     constexpr int kTileRows = G * kRpg;
     constexpr int kPipeD = D;                            // slots per row
     constexpr int kSlots = kTileRows * kPipeD, kH = (kSlots + kWave - 1) / kWave;
-    constexpr int kRowShift = L == 4 ? 6 : L == 8 ? 7 : L == 16 ? 8 : L == 32 ? 9 : 10;   // log2 of a feature row's bytes
-    static_assert(L == 4 || L == 8 || L == 16 || L == 32 || L == 64, "one float4 per lane");
+    constexpr int kRowShift = L == 8 ? 7 : L == 16 ? 8 : L == 32 ? 9 : 10;   // log2 of a feature row's bytes
+    static_assert(L == 8 || L == 16 || L == 32 || L == 64, "one float4 per lane");
     auto row_bytes = [&](int64_t row) -> int64_t { return S ? row * (F4 * 16) : row << kRowShift; };
     static_assert(kTileRows + 1 <= kWave, "row pointers of a tile fit one wavefront");
     // a slot: byte offset of the gathered row from X; with explicit weights the entry's weight rides in the
@@ -423,7 +423,6 @@ static void pipe_dispatch_l(int32_t F4, const PipeArgs &a)
     if (F4 == 8) pipe_launch<8, W, pipe_groups(8), D>(a);
     else if (F4 == 16) pipe_launch<16, W, pipe_groups(16), D>(a);
     else if (F4 == 32) pipe_launch<32, W, pipe_groups(32), D>(a);
-    else if (F4 <= 4) pipe_launch_any<4, W, pipe_groups(4), D>(a);
     else if (F4 < 8) pipe_launch_any<8, W, pipe_groups(8), D>(a);
     else if (F4 < 16) pipe_launch_any<16, W, pipe_groups(16), D>(a);
     else if (F4 < 32) pipe_launch_any<32, W, pipe_groups(32), D>(a);
@@ -456,7 +455,6 @@ static int pipe_allow_lds_l()
     int err = pipe_allow_lds<8, W, D, false>();
     if (!err) err = pipe_allow_lds<16, W, D, false>();
     if (!err) err = pipe_allow_lds<32, W, D, false>();
-    if (!err) err = pipe_allow_lds<4, W, D, true>();
     if (!err) err = pipe_allow_lds<8, W, D, true>();
     if (!err) err = pipe_allow_lds<16, W, D, true>();
     if (!err) err = pipe_allow_lds<32, W, D, true>();
@@ -512,7 +510,7 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     if (n_rows < 0 || n_rows > dp.n) return (int)hipErrorInvalidValue;
     if (n_rows == 0) return 0;
     const int32_t F4 = F / 4;
-    if (F4 < 1 || F4 > kWave || (out && F4 != 8 && F4 != 16 && F4 != 32)) return (int)hipErrorInvalidValue;
+    if (F4 <= 4 || F4 > kWave || (out && F4 != 8 && F4 != 16 && F4 != 32)) return (int)hipErrorInvalidValue;
     if (!weights_ok(dp) || !dp.zero_row) return (int)hipErrorInvalidValue;
     if (dp.pipe_depth < kPipeMinDepth || dp.pipe_depth > kPipeMaxDepth) return (int)hipErrorInvalidValue;
     if (dp.n_mid_rows && !dp.mid_rows) return (int)hipErrorInvalidValue;
@@ -521,7 +519,7 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     if (e != hipSuccess) return (int)e;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return (int)e;
-    int L = 4;                                           // lanes per row
+    int L = 8;                                           // lanes per row
     while (L < F4) L *= 2;
     const int tile_rows = pipe_groups(L) * (kWave / L);
     const int64_t n_tiles = (n_rows + tile_rows - 1) / tile_rows;
