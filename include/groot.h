@@ -20,8 +20,17 @@
  *   - Node ids and columns are int32 (N < 2^31), row pointers are int64.
  *   - No global state except a thread-local error string, the tuning table of
  *     groot_set_tuning() (atomic integers, each read at the call its
- *     description names) and the fixed scratch array of
- *     groot_plan_lists_device_static().
+ *     description names), the fixed scratch array of
+ *     groot_plan_lists_device_static() and the device memory kept between
+ *     objects (next item).
+ *   - Device memory of freed objects and of scratch is kept for the next ones
+ *     while any object of the library lives on the device: at most 1 / 128 of
+ *     the device's memory (2.25 GiB on an MI355X), which other allocators of
+ *     the process do not see as free; all of it goes back when the last object
+ *     is freed, or when an allocation of the library fails.  Freeing an object
+ *     does not wait for kernels that still use it; an allocation that takes
+ *     such memory over waits for the device first.  One lock per device, held
+ *     during neither.
  */
 #ifndef GROOT_H
 #define GROOT_H

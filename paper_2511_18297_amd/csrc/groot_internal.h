@@ -189,7 +189,7 @@ const char *hip_error_text(int err);
 
 // Device memory of the library (groot_pool.hip): every allocation that it makes.  dev_alloc returns a hipError_t as int and
 // leaves no HIP error behind; dev_free takes NULL, may be called while the block is still in use by running kernels, and waits
-// for nothing.
+// for the device only where the block, or with the last one all that are kept, goes back to it.
 int dev_alloc(void **p, size_t bytes);
 void dev_free(void *p);
 // (groot_kernels.hip, so that the host file needs no HIP headers)

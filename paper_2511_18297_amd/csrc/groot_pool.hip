@@ -2,11 +2,13 @@
 // plan take about 40 allocations, and hipMalloc and hipFree of a few megabytes cost 60 and 25 us each: eight parts of a
 // 512-bit multiplier x 4 took 27 ms, 5 of them kernels.  So freed blocks are kept for the next allocation:
 //   * A kept block is handed out again only after the device has been waited for once since it was freed, so whatever
-//     was still running on any stream when its owner let it go has ended.  Freeing itself waits for nothing.
-//   * At most 1 / 128 of the device's memory is kept; a block beyond that goes back to the device at once, and so do
-//     all of them when the library's last block has been freed, or when an allocation fails.
+//     was still running on any stream when its owner let it go has ended.  Freeing a block that is kept waits for nothing.
+//   * At most 1 / 128 of the device's memory is kept, in blocks of at most an eighth of that; a block beyond that goes back to
+//     the device at once, and so do all of them when the library's last block has been freed, or when an allocation fails.
+//     hipFree waits for the device.
 //   * A request takes the smallest kept block that is large enough and at most a quarter larger.
-// One table per device behind one mutex.
+// One table and one mutex per device, held neither while the device is waited for nor while it allocates or frees.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -23,18 +25,22 @@ constexpr int kPoolDevices = 64;
 
 struct Kept {
     void *p;
-    bool idle;                               // the device has been waited for since it was freed
+    uint64_t freed;                          // the device's count of freed blocks, this one included
 };
+typedef std::multimap<size_t, Kept> KeptBlocks;   // by size
 
 struct DevicePool {
-    std::multimap<size_t, Kept> kept;        // by size
+    std::mutex m;
+    KeptBlocks kept;
     size_t kept_bytes = 0, cap = 0;
-    int64_t in_use = 0;                      // blocks handed out
+    int64_t in_use = 0;                      // blocks handed out or about to be
+    uint64_t freed = 0;                      // blocks freed and kept so far
+    uint64_t idle = 0;                       // of these, the device has been waited for since the first `idle` were freed
 };
 
 struct Pool {
-    std::mutex m;
     DevicePool dev[kPoolDevices];
+    std::mutex m;                            // of out
     std::unordered_map<void *, std::pair<size_t, int>> out;   // block -> size, device
 };
 
@@ -52,102 +58,150 @@ size_t pool_round(size_t bytes)
     return (bytes + step - 1) / step * step;
 }
 
-void give_back(DevicePool &d)
+// all kept blocks of a device (its mutex is held): the caller frees them after letting go of the mutex
+void take_all(DevicePool &d, KeptBlocks &drop)
 {
-    for (auto &k : d.kept) (void)hipFree(k.second.p);
-    d.kept.clear();
-    d.kept_bytes = 0;
+    drop.swap(d.kept);
+    for (auto &k : drop) d.kept_bytes -= k.first;
+}
+
+void give_back(const KeptBlocks &drop)
+{
+    for (auto &k : drop) (void)hipFree(k.second.p);
+}
+
+// Takes a kept block for `size` bytes, its size in *have; NULL if there is none that may be used.
+void *take_kept(DevicePool &d, size_t size, size_t *have)
+{
+    KeptBlocks::node_type node;
+    uint64_t upto = 0;
+    bool idle = false;
+    {
+        std::lock_guard<std::mutex> lock(d.m);
+        const auto it = d.kept.lower_bound(size);
+        if (it == d.kept.end() || it->first > size + size / 4) return nullptr;
+        node = d.kept.extract(it);           // still counted in kept_bytes: it may come back
+        idle = node.mapped().freed <= d.idle;
+        upto = d.freed;
+    }
+    if (!idle && hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();             // the device cannot be waited for now: a new block
+        std::lock_guard<std::mutex> lock(d.m);
+        d.kept.insert(std::move(node));
+        return nullptr;
+    }
+    std::lock_guard<std::mutex> lock(d.m);
+    if (!idle) d.idle = std::max(d.idle, upto);
+    d.kept_bytes -= node.key();
+    *have = node.key();
+    return node.mapped().p;
+}
+
+int new_block(DevicePool &d, size_t size, void **q)
+{
+    hipError_t e = hipMalloc(q, size);
+    if (e == hipErrorOutOfMemory) {
+        KeptBlocks drop;
+        {
+            std::lock_guard<std::mutex> lock(d.m);
+            take_all(d, drop);
+        }
+        if (!drop.empty()) {
+            (void)hipGetLastError();
+            give_back(drop);
+            e = hipMalloc(q, size);
+        }
+    }
+    if (e != hipSuccess) (void)hipGetLastError();
+    return (int)e;
+}
+
+// one block less in use: with the last one, what is kept goes back
+void end_use(DevicePool &d)
+{
+    KeptBlocks drop;
+    {
+        std::lock_guard<std::mutex> lock(d.m);
+        if (--d.in_use == 0) take_all(d, drop);
+    }
+    give_back(drop);
 }
 
 }  // namespace
-
-static int alloc_block(Pool &pl, int dev, void **p, size_t bytes)
-{
-    DevicePool &d = pl.dev[dev];
-    if (!d.cap) {
-        size_t free_bytes = 0, total = 0;
-        const hipError_t e = hipMemGetInfo(&free_bytes, &total);
-        if (e != hipSuccess) return (int)e;
-        d.cap = total / 128 + 1;
-    }
-    const size_t size = bytes <= d.cap / 8 ? pool_round(bytes ? bytes : 1) : bytes;   // what would not be kept is not rounded
-    const auto out = pl.out.emplace(nullptr, std::make_pair(size, dev)).first;        // a place in the table before the memory
-    auto node = pl.out.extract(out);
-    auto hand_out = [&](void *q, size_t have) {
-        node.key() = q;
-        node.mapped().first = have;
-        pl.out.insert(std::move(node));
-        ++d.in_use;
-        *p = q;
-        return 0;
-    };
-    const auto it = d.kept.lower_bound(size);
-    if (it != d.kept.end() && it->first <= size + size / 4) {
-        if (!it->second.idle) {
-            if (hipDeviceSynchronize() == hipSuccess)
-                for (auto &k : d.kept) k.second.idle = true;
-            else
-                (void)hipGetLastError();     // the device cannot be waited for now: a new block
-        }
-        if (it->second.idle) {
-            void *const q = it->second.p;
-            const size_t have = it->first;
-            d.kept_bytes -= have;
-            d.kept.erase(it);
-            return hand_out(q, have);
-        }
-    }
-    void *q = nullptr;
-    hipError_t e = hipMalloc(&q, size);
-    if (e == hipErrorOutOfMemory && !d.kept.empty()) {
-        (void)hipGetLastError();
-        give_back(d);
-        e = hipMalloc(&q, size);
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return (int)e;
-    }
-    return hand_out(q, size);
-}
 
 int dev_alloc(void **p, size_t bytes)
 {
     *p = nullptr;
     int dev = 0;
-    const hipError_t e = hipGetDevice(&dev);
+    hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return (int)e;
     if (dev < 0 || dev >= kPoolDevices) return (int)hipErrorInvalidDevice;
+    Pool *pl;
     try {
-        Pool &pl = pool();
-        std::lock_guard<std::mutex> lock(pl.m);
-        return alloc_block(pl, dev, p, bytes);
-    } catch (...) {                          // no host memory for the tables
+        pl = &pool();
+    } catch (...) {
         return (int)hipErrorOutOfMemory;
     }
+    DevicePool &d = pl->dev[dev];
+    size_t size = 0;
+    {
+        std::lock_guard<std::mutex> lock(d.m);
+        if (!d.cap) {
+            size_t free_bytes = 0, total = 0;
+            e = hipMemGetInfo(&free_bytes, &total);
+            if (e != hipSuccess) return (int)e;
+            d.cap = total / 128 + 1;
+        }
+        size = bytes <= d.cap / 8 ? pool_round(bytes ? bytes : 1) : bytes;   // what would not be kept is not rounded
+        ++d.in_use;
+    }
+    void *q = take_kept(d, size, &size);
+    int err = q ? 0 : new_block(d, size, &q);
+    if (!err) {
+        try {
+            std::lock_guard<std::mutex> lock(pl->m);
+            pl->out.emplace(q, std::make_pair(size, dev));
+            *p = q;
+            return 0;
+        } catch (...) {                      // no host memory for the table
+            (void)hipFree(q);
+            err = (int)hipErrorOutOfMemory;
+        }
+    }
+    end_use(d);
+    return err;
 }
 
 void dev_free(void *p)
 {
     if (!p) return;
     Pool &pl = pool();
-    std::lock_guard<std::mutex> lock(pl.m);
-    const auto it = pl.out.find(p);
-    if (it == pl.out.end()) return;
-    const size_t size = it->second.first;
-    DevicePool &d = pl.dev[it->second.second];
-    pl.out.erase(it);
-    bool keep = size <= d.cap / 8 && d.kept_bytes + size <= d.cap;
-    if (keep) {
-        try {
-            d.kept.emplace(size, Kept{p, false});
-            d.kept_bytes += size;
-        } catch (...) {
-            keep = false;
+    size_t size = 0;
+    int dev = 0;
+    {
+        std::lock_guard<std::mutex> lock(pl.m);
+        const auto it = pl.out.find(p);
+        if (it == pl.out.end()) return;
+        size = it->second.first;
+        dev = it->second.second;
+        pl.out.erase(it);
+    }
+    DevicePool &d = pl.dev[dev];
+    bool keep = false;
+    {
+        std::lock_guard<std::mutex> lock(d.m);
+        if (size <= d.cap / 8 && d.kept_bytes + size <= d.cap) {
+            try {
+                d.kept.emplace(size, Kept{p, d.freed + 1});
+                ++d.freed;
+                d.kept_bytes += size;
+                keep = true;
+            } catch (...) {                  // no host memory for the table
+            }
         }
     }
     if (!keep) (void)hipFree(p);
-    if (--d.in_use == 0) give_back(d);
+    end_use(d);
 }
 
 }  // namespace groot

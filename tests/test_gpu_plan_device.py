@@ -100,58 +100,82 @@ def test_threshold_above_the_device_limit(torch_cuda):
     assert e.value.status == G.GROOT_ERANGE
 
 
-def test_plan_freed_while_its_kernels_run(torch_cuda):
-    """A plan may be freed right after its last call: its device memory goes to the next plan only once the kernels
-    that read it have ended, on whatever stream they run.  The second plan is of the same size, so it would take
-    the first one's blocks; repeated, so that blocks are handed back and forth."""
+def test_part_freed_while_its_kernels_run(torch_cuda):
+    """A part and its plan may be freed while their kernels are still queued, on whatever stream: their memory goes to the next
+    object only once those kernels have ended.  Another part stays alive, so freed blocks are kept; the next part is built
+    on the current stream, which waits for nothing on the side stream by itself, and takes over blocks of the freed one
+    (its arrays lie where that one's lay): by then the side stream must have run dry, and every result be right."""
     torch = torch_cuda
-    aig = wl.csa_multiplier_aig(256)
-    g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 2)
-    gt = G.groot_graph_transpose(g)
-    n, F = 2 * aig.num_nodes, 64
+    aig = wl.csa_multiplier_aig(192)
+    g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 4)
+    n, F = 4 * aig.num_nodes, 64
+    whole = G.groot_spmm_plan(g, 32)
+    G.groot_plan_upload(whole, F)
     X = wl.uniform_features(3, 0, n, F, device="cuda")
-    want = torch.empty_like(X)
-    plan = G.groot_spmm_plan(g, 32)
-    G.groot_plan_upload(plan, F)
-    G.groot_spmm_execute(plan, X, want)
-    torch.cuda.synchronize()
+
+    def part(p):
+        part = G.groot_partition_regrow_device(whole, 4, p)
+        view = G.groot_dev_part_view(part)
+        sub = G.groot_dev_part_plan(part, 32, F)
+        G.groot_plan_use_global_columns(sub, view["global_id"], n)
+        where = {view[k].device_pointer for k in ("global_id", "rowptr", "col") if k in view}
+        return part, sub, view, where
+
+    stays = part(3)
     side = torch.cuda.Stream()
-    outs = [torch.full_like(X, float("nan")) for _ in range(12)]
-    side.wait_stream(torch.cuda.current_stream())
-    for k in range(3):
-        for y in outs[4 * k:4 * k + 4]:
-            G.groot_spmm_execute(plan, X, y, stream=side)
-        del plan                                          # the kernels above are still queued
-        other = G.groot_spmm_plan(gt, 32)                 # takes the memory and writes another matrix to it
-        G.groot_plan_upload(other, F)
+    outs = [torch.full_like(X, float("nan")) for _ in range(4)]
+    taken_over = 0
+    for k, y in enumerate(outs):
+        mine = part(1)
+        torch.cuda.synchronize()
+        for _ in range(400):                              # some 50 us each: longer than freeing takes
+            G.groot_spmm_execute_rows(mine[1], X, y, F, mine[2]["n_owned"], mine[2]["global_id"], stream=side)
+        where = mine[3]
+        del mine                                          # the kernels above are still queued
+        queued = not side.query()
+        other = part(1)
+        if where & other[3]:
+            taken_over += queued
+            assert side.query(), f"pass {k}: memory taken over while kernels that read it are queued"
         del other
-        plan = G.groot_spmm_plan(g, 32)
-        G.groot_plan_upload(plan, F)
+    assert taken_over > 0, "no pass took memory over behind queued kernels"
+    quiet, want = part(1), torch.full_like(X, float("nan"))
+    G.groot_spmm_execute_rows(quiet[1], X, want, F, quiet[2]["n_owned"], quiet[2]["global_id"])
     torch.cuda.synchronize()
     for k, y in enumerate(outs):
-        assert torch.equal(y, want), f"pass {k}"
+        assert torch.equal(torch.nan_to_num(y, 9.0), torch.nan_to_num(want, 9.0)), f"pass {k}"
+    del stays
 
 
 def test_device_memory_is_given_back(torch_cuda):
-    """Blocks that the library keeps between objects go back to the device with its last object."""
+    """Blocks that the library keeps between objects stay with it while one object lives and go back to the device with the
+    last one: free memory is what it was before the first object, once the runtime has loaded what it loads."""
     import gc
 
     torch = torch_cuda
-    gc.collect()
-    torch.cuda.synchronize()
     aig = wl.csa_multiplier_aig(192)
 
     def one():
         g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 4)
         plan = G.groot_spmm_plan(g, 32)
         G.groot_plan_upload(plan, 64)
-        part = G.groot_partition_regrow_device(plan, 4, 1)
-        sub = G.groot_dev_part_plan(part, 32, 64)
-        del sub, part, plan
+        return plan
+
+    def free():
         gc.collect()
-    one()                                                 # code objects, the runtime's own allocations
-    before = torch.cuda.mem_get_info()[0]
-    for _ in range(3):
-        one()
-    after = torch.cuda.mem_get_info()[0]
-    assert before - after < 16 << 20, f"{(before - after) >> 20} MiB of device memory did not come back"
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    plan = one()                                          # code objects, the runtime's own allocations
+    part = G.groot_partition_regrow_device(plan, 4, 1)
+    sub = G.groot_dev_part_plan(part, 32, 64)
+    del sub, part, plan
+    before = free()
+    stays = one()
+    alone = free()
+    assert before - alone > 32 << 20                      # a plan of 1.2 M rows
+    second = one()
+    del second
+    assert alone - free() > 16 << 20, "nothing was kept for the next object"
+    del stays
+    assert abs(before - free()) < 8 << 20, f"{(before - free()) >> 20} MiB of device memory did not come back"
