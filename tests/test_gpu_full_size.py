@@ -18,7 +18,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from util import assert_close_to_oracle, ensure_built, layer_tolerance, tolerance, wgrad_tolerance
+from util import assert_close_to_oracle, ensure_built, layer_tolerance, tolerance, wgrad_rows_per_wavefront, wgrad_tolerance
 
 pytestmark = [pytest.mark.gpu, pytest.mark.timeout(1500)]
 
@@ -133,7 +133,7 @@ def test_config3_fused_layer_backward_data(torch_cuda, one_copy):
 
 
 def test_config3_fused_layer_backward_weights(torch_cuda, one_copy):
-    """The fused layer's weight gradients on the 1024-bit multiplier (8.4 M rows: 8,192 rows per wavefront added in
+    """The fused layer's weight gradients on the 1024-bit multiplier (8.4 M rows: 4,096 rows per wavefront added in
     fp32) against the fp64 definition."""
     torch = torch_cuda
     aig, rowptr, col, val = one_copy
@@ -147,22 +147,19 @@ def test_config3_fused_layer_backward_weights(torch_cuda, one_copy):
     X_np, dZ_np = X.cpu().numpy(), dZ.cpu().numpy()
     dWn, dWs, Sn, Ss = oracle.sage_layer_backward_weights_f64(rowptr, col, val, X_np, dZ_np)
     ws = torch.empty((G.groot_sage_layer_backward_weights_workspace(plan, F) // 4,), dtype=torch.float32, device="cuda")
-    cus = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
-    rows_per_wavefront = 16 * -(-(-(-(-(-n // 16)) // 8)) // (cus // 8 * 4))
-    try:
-        for pieces in (3, 2):
-            G.groot_set_tuning("sage_pieces", pieces)
-            out = torch.full((2, F, F), float("nan"), dtype=torch.float32, device="cuda")
-            G.groot_sage_layer_backward_weights(plan, X, dZ, out[0], out[1], ws, F)
-            torch.cuda.synchronize()
-            got = out.cpu().numpy().astype(np.float64)
-            tol_n, tol_s = wgrad_tolerance(Sn, Ss, np.abs(dZ_np.astype(np.float64)).sum(axis=0), rows_per_wavefront, pieces)
-            en, es = np.abs(got[0] - dWn), np.abs(got[1] - dWs)
-            print(f"{pieces} pieces: max err/tol dWn {np.max(en / tol_n):.2e} dWs {np.max(es / tol_s):.2e}; "
-                  f"max rel err {np.max(en) / np.abs(dWn).max():.2e} {np.max(es) / np.abs(dWs).max():.2e}", flush=True)
-            assert np.isfinite(got).all() and (en <= tol_n).all() and (es <= tol_s).all()
-    finally:
-        G.groot_set_tuning("sage_pieces", 3)
+    rows = wgrad_rows_per_wavefront(n, torch.cuda.get_device_properties(0).multi_processor_count)
+    out = torch.full((2, F, F), float("nan"), dtype=torch.float32, device="cuda")
+    G.groot_sage_layer_backward_weights(plan, X, dZ, out[0], out[1], ws, F)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64)
+    tol_n, tol_s = wgrad_tolerance(Sn, Ss, np.abs(dZ_np.astype(np.float64)).sum(axis=0), rows, F, F)
+    en, es = np.abs(got[0] - dWn), np.abs(got[1] - dWs)
+    print(f"max err/tol dWn {np.max(en / tol_n):.2e} dWs {np.max(es / tol_s):.2e}; "
+          f"max rel err {np.max(en) / np.abs(dWn).max():.2e} {np.max(es) / np.abs(dWs).max():.2e}", flush=True)
+    assert np.isfinite(got).all() and (en <= tol_n).all() and (es <= tol_s).all()
+    # the bar above takes every rounding in the same direction; roundings of random sign leave 0.8e-6 of the largest element
+    # here (products of bf16 pieces in truncating sums: 1.3e-5)
+    assert np.max(en) < 4e-6 * np.abs(dWn).max() and np.max(es) < 4e-6 * np.abs(dWs).max()
 
 
 def _sample_rows(rng, n1, batch, n_random):
