@@ -70,30 +70,19 @@ void give_back(const KeptBlocks &drop)
     for (auto &k : drop) (void)hipFree(k.second.p);
 }
 
-// Takes a kept block for `size` bytes, its size in *have; NULL if there is none that may be used.
-void *take_kept(DevicePool &d, size_t size, size_t *have)
+// A kept block that the device has not been waited for since it was freed: waits, and hands it out.  NULL if that is not
+// possible now; the block is kept on.
+void *wait_for(DevicePool &d, KeptBlocks::node_type node, uint64_t upto)
 {
-    KeptBlocks::node_type node;
-    uint64_t upto = 0;
-    bool idle = false;
-    {
-        std::lock_guard<std::mutex> lock(d.m);
-        const auto it = d.kept.lower_bound(size);
-        if (it == d.kept.end() || it->first > size + size / 4) return nullptr;
-        node = d.kept.extract(it);           // still counted in kept_bytes: it may come back
-        idle = node.mapped().freed <= d.idle;
-        upto = d.freed;
-    }
-    if (!idle && hipDeviceSynchronize() != hipSuccess) {
-        (void)hipGetLastError();             // the device cannot be waited for now: a new block
-        std::lock_guard<std::mutex> lock(d.m);
+    const bool waited = hipDeviceSynchronize() == hipSuccess;
+    if (!waited) (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(d.m);
+    if (!waited) {
         d.kept.insert(std::move(node));
         return nullptr;
     }
-    std::lock_guard<std::mutex> lock(d.m);
-    if (!idle) d.idle = std::max(d.idle, upto);
+    d.idle = std::max(d.idle, upto);
     d.kept_bytes -= node.key();
-    *have = node.key();
     return node.mapped().p;
 }
 
@@ -116,17 +105,6 @@ int new_block(DevicePool &d, size_t size, void **q)
     return (int)e;
 }
 
-// one block less in use: with the last one, what is kept goes back
-void end_use(DevicePool &d)
-{
-    KeptBlocks drop;
-    {
-        std::lock_guard<std::mutex> lock(d.m);
-        if (--d.in_use == 0) take_all(d, drop);
-    }
-    give_back(drop);
-}
-
 }  // namespace
 
 int dev_alloc(void **p, size_t bytes)
@@ -143,7 +121,10 @@ int dev_alloc(void **p, size_t bytes)
         return (int)hipErrorOutOfMemory;
     }
     DevicePool &d = pl->dev[dev];
-    size_t size = 0;
+    size_t size = 0, have = 0;
+    void *q = nullptr;
+    KeptBlocks::node_type node;
+    uint64_t upto = 0;
     {
         std::lock_guard<std::mutex> lock(d.m);
         if (!d.cap) {
@@ -154,9 +135,23 @@ int dev_alloc(void **p, size_t bytes)
         }
         size = bytes <= d.cap / 8 ? pool_round(bytes ? bytes : 1) : bytes;   // what would not be kept is not rounded
         ++d.in_use;
+        const auto it = d.kept.lower_bound(size);
+        if (it != d.kept.end() && it->first <= size + size / 4) {
+            have = it->first;
+            if (it->second.freed <= d.idle) {
+                q = it->second.p;
+                d.kept_bytes -= have;
+                d.kept.erase(it);
+            } else {
+                node = d.kept.extract(it);   // still counted in kept_bytes: it may come back
+                upto = d.freed;
+            }
+        }
     }
-    void *q = take_kept(d, size, &size);
-    int err = q ? 0 : new_block(d, size, &q);
+    if (node) q = wait_for(d, std::move(node), upto);
+    int err = 0;
+    if (q) size = have;
+    else err = new_block(d, size, &q);
     if (!err) {
         try {
             std::lock_guard<std::mutex> lock(pl->m);
@@ -168,7 +163,12 @@ int dev_alloc(void **p, size_t bytes)
             err = (int)hipErrorOutOfMemory;
         }
     }
-    end_use(d);
+    KeptBlocks drop;
+    {
+        std::lock_guard<std::mutex> lock(d.m);
+        if (--d.in_use == 0) take_all(d, drop);
+    }
+    give_back(drop);
     return err;
 }
 
@@ -188,6 +188,7 @@ void dev_free(void *p)
     }
     DevicePool &d = pl.dev[dev];
     bool keep = false;
+    KeptBlocks drop;
     {
         std::lock_guard<std::mutex> lock(d.m);
         if (size <= d.cap / 8 && d.kept_bytes + size <= d.cap) {
@@ -199,9 +200,10 @@ void dev_free(void *p)
             } catch (...) {                  // no host memory for the table
             }
         }
+        if (--d.in_use == 0) take_all(d, drop);   // with the last block in use, what is kept goes back
     }
     if (!keep) (void)hipFree(p);
-    end_use(d);
+    give_back(drop);
 }
 
 }  // namespace groot
