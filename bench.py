@@ -55,10 +55,10 @@ STRESS_THRESHOLDS = (16, 32, 64, 128)
 # sources have changed since, the figure no longer describes the kernel that is timed and the line reports
 # traffic null instead.
 TRAFFIC = {
-    # FETCH_SIZE 25,925,556 KiB x 2.000 (scale of the 34.33 GB device copy in the same run: 16,762,896 KiB), WRITE_SIZE
-    # 33,526,060 KiB x 1.000 (the copy: 33,525,760); medians of 8 launches
-    ("csa1024_b16_F64", "ld_pipe_kernel"): {"bytes": 87.43e9, "read": 53.10e9, "written": 34.33e9,
-                                            "sources_sha16": "8e03b1e1d105c844"},
+    # FETCH_SIZE 26,282,590 KiB x 2.000 (scale of the 34.33 GB device copy in the same run: 16,762,896 KiB), WRITE_SIZE
+    # 33,526,345 KiB x 1.000 (the copy: 33,525,760); medians of 8 launches
+    ("csa1024_b16_F64", "ld_pipe_kernel"): {"bytes": 88.16e9, "read": 53.83e9, "written": 34.33e9,
+                                            "sources_sha16": "7da1810331d8b179"},
 }
 KERNEL_SOURCES = ("groot_device.h", "groot_kernels.hip", "groot_ld_pipe.hip", "groot_compress.hip")
 
