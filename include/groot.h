@@ -483,8 +483,9 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
 
 /* What the library decided for an uploaded plan, for diagnostics and benchmarks:
  * "ld_pipelined" (0 the plain LD kernel always, 2 the pipelined one for F = 32,
- * 64, 128 and, on whole graphs, the widths from 20 to 256), "pipe_depth" (gather slots per row of the pipelined kernel, 5 to
- * 8), "mid_rows" (low-degree rows with more entries than that, which are
+ * 64, 128 and, on whole graphs, the widths from 20 (5 gather slots per row) or 36
+ * (6 to 8) to 256), "pipe_depth" (gather slots per row of the pipelined kernel,
+ * 5 to 8), "mid_rows" (low-degree rows with more entries than that, which are
  * computed from a list), "csr_compressed" (1 when the pipelined kernel reads 4-byte
  * row pointers and 2-byte column codes instead of the 8- and 4-byte arrays), "hd_pieces" (launch size of the HD kernel),
  * "hd_partials" (partial-sum slots of split high-degree rows), "weight_mode"
@@ -535,7 +536,7 @@ groot_status groot_plan_hd_pieces(const groot_plan *plan, int64_t capacity, int6
  * or names one of the first 32,768 high-degree rows, and the matrix has fewer
  * than 2^32 entries; 0: never),
  * "ld_pipeline" (which LD kernel is used: 1 the software-pipelined one for
- * F = 32, 64, 128 and the widths between; 0 the plain one; -1 (default) the pipelined one with the
+ * the widths given above for "ld_pipelined"; 0 the plain one; -1 (default) the pipelined one with the
  * smallest number of gather slots per row, 5 to 8, that leaves at most 2
  * low-degree rows in 100 with more entries than slots, the plain one if none
  * does; read by groot_plan_upload) and "pipe_depth" (0, default: that rule;
