@@ -242,7 +242,9 @@ int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
     // Runs of 64 pieces from F = 64 on, where a stretch of X is large beside an L2 (polarized graphs, every row of X gathered
     // 70 times: 65,536 rows F = 128 90 -> 64 us, 262,144 rows F = 128 571 -> 550, F = 256 1,517 -> 1,030; multipliers, whose rows
     // are gathered once or twice, the same; runs of 16: 566 and 1,335, of 1,024: 582 and 1,073; cutting rows into slices by XCD:
-    // 594 and 1,181).  At F = 32 it costs 2 %.  Below 2,048 pieces all of them are in flight anyway.
+    // 594 and 1,181).  At F = 32 it costs 2 %.  At the line: 2,048 pieces of a 512-bit multiplier 245 us either way, 2,067 of a
+// polarized graph 61 with runs and 78 without (F = 128).  Polarized graphs gain below it too (949 pieces 43.5 and 48.7, 374
+// 25.6 and 30.9), but up to 1,024 pieces ride in the low-degree rows' launch there.
     const int32_t run = F4 >= 16 && dp.n_chunks >= 2048 ? 64 : 1;
     const int64_t grid = run > 1 ? (dp.n_chunks + kXcds * run - 1) / (kXcds * run) * (kXcds * run) : dp.n_chunks;
     if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
