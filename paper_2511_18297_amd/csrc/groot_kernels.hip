@@ -192,11 +192,16 @@ static int lanes_for(int32_t F4)
 // from 20 on with 5 slots per row (512-bit multiplier, plain against pipelined kernel: F = 16 107 and 105 us with more than
 // twice the time at 8, F = 20 145 and 122, F = 100 ... 200 a quarter less), from 36 on with 6 to 8 (shape mapped to cells, rows
 // of 6: F = 20 50 and 56 us, F = 28 54 and 60; 4-LUT shape: F = 20 55 and 62, F = 36 88 and 88, F = 124 257 and 233), up to 256
-// (64 lanes of one float4).
+// (64 lanes of one float4).  Below F = 32 a graph of middling size without high-degree rows, whose launches it would share, stays
+// on the plain kernel (rows of 4 and 5, F = 28: 65,536 rows 13.7 and 12.1 us, 131,072 15.0 and 18.1, 262,144 20.0 and 20.9, 524,288
+// 41.6 and 36.4).
 static bool ld_pipelined(const DevicePlan &dp, int32_t F4, const RowOut *out)
 {
     if (!dp.zero_row || !dp.ld_pipelined) return false;
-    return F4 == 8 || F4 == 16 || F4 == 32 || (!out && F4 <= kWave && F4 > (dp.pipe_depth <= 5 ? 4 : 8));
+    if (F4 == 8 || F4 == 16 || F4 == 32) return true;
+    if (out || F4 > kWave || F4 <= 4) return false;
+    if (F4 > 8) return true;
+    return dp.pipe_depth <= 5 && (dp.n_chunks > 0 || dp.n <= 65536 || dp.n >= 524288);
 }
 
 // Whether the pieces of the high-degree rows join the low-degree rows' launch.  In the same launch / in one of their own, us:

@@ -300,6 +300,19 @@ def test_long_rows_beside_the_sweep_and_in_a_launch_of_their_own(torch_cuda, F, 
     assert_close_to_oracle(Y, Y64, S, f"{n_long} long rows F={F}")
 
 
+@pytest.mark.parametrize("n", [65536, 65537, 524287, 524288])
+def test_narrow_matrices_without_high_degree_rows(torch_cuda, n):
+    """F = 20 and 28 around the sizes between which a graph without high-degree rows stays on the plain kernel."""
+    lens = np.random.default_rng(n).integers(3, 6, n)
+    lens[:: 1000] = 9
+    rowptr, col, val = _graph_of_row_lengths(lens, 74)
+    for F in (20, 28):
+        X = wl.uniform_features_numpy(47, 0, n, F)
+        Y, _, _, _ = _run(torch_cuda, G.groot_graph_from_csr(rowptr, col, val), 32, X)
+        Y64, S = oracle.spmm_f64(rowptr, col, val, X)
+        assert_close_to_oracle(Y, Y64, S, f"n={n} F={F}")
+
+
 def test_masked_rows_do_not_slow_the_sweep_down(torch_cuda):
     """One row in 52 with 9 to 12 entries at a width that fills no power of two of lanes: the call takes what these rows' own
     entries take (measured 1.05 to 1.1 times the call without them), not 1.6 times as when the masked rows' sums all went
