@@ -483,8 +483,8 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
 
 /* What the library decided for an uploaded plan, for diagnostics and benchmarks:
  * "ld_pipelined" (0 the plain LD kernel always, 2 the pipelined one for F = 32,
- * 64, 128 and, on whole graphs, the widths from 20 (5 gather slots per row) or 36
- * (6 to 8) to 256), "pipe_depth" (gather slots per row of the pipelined kernel,
+ * 64, 128 and, on whole graphs, the widths from 20 (5 gather slots per row, and
+ * high-degree rows or not between 65,537 and 524,287 rows) or 36 to 256), "pipe_depth" (gather slots per row of the pipelined kernel,
  * 5 to 8), "mid_rows" (low-degree rows with more entries than that, which are
  * computed from a list), "csr_compressed" (1 when the pipelined kernel reads 4-byte
  * row pointers and 2-byte column codes instead of the 8- and 4-byte arrays), "hd_pieces" (launch size of the HD kernel),
