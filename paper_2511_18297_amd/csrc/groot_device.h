@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "groot_internal.h"
 
 namespace groot {
@@ -15,6 +17,14 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kLdTileRows = 64;              // consecutive rows per wavefront tile
 constexpr int kLdTileCap = 512;              // non-zeros of a tile that are staged in LDS
 constexpr int kXcds = 8;                     // workgroups are dealt round-robin over 8 XCDs
+
+// Orders a wavefront's own accesses to its part of LDS: no other wavefront reads or writes it.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Each XCD has its own L2.  Consecutive hardware workgroup ids land on
 // different XCDs, so the logical block index is transposed: XCD x walks the
@@ -110,62 +120,107 @@ __device__ __forceinline__ v4f row_sum_ahead(int64_t s, int64_t e, const int32_t
 
 // ---------------------------------------------------------------------------
 // HD part.  One workgroup per piece of a high-degree row (the plan cuts a row
-// into balanced pieces).  The 256/L lane groups of the workgroup stride over
-// the piece's non-zeros, each keeping a register accumulator for its float4
-// slice; the group sums meet in LDS and are added by a tree.  The result goes
-// to Y (single-piece rows) or to the row's slot of partial sums.
+// into balanced pieces).  Its 256/L lane groups stride over the piece's entries,
+// kHdAhead gathers in flight each and no branch between them, with a register
+// accumulator per float4 slice: the byte offsets of the rows of X (and the
+// weights) have been put to LDS by the group's own wavefront, padded with the
+// row of zeros.  The group sums meet in LDS and are added by a tree.  The result
+// goes to Y (single-piece rows) or to the row's slot of partial sums.
+//
+// Where the pieces are few, latencies one after the other bound this: the form
+// before (every lane group fetched its own four indices, then their rows, again
+// and again) had 2 x 16 of them for a piece of 512 entries at F = 128, this one
+// has 2 + 8.  Polarized graphs, us before / now: 374 pieces F = 128 23.2 / 18.1,
+// 949 F = 64 26.2 / 20.6, F = 128 39.0 / 31.1; 4-LUT shape, 1,024 pieces, F = 64
+// 39.5 / 36.5.  Where they are many it is the vector memory units' return path:
+// 37,634 pieces F = 128 453 / 420, the offsets no longer computed lane by lane.
+// Rows of 33 and 65 entries take what they took.  Entries meet in the order that
+// they had (by lane group, four at a time, then the tree), so results have the
+// same bits.
 // ---------------------------------------------------------------------------
+constexpr int kHdAhead = 8;
+// entries of a wavefront that are staged at a time: a multiple of kHdAhead per lane group
+constexpr int hd_slots(int L) { return kHdAhead * (kWave / L) > 128 ? kHdAhead * (kWave / L) : 128; }
+template <int L>
+constexpr int kHdSmemBytes = kWavesPerBlock * hd_slots(L) * 12 + kBlock * 16;
+
 template <int L, int W>
 __device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int32_t *__restrict__ col,
-                                         const float *__restrict__ val, const v4f *__restrict__ X,
+                                         const float *__restrict__ val, const char *__restrict__ X, int64_t zero_off,
                                          v4f *__restrict__ Y, v4f *__restrict__ partials, int32_t F4,
                                          const int64_t *__restrict__ out_ids)
 {
-    constexpr int G = kBlock / L;
-    v4f(*s_red)[L] = (v4f(*)[L])smem;                    // [G][L]
-    const int g = threadIdx.x / L, f = threadIdx.x % L;
-    const int64_t end = ch.begin + ch.len;
+    constexpr int G = kBlock / L, GW = kWave / L;        // lane groups of the workgroup and of a wavefront
+    constexpr int kSlots = hd_slots(L), kRun = kSlots / GW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    int64_t *const s_off = (int64_t *)smem + wave * kSlots;
+    float *const s_val = (float *)(smem + kWavesPerBlock * kSlots * 8) + wave * kSlots;
+    v4f *const s_red = (v4f *)(smem + kWavesPerBlock * kSlots * 12);      // [G][L]
+    const int gw = lane / L, f = lane % L;
     const float rw = row_weight<W>(ch.row_nnz);
 
+#pragma unroll 1
     for (int32_t fb = 0; fb < F4; fb += L) {
         const int32_t ff = fb + f;
         const bool live = ff < F4;
+        const char *const Xf = X + 16 * ff;
         v4f acc = {0.f, 0.f, 0.f, 0.f};
-        if (live) {
-            int64_t p = ch.begin + g;
-            for (; p + 3 * G < end; p += 4 * G) {
-                int32_t c0 = col[p], c1 = col[p + G], c2 = col[p + 2 * G], c3 = col[p + 3 * G];
-                v4f x0 = X[(int64_t)c0 * F4 + ff], x1 = X[(int64_t)c1 * F4 + ff];
-                v4f x2 = X[(int64_t)c2 * F4 + ff], x3 = X[(int64_t)c3 * F4 + ff];
+#pragma unroll 1
+        for (int32_t s = 0; s < ch.len; s += kRun * G) {
+            // entry k G + (lane group) of what is left belongs to the group's step k
+            const int32_t left = ch.len - s, steps = left < kRun * G ? (left + G - 1) / G : kRun;
+            const int32_t staged = (steps + kHdAhead - 1) / kHdAhead * kHdAhead * GW;
+            if (s || fb) wave_sync();                    // the run before has been read
+#pragma unroll 2
+            for (int i = lane; i < staged; i += kWave) {
+                const int32_t e = i / GW * G + wave * GW + i % GW;
+                const int64_t p = ch.begin + s + (e < left ? e : 0);
+                const int32_t c = col[p];
+                s_off[i] = e < left ? (int64_t)c * (F4 * 16) : zero_off;
+                if (W == kExplicit) s_val[i] = e < left ? val[p] : 0.f;
+            }
+            wave_sync();
+            if (!live) continue;                         // idle lanes cost the vector memory units time, too
+#pragma unroll 1
+            for (int32_t k0 = 0; k0 < steps; k0 += kHdAhead) {
+                v4f x[kHdAhead];
+                float w[kHdAhead];
+#pragma unroll
+                for (int k = 0; k < kHdAhead; ++k) {
+                    x[k] = *(const v4f *)(Xf + s_off[(k0 + k) * GW + gw]);
+                    if (W == kExplicit) w[k] = s_val[(k0 + k) * GW + gw];
+                }
                 if (W == kExplicit) {
-                    acc += val[p] * x0;
-                    acc += val[p + G] * x1;
-                    acc += val[p + 2 * G] * x2;
-                    acc += val[p + 3 * G] * x3;
-                } else {
-                    acc += (x0 + x1) + (x2 + x3);
+#pragma unroll
+                    for (int k = 0; k < kHdAhead; ++k) acc += w[k] * x[k];
+                } else if ((k0 + kHdAhead) * G <= left) {
+#pragma unroll
+                    for (int k = 0; k < kHdAhead; k += 4) acc += (x[k] + x[k + 1]) + (x[k + 2] + x[k + 3]);
+                } else {                                 // four entries at a time while there are four, the rest one by one
+#pragma unroll
+                    for (int k = 0; k < kHdAhead; k += 4) {
+                        const v4f four = acc + ((x[k] + x[k + 1]) + (x[k + 2] + x[k + 3]));
+                        const v4f fewer = ((acc + x[k]) + x[k + 1]) + x[k + 2];
+                        acc = (k0 + k + 3) * G + wave * GW + gw < left ? four : fewer;
+                    }
                 }
             }
-            for (; p < end; p += G) {
-                v4f x = X[(int64_t)col[p] * F4 + ff];
-                if (W == kExplicit) acc += val[p] * x;
-                else acc += x;
-            }
-            if (W != kExplicit) acc *= rw;
         }
-        s_red[g][f] = acc;
+        if (W != kExplicit) acc *= rw;
+        s_red[threadIdx.x] = acc;
         __syncthreads();
+        if (wave == 0) {
+            v4f sum = (s_red[lane] + s_red[lane + 2 * kWave]) + (s_red[lane + kWave] + s_red[lane + 3 * kWave]);
 #pragma unroll
-        for (int stride = G / 2; stride > 0; stride /= 2) {
-            if (g < stride) s_red[g][f] += s_red[g + stride][f];
-            __syncthreads();
+            for (int off = kWave / 2; off >= L; off /= 2)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sum[c] += __shfl_down(sum[c], off);
+            if (gw == 0 && live) {
+                if (ch.slot < 0) Y[(out_ids ? out_ids[ch.row] : (int64_t)ch.row) * F4 + ff] = sum;
+                else partials[(int64_t)ch.slot * F4 + ff] = sum;
+            }
         }
-        if (g == 0 && live) {
-            v4f sum = s_red[0][f];
-            if (ch.slot < 0) Y[(out_ids ? out_ids[ch.row] : (int64_t)ch.row) * F4 + ff] = sum;
-            else partials[(int64_t)ch.slot * F4 + ff] = sum;
-        }
-        __syncthreads();
+        if (fb + L < F4) __syncthreads();
     }
 }
 

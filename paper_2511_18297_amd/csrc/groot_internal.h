@@ -70,8 +70,8 @@ struct DevicePlan {
     int64_t n_partials = 0;
     int64_t nnz_hd = 0;             // stored entries of the high-degree rows (sum of the pieces' lengths)
     int xcd_remap = 1;
-    float *zero_row = nullptr;      // kZeroRowFloats zeros (the gather target of unused slots in the pipelined
-                                    // kernels), followed by kTrashFloats that those kernels may overwrite
+    float *zero_row = nullptr;      // kZeroRowFloats zeros (the gather target of unused slots of the kernels),
+                                    // followed by kTrashFloats that the pipelined kernels may overwrite
     // the fused layer's view of the high-degree rows: their ids (ascending), a buffer that takes their aggregated
     // features, one row per high-degree row in that order, and the HD schedule with every row named by its place
     // in the list instead of its id (so that the HD kernels write into the buffer)
@@ -101,7 +101,7 @@ constexpr int kCodeHot = 0x8000;      // codes from here on: index into the hot 
 constexpr int kCodeBad = 0xFFFF;      // an entry that no code can express: its row is not served in compact form
 constexpr int kCodeMaxHot = 0x7FFF;
 constexpr int kPipeMinDepth = 5, kPipeMaxDepth = 8;   // gather slots per row the pipelined LD kernel is built for
-constexpr int kZeroRowFloats = 256;     // a row of the widest matrix that the pipelined kernels serve
+constexpr int kZeroRowFloats = 512;     // a row of the widest matrix
 constexpr int kTrashFloats = 2048;
 constexpr int kRowsPerLdTile = 256;   // rows of one LD block (4 wavefronts x 64 rows)
 

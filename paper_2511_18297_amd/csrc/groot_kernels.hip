@@ -100,12 +100,12 @@ template <int L, int W>
 __global__ __launch_bounds__(kBlock) void hd_kernel(const HdChunk *__restrict__ chunks,
                                                     const int32_t *__restrict__ col,
                                                     const float *__restrict__ val,
-                                                    const v4f *__restrict__ X, v4f *__restrict__ Y,
-                                                    v4f *__restrict__ partials, int32_t F4,
+                                                    const char *__restrict__ X, int64_t zero_off,
+                                                    v4f *__restrict__ Y, v4f *__restrict__ partials, int32_t F4,
                                                     const int64_t *__restrict__ out_ids, int64_t n_out, int64_t n_chunks,
                                                     int32_t run)
 {
-    __shared__ __align__(16) char smem[kBlock * sizeof(v4f)];
+    __shared__ __align__(16) char smem[kHdSmemBytes<L>];
     int64_t piece = blockIdx.x;
     if (run > 1) {
         const int64_t k = blockIdx.x / kXcds;            // the XCD's k-th workgroup
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kBlock) void hd_kernel(const HdChunk *__restrict__ 
     }
     const HdChunk ch = chunks[piece];
     if (ch.row >= n_out) return;                         // the whole workgroup: a row that is not wanted
-    hd_piece<L, W>(smem, ch, col, val, X, Y, partials, F4, out_ids);
+    hd_piece<L, W>(smem, ch, col, val, X, zero_off, Y, partials, F4, out_ids);
 }
 
 // Y[row] = partials[first] + ... + partials[first+count-1], in that order.
@@ -242,7 +242,7 @@ int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
     const int32_t F4 = F / 4;
     const int64_t *out_ids = out ? out->ids : nullptr;
     const int64_t n_out = out ? out->n_out : dp.n;
-    if (!weights_ok(dp)) return (int)hipErrorInvalidValue;
+    if (!weights_ok(dp) || !dp.zero_row) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
     // Runs of 64 pieces from F = 64 on, where a stretch of X is large beside an L2 (polarized graphs, every row of X gathered
     // 70 times: 65,536 rows F = 128 90 -> 64 us, 262,144 rows F = 128 571 -> 550, F = 256 1,517 -> 1,030; multipliers, whose rows
@@ -255,8 +255,8 @@ int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
     if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
     GROOT_DISPATCH_LW(lanes_for(F4), dp.weight_mode,
                       (hd_kernel<kL, kW><<<dim3((unsigned)grid), dim3(kBlock), 0, st>>>(
-                          dp.chunks, dp.col, dp.val, (const v4f *)X, (v4f *)Y, (v4f *)dp.partials, F4, out_ids, n_out, dp.n_chunks,
-                          run)));
+                          dp.chunks, dp.col, dp.val, (const char *)X, byte_distance(X, dp.zero_row), (v4f *)Y,
+                          (v4f *)dp.partials, F4, out_ids, n_out, dp.n_chunks, run)));
     return (int)hipGetLastError();
 }
 

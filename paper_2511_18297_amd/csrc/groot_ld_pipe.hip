@@ -44,13 +44,6 @@ constexpr int kPipeRawBuffer = 0x00027000;   // last word of a buffer descriptor
 constexpr int kPipeNontemporal = 2;
 constexpr uint32_t kPipeDropped = 0x40000000;
 
-__device__ __forceinline__ void pipe_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // What a launch does beside the sweep, in workgroups of their own behind it: the low-degree rows that the pipeline masks,
 // one lane group per row, where they are few (rows_beside_sweep), and, where those are few (ld_takes_hd), the pieces of the
 // high-degree rows.  On small
@@ -104,8 +97,8 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     // same 16-byte slot, so that one LDS read per slot serves both
     struct SlotW { int64_t off; float w; float pad; };
     using Slot = typename std::conditional<W == kExplicit, SlotW, int64_t>::type;
-    constexpr int kSlotBytes = kPipeWaves * kSlots * (int)sizeof(Slot), kRedBytes = kBlock * (int)sizeof(v4f);
-    __shared__ __align__(16) char s_buf[kSlotBytes > kRedBytes ? kSlotBytes : kRedBytes];
+    constexpr int kSlotBytes = kPipeWaves * kSlots * (int)sizeof(Slot), kHdBytes = kHdSmemBytes<L>;
+    __shared__ __align__(16) char s_buf[kSlotBytes > kHdBytes ? kSlotBytes : kHdBytes];
     Slot (*const s_slot)[kSlots] = (Slot(*)[kSlots])s_buf;
     __shared__ float s_inv[kPipeWaves][kTileRows];       // row weight (1 unless W == kMean), or -1: the row is masked
     __shared__ int64_t s_oid[M ? kPipeWaves : 1][M ? kTileRows : 1];   // M: byte offset of the row's place in Y
@@ -123,7 +116,7 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
         } else {
             const HdChunk ch = side.chunks[b - side.n_row_wg];
             if (ch.row >= n) return;                     // the whole workgroup
-            hd_piece<L, W>(s_buf, ch, col, val, (const v4f *)X, (v4f *)Y, (v4f *)side.partials, F4, M ? out_ids : nullptr);
+            hd_piece<L, W>(s_buf, ch, col, val, X, zero_off, (v4f *)Y, (v4f *)side.partials, F4, M ? out_ids : nullptr);
         }
         return;
     }
@@ -221,7 +214,7 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
         if constexpr (M) {
             if (l < kTileRows) s_oid[w][l] = oid_a << kRowShift;
         }
-        pipe_wave_sync();
+        wave_sync();
         return ok_a;
     };
 

@@ -1195,3 +1195,26 @@ def test_feature_placement_returns_a_usable_pair(torch_cuda, matrices, F):
         G.groot_feature_placement(plan, arena[: n * F + n * F // 2], F)
     with pytest.raises(G.GrootError):
         G.groot_feature_placement(G.groot_spmm_plan(g, 32), arena, F)
+
+
+@pytest.mark.parametrize("F", [4, 12, 32, 60, 128, 260, 512])
+@pytest.mark.parametrize("explicit,chunk", [(False, 512), (True, 512), (False, 1300)])
+def test_lengths_of_high_degree_pieces(torch_cuda, F, explicit, chunk):
+    """Pieces whose quarters, rounds of eight gathers and runs of 128 entries end in every way: rows of a few entries to
+    several pieces, and pieces longer than what is staged at a time (the hd_chunk knob)."""
+    lengths = [1, 2, 3, 4, 5, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 257, 509, 511, 512, 513, 516, 1024, 1025, 1300, 1301]
+    n, rng = 1400, np.random.default_rng(F)
+    cols = [np.sort(rng.choice(n, k, replace=False)) for k in lengths] + [np.array([i]) for i in range(len(lengths), n)]
+    rowptr = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int64)
+    col = np.concatenate(cols).astype(np.int32)
+    length = np.diff(rowptr)
+    val = rng.uniform(-1, 1, col.size).astype(np.float32) if explicit else np.repeat(np.float32(1) / length.astype(np.float32), length)
+    G.groot_set_tuning("hd_chunk", chunk)
+    try:
+        X = wl.uniform_features_numpy(90 + F, 0, n, F)
+        Y, plan, _, _ = _run(torch_cuda, G.groot_graph_from_csr(rowptr, col, val), 2, X)
+    finally:
+        G.groot_set_tuning("hd_chunk", 512)
+    assert G.groot_plan_view(plan)["n_hd"] == len(lengths) - 1
+    Y64, S = oracle.spmm_f64(rowptr, col, val, X)
+    assert_close_to_oracle(Y, Y64, S, f"piece lengths F={F} explicit={explicit} chunk={chunk}")
