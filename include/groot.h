@@ -486,13 +486,14 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
  * 64, 128 and, on whole graphs, the widths from 20 (5 gather slots per row, and
  * high-degree rows or not between 65,537 and 524,287 rows) or 36 to 256), "pipe_depth" (gather slots per row of the pipelined kernel,
  * 5 to 8), "mid_rows" (low-degree rows with more entries than that, which are
- * computed from a list), "csr_compressed" (1 when the pipelined kernel reads 4-byte
- * row pointers and 2-byte column codes instead of the 8- and 4-byte arrays), "hd_pieces" (launch size of the HD kernel),
+ * computed from a list), "csr_compressed" (1 when the plan holds 4-byte row pointers and
+ * 2-byte column codes, which the pipelined kernel reads instead of the 8- and 4-byte arrays
+ * where X has 192 MiB or more, 1 GiB with more than 5 gather slots), "hd_pieces" (launch size of the HD kernel),
  * "hd_partials" (partial-sum slots of split high-degree rows), "weight_mode"
  * (how the kernels take the weights: 0 all 1, 1 fl(1 / row length) recomputed
  * from the row pointer, 2 read from the weight array), "nnz_hd" (stored entries
  * of the high-degree rows), "csr_bytes" (bytes of the graph's device arrays
- * that one execute reads: row pointers, column indices, the weights only when
+ * that one execute at max_F reads: row pointers, column indices, the weights only when
  * the kernels read them, the high-degree pieces' descriptors; "csr_bytes_ld" /
  * "csr_bytes_hd" its split over the low-degree and the high-degree kernel).
  * Errors: EINVAL (NULL, unknown name, plan not uploaded). */

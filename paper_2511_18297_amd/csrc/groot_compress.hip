@@ -77,14 +77,14 @@ int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd
     };
     if (dev_alloc((void **)&dp.rp32, (size_t)(dp.n + 1) * 4) != 0 ||
         dev_alloc((void **)&dp.col16, (size_t)dp.nnz * 2) != 0 ||
-        dev_alloc((void **)&dp.hot_cols, (size_t)(n_hot ? n_hot : 1) * 4) != 0 ||
+        dev_alloc((void **)&dp.hot_cols, (size_t)hot_ints(n_hot) * 4) != 0 ||
         dev_alloc((void **)&bad_rows, (size_t)bad_cap * 4) != 0 ||
         dev_alloc((void **)&n_bad, 4) != 0) {
         (void)hipGetLastError();
         return give_up(0);                                           // out of device memory: not an error, the plain arrays serve
     }
     hipError_t e = hipMemsetAsync(n_bad, 0, 4, st);
-    if (e == hipSuccess) e = hipMemsetAsync(dp.hot_cols, 0, (size_t)(n_hot ? n_hot : 1) * 4, st);
+    if (e == hipSuccess) e = hipMemsetAsync(dp.hot_cols, 0, (size_t)hot_ints(n_hot) * 4, st);
     if (e == hipSuccess && n_hot)
         e = hipMemcpyAsync(dp.hot_cols, hd_rows_dev, (size_t)n_hot * 4, hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return give_up((int)e);

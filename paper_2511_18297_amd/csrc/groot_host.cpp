@@ -1466,8 +1466,8 @@ extern "C" groot_status groot_plan_query(const groot_plan *plan, const char *wha
         const DevicePlan &d = plan->dev;
         const int64_t w_bytes = d.weight_mode == (int)WeightMode::Explicit ? 4 : 0;
         const int64_t per_entry = 4 + w_bytes;
-        // the pipelined LD kernel reads the compact form when the plan has one
-        const bool compact = d.ld_pipelined && d.compressed;
+        // (of the widest matrix that the plan serves) whether the pipelined LD kernel reads the compact form
+        const bool compact = d.ld_pipelined && ld_reads_compact(d, plan->max_F);
         const int64_t ld = compact ? 4 * (d.n + 1) + (2 + w_bytes) * (d.nnz - d.nnz_hd)
                                    : 8 * (d.n + 1) + per_entry * (d.nnz - d.nnz_hd);
         const int64_t hd = per_entry * d.nnz_hd + (int64_t)sizeof(HdChunk) * d.n_chunks;

@@ -45,7 +45,7 @@ struct Tuning {
     std::atomic<int> sage_kernel{1};       // fused layer: 1 one self-contained wavefront per SIMD, 0 the 12-wavefront kernel
     std::atomic<int> sage_pieces{3};       // fused layer (sage_kernel 1): bf16 pieces per fp32 operand of the dense products, 3 or 2
     std::atomic<int> uniform_detect{1};    // groot_plan_upload looks whether explicit weights are row-uniform (see DevicePlan)
-    std::atomic<int> csr_compress{1};      // groot_plan_upload builds the compact CSR for the pipelined LD kernel when it can
+    std::atomic<int> csr_compress{1};      // groot_plan_upload builds the compact CSR for the pipelined LD kernel when it can; it is read where it pays (ld_reads_compact)
     std::atomic<int> pipe_depth{0};        // gather slots per row of the pipelined LD kernel: 0 the smallest that fits, or 5..8
     std::atomic<int> ld_pipeline{-1};      // pipelined LD kernel: 1 always (where it applies), 0 never, -1 by the row lengths
 };
@@ -100,6 +100,7 @@ constexpr int kCodeNear = 0x4000;     // column codes below kCodeHot: row + code
 constexpr int kCodeHot = 0x8000;      // codes from here on: index into the hot list
 constexpr int kCodeBad = 0xFFFF;      // an entry that no code can express: its row is not served in compact form
 constexpr int kCodeMaxHot = 0x7FFF;
+constexpr int32_t hot_ints(int32_t n_hot) { return n_hot ? (n_hot + 3) / 4 * 4 : 4; }   // the hot list as it is stored: whole 16 bytes
 constexpr int kPipeMinDepth = 5, kPipeMaxDepth = 8;   // gather slots per row the pipelined LD kernel is built for
 constexpr int kZeroRowFloats = 512;     // a row of the widest matrix
 constexpr int kTrashFloats = 2048;
@@ -117,6 +118,7 @@ struct RowOut {
 int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out = nullptr,
               bool with_hd = false);
 bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out = nullptr);
+bool ld_reads_compact(const DevicePlan &dp, int32_t F);
 int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream,
                         const RowOut *out, bool with_hd);   // F up to 256; with out F = 32, 64, 128
 int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out = nullptr);

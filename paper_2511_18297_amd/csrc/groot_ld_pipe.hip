@@ -39,6 +39,9 @@ constexpr int kPipeWaves = 4;                // wavefronts per workgroup, one wo
 // 31.3 ms per step for 5 / 7 / 8
 constexpr int pipe_groups(int) { return 7; }
 
+typedef int pipe_i4 __attribute__((ext_vector_type(4)));
+constexpr int kHotAhead = 8;                  // 16-byte loads of the hot list that a lane has in flight
+
 typedef unsigned int pipe_u4 __attribute__((ext_vector_type(4)));
 constexpr int kPipeRawBuffer = 0x00027000;   // last word of a buffer descriptor: raw 32-bit data, offsets checked against the size
 constexpr int kPipeNontemporal = 2;
@@ -128,7 +131,8 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     const int64_t x_begin = part * tiles_per_part;
     const int64_t x_end = x_begin + tiles_per_part < n_tiles ? x_begin + tiles_per_part : n_tiles;
     const int64_t t_first = x_begin + j, stride = waves_per_part;
-    extern __shared__ int32_t s_hot[];                   // C: the hot list (at least one element)
+    extern __shared__ __align__(16) int32_t s_hot[];     // C: the hot list (hot_ints of it)
+    const int n_hot4 = C ? hot_ints(cz.n_hot) / 4 : 0;
     const char *Xf = X + 16 * f;
 
     // ---- CSR pipeline: rp_a and cc/vv belong to the next tile to be staged, rp_b to the one after
@@ -253,20 +257,41 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     };
 
     char *const tbase = trash + 16 * f;
-    int64_t rp_first = 0;
-    if (t_first < x_end) rp_first = load_rp(t_first);    // on its way while the hot list is copied
-    if constexpr (C) {
-        for (int i = threadIdx.x; i < cz.n_hot; i += kPipeWaves * kWave) s_hot[i] = cz.hot[i];
-        if (threadIdx.x == 0 && cz.n_hot == 0) s_hot[0] = 0;
-        __syncthreads();                                 // every wavefront of the sweep gets here: none has left
-    }
-    if (t_first >= x_end) return;
-    // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way
-    rp_a = rp_first;
+    // ---- prologue: the first tile is staged and put in flight, the CSR of the next two is on its way.  The hot list is copied
+    // meanwhile, 32 KB in flight at a time: a load and a store at a time, before the first row pointer was used, the copy
+    // was a latency per 256 rows of the list in front of everything (4-LUT shape, 1 M rows, 4,096 of them hot, F = 64: 220 us, now 213).
+    // Every wavefront takes part, also one without a tile: its loads read what exists.
+    rp_a = load_rp(t_first);
     oid_a = load_oid(t_first);
+    pipe_i4 hot_a[kHotAhead];
+    auto load_hot = [&](int base) {
+#pragma unroll
+        for (int k = 0; k < kHotAhead; ++k) {
+            const int i = base + k * (kPipeWaves * kWave) + threadIdx.x;
+            hot_a[k] = ((const pipe_i4 *)cz.hot)[i < n_hot4 ? i : 0];
+        }
+    };
+    auto store_hot = [&](int base) {
+#pragma unroll
+        for (int k = 0; k < kHotAhead; ++k) {
+            const int i = base + k * (kPipeWaves * kWave) + threadIdx.x;
+            if (i < n_hot4) ((pipe_i4 *)s_hot)[i] = hot_a[k];
+        }
+    };
+    if constexpr (C) load_hot(0);
     load_cols(t_first);
     rp_b = load_rp(t_first + stride);                    // arrives with the columns
     oid_b = load_oid(t_first + stride);
+    if constexpr (C) {
+        store_hot(0);
+#pragma unroll 1
+        for (int base = kHotAhead * kPipeWaves * kWave; base < n_hot4; base += kHotAhead * kPipeWaves * kWave) {
+            load_hot(base);
+            store_hot(base);
+        }
+        __syncthreads();                                 // every wavefront of the sweep gets here: none has left
+    }
+    if (t_first >= x_end) return;
     bool ok_cur = stage();
 #pragma unroll
     for (int grp = 0; grp < G; ++grp) issue(rr[grp], grp);
@@ -370,7 +395,7 @@ static void pipe_launch(const PipeArgs &a)
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
             a.waves_per_part, a.parts, a.out_ids, a.F4, a.side);
     } else if (a.compact) {
-        const size_t lds = (size_t)(a.cz.n_hot ? a.cz.n_hot : 1) * sizeof(int32_t);
+        const size_t lds = (size_t)hot_ints(a.cz.n_hot) * sizeof(int32_t);
         ld_pipe_kernel<L, W, G, D, true><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
             a.waves_per_part, a.parts, nullptr, a.F4, a.side);
@@ -386,7 +411,7 @@ static void pipe_launch_any(const PipeArgs &a)
 {
     const dim3 grid((unsigned)(a.n_wg + a.side.n_row_wg + a.n_hd));
     if (a.compact) {
-        const size_t lds = (size_t)(a.cz.n_hot ? a.cz.n_hot : 1) * sizeof(int32_t);
+        const size_t lds = (size_t)hot_ints(a.cz.n_hot) * sizeof(int32_t);
         ld_pipe_kernel<L, W, G, D, true, false, true><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
             a.waves_per_part, a.parts, nullptr, a.F4, a.side);
@@ -440,7 +465,7 @@ template <int L, int W, int D, bool S>
 static int pipe_allow_lds()
 {
     return (int)hipFuncSetAttribute((const void *)&ld_pipe_kernel<L, W, pipe_groups(L), D, true, false, S>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kCodeMaxHot * (int)sizeof(int32_t));
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, hot_ints(kCodeMaxHot) * (int)sizeof(int32_t));
 }
 template <int W, int D>
 static int pipe_allow_lds_l()
@@ -495,6 +520,21 @@ static int64_t rows_beside_sweep(int depth, int32_t F4, int64_t n_rows)
     return n_rows * F4 * 16 < kCacheBytes ? 4096 : n_rows;
 }
 
+// Whether a whole-graph call reads the compact matrix.  It halves the bytes of the matrix and costs the decoding of every
+// slot, so it pays where the feature matrices come from HBM.  Whole step, us, compact / plain arrays, by the bytes of X:
+//   5 slots: 67 MB (multiplier, F = 32) 36.0 / 32.4; 134 MB (F = 32) 59.9 / 55.9, (F = 64) 49.3 / 48.7, (Booth, F = 32) 66.6 / 63.3;
+//     208 MB (F = 100) 77.7 / 78.5, (Booth, F = 128) 82.8 / 81.0; 267 MB (F = 32) 123.7 / 124.0, (F = 64) 118.9 / 118.4, (F = 128)
+//     117.5 / 124.2; 535 MB (F = 64) 233.9 / 238.3; 2.1 GB (F = 64) 941 / 962
+//   6 and 7 slots: 134 MB (4-LUT, F = 32) 104.8 / 94.4; 271 MB (cells, F = 32) 172.7 / 166.0, (4-LUT, F = 64) 212.2 / 215.4; 424 MB
+//     (4-LUT, F = 100) 369.8 / 364.2; 540 MB (F = 64) 423.9 / 423.6, (cells) 317.5 / 316.4; 844 MB 710.1 / 710.8; 1.1 GB (4-LUT, F = 32)
+//     803 / 811, (cells) 628 / 640
+bool ld_reads_compact(const DevicePlan &dp, int32_t F)
+{
+    if (!dp.compressed || !dp.rp32 || !dp.col16 || !dp.hot_cols) return false;
+    const int64_t line = dp.pipe_depth <= 5 ? (int64_t)192 << 20 : (int64_t)1 << 30;
+    return dp.n_cols * F * 4 >= line;
+}
+
 // out: the leading out->n_out rows only, row r written to row out->ids[r] of Y (ids NULL: to row r)
 int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out, bool with_hd)
 {
@@ -534,7 +574,7 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
                   "a tile's masked sums fit the trash area");
     hipStream_t st = (hipStream_t)stream;
     // the compact matrix codes rows that the row list serves as uncoded, which only holds for whole-graph calls
-    const bool compact = !out && dp.compressed && dp.rp32 && dp.col16 && dp.hot_cols;
+    const bool compact = !out && ld_reads_compact(dp, F);
     // the low-degree rows with more entries than the pipeline has slots; the rows that the compact matrix cannot
     // code stand at the end of the list and are the pipeline's own whenever it reads the plain arrays
     const int64_t n_mid = compact ? dp.n_mid_rows : dp.n_mid_rows - dp.n_bad_rows;

@@ -1218,3 +1218,52 @@ def test_lengths_of_high_degree_pieces(torch_cuda, F, explicit, chunk):
     assert G.groot_plan_view(plan)["n_hd"] == len(lengths) - 1
     Y64, S = oracle.spmm_f64(rowptr, col, val, X)
     assert_close_to_oracle(Y, Y64, S, f"piece lengths F={F} explicit={explicit} chunk={chunk}")
+
+
+@pytest.mark.parametrize("F,depth,explicit", [(32, 5, False), (64, 5, True), (100, 5, False), (128, 7, False), (200, 5, True),
+                                              (252, 8, False)])
+def test_compact_matrix_where_it_is_read(torch_cuda, F, depth, explicit):
+    """The compact matrix against the plain arrays on either side of the size of X from which it is read: the same sums in the
+    same order, so the same bits.  Rows of 1 to depth entries near the row or among the high-degree rows, a few longer ones,
+    a few with an entry that no code expresses, a high-degree row count that is no multiple of four, a ragged last tile."""
+    line = (192 << 20) if depth == 5 else (1 << 30)
+    rng = np.random.default_rng(F)
+    for n in ((line - 1) // (4 * F), -(-line // (4 * F)) + 1):
+        length = rng.integers(max(1, depth - 1), depth + 1, n)
+        hot = np.sort(16000 + rng.choice(n - 32000, 1021, replace=False))
+        length[rng.choice(n, n // 400, replace=False)] = depth + 2
+        length[hot] = 60
+        row = np.repeat(np.arange(n), length)
+        col = np.clip(row + rng.integers(-16000, 16001, row.size), 0, n - 1)
+        pick = rng.random(row.size)
+        col = np.where(pick < 0.2, hot[rng.integers(0, hot.size, row.size)], col)
+        col = np.where(pick > 0.9999, rng.integers(0, n, row.size), col)
+        row, col = np.divmod(np.unique(row * n + col), n)        # ascending, no column twice in a row
+        length = np.bincount(row, minlength=n)
+        rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+        col = col.astype(np.int32)
+        val = rng.uniform(-1, 1, col.size).astype(np.float32) if explicit else np.repeat(
+            np.float32(1) / np.maximum(length, 1).astype(np.float32), length)
+        g = G.groot_graph_from_csr(rowptr, col, val)
+        X = torch_cuda.empty((n, F), device="cuda").uniform_(-1, 1)
+        out = []
+        for compress in (1, 0):
+            G.groot_set_tuning("csr_compress", compress)
+            G.groot_set_tuning("pipe_depth", depth)
+            try:
+                plan = G.groot_spmm_plan(g, 32)
+                G.groot_plan_upload(plan, F)
+            finally:
+                G.groot_set_tuning("csr_compress", 1)
+                G.groot_set_tuning("pipe_depth", 0)
+            if G.groot_plan_query(plan, "ld_pipelined"):
+                assert G.groot_plan_query(plan, "csr_compressed") == compress
+                if compress:
+                    entries = int(rowptr[-1]) - G.groot_plan_query(plan, "nnz_hd")
+                    weights = 4 if explicit else 0
+                    read = 4 * (n + 1) + (2 + weights) * entries if 4 * F * n >= line else 8 * (n + 1) + (4 + weights) * entries
+                    assert G.groot_plan_query(plan, "csr_bytes_ld") == read
+            Y = torch_cuda.full((n, F), float("nan"), device="cuda")
+            G.groot_spmm_execute(plan, X, Y, F)
+            out.append(Y)
+        assert torch_cuda.equal(out[0], out[1]), f"F={F} n={n}"
