@@ -489,6 +489,9 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
  * computed from a list), "csr_compressed" (1 when the plan holds 4-byte row pointers and
  * 2-byte column codes, which the pipelined kernel reads instead of the 8- and 4-byte arrays
  * where X has 192 MiB or more, 1 GiB with more than 5 gather slots), "hd_pieces" (launch size of the HD kernel),
+ * "dense_rows" (high-degree rows with so many entries that groot_spmm_execute computes
+ * them as a dense product instead of by their pieces, where their entries times F
+ * come to 2^25 or more and F is 8 or more),
  * "hd_partials" (partial-sum slots of split high-degree rows), "weight_mode"
  * (how the kernels take the weights: 0 all 1, 1 fl(1 / row length) recomputed
  * from the row pointer, 2 read from the weight array), "nnz_hd" (stored entries

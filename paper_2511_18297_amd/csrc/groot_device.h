@@ -121,7 +121,7 @@ __device__ __forceinline__ v4f row_sum_ahead(int64_t s, int64_t e, const int32_t
 // ---------------------------------------------------------------------------
 // HD part.  One workgroup per piece of a high-degree row (the plan cuts a row
 // into balanced pieces).  Its 256/L lane groups stride over the piece's entries,
-// kHdAhead gathers in flight each and no branch between them, with a register
+// up to 8 gathers in flight each and no branch between them, with a register
 // accumulator per float4 slice: the byte offsets of the rows of X (and the
 // weights) have been put to LDS by the group's own wavefront, padded with the
 // row of zeros.  The group sums meet in LDS and are added by a tree.  The result
@@ -138,9 +138,10 @@ __device__ __forceinline__ v4f row_sum_ahead(int64_t s, int64_t e, const int32_t
 // they had (by lane group, four at a time, then the tree), so results have the
 // same bits.
 // ---------------------------------------------------------------------------
-constexpr int kHdAhead = 8;
-// entries of a wavefront that are staged at a time: a multiple of kHdAhead per lane group
-constexpr int hd_slots(int L) { return kHdAhead * (kWave / L) > 128 ? kHdAhead * (kWave / L) : 128; }
+// gathers of a lane group in flight: no more than a usual piece of 512 entries has for it (F = 4, 18 M entries: with 8 it
+// was 119 us, now 69)
+constexpr int hd_ahead(int L) { return L >= 4 ? 8 : 2 * L; }
+constexpr int hd_slots(int) { return 128; }  // entries of a wavefront that are staged at a time
 template <int L>
 constexpr int kHdSmemBytes = kWavesPerBlock * hd_slots(L) * 12 + kBlock * 16;
 
@@ -151,7 +152,7 @@ __device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int
                                          const int64_t *__restrict__ out_ids)
 {
     constexpr int G = kBlock / L, GW = kWave / L;        // lane groups of the workgroup and of a wavefront
-    constexpr int kSlots = hd_slots(L), kRun = kSlots / GW;
+    constexpr int kSlots = hd_slots(L), kRun = kSlots / GW, kHdAhead = hd_ahead(L);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     int64_t *const s_off = (int64_t *)smem + wave * kSlots;
     float *const s_val = (float *)(smem + kWavesPerBlock * kSlots * 8) + wave * kSlots;
@@ -169,15 +170,21 @@ __device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int
         for (int32_t s = 0; s < ch.len; s += kRun * G) {
             // entry k G + (lane group) of what is left belongs to the group's step k
             const int32_t left = ch.len - s, steps = left < kRun * G ? (left + G - 1) / G : kRun;
-            const int32_t staged = (steps + kHdAhead - 1) / kHdAhead * kHdAhead * GW;
             if (s || fb) wave_sync();                    // the run before has been read
-#pragma unroll 2
-            for (int i = lane; i < staged; i += kWave) {
-                const int32_t e = i / GW * G + wave * GW + i % GW;
-                const int64_t p = ch.begin + s + (e < left ? e : 0);
-                const int32_t c = col[p];
-                s_off[i] = e < left ? (int64_t)c * (F4 * 16) : zero_off;
-                if (W == kExplicit) s_val[i] = e < left ? val[p] : 0.f;
+            int32_t c[kSlots / kWave];
+            float v[kSlots / kWave];
+#pragma unroll
+            for (int h = 0; h < kSlots / kWave; ++h) {   // past the end: the last entry again, its offset is not used
+                const int i = lane + h * kWave, e = i / GW * G + wave * GW + i % GW;
+                const int64_t p = ch.begin + s + (e < left ? e : left - 1);
+                c[h] = col[p];
+                if (W == kExplicit) v[h] = val[p];
+            }
+#pragma unroll
+            for (int h = 0; h < kSlots / kWave; ++h) {
+                const int i = lane + h * kWave, e = i / GW * G + wave * GW + i % GW;
+                s_off[i] = e < left ? (int64_t)c[h] * (F4 * 16) : zero_off;
+                if (W == kExplicit) s_val[i] = e < left ? v[h] : 0.f;
             }
             wave_sync();
             if (!live) continue;                         // idle lanes cost the vector memory units time, too
@@ -193,6 +200,9 @@ __device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int
                 if (W == kExplicit) {
 #pragma unroll
                     for (int k = 0; k < kHdAhead; ++k) acc += w[k] * x[k];
+                } else if constexpr (kHdAhead < 4) {
+#pragma unroll
+                    for (int k = 0; k < kHdAhead; ++k) acc += x[k];
                 } else if ((k0 + kHdAhead) * G <= left) {
 #pragma unroll
                     for (int k = 0; k < kHdAhead; k += 4) acc += (x[k] + x[k + 1]) + (x[k + 2] + x[k + 3]);
@@ -221,6 +231,28 @@ __device__ __forceinline__ void hd_piece(char *smem, const HdChunk ch, const int
             }
         }
         if (fb + L < F4) __syncthreads();
+    }
+}
+
+// Y[row] = partials[first] + ... + partials[first+count-1], in that order: lane f of the L lanes of a row.
+template <int L>
+__device__ __forceinline__ void hd_finish_row(const HdSplitRow sr, const v4f *__restrict__ partials, v4f *__restrict__ Y,
+                                              int32_t F4, const int64_t *__restrict__ out_ids, int f)
+{
+    const int64_t orow = out_ids ? out_ids[sr.row] : (int64_t)sr.row;
+    for (int32_t ff = f; ff < F4; ff += L) {
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        const v4f *p = partials + (int64_t)sr.first * F4 + ff;
+        int32_t c = 0;
+        for (; c + 8 <= sr.count; c += 8, p += 8 * (int64_t)F4) {   // eight loads in flight: a row may have hundreds of pieces
+            v4f x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = p[i * (int64_t)F4];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc += x[i];
+        }
+        for (; c < sr.count; ++c, p += F4) acc += *p;
+        Y[orow * F4 + ff] = acc;
     }
 }
 

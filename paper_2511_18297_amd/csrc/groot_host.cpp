@@ -460,6 +460,7 @@ void release_device(groot_plan *pl)
     dev_free(d.rowptr); dev_free(d.col); dev_free(d.val);
     dev_free(d.chunks); dev_free(d.split_rows); dev_free(d.partials); dev_free(d.zero_row); dev_free(d.mid_rows);
     dev_free(d.rp32); dev_free(d.col16); dev_free(d.hot_cols);
+    dev_free(d.dense_rows); dev_free(d.dense_mask); dev_free(d.dense_partials); dev_free(d.other_chunks); dev_free(d.other_split_rows);
     dev_free(d.hd_rows); dev_free(d.hd_agg); dev_free(d.chunks_rank); dev_free(d.split_rows_rank);
     d = DevicePlan{};
     pl->resident = false;
@@ -544,6 +545,87 @@ groot_status upload_layer_hd_side(groot_plan *pl, const int32_t *hd_rows_host, i
         (st = to_device(&d.hd_rows, hd_rows_host, (size_t)n_hd, "high-degree row list")) != GROOT_OK)
         return st;
     return GROOT_OK;
+}
+}  // namespace
+
+namespace {
+// The high-degree rows that are cheaper as a dense product than by gathers, longest first, and how many are multiplied at a
+// time.  A tile of rows costs what its padded rows times all columns cost, whatever they hold; a gather costs its entry: a tile
+// pays when its rows together hold one in kDenseShare of the columns each, on average.
+constexpr int64_t kDenseShare = 14;
+constexpr int64_t kDenseMinEntries = 32768;  // below, the launches are what a call takes
+
+std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<int32_t> &hd_rows, int32_t &tile_rows)
+{
+    std::vector<HdChunk> rows;
+    for (int32_t r : hd_rows) {
+        const int64_t b = g->rowptr[r], len = g->rowptr[r + 1] - b;
+        if (len * kDenseShare * 4 >= g->n && len <= std::numeric_limits<int32_t>::max())
+            rows.push_back(HdChunk{b, (int32_t)len, r, -1, (int32_t)len});
+    }
+    std::stable_sort(rows.begin(), rows.end(), [](const HdChunk &a, const HdChunk &b) { return a.len > b.len; });
+    for (tile_rows = 64; tile_rows >= 16; tile_rows /= 2) {
+        size_t keep = 0;
+        int64_t entries = 0;
+        for (size_t first = 0; first < rows.size(); first += tile_rows) {
+            const size_t end = std::min(rows.size(), first + (size_t)tile_rows);
+            int64_t in_tile = 0;
+            for (size_t k = first; k < end; ++k) in_tile += rows[k].len;
+            if (in_tile * kDenseShare < g->n * tile_rows) break;
+            keep = end;
+            entries += in_tile;
+        }
+        if (keep && entries >= kDenseMinEntries) {
+            rows.resize(keep);
+            while (tile_rows > 16 && rows.size() * 2 <= (size_t)tile_rows) tile_rows /= 2;
+            return rows;
+        }
+    }
+    rows.clear();
+    return rows;
+}
+
+// false: the rows stay with the gathers, also where there is no memory for this
+bool upload_dense_rows(groot_plan *pl, int32_t max_F)
+{
+    DevicePlan &d = pl->dev;
+    const groot_graph *g = pl->g;
+    if (d.weight_mode == (int)WeightMode::Explicit || max_F < kDenseMinF || (int64_t)g->n < 1) return true;
+    int32_t tile_rows = 0;
+    const std::vector<HdChunk> rows = choose_dense_rows(g, pl->hd_rows, tile_rows);
+    if (rows.empty()) return true;
+    std::vector<int32_t> ids;
+    d.dense_entries = 0;
+    for (const HdChunk &r : rows) {
+        ids.push_back(r.row);
+        d.dense_entries += r.len;
+    }
+    std::sort(ids.begin(), ids.end());
+    auto other = [&](int32_t row) { return !std::binary_search(ids.begin(), ids.end(), row); };
+    std::vector<HdChunk> chunks;
+    std::vector<HdSplitRow> split;
+    std::copy_if(pl->chunks.begin(), pl->chunks.end(), std::back_inserter(chunks), [&](const HdChunk &c) { return other(c.row); });
+    std::copy_if(pl->split_rows.begin(), pl->split_rows.end(), std::back_inserter(split), [&](const HdSplitRow &r) { return other(r.row); });
+    d.n_dense_rows = (int32_t)rows.size();
+    d.dense_tile_rows = tile_rows;
+    bool ok = to_device(&d.dense_rows, rows.data(), rows.size(), "dense rows") == GROOT_OK &&
+              to_device(&d.other_chunks, chunks.data(), chunks.size(), "HD schedule beside the dense rows") == GROOT_OK &&
+              to_device(&d.other_split_rows, split.data(), split.size(), "HD split rows beside the dense rows") == GROOT_OK &&
+              to_device<uint32_t>(&d.dense_mask, nullptr, dense_mask_words(d), "columns of the dense rows") == GROOT_OK &&
+              to_device<float>(&d.dense_partials, nullptr, dense_partials_floats(d, max_F), "sums of the dense rows") == GROOT_OK;
+    const int err = ok ? launch_dense_mask(d, nullptr) : 0;
+    if (ok && !err) {
+        d.n_other_chunks = (int64_t)chunks.size();
+        d.n_other_split_rows = (int64_t)split.size();
+        return device_wait(nullptr) == 0;
+    }
+    dev_free(d.dense_rows); dev_free(d.other_chunks); dev_free(d.other_split_rows); dev_free(d.dense_mask); dev_free(d.dense_partials);
+    d.dense_rows = d.other_chunks = nullptr;
+    d.other_split_rows = nullptr;
+    d.dense_mask = nullptr;
+    d.dense_partials = nullptr;
+    d.n_dense_rows = 0;
+    return err == 0;
 }
 }  // namespace
 
@@ -648,6 +730,10 @@ extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
         set_error(keep);
         return st;
     }
+    if (!upload_dense_rows(plan, max_F)) {
+        release_device(plan);
+        return fail(GROOT_EHIP, "groot_plan_upload: columns of the dense rows: launch failed");
+    }
     d.n_chunks = (int64_t)plan->chunks.size();
     d.nnz_hd = 0;
     for (const HdChunk &ch : plan->chunks) d.nnz_hd += ch.len;
@@ -682,10 +768,20 @@ extern "C" groot_status groot_spmm_execute_phases(const groot_plan *plan, const 
     const int64_t x_bytes = plan->dev.n_cols * (int64_t)F * 4, y_bytes = plan->dev.n * (int64_t)F * 4;
     if (a < b + y_bytes && b < a + x_bytes) return fail(GROOT_EINVAL, "groot_spmm_execute: X and Y overlap");
     int err = 0;
-    const bool together = (phases & GROOT_PHASE_LD) && (phases & GROOT_PHASE_HD) && ld_takes_hd(plan->dev, F);
-    if (!err && (phases & GROOT_PHASE_LD)) err = launch_ld(plan->dev, X_dev, Y_dev, F, hip_stream, nullptr, together);
-    if (!err && !together && (phases & GROOT_PHASE_HD) && plan->dev.n_chunks) err = launch_hd(plan->dev, X_dev, Y_dev, F, hip_stream);
-    if (!err && (phases & GROOT_PHASE_FINISH) && plan->dev.n_split_rows) err = launch_hd_finish(plan->dev, Y_dev, F, hip_stream);
+    const bool dense = hd_dense_serves(plan->dev, F);
+    DevicePlan dp = plan->dev;
+    if (dense) {                                          // the schedule of the other high-degree rows
+        dp.chunks = dp.other_chunks;
+        dp.n_chunks = dp.n_other_chunks;
+        dp.split_rows = dp.other_split_rows;
+        dp.n_split_rows = dp.n_other_split_rows;
+    }
+    const bool together = (phases & GROOT_PHASE_LD) && (phases & GROOT_PHASE_HD) && ld_takes_hd(dp, F);
+    if (!err && (phases & GROOT_PHASE_LD)) err = launch_ld(dp, X_dev, Y_dev, F, hip_stream, nullptr, together);
+    if (!err && dense && (phases & GROOT_PHASE_HD)) err = launch_hd_dense(dp, X_dev, Y_dev, F, together ? 0 : dp.n_chunks, hip_stream);
+    if (!err && !dense && !together && (phases & GROOT_PHASE_HD) && dp.n_chunks) err = launch_hd(dp, X_dev, Y_dev, F, hip_stream);
+    if (!err && dense && (phases & GROOT_PHASE_FINISH)) err = launch_hd_dense_finish(dp, X_dev, Y_dev, F, hip_stream);
+    if (!err && !dense && (phases & GROOT_PHASE_FINISH) && dp.n_split_rows) err = launch_hd_finish(dp, Y_dev, F, hip_stream);
     if (err) return fail(GROOT_EHIP, std::string("groot_spmm_execute: launch failed: ") + hip_error_text(err));
     return GROOT_OK;
 }
@@ -1459,6 +1555,7 @@ extern "C" groot_status groot_plan_query(const groot_plan *plan, const char *wha
     else if (k == "csr_compressed") *value = plan->dev.compressed;
     else if (k == "uncoded_rows") *value = plan->dev.n_bad_rows;
     else if (k == "mid_rows") *value = plan->dev.n_mid_rows;
+    else if (k == "dense_rows") *value = plan->dev.n_dense_rows;
     else if (k == "csr_bytes" || k == "csr_bytes_ld" || k == "csr_bytes_hd") {
         // what the kernels read of the graph per execute: every row pointer and every entry's column index, the
         // entry's weight only when the kernels take the weights from the array; the HD kernel reads its pieces'

@@ -80,6 +80,17 @@ struct DevicePlan {
     float *hd_agg = nullptr;        // [n_hd_rows, max_F]
     HdChunk *chunks_rank = nullptr; // [n_chunks]
     HdSplitRow *split_rows_rank = nullptr;   // [n_split_rows]
+    // high-degree rows that groot_spmm_execute computes as a dense product (groot_hd_dense.hip), and the schedule of the others
+    HdChunk *dense_rows = nullptr;  // [n_dense_rows] the whole row as one piece
+    int32_t n_dense_rows = 0;
+    int64_t dense_entries = 0;
+    int32_t dense_tile_rows = 0;    // 16, 32 or 64 rows at a time
+    uint32_t *dense_mask = nullptr; // one bit per column and row, rows padded to whole tiles
+    float *dense_partials = nullptr;
+    HdChunk *other_chunks = nullptr;
+    int64_t n_other_chunks = 0;
+    HdSplitRow *other_split_rows = nullptr;
+    int64_t n_other_split_rows = 0;
     // compact CSR for the pipelined LD kernel (groot_compress.hip); all NULL / 0 unless compressed
     uint32_t *rp32 = nullptr;       // [n+1] low 32 bits of rowptr (nnz < 2^32)
     uint16_t *col16 = nullptr;      // [nnz] column codes of the rows the pipelined kernel serves
@@ -149,6 +160,15 @@ void free_device_hd_schedule(DeviceHdSchedule &s);
 // Compact CSR for the pipelined LD kernel, built on the device (groot_compress.hip); synchronises the stream.
 int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, void *stream);
 int pipe_compact_prepare();   // once per process, before the first launch with a compact CSR; hipError_t as int
+// High-degree rows as a dense product (groot_hd_dense.hip): whole-graph calls, row-uniform weights.
+constexpr int kDenseMaxWorkgroups = 256;
+constexpr int32_t kDenseMinF = 8;            // narrowest matrix that the kernel serves
+bool hd_dense_serves(const DevicePlan &dp, int32_t F);
+size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F);
+size_t dense_mask_words(const DevicePlan &dp);
+int launch_dense_mask(const DevicePlan &dp, void *stream);
+int launch_hd_dense(const DevicePlan &dp, const float *X, float *Y, int32_t F, int64_t n_chunks, void *stream);
+int launch_hd_dense_finish(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream);
 // col[p] = ids[col[p]] for p < nnz, in place (a part's local columns -> rows of the whole graph's feature matrix)
 int launch_col_map(int32_t *col, int64_t nnz, const int64_t *ids, void *stream);
 int launch_rows_gather(const int64_t *ids, int64_t n, const float *X, float *out, int32_t F, void *stream);

@@ -130,21 +130,7 @@ __global__ __launch_bounds__(kBlock) void hd_finish_kernel(const HdSplitRow *__r
     if (k >= n_rows) return;
     const HdSplitRow sr = rows[k];
     if (sr.row >= n_out) return;
-    const int64_t orow = out_ids ? out_ids[sr.row] : (int64_t)sr.row;
-    for (int32_t ff = threadIdx.x % L; ff < F4; ff += L) {
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        const v4f *p = partials + (int64_t)sr.first * F4 + ff;
-        int32_t c = 0;
-        for (; c + 8 <= sr.count; c += 8, p += 8 * (int64_t)F4) {   // eight loads in flight: a row may have hundreds of pieces
-            v4f x[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = p[i * (int64_t)F4];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc += x[i];
-        }
-        for (; c < sr.count; ++c, p += F4) acc += *p;
-        Y[orow * F4 + ff] = acc;
-    }
+    hd_finish_row<L>(sr, partials, Y, F4, out_ids, threadIdx.x % L);
 }
 
 // out[i] = X[ids[i]]  (kScatter = false)   or   Y[ids[i]] = in[i]  (kScatter = true)

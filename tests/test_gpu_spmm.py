@@ -1267,3 +1267,64 @@ def test_compact_matrix_where_it_is_read(torch_cuda, F, depth, explicit):
             G.groot_spmm_execute(plan, X, Y, F)
             out.append(Y)
         assert torch_cuda.equal(out[0], out[1]), f"F={F} n={n}"
+
+
+def _dense_rows_graph(n, n_dense, share, rng):
+    """n_dense rows with a share of all columns each, a few of 40 entries, the others short; columns ascending, weights
+    1 / row length"""
+    length = rng.integers(1, 5, n)
+    dense = rng.choice(n, n_dense, replace=False)
+    length[rng.choice(n, 20, replace=False)] = 40
+    length[dense] = int(share * n)
+    cols = [np.sort(rng.choice(n, k, replace=False)) for k in length]
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    return rowptr, np.concatenate(cols).astype(np.int32), np.repeat(np.float32(1) / length.astype(np.float32), length), dense
+
+
+@pytest.mark.parametrize("n,n_dense,want,widths", [(3001, 10, 0, [64]), (20011, 130, 128, [64, 100, 132]), (30016, 33, 33, [140, 260]),
+                                                   (40001, 16, 16, [212, 512]), (50020, 300, 300, [12, 64]),
+                                                   (90049, 200, 192, [8, 12, 32, 36])])
+@pytest.mark.parametrize("ones", [False, True])
+def test_high_degree_rows_as_a_dense_product(torch_cuda, n, n_dense, want, widths, ones):
+    """Rows that hold a quarter of all columns: 16, 32 or 64 at a time, a last tile that is not full, columns that are no
+    multiple of 32 or 128, every kind of feature tile, from 2^25 entries times features on."""
+    rng = np.random.default_rng(n + n_dense)
+    rowptr, col, val, dense = _dense_rows_graph(n, n_dense, 0.25, rng)
+    if ones:
+        val = np.ones_like(val)
+    g = G.groot_graph_from_csr(rowptr, col, val)
+    for F in widths:
+        X = wl.uniform_features_numpy(n + F, 0, n, F)
+        Y, plan, _, _ = _run(torch_cuda, g, 32, X)
+        assert G.groot_plan_query(plan, "dense_rows") == want
+        assert not want or want * (n // 4) * F >= 2 ** 25
+        assert G.groot_plan_query(plan, "weight_mode") == (0 if ones else 1)
+        Y64, S = oracle.spmm_f64(rowptr, col, val, X)
+        assert_close_to_oracle(Y, Y64, S, f"dense rows n={n} {n_dense} F={F}")
+
+
+def test_dense_product_with_numbers_that_are_not_finite(torch_cuda):
+    """An infinity or a NaN in X reaches the rows that have its column and no others."""
+    n, F = 30020, 100
+    rng = np.random.default_rng(5)
+    rowptr, col, val, dense = _dense_rows_graph(n, 64, 0.2, rng)
+    g = G.groot_graph_from_csr(rowptr, col, val)
+    X = wl.uniform_features_numpy(6, 0, n, F)
+    X[17, 3], X[n - 1, 35], X[2000, 8] = np.inf, -np.inf, np.nan
+    X[31, 20], X[32, 20] = 3e38, 3e38                    # finite, their sum is not
+    plan = G.groot_spmm_plan(g, 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == 64
+    Xd = torch_cuda.from_numpy(X).cuda()
+    Y = torch_cuda.empty_like(Xd)
+    G.groot_spmm_execute(plan, Xd, Y, F)
+    Y = Y.cpu().numpy()
+    row = np.repeat(np.arange(n), np.diff(rowptr))
+    for c, f, bad in ((17, 3, lambda y: np.isposinf(y)), (n - 1, 35, lambda y: np.isneginf(y)), (2000, 8, np.isnan)):
+        has = np.zeros(n, bool)
+        has[row[col == c]] = True
+        assert has[dense].any() and not has[dense].all()
+        assert bad(Y[has, f]).all() and np.isfinite(Y[~has, f]).all(), (c, f)
+    keep = np.array([k for k in range(F) if k not in (3, 8, 20, 35)])
+    Y64, S = oracle.spmm_f64(rowptr, col, val, X[:, keep])
+    assert_close_to_oracle(Y[:, keep], Y64, S, "the other features")
