@@ -38,6 +38,31 @@ constexpr int kPipeWaves = 4;                // wavefronts per workgroup, one wo
 // 14.0 / 13.8 / 13.9 ms for 2..8); 8 lanes (F = 32): 6.46 / 6.36 ms for 5 / 7; 32 lanes (F = 128): 31.0 / 30.5 /
 // 31.3 ms per step for 5 / 7 / 8
 constexpr int pipe_groups(int) { return 7; }
+// S = 2: rows of a tile.  As many as the sweeps' 64 lanes hold; pipe_max_rows: at the narrowest width (9, 17, 33 float4) that is
+// served with L lanes' template.
+constexpr int pipe_max_rows(int L) { return pipe_groups(L) * kWave / (L / 2 + 1); }
+
+// Whether rows take F4 lanes (S = 2): the rows of a tile, or 0.  They do where that fills a quarter more of the lanes: with L lanes
+// per row and 9 of 16, 17 of 32 or 34 of 64 in use a sweep did half of what it costs.  2.1 M rows of a carry-save multiplier,
+// us, L / F4 lanes: F = 36 192 / 154, 72 357 / 284, 136 689 / 550, 164 759 / 700; 4-LUT shape, 1.1 M rows: 36 142 / 120, 72
+// 298 / 257, 136 567 / 490.  With less to gain the lines that two sweeps share cost more: F = 60 (15 of 16) 245 / 260, 28 (7 of 8)
+// 120 / 123; F = 100 (25 of 32; 16 of 17.9 rows) 424 / 406, but 79.5 / 81.8 at 0.5 M rows and 369 / 375 on the 4-LUT shape;
+// F = 180 (45 of 64) 815 / 790, 4-LUT 685 / 703.  With 5 slots the kernel has a little more than half of the registers, so what
+// rides along waits for the sweep, and small graphs lose: below 64 MB of X 12.0 / 12.7 (64-bit multiplier x 2, F = 36), 43 / 46.5
+// (polarized, 65,536 rows, F = 72), at 75 MB 47 / 39 (128-bit x 4, F = 36); with 6 to 8 slots it is so either way.
+static int pipe_tile_rows(int L, int32_t F4, int depth, int64_t n_rows)
+{
+    const int lanes = pipe_groups(L) * kWave, by_lanes = pipe_groups(L) * (kWave / L);
+    if (L < 16 || F4 == L || (depth == 5 && n_rows * F4 * 16 < (int64_t)64 << 20)) return 0;
+    int rows = lanes / F4;
+    // whole 128-byte lines per tile where that leaves three quarters of the lanes in use: the sweeps' stores, 1 KB each,
+    // then begin and end with a line
+    int unit = 8;
+    for (int32_t f = F4; unit > 1 && f % 2 == 0; f /= 2) unit /= 2;
+    const int whole = rows / unit * unit;
+    if (whole * F4 * 4 >= lanes * 3) rows = whole;
+    return rows * 4 >= by_lanes * 5 ? rows : 0;
+}
 
 typedef int pipe_i4 __attribute__((ext_vector_type(4)));
 constexpr int kHotAhead = 8;                  // 16-byte loads of the hot list that a lane has in flight
@@ -73,29 +98,31 @@ struct CompactCsr {
 
 // M: the sum of row r goes to row out_ids[r] of Y (the owned rows of a part written into place in the matrix of
 // the whole graph); n is then the number of leading rows that are wanted.  Only without the compact matrix.
-// S: rows of F4 float4, any number up to L (otherwise F4 = L): the lanes past a row's end do what the lane of its last
-// float4 does, and store the same value to the same place.  No trash area here: parts of a line written to one place by all
+// S: rows of F4 float4, any number up to L (0: F4 = L).  1: a row has L lanes, the ones past its end do what the lane of its last
+// float4 does, and store the same value to the same place.  2: a row has F4 lanes, the sweeps deal the tile's float4 out to all
+// of them, 64 after 64, whatever row they belong to (pipe_tile_rows says where).  No trash area here: parts of a line written to one place by all
 // wavefronts wait for one another (lanes past the end, 4-LUT shape, 0.5 M rows, F = 124: 574 us, now 233; masked rows, 4 M
 // rows, one in 27 masked, F = 100: 2,140 us, now 1,095).  With whole lines it costs next to nothing and the plain store is
 // the faster one (8.4 M rows of carry-save multipliers, F = 32: 491 us, through the descriptor 502; F = 64 942 and 951).
 // The workgroups behind the first n_ld of the grid compute the rows of the row list, then (n_hd of them) the pieces of the
 // high-degree rows: see SideWork.
-template <int L, int W, int G, int D, bool C, bool M = false, bool S = false>
+template <int L, int W, int G, int D, bool C, bool M = false, int S = 0>
 __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per_eu(1, 2))) void ld_pipe_kernel(
     const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col, const float *__restrict__ val,
     const CompactCsr cz, const char *__restrict__ X, char *__restrict__ Y, int64_t zero_off, char *trash, int64_t n,
     int32_t T, int64_t n_tiles, int64_t tiles_per_part, int64_t waves_per_part, int32_t parts,
-    const int64_t *__restrict__ out_ids, int32_t F4, const SideWork side)
+    const int64_t *__restrict__ out_ids, int32_t F4, int32_t tile_rows, const SideWork side)
 {
     static_assert(!(C && M) && !(S && M), "the row-mapped form reads the plain arrays and has rows of L float4");
-    constexpr int kRpg = kWave / L;                      // rows per lane group sweep
-    constexpr int kTileRows = G * kRpg;
+    constexpr int kRpg = kWave / L;                      // rows per lane group sweep (S < 2)
+    constexpr int kMaxRows = S == 2 ? pipe_max_rows(L) : G * kRpg;
+    const int kTileRows = S == 2 ? tile_rows : G * kRpg; // rows of a tile, a constant with S < 2
     constexpr int kPipeD = D;                            // slots per row
-    constexpr int kSlots = kTileRows * kPipeD, kH = (kSlots + kWave - 1) / kWave;
+    constexpr int kSlots = kMaxRows * kPipeD, kH = (kSlots + kWave - 1) / kWave;
     constexpr int kRowShift = L == 8 ? 7 : L == 16 ? 8 : L == 32 ? 9 : 10;   // log2 of a feature row's bytes
     static_assert(L == 8 || L == 16 || L == 32 || L == 64, "one float4 per lane");
     auto row_bytes = [&](int64_t row) -> int64_t { return S ? row * (F4 * 16) : row << kRowShift; };
-    static_assert(kTileRows + 1 <= kWave, "row pointers of a tile fit one wavefront");
+    static_assert(kMaxRows + 1 <= kWave, "row pointers of a tile fit one wavefront");
     // a slot: byte offset of the gathered row from X; with explicit weights the entry's weight rides in the
     // same 16-byte slot, so that one LDS read per slot serves both
     struct SlotW { int64_t off; float w; float pad; };
@@ -103,8 +130,8 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     constexpr int kSlotBytes = kPipeWaves * kSlots * (int)sizeof(Slot), kHdBytes = kHdSmemBytes<L>;
     __shared__ __align__(16) char s_buf[kSlotBytes > kHdBytes ? kSlotBytes : kHdBytes];
     Slot (*const s_slot)[kSlots] = (Slot(*)[kSlots])s_buf;
-    __shared__ float s_inv[kPipeWaves][kTileRows];       // row weight (1 unless W == kMean), or -1: the row is masked
-    __shared__ int64_t s_oid[M ? kPipeWaves : 1][M ? kTileRows : 1];   // M: byte offset of the row's place in Y
+    __shared__ float s_inv[kPipeWaves][kMaxRows];       // row weight (1 unless W == kMean), or -1: the row is masked
+    __shared__ int64_t s_oid[M ? kPipeWaves : 1][M ? kMaxRows : 1];   // M: byte offset of the row's place in Y
 
     if (blockIdx.x >= side.n_ld) {
         const int64_t b = blockIdx.x - side.n_ld;
@@ -124,7 +151,14 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
         return;
     }
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = threadIdx.x % kWave;
-    const int g = l / L, f = S ? (l % L < F4 ? l % L : F4 - 1) : l % L;
+    const int g = l / L, f = S == 2 ? 0 : S == 1 ? (l % L < F4 ? l % L : F4 - 1) : l % L;
+    // S = 2.  slot_at: byte offset of the first slot of the lane's row in the slot table; f_at: byte offset of its float4 in the
+    // row.  Both move on with every sweep that is issued (a pair of registers per sweep would cost the second wavefront of a
+    // SIMD, where the pieces of the high-degree rows run).
+    constexpr int kRowSlots = kPipeD * (int)sizeof(Slot);
+    const int slot_0 = S == 2 ? l / F4 * kRowSlots : 0, f_0 = S == 2 ? l % F4 * 16 : 0;
+    const int slot_step = S == 2 ? kWave / F4 * kRowSlots : 0, f_step = S == 2 ? kWave % F4 * 16 : 0;
+    int slot_at = slot_0, f_at = f_0;
     // Part x (an XCD) owns tiles [x TP, (x+1) TP); its wavefronts take them round-robin, so that the
     // part sweeps a narrow window of rows at any time.
     const int64_t part = blockIdx.x % parts, j = (blockIdx.x / parts) * kPipeWaves + w;
@@ -232,17 +266,27 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
     Regs rr[G];
     auto issue = [&](Regs &q, int grp) {
         const int lr = grp * kRpg + g;
-        q.inv = s_inv[w][lr];
+        const int last = (kTileRows - 1) * kRowSlots;    // past the tile's last float4: its last row again, not stored
+        const uint32_t at = (uint32_t)(slot_at < last ? slot_at : last);
+        const Slot *const slots = S == 2 ? (const Slot *)((const char *)s_slot[w] + at) : s_slot[w] + lr * kPipeD;
+        const char *const Xg = S == 2 ? X + f_at : Xf;
+        q.inv = S == 2 ? s_inv[w][at / kRowSlots] : s_inv[w][lr];
         if constexpr (M) q.oid = s_oid[w][lr];
 #pragma unroll
         for (int k = 0; k < kPipeD; ++k) {
             if constexpr (W == kExplicit) {
-                const SlotW sl = s_slot[w][lr * kPipeD + k];
-                q.xs[k] = *(const v4f *)(Xf + sl.off);
+                const SlotW sl = slots[k];
+                q.xs[k] = *(const v4f *)(Xg + sl.off);
                 q.ws[k] = sl.w;
             } else {
-                q.xs[k] = *(const v4f *)(Xf + s_slot[w][lr * kPipeD + k]);
+                q.xs[k] = *(const v4f *)(Xg + slots[k]);
             }
+        }
+        if constexpr (S == 2) {                          // on to the next sweep; after the last one from the start
+            const int f_next = f_at + f_step;
+            const bool over = f_next >= F4 * 16;
+            f_at = grp == G - 1 ? f_0 : over ? f_next - F4 * 16 : f_next;
+            slot_at = grp == G - 1 ? slot_0 : slot_at + slot_step + (over ? kRowSlots : 0);
         }
     };
     auto sum = [&](const Regs &q) -> v4f {
@@ -321,7 +365,8 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
             const int lr = grp * kRpg + g;
             // a masked row (every row of a tile that is not ok) is not stored: a select of the address, no branch
             if constexpr (S) {
-                const uint32_t off = rr[grp].inv >= 0.f ? (uint32_t)row_bytes(lr) + 16 * f : kPipeDropped;
+                const uint32_t at = S == 2 ? 16 * (grp * kWave + l) : (uint32_t)row_bytes(lr) + 16 * f;   // past the tile's end: dropped
+                const uint32_t off = rr[grp].inv >= 0.f ? at : kPipeDropped;
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(pipe_u4, a), ytile, (int)off, 0, kPipeNontemporal);
             } else {
                 char *const yrow = M ? Y + rr[grp].oid + 16 * f : ybase + (int)row_bytes(lr);
@@ -334,12 +379,13 @@ __global__ __launch_bounds__(kPipeWaves * kWave) __attribute__((amdgpu_waves_per
             // plain path: the rows of this tile that the pipeline serves elsewhere, straight from global memory
 #pragma unroll 1
             for (int grp = 0; grp < G; ++grp) {
-                const int64_t row = base + grp * kRpg + g;
-                if (row < n) {
+                const int i = grp * kWave + l, lr = S == 2 ? i / F4 : grp * kRpg + g, fr = S == 2 ? i % F4 : f;
+                const int64_t row = base + lr;
+                if (lr < kTileRows && row < n) {
                     const int64_t s = rowptr[row], e = rowptr[row + 1];
                     if (e - s < T && e - s <= kPipeD)
-                        __builtin_nontemporal_store(ld_row_sum<W, false>(s, e, col, val, (const v4f *)X, S ? F4 : L, f),
-                                                    (v4f *)(Y + row_bytes(M ? out_ids[row] : row) + 16 * f));
+                        __builtin_nontemporal_store(ld_row_sum<W, false>(s, e, col, val, (const v4f *)X, S ? F4 : L, fr),
+                                                    (v4f *)(Y + row_bytes(M ? out_ids[row] : row) + 16 * fr));
                 }
             }
         }
@@ -382,6 +428,7 @@ struct PipeArgs {
     hipStream_t st;
     const int64_t *out_ids;                  // row-mapped form, else NULL
     int32_t F4;                              // float4 per row
+    int32_t tile_rows;                       // S = 2: rows of a tile; else 0
     SideWork side;
     int64_t n_hd;                            // pieces of high-degree rows in this launch
 };
@@ -393,32 +440,32 @@ static void pipe_launch(const PipeArgs &a)
     if (a.out_ids) {
         ld_pipe_kernel<L, W, G, D, false, true><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, a.out_ids, a.F4, a.side);
+            a.waves_per_part, a.parts, a.out_ids, a.F4, a.tile_rows, a.side);
     } else if (a.compact) {
         const size_t lds = (size_t)hot_ints(a.cz.n_hot) * sizeof(int32_t);
         ld_pipe_kernel<L, W, G, D, true><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
+            a.waves_per_part, a.parts, nullptr, a.F4, a.tile_rows, a.side);
     } else {
         ld_pipe_kernel<L, W, G, D, false><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
+            a.waves_per_part, a.parts, nullptr, a.F4, a.tile_rows, a.side);
     }
 }
 
-template <int L, int W, int G, int D>
+template <int L, int W, int G, int D, int S>
 static void pipe_launch_any(const PipeArgs &a)
 {
     const dim3 grid((unsigned)(a.n_wg + a.side.n_row_wg + a.n_hd));
     if (a.compact) {
         const size_t lds = (size_t)hot_ints(a.cz.n_hot) * sizeof(int32_t);
-        ld_pipe_kernel<L, W, G, D, true, false, true><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
+        ld_pipe_kernel<L, W, G, D, true, false, S><<<grid, dim3(kPipeWaves * kWave), lds, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
+            a.waves_per_part, a.parts, nullptr, a.F4, a.tile_rows, a.side);
     } else {
-        ld_pipe_kernel<L, W, G, D, false, false, true><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
+        ld_pipe_kernel<L, W, G, D, false, false, S><<<grid, dim3(kPipeWaves * kWave), 0, a.st>>>(
             a.rowptr, a.col, a.val, a.cz, a.X, a.Y, a.zero_off, a.trash, a.n, a.T, a.n_tiles, a.tiles_per_part,
-            a.waves_per_part, a.parts, nullptr, a.F4, a.side);
+            a.waves_per_part, a.parts, nullptr, a.F4, a.tile_rows, a.side);
     }
 }
 
@@ -441,10 +488,10 @@ static void pipe_dispatch_l(int32_t F4, const PipeArgs &a)
     if (F4 == 8) pipe_launch<8, W, pipe_groups(8), D>(a);
     else if (F4 == 16) pipe_launch<16, W, pipe_groups(16), D>(a);
     else if (F4 == 32) pipe_launch<32, W, pipe_groups(32), D>(a);
-    else if (F4 < 8) pipe_launch_any<8, W, pipe_groups(8), D>(a);
-    else if (F4 < 16) pipe_launch_any<16, W, pipe_groups(16), D>(a);
-    else if (F4 < 32) pipe_launch_any<32, W, pipe_groups(32), D>(a);
-    else pipe_launch_any<64, W, pipe_groups(64), D>(a);
+    else if (F4 < 8) pipe_launch_any<8, W, pipe_groups(8), D, 1>(a);
+    else if (F4 < 16) a.tile_rows ? pipe_launch_any<16, W, pipe_groups(16), D, 2>(a) : pipe_launch_any<16, W, pipe_groups(16), D, 1>(a);
+    else if (F4 < 32) a.tile_rows ? pipe_launch_any<32, W, pipe_groups(32), D, 2>(a) : pipe_launch_any<32, W, pipe_groups(32), D, 1>(a);
+    else a.tile_rows ? pipe_launch_any<64, W, pipe_groups(64), D, 2>(a) : pipe_launch_any<64, W, pipe_groups(64), D, 1>(a);
 }
 
 template <int W>
@@ -461,7 +508,7 @@ static void pipe_dispatch_d(int depth, int32_t F4, const PipeArgs &a)
 // The compact form keeps the hot list in dynamic LDS, up to 128 KB: the runtime wants to be told once per
 // kernel that more than its default limit may be asked for.  Called when a plan gets its compact CSR (not at
 // launch, which may be under stream capture).
-template <int L, int W, int D, bool S>
+template <int L, int W, int D, int S>
 static int pipe_allow_lds()
 {
     return (int)hipFuncSetAttribute((const void *)&ld_pipe_kernel<L, W, pipe_groups(L), D, true, false, S>,
@@ -470,13 +517,16 @@ static int pipe_allow_lds()
 template <int W, int D>
 static int pipe_allow_lds_l()
 {
-    int err = pipe_allow_lds<8, W, D, false>();
-    if (!err) err = pipe_allow_lds<16, W, D, false>();
-    if (!err) err = pipe_allow_lds<32, W, D, false>();
-    if (!err) err = pipe_allow_lds<8, W, D, true>();
-    if (!err) err = pipe_allow_lds<16, W, D, true>();
-    if (!err) err = pipe_allow_lds<32, W, D, true>();
-    if (!err) err = pipe_allow_lds<64, W, D, true>();
+    int err = pipe_allow_lds<8, W, D, 0>();
+    if (!err) err = pipe_allow_lds<16, W, D, 0>();
+    if (!err) err = pipe_allow_lds<32, W, D, 0>();
+    if (!err) err = pipe_allow_lds<8, W, D, 1>();
+    if (!err) err = pipe_allow_lds<16, W, D, 1>();
+    if (!err) err = pipe_allow_lds<32, W, D, 1>();
+    if (!err) err = pipe_allow_lds<64, W, D, 1>();
+    if (!err) err = pipe_allow_lds<16, W, D, 2>();
+    if (!err) err = pipe_allow_lds<32, W, D, 2>();
+    if (!err) err = pipe_allow_lds<64, W, D, 2>();
     return err;
 }
 template <int W>
@@ -554,7 +604,7 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     if (e != hipSuccess) return (int)e;
     int L = 8;                                           // lanes per row
     while (L < F4) L *= 2;
-    const int tile_rows = pipe_groups(L) * (kWave / L);
+    const int packed_rows = pipe_tile_rows(L, F4, dp.pipe_depth, n_rows), tile_rows = packed_rows ? packed_rows : pipe_groups(L) * (kWave / L);
     const int64_t n_tiles = (n_rows + tile_rows - 1) / tile_rows;
     // one workgroup per CU; consecutive workgroup ids land on different XCDs
     int64_t n_wg = cus / kXcds * kXcds;
@@ -585,7 +635,7 @@ int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t 
     if (!grid_ok(n_wg + n_row_wg + n_hd)) return (int)hipErrorInvalidConfiguration;
     const PipeArgs a{dp.rowptr, col_arg, val_arg, CompactCsr{dp.rp32, dp.col16, dp.hot_cols, dp.n_hot}, compact,
                      (const char *)X, (char *)Y, byte_distance(X, dp.zero_row), trash, n_rows,
-                     dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, n_wg, st, out_ids, F4,
+                     dp.threshold, n_tiles, tiles_per_part, waves_per_part, parts, n_wg, st, out_ids, F4, packed_rows,
                      SideWork{n_wg, dp.mid_rows, n_mid, n_row_wg, dp.chunks, dp.partials}, n_hd};
     GROOT_DISPATCH_W(dp.weight_mode, (pipe_dispatch_d<kW>(dp.pipe_depth, F4, a)));
     e = hipGetLastError();

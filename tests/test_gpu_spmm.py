@@ -1328,3 +1328,43 @@ def test_dense_product_with_numbers_that_are_not_finite(torch_cuda):
     keep = np.array([k for k in range(F) if k not in (3, 8, 20, 35)])
     Y64, S = oracle.spmm_f64(rowptr, col, val, X[:, keep])
     assert_close_to_oracle(Y[:, keep], Y64, S, "the other features")
+
+
+@pytest.mark.parametrize("F,depth,explicit", [(36, 5, False), (40, 5, True), (48, 5, False), (72, 5, True), (92, 5, False), (132, 5, False),
+                                              (164, 5, True), (176, 5, False), (36, 6, True), (44, 7, False), (72, 8, False),
+                                              (96, 6, False), (136, 7, True), (188, 8, False)])
+def test_rows_that_share_their_lanes(torch_cuda, F, depth, explicit):
+    """Widths at which a sweep deals a tile's float4 out to all lanes (half to three quarters of L lanes per row otherwise): a
+    ragged last tile, empty rows, masked rows first and last in a tile, on either side of 64 MB of X.  Against the plain
+    kernel, which adds a row's entries in the same order."""
+    rng = np.random.default_rng(F + depth)
+    line = (64 << 20) // (4 * F)
+    for n in ((line - 1, line + 38) if depth == 5 else (1, 47, 9001)):
+        length = rng.integers(max(0, depth - 5), depth + 1, n)
+        length[rng.choice(n, n // 30, replace=False)] = depth + 3
+        length[rng.choice(n, n // 300, replace=False)] = 40
+        length = np.minimum(length, n)
+        row = np.repeat(np.arange(n), length)
+        col = (row + rng.integers(-300, 301, row.size)) % n
+        row, col = np.divmod(np.unique(row * n + col), n)
+        length = np.bincount(row, minlength=n)
+        rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+        val = rng.uniform(-1, 1, col.size).astype(np.float32) if explicit else np.repeat(
+            np.float32(1) / np.maximum(length, 1).astype(np.float32), length)
+        g = G.groot_graph_from_csr(rowptr, col.astype(np.int32), val)
+        X = torch_cuda.empty((n, F), device="cuda").uniform_(-1, 1)
+        out = []
+        for pipeline in (1, 0):
+            G.groot_set_tuning("ld_pipeline", pipeline)
+            G.groot_set_tuning("pipe_depth", depth)
+            try:
+                plan = G.groot_spmm_plan(g, 32)
+                G.groot_plan_upload(plan, F)
+            finally:
+                G.groot_set_tuning("ld_pipeline", -1)
+                G.groot_set_tuning("pipe_depth", 0)
+            buf = torch_cuda.full((n + 6, F), float("nan"), device="cuda")
+            G.groot_spmm_execute(plan, X, buf[3:n + 3], F)
+            assert torch_cuda.isnan(buf[:3]).all() and torch_cuda.isnan(buf[n + 3:]).all(), "wrote outside Y"
+            out.append(buf[3:n + 3])
+        assert torch_cuda.equal(out[0], out[1]), f"F={F} depth={depth} n={n}"
