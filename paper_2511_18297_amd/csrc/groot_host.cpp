@@ -1298,8 +1298,8 @@ extern "C" groot_status groot_partition_regrow_device(const groot_plan *plan, in
     if (!part) return fail(GROOT_ENOMEM, "groot_partition_regrow_device: out of host memory");
     part->weight_mode = (WeightMode)plan->dev.graph_weight_mode;
     const int64_t n1 = plan->g ? plan->g->n1 : n;
-    int err = launch_regrow_device(plan->dev, n1, num_parts, part_of_dev, p, (flags & GROOT_REGROW) ? 1 : 0, hip_stream,
-                                   &part->d);
+    int err = launch_regrow_device(plan->dev, n1, num_parts, part_of_dev, p, (flags & GROOT_REGROW) ? 1 : 0,
+                                   plan->g && plan->g->symmetric, hip_stream, &part->d);
     if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, "groot_partition_regrow_device: device allocation failed");
     if (err == kErrBadPartId) return fail(GROOT_EINVAL, "groot_partition_regrow_device: a part_of entry lies outside [0,P)");
     if (err) return fail(GROOT_EHIP, std::string("groot_partition_regrow_device: ") + hip_error_text(err));

@@ -197,9 +197,10 @@ struct DevicePart {
     float *val = nullptr;           // [nnz] or NULL
 };
 constexpr int kErrBadPartId = -2;   // a caller-supplied part id outside [0, P)
-// Synchronises the stream.  part_of_dev may be NULL (built-in rule with n1 nodes per copy).
+// Synchronises the stream.  part_of_dev may be NULL (built-in rule with n1 nodes per copy).  symmetric: every edge of the
+// graph is known to be stored in both directions (the result is the same either way).
 int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int32_t *part_of_dev, int32_t p,
-                         int regrow, void *stream, DevicePart *out);
+                         int regrow, bool symmetric, void *stream, DevicePart *out);
 void free_device_part(DevicePart &part);
 // Small synchronous device reads and copies (sizes and lists of a plan built from device arrays).
 int device_time_ms(void *stream, int reps, int (*fn)(void *ctx), void *ctx, float *ms);

@@ -3,7 +3,7 @@
 // keeps on the device.  All integer work; the result is bit-identical to the host's groot_partition_regrow.
 //
 // For part p with node set S_p:
-//   rg_mark      every owned row flags the columns that live in another part: B_p (Eq. (1))
+//   rg_mark      (or rg_mark_slices) every owned row flags the columns that live in another part: B_p (Eq. (1))
 //   rg_count / rg_scan_counts / rg_scatter
 //                stable compaction of the owned ids and of the flagged ids, both ascending: the local
 //                numbering S_p first, B_p after (global_id), and its inverse (local_of)
@@ -53,6 +53,7 @@ struct RgGraph {
     const int32_t *part_of;    // NULL: the built-in rule
     int32_t p;
     uint32_t lo, hi;           // built-in rule: part p owns the nodes with lo <= (v mod n1) < hi
+    bool symmetric;            // every edge is known to be stored in both directions
 };
 
 // Is node v in part p?  The caller's array, or the p-th contiguous slice of every copy:
@@ -91,6 +92,23 @@ __global__ __launch_bounds__(kBlock) void rg_mark(RgGraph g, int32_t *__restrict
     for (int64_t q = b; q < e; ++q) {
         const int32_t u = g.col[q];
         if (!rg_owned(g, u)) local_of[u] = kRgHalo;
+    }
+}
+
+// The same with the built-in rule: the part's rows of a copy (blockIdx.y) are consecutive, and so are their entries; which row
+// an entry belongs to does not matter.  By rows the part that owns the primary inputs of a multiplier took 367 us (a lane walked
+// 513 entries one after the other), and 346 with a wavefront per such row, 64 of which stand side by side; the others 13.
+__global__ __launch_bounds__(kBlock) void rg_mark_slices(RgGraph g, int32_t *__restrict__ local_of)
+{
+    const int64_t first = (int64_t)blockIdx.y * g.n1;
+    const int64_t b = g.rowptr[first + g.lo], e = g.rowptr[first + g.hi], step = (int64_t)gridDim.x * kBlock;
+    for (int64_t q = b + (int64_t)blockIdx.x * kBlock + threadIdx.x; q < e; q += 4 * step) {
+        int32_t u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = g.col[q + k * step < e ? q + k * step : q];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (!rg_owned(g, u[k])) local_of[u[k]] = kRgHalo;
     }
 }
 
@@ -214,13 +232,12 @@ __device__ __forceinline__ bool rg_row_has(const RgGraph &g, int64_t v, int32_t 
     return false;
 }
 
-// Does entry (column c) of local row k (global v) belong to the sub-graph?  cross: it also is one crossing
+// Does entry (column c, lc = local_of[c]) of local row k (global v) belong to the sub-graph?  cross: it also is one crossing
 // pair that no other entry counts.
-__device__ __forceinline__ bool rg_keep(const RgGraph &g, const int32_t *__restrict__ local_of, int64_t n_owned,
-                                        bool row_owned, int64_t v, int32_t c, bool &cross)
+__device__ __forceinline__ bool rg_keep(const RgGraph &g, int32_t lc, int64_t n_owned, bool row_owned, int64_t v, int32_t c,
+                                        bool &cross)
 {
     cross = false;
-    const int32_t lc = local_of[c];
     if (row_owned) {
         if (lc < 0) return false;
         cross = lc >= n_owned;
@@ -229,7 +246,7 @@ __device__ __forceinline__ bool rg_keep(const RgGraph &g, const int32_t *__restr
     if (c == v) return true;                                     // stored self-loop of a boundary node
     if (lc < 0 || lc >= n_owned) return false;                   // boundary-boundary edge: not in E_p+
     // an edge stored only in this direction is a crossing pair that its owned end did not count
-    cross = !rg_row_has(g, c, (int32_t)v);
+    cross = !g.symmetric && !rg_row_has(g, c, (int32_t)v);
     return true;
 }
 
@@ -261,10 +278,18 @@ __global__ __launch_bounds__(kBlock) void rg_row_len(RgGraph g, const int32_t *_
             long_list[atomicAdd(n_long, 1)] = (int32_t)k;
         } else {
             int32_t count = 0;
-            for (int64_t q = b; q < e; ++q) {
-                bool x;
-                if (rg_keep(g, local_of, n_owned, k < n_owned, v, g.col[q], x)) ++count;
-                if (x) ++cross;
+            for (int64_t q = b; q < e; q += 8) {         // eight columns, then their places, in flight at a time
+                int32_t c[8], lc[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) c[i] = g.col[q + i < e ? q + i : e - 1];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) lc[i] = local_of[c[i]];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    bool x = false;
+                    if (q + i < e && rg_keep(g, lc[i], n_owned, k < n_owned, v, c[i], x)) ++count;
+                    if (x) ++cross;
+                }
             }
             len[k] = count;
         }
@@ -300,7 +325,7 @@ __global__ __launch_bounds__(kBlock) void rg_row_len_long(RgGraph g, const int32
 #pragma unroll
             for (int u = 0; u < kRgUnroll; ++u) {
                 bool keep = false, x = false;
-                if (c[u] >= 0) keep = rg_keep(g, local_of, n_owned, row_owned, v, c[u], x);
+                if (c[u] >= 0) keep = rg_keep(g, local_of[c[u]], n_owned, row_owned, v, c[u], x);
                 count += __popcll(__ballot(keep));
                 cross += x ? 1 : 0;
             }
@@ -408,6 +433,36 @@ __global__ __launch_bounds__(kBlock) void rg_fill(RgGraph g, const int32_t *__re
     if (e - b > kRgShort) return;
     int64_t w = sub_rowptr[k];
     const int64_t w_end = sub_rowptr[k + 1];
+    if (e - b <= 8 && e > b) {                                   // nearly all rows: everything loaded before anything is placed
+        int32_t c[8], lc[8];
+        float val[8];
+        uint32_t kept = 0, owned = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t q = b + i < e ? b + i : e - 1;
+            c[i] = g.col[q];
+            if (sub_val) val[i] = g.val[q];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) lc[i] = local_of[c[i]];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bool keep = b + i < e && (k < n_owned ? lc[i] >= 0 : c[i] == v || (lc[i] >= 0 && lc[i] < n_owned));
+            kept |= (uint32_t)keep << i;
+            owned |= (uint32_t)(keep && lc[i] < n_owned) << i;
+        }
+        const int n_own = __popc(owned);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t before = (1u << i) - 1, bit = 1u << i;
+            const int64_t at = w + ((owned & bit) ? __popc(owned & before) : n_own + __popc(kept & ~owned & before));
+            if ((kept & bit) && at < w_end) {                    // always true when the lengths match this walk
+                sub_col[at] = lc[i];
+                if (sub_val) sub_val[at] = val[i];
+            }
+        }
+        return;
+    }
     for (int pass = 0; pass < 2; ++pass)
         for (int64_t q = b; q < e; ++q) {
             const int32_t c = g.col[q];
@@ -502,7 +557,7 @@ void free_device_part(DevicePart &part)
 
 // Returns 0, a hipError_t, kErrOutOfDeviceMemory, or kErrBadPartId (a part id outside [0, P)).
 int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int32_t *part_of_dev, int32_t p,
-                         int regrow, void *stream, DevicePart *out)
+                         int regrow, bool symmetric, void *stream, DevicePart *out)
 {
     hipStream_t st = (hipStream_t)stream;
     const int64_t n = dp.n;
@@ -510,7 +565,7 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
     if (n < 1 || n > 0x7fffffffLL || n1 < 1 || n1 > n || P < 1 || p < 0 || p >= P) return (int)hipErrorInvalidValue;
     // slice of the built-in rule: ceil(p n1 / P) .. ceil((p + 1) n1 / P), exact in 64 bits (n1, P < 2^31)
     const uint32_t lo = (uint32_t)(((int64_t)p * n1 + P - 1) / P), hi = (uint32_t)(((int64_t)(p + 1) * n1 + P - 1) / P);
-    RgGraph g{dp.rowptr, dp.col, dp.graph_weight_mode == kExplicit ? dp.val : nullptr, n, n1, part_of_dev, p, lo, hi};
+    RgGraph g{dp.rowptr, dp.col, dp.graph_weight_mode == kExplicit ? dp.val : nullptr, n, n1, part_of_dev, p, lo, hi, symmetric};
     const int64_t n_blocks = (n + kRgRowsPerBlock - 1) / kRgRowsPerBlock;
 
     Scratch scratch;
@@ -533,7 +588,14 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
     unsigned long long *cross_slots = (unsigned long long *)(total + 4);
     rg_fill_i32<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, st>>>(local_of, n, kRgNone);
     if (part_of_dev) rg_check_parts<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, st>>>(part_of_dev, n, P, flag);
-    if (regrow) rg_mark<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, st>>>(g, local_of);
+    const int64_t copies = n / n1;
+    if (regrow && !part_of_dev && n % n1 == 0 && copies <= 65535) {
+        int64_t per_copy = dp.nnz / copies / P / (4 * kBlock) + 1;        // workgroups that walk a copy's entries once, about
+        if (per_copy > 2048) per_copy = 2048;
+        rg_mark_slices<<<dim3((unsigned)per_copy, (unsigned)copies), dim3(kBlock), 0, st>>>(g, local_of);
+    } else if (regrow) {
+        rg_mark<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, st>>>(g, local_of);
+    }
     rg_count<<<dim3((unsigned)n_blocks), dim3(kBlock), 0, st>>>(g, local_of, cnt);
     rg_scan_counts<<<dim3(2), dim3(kBlock), 0, st>>>(cnt, n_blocks, 2, total);
     if ((e = hipGetLastError()) != hipSuccess) return done((int)e);

@@ -103,6 +103,26 @@ def test_user_parts_weight_modes_and_directed_graph(torch_cuda):
     assert want["n_halo"] == 0 and np.array_equal(want["rowptr"], s.rowptr)
 
 
+@pytest.mark.parametrize("P", [1, 2, 7])
+@pytest.mark.parametrize("rule", [True, False])
+def test_rows_of_every_length_of_a_directed_graph(torch_cuda, P, rule):
+    """Rows of 0 to 20 entries (8, 9, 16 and 17 are where the kernels change hands) and a few of hundreds side by side, edges
+    stored in one direction, weights carried along, parts by the built-in rule and at random."""
+    rng = np.random.default_rng(P)
+    n = 4096 + 333
+    length = rng.integers(0, 21, n)
+    length[1000:1070] = 500
+    cols = [np.sort(rng.choice(n, k, replace=False)) for k in length]
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    col = np.concatenate(cols).astype(np.int32)
+    w = rng.random(col.size).astype(np.float32)
+    plan = _resident_plan(G.groot_graph_from_csr(rowptr, col, w))
+    part_of = oracle.part_of_default(n, n, P) if rule else rng.integers(0, P, n).astype(np.int32)
+    for flags in (G.GROOT_REGROW, 0):
+        for p in range(P):
+            _check_part(torch_cuda, plan, rowptr, col, w, part_of, P, p, flags, 2, rule, "row lengths")
+
+
 @pytest.mark.parametrize("n,batch,P,T,F", [(32, 2, 4, 32, 64), (48, 1, 5, 8, 32), (24, 3, 2, 200, 20)])
 def test_device_built_plans_fill_the_full_result(torch_cuda, n, batch, P, T, F):
     """Partitioned mode with nothing built on the host: every part re-grown on the device, its plan made from
