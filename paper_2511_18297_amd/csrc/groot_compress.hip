@@ -14,23 +14,18 @@
 
 namespace groot {
 
-// rp32[i] = low 32 bits of rowptr[i]; the caller has checked that the last row pointer fits
-__global__ __launch_bounds__(kBlock) void rp32_kernel(const int64_t *__restrict__ rowptr, int64_t count,
-                                                      uint32_t *__restrict__ out)
-{
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (int64_t)gridDim.x * kBlock)
-        out[i] = (uint32_t)rowptr[i];
-}
-
-// One thread per row.  An entry that fits neither range gets kCodeBad and its row is appended to bad_rows (in no
-// particular order): the pipelined kernel masks such a row, which is then computed by list.
+// One thread per row, which copies the low half of its row pointer, too.  An entry that fits neither range gets kCodeBad and
+// its row is appended to bad_rows (in no particular order): the pipelined kernel masks such a row, which is then computed by list.
 __global__ __launch_bounds__(kBlock) void col16_kernel(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                                        int64_t n, int32_t T, int32_t depth, const int32_t *__restrict__ hot,
-                                                       int32_t n_hot, uint16_t *__restrict__ out, int32_t *__restrict__ bad_rows,
-                                                       int32_t bad_cap, int32_t *__restrict__ n_bad)
+                                                       int32_t n_hot, uint32_t *__restrict__ rp32, uint16_t *__restrict__ out,
+                                                       int32_t *__restrict__ bad_rows, int32_t bad_cap,
+                                                       int32_t *__restrict__ n_bad)
 {
     for (int64_t row = (int64_t)blockIdx.x * kBlock + threadIdx.x; row < n; row += (int64_t)gridDim.x * kBlock) {
         const int64_t s = rowptr[row], e = rowptr[row + 1];
+        rp32[row] = (uint32_t)s;
+        if (row == n - 1) rp32[n] = (uint32_t)e;
         if (e - s > depth || e - s >= T) continue;                  // never read in compact form
         bool bad = false;
         for (int64_t p = s; p < e; ++p) {
@@ -56,70 +51,99 @@ __global__ __launch_bounds__(kBlock) void col16_kernel(const int64_t *__restrict
     }
 }
 
-// Builds dp.rp32 / dp.col16 / dp.hot_cols from the resident CSR and the (device) list of high-degree rows,
-// ascending, and appends the rows it cannot encode to dp.mid_rows.  Synchronises the stream.  On return
-// dp.compressed says whether the compact form is usable; when it is not (too many entries for 32-bit row
-// pointers, more than one low-degree row in 50 not encodable, no memory) its arrays are released and 0 is
-// returned all the same: the plain arrays serve.
-int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, void *stream)
+// hot_cols (padding included) from the list of high-degree rows, and the count of rows without a code
+__global__ __launch_bounds__(kBlock) void hot_kernel(const int32_t *__restrict__ hd_rows, int32_t n_hot, int32_t *__restrict__ hot,
+                                                     int32_t *__restrict__ n_bad)
+{
+    const int32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < hot_ints(n_hot)) hot[i] = i < n_hot ? hd_rows[i] : 0;
+    if (i == 0) *n_bad = 0;
+}
+
+int32_t csr_bad_capacity(int64_t n) { return (int32_t)(n / 50 + 1024); }
+
+// Enqueues the building of dp.rp32 / dp.col16 / dp.hot_cols from the resident CSR and the (device) list of high-degree rows,
+// ascending.  The rows without a code go to bad_rows (room for csr_bad_capacity), their number to n_bad_dev; once that has been
+// read, csr_compress_end decides.  *begun: whether there is anything to decide (not for matrices without entries or with too many
+// for 32-bit row pointers, and not without memory: no error, the plain arrays serve).
+int csr_compress_begin(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, int32_t *bad_rows, int32_t *n_bad_dev, void *stream,
+                       bool *begun)
 {
     hipStream_t st = (hipStream_t)stream;
     dp.compressed = 0;
+    *begun = false;
     if (dp.n <= 0 || dp.nnz <= 0 || dp.nnz >= ((int64_t)1 << 32)) return 0;
-    const int32_t n_hot = (int32_t)(n_hd < kCodeMaxHot ? n_hd : kCodeMaxHot);
-    const int32_t bad_cap = (int32_t)(dp.n / 50 + 1024);
-    int32_t *n_bad = nullptr, *bad_rows = nullptr, *merged = nullptr;
-    auto give_up = [&](int err) {
-        dev_free(dp.rp32); dev_free(dp.col16); dev_free(dp.hot_cols); dev_free(n_bad);
-        dev_free(bad_rows); dev_free(merged);
-        dp.rp32 = nullptr; dp.col16 = nullptr; dp.hot_cols = nullptr; dp.n_hot = 0;
-        return err;
-    };
+    dp.n_hot = (int32_t)(n_hd < kCodeMaxHot ? n_hd : kCodeMaxHot);
     if (dev_alloc((void **)&dp.rp32, (size_t)(dp.n + 1) * 4) != 0 ||
         dev_alloc((void **)&dp.col16, (size_t)dp.nnz * 2) != 0 ||
-        dev_alloc((void **)&dp.hot_cols, (size_t)hot_ints(n_hot) * 4) != 0 ||
-        dev_alloc((void **)&bad_rows, (size_t)bad_cap * 4) != 0 ||
-        dev_alloc((void **)&n_bad, 4) != 0) {
+        dev_alloc((void **)&dp.hot_cols, (size_t)hot_ints(dp.n_hot) * 4) != 0) {
         (void)hipGetLastError();
-        return give_up(0);                                           // out of device memory: not an error, the plain arrays serve
+        csr_compress_drop(dp);
+        return 0;
     }
-    hipError_t e = hipMemsetAsync(n_bad, 0, 4, st);
-    if (e == hipSuccess) e = hipMemsetAsync(dp.hot_cols, 0, (size_t)hot_ints(n_hot) * 4, st);
-    if (e == hipSuccess && n_hot)
-        e = hipMemcpyAsync(dp.hot_cols, hd_rows_dev, (size_t)n_hot * 4, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return give_up((int)e);
-    const unsigned grid = 16384;
-    rp32_kernel<<<dim3(grid), dim3(kBlock), 0, st>>>(dp.rowptr, dp.n + 1, dp.rp32);
-    col16_kernel<<<dim3(grid), dim3(kBlock), 0, st>>>(dp.rowptr, dp.col, dp.n, dp.threshold, dp.pipe_depth, dp.hot_cols, n_hot, dp.col16,
-                                                      bad_rows, bad_cap, n_bad);
-    e = hipGetLastError();
-    int32_t h_bad = bad_cap + 1;
-    if (e == hipSuccess) e = hipMemcpyAsync(&h_bad, n_bad, 4, hipMemcpyDeviceToHost, st);
-    hipError_t e2 = hipStreamSynchronize(st);
-    if (e != hipSuccess || e2 != hipSuccess) return give_up((int)(e != hipSuccess ? e : e2));
-    if (h_bad > bad_cap || (int64_t)h_bad * 50 > dp.n) return give_up(0);
-    if (h_bad > 0) {
-        // the rows that could not be encoded join the list of rows that are computed one by one
-        if (dev_alloc((void **)&merged, (size_t)(dp.n_mid_rows + h_bad) * 4) != 0) {
-            (void)hipGetLastError();
-            return give_up(0);
-        }
-        e = hipSuccess;
-        if (dp.n_mid_rows) e = hipMemcpyAsync(merged, dp.mid_rows, (size_t)dp.n_mid_rows * 4, hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(merged + dp.n_mid_rows, bad_rows, (size_t)h_bad * 4, hipMemcpyDeviceToDevice, st);
-        e2 = hipStreamSynchronize(st);
-        if (e != hipSuccess || e2 != hipSuccess) return give_up((int)(e != hipSuccess ? e : e2));
-        dev_free(dp.mid_rows);
-        dp.mid_rows = merged;
-        merged = nullptr;
-        dp.n_mid_rows += h_bad;
+    hot_kernel<<<dim3((unsigned)((hot_ints(dp.n_hot) + kBlock - 1) / kBlock)), dim3(kBlock), 0, st>>>(hd_rows_dev, dp.n_hot, dp.hot_cols,
+                                                                                                   n_bad_dev);
+    const int64_t grid = (dp.n + kBlock - 1) / kBlock;
+    col16_kernel<<<dim3((unsigned)(grid < 16384 ? grid : 16384)), dim3(kBlock), 0, st>>>(
+        dp.rowptr, dp.col, dp.n, dp.threshold, dp.pipe_depth, dp.hot_cols, dp.n_hot, dp.rp32, dp.col16, bad_rows,
+        csr_bad_capacity(dp.n), n_bad_dev);
+    const int err = (int)hipGetLastError();
+    if (err) csr_compress_drop(dp);
+    *begun = !err;
+    return err;
+}
+
+// h_bad: rows without a code.  False, and the compact form is gone, when they are more than one row in 50; else they are part
+// of dp.mid_rows already or become it now (the caller's business) and count here.
+bool csr_compress_end(DevicePlan &dp, int32_t h_bad)
+{
+    if (h_bad < 0 || h_bad > csr_bad_capacity(dp.n) || (int64_t)h_bad * 50 > dp.n) {
+        csr_compress_drop(dp);
+        return false;
     }
-    dev_free(n_bad);
-    dev_free(bad_rows);
-    dp.n_hot = n_hot;
+    dp.n_mid_rows += h_bad;
     dp.n_bad_rows = h_bad;
     dp.compressed = 1;
-    return 0;
+    return true;
+}
+
+void csr_compress_drop(DevicePlan &dp)
+{
+    dev_free(dp.rp32); dev_free(dp.col16); dev_free(dp.hot_cols);
+    dp.rp32 = nullptr; dp.col16 = nullptr; dp.hot_cols = nullptr; dp.n_hot = 0;
+}
+
+// Builds the compact form and appends the rows it cannot encode to dp.mid_rows.  Synchronises the stream.  On return
+// dp.compressed says whether it is usable; when it is not its arrays are released and 0 is returned all the same.
+int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    int32_t *n_bad = nullptr, *rows = nullptr;
+    bool begun = false;
+    dp.compressed = 0;
+    if (dp.n <= 0) return 0;
+    if (dev_alloc((void **)&rows, ((size_t)dp.n_mid_rows + csr_bad_capacity(dp.n)) * 4) != 0 || dev_alloc((void **)&n_bad, 4) != 0) {
+        (void)hipGetLastError();
+        dev_free(rows);
+        return 0;                                                    // no memory: the plain arrays serve
+    }
+    hipError_t e = dp.n_mid_rows ? hipMemcpyAsync(rows, dp.mid_rows, (size_t)dp.n_mid_rows * 4, hipMemcpyDeviceToDevice, st) : hipSuccess;
+    int err = e != hipSuccess ? (int)e : csr_compress_begin(dp, hd_rows_dev, n_hd, rows + dp.n_mid_rows, n_bad, stream, &begun);
+    int32_t h_bad = -1;
+    if (!err && begun) {
+        err = device_download(&h_bad, n_bad, 4, stream);             // waits for the stream
+        if (err) csr_compress_drop(dp);
+    } else {
+        (void)hipStreamSynchronize(st);
+    }
+    if (!err && begun && csr_compress_end(dp, h_bad) && h_bad > 0) {
+        dev_free(dp.mid_rows);
+        dp.mid_rows = rows;
+        rows = nullptr;
+    }
+    dev_free(rows);
+    dev_free(n_bad);
+    return err;
 }
 
 }  // namespace groot

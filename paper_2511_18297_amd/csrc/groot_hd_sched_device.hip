@@ -15,9 +15,6 @@ namespace groot {
 
 namespace {
 
-struct HsTotals {
-    unsigned long long n_chunks, n_slots, n_split, nnz_hd;
-};
 
 __device__ __forceinline__ int64_t hs_pieces(int64_t d, int64_t chunk)
 {
@@ -27,11 +24,11 @@ __device__ __forceinline__ int64_t hs_pieces(int64_t d, int64_t chunk)
 
 // per high-degree row k: number of pieces, of partial-sum slots (0 for a single piece), 1 if it is split
 __global__ __launch_bounds__(kBlock) void hs_count(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ hd_rows,
-                                                   int64_t n_hd, int64_t chunk, int64_t *__restrict__ pieces,
+                                                   const int64_t *__restrict__ n_hd, int64_t chunk, int64_t *__restrict__ pieces,
                                                    int64_t *__restrict__ slots, int64_t *__restrict__ split)
 {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= n_hd) return;
+    if (k >= *n_hd) return;
     const int64_t r = hd_rows[k], d = rowptr[r + 1] - rowptr[r];
     const int64_t p = hs_pieces(d < 0 ? 0 : d, chunk);
     pieces[k] = p;
@@ -42,9 +39,11 @@ __global__ __launch_bounds__(kBlock) void hs_count(const int64_t *__restrict__ r
 // Exclusive prefix sums of the three arrays in place (one workgroup walks them in runs of its size), the totals and
 // the number of entries of all high-degree rows.
 __global__ __launch_bounds__(1024) void hs_scan(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ hd_rows,
-                                                int64_t n_hd, int64_t *__restrict__ pieces, int64_t *__restrict__ slots,
-                                                int64_t *__restrict__ split, HsTotals *__restrict__ totals)
+                                                const int64_t *__restrict__ n_hd_dev, int64_t *__restrict__ pieces,
+                                                int64_t *__restrict__ slots, int64_t *__restrict__ split,
+                                                HdTotals *__restrict__ totals)
 {
+    const int64_t n_hd = *n_hd_dev;
     __shared__ int64_t s_part[3][16];                    // per wavefront
     __shared__ int64_t s_carry[4];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
@@ -177,29 +176,47 @@ void free_device_hd_schedule(DeviceHdSchedule &s)
     s = DeviceHdSchedule{};
 }
 
-// hd_rows_dev: the n_hd high-degree rows, ascending.  Waits for the stream once (sizes are read back between the
-// passes); the schedule itself is complete when the stream has reached the end of what is enqueued here.  kErrOutOfDeviceMemory when an allocation fails, kErrTooManyPieces when the slots do not fit 31 bits.
+void free_hd_counts(HdCounts &c)
+{
+    dev_free(c.pieces); dev_free(c.slots); dev_free(c.split);
+    c = HdCounts{};
+}
+
+// Enqueues the counting of pieces, slots and split rows.  n_hd_dev: number of high-degree rows, on the device, at most `most`;
+// totals_dev receives the sizes.  The counts belong to the caller.
+int launch_hd_schedule_count(const int64_t *rowptr_dev, const int32_t *hd_rows_dev, const int64_t *n_hd_dev, int64_t most,
+                             int32_t hd_chunk, void *stream, HdTotals *totals_dev, HdCounts *out)
+{
+    hipStream_t st = (hipStream_t)stream;
+    HdCounts c;
+    const size_t bytes = (size_t)(most > 0 ? most : 1) * sizeof(int64_t);
+    if (dev_alloc((void **)&c.pieces, bytes) || dev_alloc((void **)&c.slots, bytes) || dev_alloc((void **)&c.split, bytes)) {
+        free_hd_counts(c);
+        return kErrOutOfDeviceMemory;
+    }
+    if (most > 0)
+        hs_count<<<dim3((unsigned)((most + kBlock - 1) / kBlock)), dim3(kBlock), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd_dev,
+                                                                                       hd_chunk < 64 ? 64 : hd_chunk, c.pieces, c.slots,
+                                                                                       c.split);
+    hs_scan<<<dim3(1), dim3(1024), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd_dev, c.pieces, c.slots, c.split, totals_dev);
+    *out = c;
+    return (int)hipGetLastError();
+}
+
+// hd_rows_dev: the n_hd high-degree rows, ascending; counts and h from launch_hd_schedule_count, h read back since.  The schedule is
+// complete when the stream has reached the end of what is enqueued here.  kErrOutOfDeviceMemory when an allocation
+// fails, kErrTooManyPieces when the slots do not fit 31 bits.
 int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev, const int32_t *hd_rows_dev, int64_t n_hd,
-                              int32_t hd_chunk, void *stream, DeviceHdSchedule *out)
+                              int32_t hd_chunk, const HdCounts &counts, const HdTotals &h, void *stream, DeviceHdSchedule *out)
 {
     *out = DeviceHdSchedule{};
     if (n_hd <= 0) return 0;
     hipStream_t st = (hipStream_t)stream;
     const int64_t chunk = hd_chunk < 64 ? 64 : hd_chunk;
     Tmp tmp;
-    int64_t *pieces = nullptr, *slots = nullptr, *split = nullptr;
-    HsTotals *totals = nullptr;
-    if (!tmp.get(&pieces, (size_t)n_hd) || !tmp.get(&slots, (size_t)n_hd) || !tmp.get(&split, (size_t)n_hd) ||
-        !tmp.get(&totals, 1))
-        return kErrOutOfDeviceMemory;
+    int64_t *const pieces = counts.pieces, *const slots = counts.slots, *const split = counts.split;
     const unsigned grid_rows = (unsigned)((n_hd + kBlock - 1) / kBlock);
-    hs_count<<<dim3(grid_rows), dim3(kBlock), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd, chunk, pieces, slots, split);
-    hs_scan<<<dim3(1), dim3(1024), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd, pieces, slots, split, totals);
-    hipError_t e = hipGetLastError();
-    HsTotals h = {};
-    if (e == hipSuccess) e = hipMemcpyAsync(&h, totals, sizeof h, hipMemcpyDeviceToHost, st);
-    hipError_t e2 = hipStreamSynchronize(st);
-    if (e != hipSuccess || e2 != hipSuccess) return (int)(e != hipSuccess ? e : e2);
+    hipError_t e = hipSuccess;
     if (h.n_slots > 0x3fffffffULL || h.n_chunks > 0x7fffffffULL) return kErrTooManyPieces;
     const int64_t n_chunks = (int64_t)h.n_chunks, n_split = (int64_t)h.n_split;
 

@@ -1376,16 +1376,27 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
     try {
         std::unique_ptr<groot_plan> pl(new groot_plan);
         // lists on the device; only the high-degree rows and the degree offsets are needed here
-        DevBuf row_class, hd_rows, ld_rows, by_degree, sizes;   // sizes: the two counts, then the T + 1 degree offsets
+        // sizes: the two counts, the T + 1 degree offsets, the totals of the HD schedule, the rows that the compact matrix cannot code
+        DevBuf row_class, hd_rows, ld_rows, by_degree, sizes;
+        constexpr int32_t kTotals = (int32_t)(sizeof(HdTotals) / 8);
+        struct Counts {
+            HdCounts c;
+            ~Counts() { free_hd_counts(c); }
+        } counts;
         if (row_class.alloc((size_t)n) || hd_rows.alloc((size_t)n * 4) || ld_rows.alloc((size_t)n * 4) ||
-            by_degree.alloc((size_t)n * 4) || sizes.alloc((size_t)(T + 3) * 8))
+            by_degree.alloc((size_t)n * 4) || sizes.alloc((size_t)(T + 3 + kTotals + 1) * 8))
             return fail(GROOT_ENOMEM, std::string(who) + "device allocation of the plan lists failed");
         int err = launch_plan_device(part->d.rowptr, n, T, row_class.as<uint8_t>(), hd_rows.as<int32_t>(),
                                      ld_rows.as<int32_t>(), by_degree.as<int32_t>(), sizes.as<int64_t>() + 2,
                                      sizes.as<int64_t>(), hip_stream, false);
         if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, std::string(who) + "scratch allocation failed");
         if (err) return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
-        std::vector<int64_t> h_sizes(T + 3, 0);
+        HdTotals *const totals_dev = (HdTotals *)(sizes.as<int64_t>() + T + 3);
+        err = launch_hd_schedule_count(part->d.rowptr, hd_rows.as<int32_t>(), sizes.as<int64_t>(), std::min(n, part->d.nnz / T),
+                                       tuning().hd_chunk, hip_stream, totals_dev, &counts.c);
+        if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, std::string(who) + "device allocation of the HD schedule failed");
+        if (err) return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
+        std::vector<int64_t> h_sizes(T + 3 + kTotals, 0);
         if ((err = device_download(h_sizes.data(), sizes.p, h_sizes.size() * 8, hip_stream)))
             return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
         const int64_t n_hd = h_sizes[0], n_ld = h_sizes[1];
@@ -1393,7 +1404,9 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         if (n_hd < 0 || n_ld < 0 || n_hd + n_ld != n) return fail(GROOT_EHIP, std::string(who) + "inconsistent row counts from the device");
         // the schedule of the high-degree rows, cut and ordered on the device too: only four sizes come back
         DeviceHdSchedule sched;
-        err = launch_hd_schedule_device(part->d.rowptr, part->d.col, hd_rows.as<int32_t>(), n_hd, tuning().hd_chunk,
+        HdTotals totals;
+        std::memcpy(&totals, h_sizes.data() + T + 3, sizeof totals);
+        err = launch_hd_schedule_device(part->d.rowptr, part->d.col, hd_rows.as<int32_t>(), n_hd, tuning().hd_chunk, counts.c, totals,
                                         hip_stream, &sched);
         if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, std::string(who) + "device allocation of the HD schedule failed");
         if (err == kErrTooManyPieces) return fail(GROOT_ERANGE, std::string(who) + "too many high-degree pieces");
@@ -1419,6 +1432,7 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             release_device(pl.get());
             return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
         }
+        bool compress = false;
         d.n_hd_rows = n_hd;
         d.n = d.n_cols = n;
         d.nnz = part->d.nnz;
@@ -1438,8 +1452,12 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             d.sage_depth = choose_layer_depth(n_ld, at_most);
             const int64_t first_mid = at_most(ch.depth);
             d.n_mid_rows = ch.pipelined ? n_ld - first_mid : 0;
-            if (d.n_mid_rows) {             // the tail of the degree-sorted list, which is on the device already
-                if ((st = to_device<int32_t>(&d.mid_rows, nullptr, (size_t)d.n_mid_rows, "long low-degree rows")) != GROOT_OK ||
+            // the tail of the degree-sorted list, which is on the device already, with room for the rows that the compact matrix
+            // will not code
+            compress = d.ld_pipelined && tuning().csr_compress;
+            const size_t room = (size_t)d.n_mid_rows + (compress ? csr_bad_capacity(n) : 0);
+            if (room) {
+                if ((st = to_device<int32_t>(&d.mid_rows, nullptr, room, "long low-degree rows")) != GROOT_OK ||
                     (err = device_copy(d.mid_rows, by_degree.as<int32_t>() + first_mid, (size_t)d.n_mid_rows * 4, hip_stream))) {
                     std::string keep = err ? std::string(who) + hip_error_text(err) : std::string(groot_last_error());
                     release_device(pl.get());
@@ -1456,18 +1474,19 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         part->d.col = nullptr;
         part->d.val = nullptr;
         part->csr_moved = true;
-        if (d.ld_pipelined && tuning().csr_compress) {
-            err = launch_csr_compress(d, hd_rows.as<int32_t>(), n_hd, hip_stream);
-            if (!err && d.compressed) err = pipe_compact_prepare();
-            if (err) {
-                release_device(pl.get());               // the sub-graph's arrays are the plan's by now
-                return fail(GROOT_EHIP, std::string(who) + "compact CSR: " + hip_error_text(err));
-            }
-        }
-        if ((err = device_wait(hip_stream))) {           // the plan may be used on any stream from here on
-            release_device(pl.get());
+        bool begun = false;
+        int32_t *const n_bad_dev = (int32_t *)(sizes.as<int64_t>() + T + 3 + kTotals);
+        int32_t h_bad = -1;
+        if (compress) err = csr_compress_begin(d, hd_rows.as<int32_t>(), n_hd, d.mid_rows + d.n_mid_rows, n_bad_dev, hip_stream, &begun);
+        if (!err && begun) err = pipe_compact_prepare();
+        // either way waits for the stream: the plan may be used on any from here on
+        if (!err) err = begun ? device_download(&h_bad, n_bad_dev, sizeof h_bad, hip_stream) : device_wait(hip_stream);
+        if (err) {
+            (void)device_wait(hip_stream);
+            release_device(pl.get());                   // the sub-graph's arrays are the plan's by now
             return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
         }
+        if (begun) csr_compress_end(d, h_bad);
         pl->g = nullptr;
         pl->threshold = T;
         pl->max_F = max_F;

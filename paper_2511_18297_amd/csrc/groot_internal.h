@@ -154,11 +154,27 @@ struct DeviceHdSchedule {
     int64_t n_chunks = 0, n_split_rows = 0, n_partials = 0, nnz_hd = 0;
 };
 constexpr int kErrTooManyPieces = -3;
+struct HdTotals {
+    unsigned long long n_chunks, n_slots, n_split, nnz_hd;
+};
+struct HdCounts {                            // per high-degree row, on the device
+    int64_t *pieces = nullptr, *slots = nullptr, *split = nullptr;
+};
+void free_hd_counts(HdCounts &c);
+int launch_hd_schedule_count(const int64_t *rowptr_dev, const int32_t *hd_rows_dev, const int64_t *n_hd_dev, int64_t most,
+                             int32_t hd_chunk, void *stream, HdTotals *totals_dev, HdCounts *out);
 int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev, const int32_t *hd_rows_dev, int64_t n_hd,
-                              int32_t hd_chunk, void *stream, DeviceHdSchedule *out);   // complete in stream order
+                              int32_t hd_chunk, const HdCounts &counts, const HdTotals &h, void *stream,
+                              DeviceHdSchedule *out);   // complete in stream order
 void free_device_hd_schedule(DeviceHdSchedule &s);
 // Compact CSR for the pipelined LD kernel, built on the device (groot_compress.hip); synchronises the stream.
 int launch_csr_compress(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, void *stream);
+// The same in two steps without a wait of its own.
+int32_t csr_bad_capacity(int64_t n);
+int csr_compress_begin(DevicePlan &dp, const int32_t *hd_rows_dev, int64_t n_hd, int32_t *bad_rows, int32_t *n_bad_dev, void *stream,
+                       bool *begun);
+bool csr_compress_end(DevicePlan &dp, int32_t h_bad);
+void csr_compress_drop(DevicePlan &dp);
 int pipe_compact_prepare();   // once per process, before the first launch with a compact CSR; hipError_t as int
 // High-degree rows as a dense product (groot_hd_dense.hip): whole-graph calls, row-uniform weights.
 constexpr int kDenseMaxWorkgroups = 256;
