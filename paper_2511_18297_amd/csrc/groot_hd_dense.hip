@@ -283,7 +283,7 @@ size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F)
 // 2.1 G (17 M entries, 262,144 rows): F = 8 108 / 80, F = 32 132 / 88, F = 64 223 / 143, F = 128 414 / 260.
 bool hd_dense_serves(const DevicePlan &dp, int32_t F)
 {
-    return dp.n_dense_rows > 0 && F >= kDenseMinF && dp.dense_entries * F >= (int64_t)1 << 25;
+    return dp.n_dense_rows > 0 && dp.n_cols == dp.n && F >= kDenseMinF && dp.dense_entries * F >= (int64_t)1 << 25;
 }
 
 size_t dense_mask_words(const DevicePlan &dp)

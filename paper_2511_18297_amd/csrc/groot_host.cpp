@@ -1089,8 +1089,9 @@ extern "C" groot_status groot_plan_use_global_columns(groot_plan *plan, const in
     if (plan->dev.n_cols != plan->dev.n) return fail(GROOT_EINVAL, "groot_plan_use_global_columns: the columns were renamed before");
     if (n_global < plan->dev.n) return fail(GROOT_EINVAL, "groot_plan_use_global_columns: n_global is smaller than the plan's own row count");
     if (n_global > std::numeric_limits<int32_t>::max()) return fail(GROOT_ERANGE, "groot_plan_use_global_columns: n_global does not fit int32 columns");
-    // the compact column codes name local rows: the plan goes back to the plain arrays
+    // the compact column codes and the dense rows' bits name local rows: the plan goes back to the plain arrays
     plan->dev.compressed = 0;
+    plan->dev.n_dense_rows = 0;
     int err = launch_col_map(plan->dev.col, plan->dev.nnz, global_id_dev, hip_stream);
     if (err) return fail(GROOT_EHIP, std::string("groot_plan_use_global_columns: launch failed: ") + hip_error_text(err));
     plan->dev.n_cols = n_global;

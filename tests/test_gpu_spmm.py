@@ -1368,3 +1368,27 @@ def test_rows_that_share_their_lanes(torch_cuda, F, depth, explicit):
             assert torch_cuda.isnan(buf[:3]).all() and torch_cuda.isnan(buf[n + 3:]).all(), "wrote outside Y"
             out.append(buf[3:n + 3])
         assert torch_cuda.equal(out[0], out[1]), f"F={F} depth={depth} n={n}"
+
+
+def test_dense_rows_of_a_plan_whose_columns_are_renamed(torch_cuda):
+    """Once a plan's columns name rows of a larger matrix, its dense rows are gathered like the others: the bits name the
+    plan's own rows."""
+    n, n_global, F = 20011, 23000, 64
+    rng = np.random.default_rng(8)
+    rowptr, col, val, dense = _dense_rows_graph(n, 128, 0.25, rng)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == 128
+    ids = np.sort(rng.choice(n_global, n, replace=False)).astype(np.int64)
+    ids_dev = torch_cuda.from_numpy(ids).cuda()
+    G.groot_plan_use_global_columns(plan, ids_dev, n_global)
+    assert G.groot_plan_query(plan, "dense_rows") == 0
+    X = wl.uniform_features_numpy(9, 0, n_global, F)
+    Xd = torch_cuda.from_numpy(X).cuda()
+    Y64, S = oracle.spmm_f64(rowptr, col, val, X[ids])
+    Y = torch_cuda.full((n, F), float("nan"), device="cuda")
+    G.groot_spmm_execute(plan, Xd, Y, F)
+    assert_close_to_oracle(Y.cpu().numpy(), Y64, S, "renamed columns")
+    Y = torch_cuda.full((n, F), float("nan"), device="cuda")
+    G.groot_spmm_execute_rows(plan, Xd, Y, F, n)
+    assert_close_to_oracle(Y.cpu().numpy(), Y64, S, "renamed columns, rows")
