@@ -194,7 +194,8 @@ static bool ld_pipelined(const DevicePlan &dp, int32_t F4, const RowOut *out)
 // 374 pieces (polarized degrees) F = 32 15.4 / 19.7, F = 64 13.8 / 18.5; 512 (256-bit multiplier) F = 32 42.2 / 42.7, F = 64
 // 54.3 / 60.2, F = 100 89.5 / 88.5; 512 (4-LUT shape) F = 32 17.6 / 22.2; 771 (Booth) F = 32 50.0 / 48.0, F = 64 61.6 / 69.0;
 // F = 136 183 / 209; 949 (polarized) F = 32 30.3 / 26.1, F = 64 32.2 / 34.0, F = 128 45.0 / 48.4, F = 100 61.1 / 46.9, F = 200
-// 63.7 / 60.2; 1,024 (shape mapped to cells) F = 136 78 / 94; 2,905 (polarized) F = 64 62.2 / 51.5, F = 128 94.8 / 68.1.
+// 63.7 / 60.2; 1,024 (shape mapped to cells) F = 136 78 / 94; 2,905 (polarized) F = 64 62.2 / 51.5, F = 128 94.8 / 68.1.  (With pieces
+// whose indices were not staged; they are up to a quarter faster since, in either place.)
 bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out)
 {
     const int64_t few = F == 64 || F >= 128 ? 1024 : 512;
@@ -234,8 +235,8 @@ int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
     // 70 times: 65,536 rows F = 128 90 -> 64 us, 262,144 rows F = 128 571 -> 550, F = 256 1,517 -> 1,030; multipliers, whose rows
     // are gathered once or twice, the same; runs of 16: 566 and 1,335, of 1,024: 582 and 1,073; cutting rows into slices by XCD:
     // 594 and 1,181).  At F = 32 it costs 2 %.  At the line: 2,048 pieces of a 512-bit multiplier 245 us either way, 2,067 of a
-// polarized graph 61 with runs and 78 without (F = 128).  Polarized graphs gain below it too (949 pieces 43.5 and 48.7, 374
-// 25.6 and 30.9), but up to 1,024 pieces ride in the low-degree rows' launch there.
+    // polarized graph 61 with runs and 78 without (F = 128).  Polarized graphs gain below it too (949 pieces 43.5 and 48.7, 374
+    // 25.6 and 30.9), but up to 1,024 pieces ride in the low-degree rows' launch there.
     const int32_t run = F4 >= 16 && dp.n_chunks >= 2048 ? 64 : 1;
     const int64_t grid = run > 1 ? (dp.n_chunks + kXcds * run - 1) / (kXcds * run) * (kXcds * run) : dp.n_chunks;
     if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
