@@ -11,23 +11,34 @@
 // a row is cheaper here from about 7 % of the columns on (choose_dense_rows).  One workgroup per CU multiplies, which keeps its
 // matrix cores busy; the other high-degree rows' pieces, in the same launch, take the memory system beside it (220 us together at
 // F = 128, 156 of them matrix instructions; as two launches 155 + 96; with two workgroups per CU, which leave the pieces no
-// room, 252).
+// room, 252; these times in one chain per wavefront, see dense_args).
 //
-// 0 x infinity is not 0: where X holds a number that is not finite, rows without that column would get NaN.  A row whose
-// sums do not all come out finite is therefore summed again from its entries by the finishing kernel.
+// 0 x infinity is not 0: where X holds a number that is not finite, rows without that column would get NaN.  So a run of columns
+// whose sums do not all come out finite is swept again (DensePass).  Polarized graph, 262,144 rows, F = 128, whole step, gathers / here:
+// one NaN in X 453 / 364 us, nothing but NaN 453 / 499 (a row gathered again by one workgroup of the finishing kernel: 893);
+// F = 512 2,805 / 1,570 and 2,817 / 2,344; 65,536 rows, F = 64: 46 / 43 and 46 / 44.
+#include <algorithm>
+
 #include "groot_device.h"
 
 namespace groot {
 
 constexpr int kDenseUnit = 32;               // columns per step of the loop: eight instructions a row block and feature block
 constexpr int kDenseTile = 64;               // features of a workgroup
+constexpr int kDenseRun = 16;                // units that a wavefront sums in one chain, at most
+// LDS: what the wavefronts exchange (at most eight of a tile's 4 x MB instruction results at a time), the tile's sums, the weights
+template <int MB> constexpr int kDensePartBytes = kWavesPerBlock * (MB > 1 ? 8 : 4) * kWave * 16;
+template <int MB> constexpr int kDenseOwnBytes = MB * 4 * kWave * 16;
+template <int MB> constexpr int kDenseSmemBytes = kDensePartBytes<MB> + kDenseOwnBytes<MB> + 16 * MB * 4;
 
 struct DenseArgs {
     const HdChunk *rows;                     // [n_rows] the whole row as one piece, slot -1
     const uint32_t *mask;                    // [unit / 4][padded row][k < 4]: bit 8 (unit % 4) + j is the unit's column 4 j + k
-    float *partials;                         // [k_parts][padded rows][F]
+    float *partials;                         // [k_part and group][padded rows][F]
     int32_t n_rows, tile_rows, padded;       // padded: n_rows in whole tiles
     int32_t row_tiles, f_tiles, k_parts;
+    int32_t runs, group;                     // a wavefront's stretch in runs, one chain each; runs that meet in one partial sum
+    int32_t n_partials;                      // of a row: k_parts x groups
     int64_t n_units;                         // columns in units of kDenseUnit
     int64_t n_wg;                            // row_tiles x f_tiles x k_parts
 };
@@ -39,32 +50,79 @@ __device__ __forceinline__ int64_t dense_first_column(int64_t u, int64_t n_units
     return u == n_units - 1 ? n_cols - kDenseUnit : u * kDenseUnit;
 }
 
-// One wavefront's part of a tile of 16 MB rows x 16 NV features: columns of the units [u0, u1).
+// What the second and the third sweep over a run of columns multiply, where the first, of X as it is, did not come out finite.
+// Codes: in the place of what is not finite in X a number that counts its kind in a field of its own; their sums become the
+// infinity or NaN that the accumulators start the last sweep with, over what is finite.
+enum DensePass { kDenseCodes, kDenseFinite };
+constexpr float kDenseInf = 1.f, kDenseNegInf = 1024.f, kDenseNaN = 1048576.f;
+static_assert(kDenseRun * kDenseUnit < 1024, "the count of a run fits its field");
+
+// no branches here: 32 values of a lane each
+__device__ __forceinline__ float dense_operand(float x, int pass)
+{
+    const bool finite = isfinite(x);
+    float code = x > 0.f ? kDenseInf : kDenseNegInf;
+    code = x != x ? kDenseNaN : code;
+    const float where_finite = pass == kDenseFinite ? x : 0.f, elsewhere = pass == kDenseFinite ? 0.f : code;
+    return finite ? where_finite : elsewhere;
+}
+
+__device__ __forceinline__ float dense_decode(float sum)
+{
+    const uint32_t n = (uint32_t)sum, pos = n % 1024, neg = n / 1024;
+    float inf = pos ? __builtin_inff() : -__builtin_inff();
+    inf = (sum >= kDenseNaN) | ((pos != 0) & (neg != 0)) ? __builtin_nanf("") : inf;
+    return n ? inf : 0.f;
+}
+
+// One workgroup's tile of 16 MB rows x 16 NV features: the columns of a k_part, a quarter for each wavefront.
 // Lane layout of the instruction: A row and B column are lane % 16, k is lane / 16; D rows are 4 (lane / 16) + r.  Component
 // v of the lane's NV features is the operand whose column m is feature NV m + v, so a lane's load of consecutive features
 // serves NV instructions as it is.  fp32 matrix and vector instructions of a SIMD do not overlap and changing between them costs
-// cycles, so the loop has next to no address arithmetic (a scalar base and constant offsets) and expands the bits of MB
+// cycles, so the loop has next to no address arithmetic (scalar bases and constant offsets) and expands the bits of MB
 // instructions' rows, then issues their MB NV instructions: with
 // addresses per lane and the bits expanded as the compiler placed them the polarized graph took 195 us, now 155.
-template <int MB, int NV>
-__device__ __forceinline__ void dense_sum(v4f (&acc)[MB][NV], const DenseArgs &d, const char *__restrict__ X, int32_t feature,
-                                          int64_t row_bytes, int64_t n_cols, int32_t row0, int64_t u0, int64_t u1)
+//
+// A wavefront sums a run of kDenseRun units at most, then the four of them meet in LDS, every one adds up a quarter of the tile,
+// (0 + 2) + (1 + 3), and the row's weight times that goes to the quarter's sums, in LDS too (registers for them would cost the third
+// workgroup of a CU, where the pieces of the other rows run: 286 us instead of 273).  So chains of additions stay short, and no sum
+// of more columns than a piece has entries is formed without the weight.
+template <int MB, int NV, int W>
+__device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const char *__restrict__ X, int32_t F, int64_t n_cols,
+                                           int32_t row_tile, int32_t f0, int32_t k_part)
 {
     typedef float vN __attribute__((ext_vector_type(NV)));
-    const int lane = threadIdx.x % kWave, m = lane % 16, k4 = lane / 16;
-    uint32_t x_at[8], bits_at[MB];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x_at[j] = (uint32_t)((4 * j + k4) * (int)row_bytes + 4 * feature);
-#pragma unroll
-    for (int b = 0; b < MB; ++b) bits_at[b] = (uint32_t)((row0 + 16 * b + m) * 16 + k4 * 4);
+    constexpr int kHalves = MB * NV > 8 ? 2 : 1, kNh = NV / kHalves;              // components exchanged at a time: kNh of a row block
+    constexpr int kOwn = MB * kNh > kWavesPerBlock ? MB * kNh / kWavesPerBlock : 1;   // of these a wavefront adds up
+    typedef float vOwn __attribute__((ext_vector_type(kHalves * kOwn)));
+    v4f *const s_part = (v4f *)smem;                                              // [wavefront][block and component][lane]
+    v4f *const s_own = (v4f *)(smem + kDensePartBytes<MB>);                       // [wavefront][half][own][lane]
+    float *const s_weight = (float *)(smem + kDensePartBytes<MB> + kDenseOwnBytes<MB>);   // [row]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, m = lane % 16, k4 = lane / 16;
+    const int32_t row0 = row_tile * d.tile_rows;
+    const int f = f0 + NV * m;
+    if (threadIdx.x < 16 * MB) {
+        const int32_t r = row0 + (int32_t)threadIdx.x;
+        s_weight[threadIdx.x] = r < d.n_rows ? row_weight<W>(d.rows[r].row_nnz) : 0.f;
+    }
+    const int64_t first = d.n_units * k_part / d.k_parts, behind = d.n_units * (k_part + 1) / d.k_parts;
+    const int64_t share = (behind - first + kWavesPerBlock - 1) / kWavesPerBlock;
+    const int64_t u0 = first + wave * share, u1 = u0 + share < behind ? u0 + share : behind;
+    const int64_t run = (share + d.runs - 1) / d.runs;
+
+    const int64_t row_bytes = (int64_t)F * 4;
+    const uint32_t x_at = (uint32_t)(k4 * (int)row_bytes + 4 * (f < F - NV ? f : F - NV));
+    const uint32_t bits_at = (uint32_t)((row0 + m) * 16 + k4 * 4);
     auto load = [&](int64_t u, vN (&x)[8], uint32_t (&w)[MB]) {
+        u = u < d.n_units ? u : d.n_units - 1;
         const char *const base = X + dense_first_column(u, d.n_units, n_cols) * row_bytes;
         const uint8_t *const bits = (const uint8_t *)d.mask + (u / 4) * d.padded * 16 + u % 4;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = *(const vN *)(base + x_at[j]);
+        for (int j = 0; j < 8; ++j) x[j] = *(const vN *)((base + 4 * j * row_bytes) + x_at);
 #pragma unroll
-        for (int b = 0; b < MB; ++b) w[b] = bits[bits_at[b]];
+        for (int b = 0; b < MB; ++b) w[b] = (bits + bits_at)[256 * b];
     };
+    v4f acc[MB][NV];
     auto multiply = [&](const vN (&x)[8], const uint32_t (&w)[MB]) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -79,66 +137,105 @@ __device__ __forceinline__ void dense_sum(v4f (&acc)[MB][NV], const DenseArgs &d
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    vN xa[8], xb[8];
-    uint32_t wa[MB], wb[MB];
-    load(u0, xa, wa);
-#pragma unroll 1
-    for (int64_t u = u0; u < u1; u += 2) {               // one unit is multiplied while the next is on its way
-        load(u + 1 < u1 ? u + 1 : u, xb, wb);
-        __builtin_amdgcn_sched_barrier(0);               // the compiler would sink the loads to their use
-        multiply(xa, wa);
-        load(u + 2 < u1 ? u + 2 : u, xa, wa);
-        __builtin_amdgcn_sched_barrier(0);
-        if (u + 1 < u1) multiply(xb, wb);
-    }
-}
-
-// The four wavefronts of a workgroup share a tile and split its columns; their sums meet in LDS, (0 + 2) + (1 + 3).
-template <int MB, int NV>
-__device__ __forceinline__ void dense_tile(v4f *s_sum, const DenseArgs &d, const char *__restrict__ X, int32_t F, int64_t n_cols,
-                                           int32_t row_tile, int32_t f0, int32_t k_part)
-{
-    typedef float vN __attribute__((ext_vector_type(NV)));
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, m = lane % 16;
-    const int f = f0 + NV * m;
-    v4f acc[MB][NV];
-#pragma unroll
-    for (int b = 0; b < MB; ++b)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[b][v] = v4f{0.f, 0.f, 0.f, 0.f};
-    const int64_t parts = (int64_t)d.k_parts * kWavesPerBlock, part = (int64_t)k_part * kWavesPerBlock + wave;
-    const int64_t u0 = d.n_units * part / parts, u1 = d.n_units * (part + 1) / parts;
-    if (u0 < u1)
-        dense_sum<MB, NV>(acc, d, X, f < F - NV ? f : F - NV, (int64_t)F * 4, n_cols, row_tile * d.tile_rows, u0, u1);
-#pragma unroll
-    for (int half = 2; half > 0; half /= 2) {
-        v4f *const to = s_sum + (wave - half) * MB * NV * kWave, *const from = s_sum + wave * MB * NV * kWave;
-        if (half < 2) __syncthreads();
-        if (wave >= half && wave < 2 * half) {
-#pragma unroll
-            for (int b = 0; b < MB; ++b)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) to[(b * NV + v) * kWave + lane] = acc[b][v];
-        }
-        __syncthreads();
-        if (wave < half) {
-#pragma unroll
-            for (int b = 0; b < MB; ++b)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) acc[b][v] += from[(b * NV + v) * kWave + lane];
-        }
-    }
-    if (wave == 0 && f < F) {
+    auto clear = [&]() {
 #pragma unroll
         for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                vN out;
+            for (int v = 0; v < NV; ++v) acc[b][v] = v4f{0.f, 0.f, 0.f, 0.f};
+    };
+    auto all_finite = [&]() {
+        float zero = 0.f;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) out[v] = acc[b][v][r];
-                const int64_t row = (int64_t)k_part * d.padded + row_tile * d.tile_rows + 16 * b + 4 * (lane / 16) + r;
-                *(vN *)(d.partials + row * F + f) = out;
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) zero = __builtin_fmaf(acc[b][v][r], 0.f, zero);
+        return __ballot(zero != 0.f) == 0;               // otherwise NaN
+    };
+    vN xa[8], xb[8];
+    uint32_t wa[MB], wb[MB];
+    load(u0, xa, wa);
+    bool finite = true;                                  // of the run before: if not, this one is not tried as it is
+#pragma unroll 1
+    for (int32_t i = 0, slot = k_part * (d.n_partials / d.k_parts); i < d.runs; ++i) {
+        const int64_t begin = u0 + i * run, to = begin + run < u1 ? begin + run : u1;
+        clear();
+        if (finite) {
+#pragma unroll 1
+            for (int64_t u = begin; u < to; u += 2) {    // one unit is multiplied while the next is on its way
+                load(u + 1 < to ? u + 1 : u, xb, wb);
+                __builtin_amdgcn_sched_barrier(0);       // the compiler would sink the loads to their use
+                multiply(xa, wa);
+                load(u + 2 < to ? u + 2 : to, xa, wa);   // in the end the next run's first
+                __builtin_amdgcn_sched_barrier(0);
+                if (u + 1 < to) multiply(xb, wb);
             }
+            finite = all_finite();
+            if (!finite) clear();
+        }
+        if (!finite) {
+#pragma unroll 1
+            for (int pass = kDenseCodes; pass <= kDenseFinite; ++pass) {
+#pragma unroll 1
+                for (int64_t u = begin; u < to; ++u) {
+                    uint32_t any = 0;
+                    load(u, xa, wa);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            const float x = dense_operand(xa[j][v], pass);
+                            any |= __builtin_bit_cast(uint32_t, x);   // (of a vector's component it would be the first one's)
+                            xa[j][v] = x;
+                        }
+                    if (__ballot(any)) multiply(xa, wa);   // usually nothing to code
+                }
+                if (pass == kDenseCodes) {
+#pragma unroll
+                    for (int b = 0; b < MB; ++b)
+#pragma unroll
+                        for (int v = 0; v < NV; ++v)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) acc[b][v][r] = dense_decode(acc[b][v][r]);
+                    finite = all_finite();
+                }
+            }
+            load(to, xa, wa);
+        }
+        const int b_own = wave % MB, v_own = wave / MB * kOwn;
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {
+            __syncthreads();                             // what was there has been read
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int v = 0; v < kNh; ++v) s_part[((wave * MB + b) * kNh + v) * kWave + lane] = acc[b][h * kNh + v];
+            __syncthreads();
+            if (v_own < kNh) {
+                const v4f weight = *(const v4f *)(s_weight + 16 * b_own + 4 * k4);
+#pragma unroll
+                for (int v = 0; v < kOwn; ++v) {
+                    const v4f *const p = s_part + (b_own * kNh + v_own + v) * kWave + lane;
+                    constexpr int kNext = MB * kNh * kWave;
+                    v4f *const own = s_own + ((wave * kHalves + h) * kOwn + v) * kWave + lane;
+                    const v4f sum = weight * ((p[0] + p[2 * kNext]) + (p[kNext] + p[3 * kNext]));
+                    *own = i % d.group ? *own + sum : sum;
+                }
+            }
+        }
+        if ((i + 1) % d.group && i + 1 < d.runs) continue;
+        if (v_own < kNh && f < F) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                vOwn out;
+#pragma unroll
+                for (int v = 0; v < kHalves * kOwn; ++v) out[v] = ((const float *)(s_own + (wave * kHalves * kOwn + v) * kWave + lane))[r];
+                const int64_t row = (int64_t)slot * d.padded + row0 + 16 * b_own + 4 * k4 + r;
+                *(vOwn *)(d.partials + row * F + f + v_own) = out;
+            }
+        }
+        ++slot;
     }
 }
 
@@ -150,7 +247,7 @@ __global__ __launch_bounds__(kBlock, 3) void hd_dense_kernel(const DenseArgs d, 
                                                           int64_t zero_off, v4f *__restrict__ Y, v4f *__restrict__ partials,
                                                           int32_t F4, int64_t n_cols)
 {
-    constexpr int kSums = 2 * MB * 4 * kWave * 16, kPiece = kHdSmemBytes<L>;
+    constexpr int kSums = kDenseSmemBytes<MB>, kPiece = kHdSmemBytes<L>;
     __shared__ __align__(16) char smem[kSums > kPiece ? kSums : kPiece];
     if (blockIdx.x >= d.n_wg) {
         hd_piece<L, W>(smem, chunks[blockIdx.x - d.n_wg], col, nullptr, X, zero_off, Y, partials, F4, nullptr);
@@ -159,45 +256,42 @@ __global__ __launch_bounds__(kBlock, 3) void hd_dense_kernel(const DenseArgs d, 
     const int32_t t = (int32_t)blockIdx.x, row_tile = t % d.row_tiles, f_tile = t / d.row_tiles % d.f_tiles;
     const int32_t k_part = t / d.row_tiles / d.f_tiles, F = 4 * F4;
     if (F - f_tile * kDenseTile > kDenseTile / 2)
-        dense_tile<MB, 4>((v4f *)smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
+        dense_tile<MB, 4, W>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
     else
-        dense_tile<MB, 2>((v4f *)smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
+        dense_tile<MB, 2, W>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
 }
 
-// Workgroups [0, d.n_rows): one dense row each, the sums of its column parts and its weight; a row with a sum that is not
-// finite is computed from its entries.  The ones behind: the split rows among the others, as in hd_finish_kernel.
-template <int L, int W>
+// Workgroups [0, d.n_rows): one dense row each, its partial sums meet in fp64.  The ones behind: the split rows among the others, as
+// in hd_finish_kernel.
+template <int L>
 __global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs d, const HdSplitRow *__restrict__ split,
                                                                  int64_t n_split, const v4f *__restrict__ partials,
-                                                                 const int32_t *__restrict__ col, const char *__restrict__ X,
-                                                                 int64_t zero_off, v4f *__restrict__ Y, int32_t F4)
+                                                                 v4f *__restrict__ Y, int32_t F4)
 {
     constexpr int G = kBlock / L;
-    __shared__ __align__(16) char smem[kHdSmemBytes<L>];
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    auto wide = [](v4f x) { return __builtin_convertvector(x, v4d); };
+    __shared__ v4d s_red[kBlock];                        // [G][L]
     const int g = threadIdx.x / L, f = threadIdx.x % L;
     if (blockIdx.x >= d.n_rows) {
         const int64_t k = (int64_t)(blockIdx.x - d.n_rows) * G + g;
         if (k < n_split) hd_finish_row<L>(split[k], partials, Y, F4, nullptr, f);
         return;
     }
-    const HdChunk row = d.rows[blockIdx.x];
-    const float rw = row_weight<W>(row.row_nnz);
-    v4f *const s_red = (v4f *)smem;                      // [G][L]
-    __shared__ int s_bad;
-    if (threadIdx.x == 0) s_bad = 0;                     // a barrier lies between this and every use
+    const int64_t row = d.rows[blockIdx.x].row;
 #pragma unroll 1
     for (int32_t fb = 0; fb < F4; fb += L) {
         const int32_t ff = fb + f;
         const bool live = ff < F4;
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
+        v4d acc = {0., 0., 0., 0.};
         const v4f *p = (const v4f *)d.partials + (int64_t)blockIdx.x * F4 + (live ? ff : 0);
         const int64_t step = (int64_t)d.padded * F4;
         int32_t k = g;
-        for (; k + 3 * G < d.k_parts; k += 4 * G) {
+        for (; k + 3 * G < d.n_partials; k += 4 * G) {
             const v4f x0 = p[k * step], x1 = p[(k + G) * step], x2 = p[(k + 2 * G) * step], x3 = p[(k + 3 * G) * step];
-            acc += (x0 + x1) + (x2 + x3);
+            acc += (wide(x0) + wide(x1)) + (wide(x2) + wide(x3));
         }
-        for (; k < d.k_parts; k += G) acc += p[k * step];
+        for (; k < d.n_partials; k += G) acc += wide(p[k * step]);
         s_red[threadIdx.x] = acc;
         __syncthreads();
 #pragma unroll
@@ -205,14 +299,9 @@ __global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs
             if (g < stride) s_red[threadIdx.x] += s_red[threadIdx.x + stride * L];
             __syncthreads();
         }
-        if (g == 0 && live) {
-            const v4f sum = s_red[f] * rw;
-            if (!(isfinite(sum[0]) && isfinite(sum[1]) && isfinite(sum[2]) && isfinite(sum[3]))) s_bad = 1;
-            Y[(int64_t)row.row * F4 + ff] = sum;
-        }
+        if (g == 0 && live) Y[row * F4 + ff] = __builtin_convertvector(s_red[f], v4f);
         __syncthreads();
     }
-    if (s_bad) hd_piece<L, W>(smem, row, col, nullptr, X, zero_off, Y, (v4f *)d.partials, F4, nullptr);   // slot -1: to Y
 }
 
 // the four mask words of row r and units 4 b .. 4 b + 3, one thread each; padding rows get zeros
@@ -260,21 +349,36 @@ static DenseArgs dense_args(const DevicePlan &dp, int32_t F)
     d.f_tiles = (F + kDenseTile - 1) / kDenseTile;
     d.n_units = (dp.n_cols + kDenseUnit - 1) / kDenseUnit;
     // one workgroup per CU while a wavefront has two units or more to sum
-    const int32_t tiles = d.row_tiles * d.f_tiles;
+    const int64_t tiles = (int64_t)d.row_tiles * d.f_tiles;
     int64_t k = kDenseMaxWorkgroups / tiles;
     const int64_t most = (d.n_units + 2 * kWavesPerBlock - 1) / (2 * kWavesPerBlock);
     if (k > most) k = most;
     d.k_parts = (int32_t)(k < 1 ? 1 : k);
-    d.n_wg = (int64_t)tiles * d.k_parts;
+    // How long a run is, and how many meet in fp32, so that the error is no larger than that of the gathers, which grows with a
+    // row's pieces.  Error of the dense rows in the 2-norm, U(-1, 1), here / gathers, 1e-7, F = 128: polarized graphs of 32,768 rows
+    // 0.74 / 1.12, 65,536 1.11 / 1.42, 131,072 1.31 / 1.51, 262,144 1.77 / 2.01 (F = 512 1.96 / 2.11); 64 rows of half of 65,536
+    // columns 1.64 / 1.83; 1,024 rows of a twelfth of them 1.10 / 1.20, of a quarter of 20,000 1.06 / 1.22.  In one chain per
+    // wavefront the 262,144 rows were at 4.1 (F = 512: 8.2).  A run costs 2 us: 260 us a step in one chain, 272 in six (F = 128).
+    const double length = (double)dp.dense_entries / dp.n_dense_rows, pieces = length / 512, per_unit = length / d.n_units;
+    const double run = (14 + 1.1 * pieces) / (1 + per_unit);
+    const int64_t share = ((d.n_units + d.k_parts - 1) / d.k_parts + kWavesPerBlock - 1) / kWavesPerBlock;
+    const int64_t units = run < 2 ? 2 : run > kDenseRun ? kDenseRun : (int64_t)run;
+    d.runs = (int32_t)((share + units - 1) / units);
+    d.group = 4 + (int32_t)(pieces < 1024 ? pieces / 8 : 128);
+    d.n_partials = d.k_parts * ((d.runs + d.group - 1) / d.group);
+    d.n_wg = tiles * d.k_parts;
     return d;
 }
 
-// floats of dense_partials for widths up to max_F: a workgroup's tile each, and one part at least
+// floats of dense_partials for widths up to max_F
 size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F)
 {
-    const size_t padded = (size_t)(dp.n_dense_rows + dp.dense_tile_rows - 1) / dp.dense_tile_rows * dp.dense_tile_rows;
-    const size_t most = (size_t)kDenseMaxWorkgroups * dp.dense_tile_rows * kDenseTile, one = padded * max_F;
-    return most > one ? most : one;
+    size_t most = 0;
+    for (int32_t F = kDenseMinF; F <= max_F; F += 4) {
+        const DenseArgs d = dense_args(dp, F);
+        most = std::max(most, (size_t)d.n_partials * d.padded * F);
+    }
+    return most;
 }
 
 // A launch and the finishing kernel more than with the gathers: polarized graphs, whole step, us, gathers / dense product, by
@@ -342,19 +446,14 @@ int launch_hd_dense(const DevicePlan &dp, const float *X, float *Y, int32_t F, i
     return (int)hipGetLastError();
 }
 
-int launch_hd_dense_finish(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream)
+int launch_hd_dense_finish(const DevicePlan &dp, float *Y, int32_t F, void *stream)
 {
     const DenseArgs d = dense_args(dp, F);
-    hipStream_t st = (hipStream_t)stream;
     const int L = dense_lanes(F / 4);
     const int64_t n_wg = d.n_rows + (dp.n_split_rows + kBlock / L - 1) / (kBlock / L);
     if (!grid_ok(n_wg)) return (int)hipErrorInvalidConfiguration;
-    auto go = [&](auto kernel) {
-        kernel<<<dim3((unsigned)n_wg), dim3(kBlock), 0, st>>>(d, dp.split_rows, dp.n_split_rows, (const v4f *)dp.partials, dp.col,
-                                                             (const char *)X, byte_distance(X, dp.zero_row), (v4f *)Y, F / 4);
-    };
-    if (dp.weight_mode == kMean) { GROOT_DENSE_L(L, (go(hd_dense_finish_kernel<kL, kMean>))) }
-    else { GROOT_DENSE_L(L, (go(hd_dense_finish_kernel<kL, kOnes>))) }
+    GROOT_DENSE_L(L, (hd_dense_finish_kernel<kL><<<dim3((unsigned)n_wg), dim3(kBlock), 0, (hipStream_t)stream>>>(
+                         d, dp.split_rows, dp.n_split_rows, (const v4f *)dp.partials, (v4f *)Y, F / 4)));
     return (int)hipGetLastError();
 }
 

@@ -780,7 +780,7 @@ extern "C" groot_status groot_spmm_execute_phases(const groot_plan *plan, const 
     if (!err && (phases & GROOT_PHASE_LD)) err = launch_ld(dp, X_dev, Y_dev, F, hip_stream, nullptr, together);
     if (!err && dense && (phases & GROOT_PHASE_HD)) err = launch_hd_dense(dp, X_dev, Y_dev, F, together ? 0 : dp.n_chunks, hip_stream);
     if (!err && !dense && !together && (phases & GROOT_PHASE_HD) && dp.n_chunks) err = launch_hd(dp, X_dev, Y_dev, F, hip_stream);
-    if (!err && dense && (phases & GROOT_PHASE_FINISH)) err = launch_hd_dense_finish(dp, X_dev, Y_dev, F, hip_stream);
+    if (!err && dense && (phases & GROOT_PHASE_FINISH)) err = launch_hd_dense_finish(dp, Y_dev, F, hip_stream);
     if (!err && !dense && (phases & GROOT_PHASE_FINISH) && dp.n_split_rows) err = launch_hd_finish(dp, Y_dev, F, hip_stream);
     if (err) return fail(GROOT_EHIP, std::string("groot_spmm_execute: launch failed: ") + hip_error_text(err));
     return GROOT_OK;

@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from util import wgrad_rows_per_wavefront, wgrad_tolerance, assert_close_to_oracle, ensure_built, layer_tolerance
+from util import wgrad_rows_per_wavefront, wgrad_tolerance, assert_close_to_oracle, ensure_built, layer_tolerance, tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -1392,3 +1392,90 @@ def test_dense_rows_of_a_plan_whose_columns_are_renamed(torch_cuda):
     Y = torch_cuda.full((n, F), float("nan"), device="cuda")
     G.groot_spmm_execute_rows(plan, Xd, Y, F, n)
     assert_close_to_oracle(Y.cpu().numpy(), Y64, S, "renamed columns, rows")
+
+
+def _dense_rows_of(rowptr, col, val, rows):
+    """the rows as a matrix of their own"""
+    length = np.diff(rowptr)[rows]
+    pick = np.concatenate([np.arange(rowptr[r], rowptr[r + 1]) for r in rows])
+    return np.concatenate([[0], np.cumsum(length)]).astype(np.int64), col[pick], val[pick]
+
+
+@pytest.mark.parametrize("n,n_dense,share,F", [(20011, 512, 0.25, 128), (65536, 320, 0.25, 256), (65536, 64, 0.5, 512),
+                                               (100003, 640, 0.08, 128), (131072, 320, 0.25, 64)])
+def test_dense_product_is_no_less_precise_than_the_gathers(torch_cuda, n, n_dense, share, F):
+    """The sums of dense rows against fp64, in the 2-norm over all of them, beside the sums that the same rows get by gathers
+    (groot_spmm_execute_rows), for inputs that cancel: however many columns there are, no chain of additions grows with them."""
+    rng = np.random.default_rng(n + F)
+    rowptr, col, val, dense = _dense_rows_graph(n, n_dense, share, rng)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == n_dense and n_dense * int(share * n) * F >= 2 ** 25
+    X = wl.uniform_features_numpy(n_dense, 0, n, F)
+    Xd = torch_cuda.from_numpy(X).cuda()
+    want, _ = oracle.spmm_f64(*_dense_rows_of(rowptr, col, val, dense), X)
+    Y = torch_cuda.empty_like(Xd)
+    off = []
+    for call in (lambda: G.groot_spmm_execute(plan, Xd, Y, F), lambda: G.groot_spmm_execute_rows(plan, Xd, Y, F, n)):
+        call()
+        off.append(np.linalg.norm(Y.cpu().numpy()[dense].astype(np.float64) - want) / np.linalg.norm(want))
+    assert off[0] <= off[1], off
+
+
+@pytest.mark.parametrize("how", ["one", "a hundredth", "a stretch", "all"])
+@pytest.mark.parametrize("ones", [False, True])
+def test_dense_product_gives_infinities_and_nan_like_the_gathers(torch_cuda, how, ones):
+    """Any number of infinities and NaN in X, in any order: the same elements are infinite, of the same sign, and NaN as by
+    gathers, and the others are as close to them as two orders of summation are."""
+    n, F = 40013, 68
+    rng = np.random.default_rng(11)
+    rowptr, col, val, dense = _dense_rows_graph(n, 96, 0.2, rng)
+    if ones:
+        val = np.ones_like(val)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == 96
+    X = wl.uniform_features_numpy(12, 0, n, F)
+    kinds = np.array([np.inf, -np.inf, np.nan], np.float32)
+    if how == "one":
+        X[n // 2, 7] = -np.inf
+    elif how == "a hundredth":                               # of the columns, in a few features
+        rows = rng.choice(n, n // 100, replace=False)
+        X[rows, rng.integers(0, 9, rows.size)] = kinds[rng.integers(0, 3, rows.size)]
+        X[rng.choice(n, 3, replace=False), 20] = np.inf
+        X[rng.choice(n, 2, replace=False), 21] = np.inf, -np.inf
+    elif how == "a stretch":
+        X[5000:5040, 10:30] = np.inf
+        X[9000:9900, 40] = -np.inf
+    else:
+        X[:] = kinds[rng.integers(0, 2, X.shape)]
+        X[:, 3], X[:, 4], X[:, 5] = np.inf, -np.inf, np.nan
+    Xd = torch_cuda.from_numpy(X).cuda()
+    out = []
+    for call in (lambda Y: G.groot_spmm_execute(plan, Xd, Y, F), lambda Y: G.groot_spmm_execute_rows(plan, Xd, Y, F, n)):
+        Y = torch_cuda.full((n, F), 7.0, device="cuda")
+        call(Y)
+        out.append(Y.cpu().numpy())
+    a, b = out
+    assert (np.isnan(a) == np.isnan(b)).all() and (np.isposinf(a) == np.isposinf(b)).all() and (np.isneginf(a) == np.isneginf(b)).all()
+    assert how == "all" or np.isfinite(b[dense]).any()
+    keep = np.isfinite(b)
+    terms, bound = np.where(np.isfinite(X), np.abs(X), 0), np.zeros((n, F))
+    bound[dense] = oracle.spmm_f64(*_dense_rows_of(rowptr, col, val, dense), terms.astype(np.float32))[0]
+    assert (np.abs(np.where(keep, a, 0) - np.where(keep, b, 0)) <= 2 * tolerance(bound)).all()
+
+
+def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torch_cuda):
+    """Only the stretch of columns that holds it is summed again (a row that was gathered again by a single workgroup took 3.4
+    times as long); the allowance is for the box."""
+    n, F = 131072, 128
+    rng = np.random.default_rng(13)
+    rowptr, col, val, _ = _dense_rows_graph(n, 320, 0.25, rng)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    X = torch_cuda.empty((n, F), device="cuda").uniform_(-1, 1)
+    Y = torch_cuda.empty_like(X)
+    run = lambda: G.groot_spmm_execute(plan, X, Y, F)
+    finite = _best_time(torch_cuda, run)
+    X[n // 3, 5] = float("nan")
+    assert _best_time(torch_cuda, run) < 1.7 * finite
