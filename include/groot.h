@@ -538,7 +538,8 @@ groot_status groot_plan_hd_pieces(const groot_plan *plan, int64_t capacity, int6
  * the matrix for the pipelined LD kernel, 4-byte row pointers and 2-byte column
  * codes, when every entry of a short row lies within 16,384 rows of its own row
  * or names one of the first 32,768 high-degree rows, and the matrix has fewer
- * than 2^32 entries; 0: never),
+ * than 2^32 entries, and execute reads it where X is as large as said above for
+ * "csr_compressed"; 2: execute reads it at every size of X; 0: never),
  * "ld_pipeline" (which LD kernel is used: 1 the software-pipelined one for
  * the widths given above for "ld_pipelined"; 0 the plain one; -1 (default) the pipelined one with the
  * smallest number of gather slots per row, 5 to 8, that leaves at most 2

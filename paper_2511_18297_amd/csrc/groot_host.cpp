@@ -708,7 +708,9 @@ extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
         }
     }
     // compact CSR for the pipelined kernel (4-byte row pointers, 2-byte column codes), when the graph allows it
-    if (d.ld_pipelined && tuning().csr_compress) {
+    const int compress = tuning().csr_compress;
+    d.compact_always = compress == 2;
+    if (d.ld_pipelined && compress) {
         int32_t *hd_dev = nullptr;
         if ((st = to_device(&hd_dev, plan->hd_rows.data(), plan->hd_rows.size(), "high-degree row list")) != GROOT_OK) {
             std::string keep = groot_last_error();
@@ -1455,7 +1457,9 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             d.n_mid_rows = ch.pipelined ? n_ld - first_mid : 0;
             // the tail of the degree-sorted list, which is on the device already, with room for the rows that the compact matrix
             // will not code
-            compress = d.ld_pipelined && tuning().csr_compress;
+            const int knob = tuning().csr_compress;
+            d.compact_always = knob == 2;
+            compress = d.ld_pipelined && knob;
             const size_t room = (size_t)d.n_mid_rows + (compress ? csr_bad_capacity(n) : 0);
             if (room) {
                 if ((st = to_device<int32_t>(&d.mid_rows, nullptr, room, "long low-degree rows")) != GROOT_OK ||
@@ -1611,7 +1615,7 @@ extern "C" groot_status groot_set_tuning(const char *name, int64_t value)
         return GROOT_OK;
     }
     if (k == "csr_compress") {
-        if (value < 0 || value > 1) return fail(GROOT_EINVAL, "groot_set_tuning: csr_compress must be 0 or 1");
+        if (value < 0 || value > 2) return fail(GROOT_EINVAL, "groot_set_tuning: csr_compress must be 0, 1 or 2");
         tuning().csr_compress = (int)value;
         return GROOT_OK;
     }

@@ -45,7 +45,7 @@ struct Tuning {
     std::atomic<int> sage_kernel{1};       // fused layer: 1 one self-contained wavefront per SIMD, 0 the 12-wavefront kernel
     std::atomic<int> sage_pieces{3};       // fused layer (sage_kernel 1): bf16 pieces per fp32 operand of the dense products, 3 or 2
     std::atomic<int> uniform_detect{1};    // groot_plan_upload looks whether explicit weights are row-uniform (see DevicePlan)
-    std::atomic<int> csr_compress{1};      // groot_plan_upload builds the compact CSR for the pipelined LD kernel when it can; it is read where it pays (ld_reads_compact)
+    std::atomic<int> csr_compress{1};      // compact CSR for the pipelined LD kernel: 0 never, 1 where it pays (ld_reads_compact), 2 wherever it can be built
     std::atomic<int> pipe_depth{0};        // gather slots per row of the pipelined LD kernel: 0 the smallest that fits, or 5..8
     std::atomic<int> ld_pipeline{-1};      // pipelined LD kernel: 1 always (where it applies), 0 never, -1 by the row lengths
 };
@@ -92,6 +92,7 @@ struct DevicePlan {
     HdSplitRow *other_split_rows = nullptr;
     int64_t n_other_split_rows = 0;
     // compact CSR for the pipelined LD kernel (groot_compress.hip); all NULL / 0 unless compressed
+    int compact_always = 0;         // it is read whatever the size of X (the csr_compress knob)
     uint32_t *rp32 = nullptr;       // [n+1] low 32 bits of rowptr (nnz < 2^32)
     uint16_t *col16 = nullptr;      // [nnz] column codes of the rows the pipelined kernel serves
     int32_t *hot_cols = nullptr;    // [n_hot] the high-degree rows that a code can name, ascending

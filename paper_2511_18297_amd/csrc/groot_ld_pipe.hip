@@ -581,6 +581,7 @@ static int64_t rows_beside_sweep(int depth, int32_t F4, int64_t n_rows)
 bool ld_reads_compact(const DevicePlan &dp, int32_t F)
 {
     if (!dp.compressed || !dp.rp32 || !dp.col16 || !dp.hot_cols) return false;
+    if (dp.compact_always) return true;
     const int64_t line = dp.pipe_depth <= 5 ? (int64_t)192 << 20 : (int64_t)1 << 30;
     return dp.n_cols * F * 4 >= line;
 }

@@ -106,7 +106,15 @@ def test_config1_32bit_structural_features(torch_cuda):
     assert_close_to_oracle(Y, Y64, S, "config 1")
 
 
-def test_config2_256bit(torch_cuda):
+@pytest.fixture
+def compact_always():
+    """The compact matrix is read at every size of X."""
+    G.groot_set_tuning("csr_compress", 2)
+    yield
+    G.groot_set_tuning("csr_compress", 1)
+
+
+def test_config2_256bit(torch_cuda, compact_always):
     """256-bit multiplier (522,496 nodes), F = 64, seed 1, T = 32."""
     aig, g, (rowptr, col, val, pol) = _aig_case(256, 1)
     X = wl.uniform_features_numpy(1, 0, aig.num_nodes, 64)
@@ -198,7 +206,7 @@ def test_stress_graph_threshold_sweep(torch_cuda, uniform_detect, T):
 
 @pytest.mark.parametrize("max_len,T,F,explicit", [(14, 32, 64, False), (14, 9, 32, False), (10, 4, 128, True),
                                                    (9, 32, 64, True), (40, 16, 64, False), (8, 32, 32, False)])
-def test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit):
+def test_mixed_row_lengths(torch_cuda, compact_always, max_len, T, F, explicit):
     """Row lengths drawn uniformly from 0..max_len (empty rows included), 20,011 rows (a ragged last tile at every
     width): in the pipelined kernel every tile mixes rows that fit its 5 to 8 slots, longer low-degree rows (masked
     there, computed from the row list) and high-degree rows (masked, computed by the HD kernel); with max_len = 40
@@ -237,16 +245,19 @@ def test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit):
             assert G.groot_plan_query(plan, "csr_compressed") == 0
     Y64, S = oracle.spmm_f64(rowptr, col, val, X)
     assert_close_to_oracle(Y, Y64, S, f"mixed rows max_len={max_len} T={T} F={F}")
+    G.groot_set_tuning("csr_compress", 1)                    # the plain arrays at this size
+    Y, _, _, _ = _run(torch_cuda, g, T, X)
+    assert_close_to_oracle(Y, Y64, S, f"plain arrays, mixed rows max_len={max_len} T={T} F={F}")
 
 
 @pytest.mark.parametrize("max_len,T,F,explicit", [(5, 32, 20, False), (6, 9, 28, True), (8, 32, 36, False), (8, 32, 60, True),
                                                    (7, 32, 124, False), (5, 6, 132, True), (5, 32, 252, False),
                                                    (8, 4, 256, True), (40, 16, 100, False), (4, 4, 48, False)])
-def test_mixed_row_lengths_at_other_widths(torch_cuda, max_len, T, F, explicit):
+def test_mixed_row_lengths_at_other_widths(torch_cuda, compact_always, max_len, T, F, explicit):
     """The same at widths that fill no power of two of lanes (the lanes past a row's end double its last one), with 5 to 8
     slots per row, and with the high-degree rows in the low-degree launch (T = 9 with rows up to 6: none at all) or in
     one of their own (thousands of pieces)."""
-    test_mixed_row_lengths(torch_cuda, max_len, T, F, explicit)
+    test_mixed_row_lengths(torch_cuda, compact_always, max_len, T, F, explicit)
 
 
 @pytest.mark.parametrize("pieces", [512, 513, 1023, 1024, 1025, 2047, 2048, 2600])
@@ -966,13 +977,13 @@ def test_tuning_knobs_do_not_change_results(torch_cuda):
                 assert_close_to_oracle(Y, Y64, S, f"remap={remap} chunk={chunk}")
         G.groot_set_tuning("xcd_remap", 1)
         G.groot_set_tuning("hd_chunk", 512)
-        for compress in (0, 1):
+        for compress in (0, 2):
             for depth in (0, 5, 6, 7, 8):
                 G.groot_set_tuning("csr_compress", compress)
                 G.groot_set_tuning("pipe_depth", depth)
                 Y, plan, _, _ = _run(torch_cuda, g, 12, X)
                 if G.groot_plan_query(plan, "ld_pipelined"):
-                    assert G.groot_plan_query(plan, "csr_compressed") == compress
+                    assert G.groot_plan_query(plan, "csr_compressed") == (compress == 2)
                     assert G.groot_plan_query(plan, "pipe_depth") == (depth or 5)
                 assert_close_to_oracle(Y, Y64, S, f"compress={compress} depth={depth}")
     finally:
@@ -1221,7 +1232,7 @@ def test_lengths_of_high_degree_pieces(torch_cuda, F, explicit, chunk):
 
 
 @pytest.mark.parametrize("F,depth,explicit", [(32, 5, False), (64, 5, True), (100, 5, False), (128, 7, False), (200, 5, True),
-                                              (252, 8, False)])
+                                              (252, 8, False), (36, 5, False), (72, 5, True), (136, 5, False), (136, 6, False)])
 def test_compact_matrix_where_it_is_read(torch_cuda, F, depth, explicit):
     """The compact matrix against the plain arrays on either side of the size of X from which it is read: the same sums in the
     same order, so the same bits.  Rows of 1 to depth entries near the row or among the high-degree rows, a few longer ones,
@@ -1330,9 +1341,9 @@ def test_dense_product_with_numbers_that_are_not_finite(torch_cuda):
     assert_close_to_oracle(Y[:, keep], Y64, S, "the other features")
 
 
-@pytest.mark.parametrize("F,depth,explicit", [(36, 5, False), (40, 5, True), (48, 5, False), (72, 5, True), (92, 5, False), (132, 5, False),
+@pytest.mark.parametrize("F,depth,explicit", [(36, 5, False), (40, 5, True), (48, 5, False), (72, 5, True), (80, 5, False), (132, 5, False),
                                               (164, 5, True), (176, 5, False), (36, 6, True), (44, 7, False), (72, 8, False),
-                                              (96, 6, False), (136, 7, True), (188, 8, False)])
+                                              (96, 6, False), (136, 7, True), (148, 8, False)])
 def test_rows_that_share_their_lanes(torch_cuda, F, depth, explicit):
     """Widths at which a sweep deals a tile's float4 out to all lanes (half to three quarters of L lanes per row otherwise): a
     ragged last tile, empty rows, masked rows first and last in a tile, on either side of 64 MB of X.  Against the plain
@@ -1368,6 +1379,55 @@ def test_rows_that_share_their_lanes(torch_cuda, F, depth, explicit):
             assert torch_cuda.isnan(buf[:3]).all() and torch_cuda.isnan(buf[n + 3:]).all(), "wrote outside Y"
             out.append(buf[3:n + 3])
         assert torch_cuda.equal(out[0], out[1]), f"F={F} depth={depth} n={n}"
+
+
+@pytest.mark.parametrize("F,depth,T,weights", [(36, 5, 32, "mean"), (44, 5, 4, "explicit"), (72, 5, 32, "ones"), (80, 5, 32, "mean"),
+                                               (136, 5, 32, "explicit"), (176, 5, 5, "ones"), (36, 6, 32, "explicit"), (48, 7, 5, "mean"),
+                                               (40, 8, 32, "ones"), (72, 6, 32, "mean"), (96, 7, 32, "explicit"), (76, 8, 6, "ones"),
+                                               (132, 6, 32, "ones"), (148, 7, 32, "mean"), (136, 8, 32, "explicit")])
+def test_rows_that_share_their_lanes_on_the_compact_matrix(torch_cuda, F, depth, T, weights):
+    """The same widths with the matrix as 2-byte codes: entries near the row, at either end of what a code reaches, among the
+    high-degree rows and beyond any code (a row with such an entry is masked, wherever it lies in a tile), empty rows, rows longer
+    than the slots, a threshold below them, a ragged last tile.  Against the plain kernel, which adds in the same order."""
+    rng = np.random.default_rng(F * depth)
+    n = (64 << 20) // (4 * F) + 38 if depth == 5 else 40013
+    length = rng.integers(max(0, min(depth, T - 1) - 5), min(depth, T - 1) + 1, n)
+    length[rng.choice(n, n // 200, replace=False)] = min(depth, T) + 3
+    length[rng.choice(n, n // 900, replace=False)] = min(depth, T)
+    hot = np.sort(rng.choice(n, n // 300, replace=False))
+    length[hot] = 40
+    row = np.repeat(np.arange(n), length)
+    pick = rng.random(row.size)
+    col = row + rng.integers(-300, 301, row.size)
+    col = np.where(pick < 0.02, row - 16384, np.where(pick < 0.04, row + 16383, col))
+    col = np.where((col < 0) | (col >= n), row, col)
+    col = np.where(pick > 0.8, hot[rng.integers(0, hot.size, row.size)], col)
+    col = np.where(pick > 0.9995, rng.integers(0, n, row.size), col)
+    row, col = np.divmod(np.unique(row * n + col), n)
+    length = np.bincount(row, minlength=n)
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    val = {"mean": np.repeat(np.float32(1) / np.maximum(length, 1).astype(np.float32), length), "ones": np.ones(col.size, np.float32),
+           "explicit": rng.uniform(-1, 1, col.size).astype(np.float32)}[weights]
+    g = G.groot_graph_from_csr(rowptr, col.astype(np.int32), val)
+    X = torch_cuda.empty((n, F), device="cuda").uniform_(-1, 1)
+    out = []
+    for pipeline in (1, 0):
+        for name, value in (("ld_pipeline", pipeline), ("pipe_depth", depth), ("csr_compress", 2)):
+            G.groot_set_tuning(name, value)
+        try:
+            plan = G.groot_spmm_plan(g, T)
+            G.groot_plan_upload(plan, F)
+        finally:
+            for name, value in (("ld_pipeline", -1), ("pipe_depth", 0), ("csr_compress", 1)):
+                G.groot_set_tuning(name, value)
+        if pipeline:
+            assert G.groot_plan_query(plan, "csr_compressed") == 1 and 0 < G.groot_plan_query(plan, "uncoded_rows") < n // 50
+            assert G.groot_plan_query(plan, "weight_mode") == {"ones": 0, "mean": 1, "explicit": 2}[weights]
+        buf = torch_cuda.full((n + 6, F), float("nan"), device="cuda")
+        G.groot_spmm_execute(plan, X, buf[3:n + 3], F)
+        assert torch_cuda.isnan(buf[:3]).all() and torch_cuda.isnan(buf[n + 3:]).all(), "wrote outside Y"
+        out.append(buf[3:n + 3])
+    assert torch_cuda.equal(out[0], out[1])
 
 
 def test_dense_rows_of_a_plan_whose_columns_are_renamed(torch_cuda):
