@@ -488,7 +488,8 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
  * 5 to 8), "mid_rows" (low-degree rows with more entries than that, which are
  * computed from a list), "csr_compressed" (1 when the plan holds 4-byte row pointers and
  * 2-byte column codes, which the pipelined kernel reads instead of the 8- and 4-byte arrays
- * where X has 192 MiB or more, 1 GiB with more than 5 gather slots), "hd_pieces" (launch size of the HD kernel),
+ * where X has 192 MiB or more, 1 GiB with more than 5 gather slots; a plan holds them where
+ * a matrix of max_F columns, or of 256 if that is less, has as much), "hd_pieces" (launch size of the HD kernel),
  * "dense_rows" (high-degree rows with so many entries that groot_spmm_execute computes
  * them as a dense product instead of by their pieces, where their entries times F
  * come to 2^25 or more and F is 8 or more),
@@ -534,12 +535,12 @@ groot_status groot_plan_hd_pieces(const groot_plan *plan, int64_t capacity, int6
  * kept, fp32 accuracy; 2: two pieces and three products, half the matrix
  * instructions, every product exact to 3 x 2^-18 of its magnitude instead of
  * 2^-23; read at each call),
- * "csr_compress" (1, default: groot_plan_upload also builds a compact copy of
- * the matrix for the pipelined LD kernel, 4-byte row pointers and 2-byte column
- * codes, when every entry of a short row lies within 16,384 rows of its own row
- * or names one of the first 32,768 high-degree rows, and the matrix has fewer
- * than 2^32 entries, and execute reads it where X is as large as said above for
- * "csr_compressed"; 2: execute reads it at every size of X; 0: never),
+ * "csr_compress" (1, default: groot_plan_upload and groot_dev_part_plan also
+ * build a compact copy of the matrix for the pipelined LD kernel, 4-byte row
+ * pointers and 2-byte column codes, when X is as large at max_F as said above for
+ * "csr_compressed", every entry of all but one short row in 50 lies within 16,384
+ * rows of its own row or names one of the first 32,767 high-degree rows, and the
+ * matrix has fewer than 2^32 entries; 2: at every size of X; 0: never),
  * "ld_pipeline" (which LD kernel is used: 1 the software-pipelined one for
  * the widths given above for "ld_pipelined"; 0 the plain one; -1 (default) the pipelined one with the
  * smallest number of gather slots per row, 5 to 8, that leaves at most 2

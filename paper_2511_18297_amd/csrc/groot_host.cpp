@@ -710,7 +710,7 @@ extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
     // compact CSR for the pipelined kernel (4-byte row pointers, 2-byte column codes), when the graph allows it
     const int compress = tuning().csr_compress;
     d.compact_always = compress == 2;
-    if (d.ld_pipelined && compress) {
+    if (ld_builds_compact(d, max_F, compress)) {
         int32_t *hd_dev = nullptr;
         if ((st = to_device(&hd_dev, plan->hd_rows.data(), plan->hd_rows.size(), "high-degree row list")) != GROOT_OK) {
             std::string keep = groot_last_error();
@@ -1459,7 +1459,7 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             // will not code
             const int knob = tuning().csr_compress;
             d.compact_always = knob == 2;
-            compress = d.ld_pipelined && knob;
+            compress = ld_builds_compact(d, max_F, knob);
             const size_t room = (size_t)d.n_mid_rows + (compress ? csr_bad_capacity(n) : 0);
             if (room) {
                 if ((st = to_device<int32_t>(&d.mid_rows, nullptr, room, "long low-degree rows")) != GROOT_OK ||

@@ -114,6 +114,7 @@ constexpr int kCodeBad = 0xFFFF;      // an entry that no code can express: its 
 constexpr int kCodeMaxHot = 0x7FFF;
 constexpr int32_t hot_ints(int32_t n_hot) { return n_hot ? (n_hot + 3) / 4 * 4 : 4; }   // the hot list as it is stored: whole 16 bytes
 constexpr int kPipeMinDepth = 5, kPipeMaxDepth = 8;   // gather slots per row the pipelined LD kernel is built for
+constexpr int32_t kPipeMaxF = 256;       // widest matrix that the pipelined kernels serve
 constexpr int kZeroRowFloats = 512;     // a row of the widest matrix
 constexpr int kTrashFloats = 2048;
 constexpr int kRowsPerLdTile = 256;   // rows of one LD block (4 wavefronts x 64 rows)
@@ -131,6 +132,8 @@ int launch_ld(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
               bool with_hd = false);
 bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out = nullptr);
 bool ld_reads_compact(const DevicePlan &dp, int32_t F);
+bool compact_pays(const DevicePlan &dp, int32_t F);   // ... if the plan has it; true for a wider matrix, too, if for F
+bool ld_builds_compact(const DevicePlan &dp, int32_t max_F, int knob);
 int launch_ld_pipelined(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream,
                         const RowOut *out, bool with_hd);   // F up to 256; with out F = 32, 64, 128
 int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *stream, const RowOut *out = nullptr);

@@ -578,12 +578,22 @@ static int64_t rows_beside_sweep(int depth, int32_t F4, int64_t n_rows)
 //   6 and 7 slots: 134 MB (4-LUT, F = 32) 104.8 / 94.4; 271 MB (cells, F = 32) 172.7 / 166.0, (4-LUT, F = 64) 212.2 / 215.4; 424 MB
 //     (4-LUT, F = 100) 369.8 / 364.2; 540 MB (F = 64) 423.9 / 423.6, (cells) 317.5 / 316.4; 844 MB 710.1 / 710.8; 1.1 GB (4-LUT, F = 32)
 //     803 / 811, (cells) 628 / 640
+bool compact_pays(const DevicePlan &dp, int32_t F)
+{
+    const int64_t line = dp.pipe_depth <= 5 ? (int64_t)192 << 20 : (int64_t)1 << 30;
+    return dp.compact_always || dp.n_cols * F * 4 >= line;
+}
+
 bool ld_reads_compact(const DevicePlan &dp, int32_t F)
 {
-    if (!dp.compressed || !dp.rp32 || !dp.col16 || !dp.hot_cols) return false;
-    if (dp.compact_always) return true;
-    const int64_t line = dp.pipe_depth <= 5 ? (int64_t)192 << 20 : (int64_t)1 << 30;
-    return dp.n_cols * F * 4 >= line;
+    return dp.compressed && dp.rp32 && dp.col16 && dp.hot_cols && compact_pays(dp, F);
+}
+
+// Whether a plan for widths up to max_F gets it: where some width reads it.  For no reader it would be 4 n + 2 nnz bytes, two
+// kernels over the matrix and, in groot_plan_upload, a wait.
+bool ld_builds_compact(const DevicePlan &dp, int32_t max_F, int knob)
+{
+    return dp.ld_pipelined && knob && compact_pays(dp, max_F < kPipeMaxF ? max_F : kPipeMaxF);
 }
 
 // out: the leading out->n_out rows only, row r written to row out->ids[r] of Y (ids NULL: to row r)

@@ -1268,7 +1268,7 @@ def test_compact_matrix_where_it_is_read(torch_cuda, F, depth, explicit):
                 G.groot_set_tuning("csr_compress", 1)
                 G.groot_set_tuning("pipe_depth", 0)
             if G.groot_plan_query(plan, "ld_pipelined"):
-                assert G.groot_plan_query(plan, "csr_compressed") == compress
+                assert G.groot_plan_query(plan, "csr_compressed") == (compress and 4 * F * n >= line)   # not built for no reader
                 if compress:
                     entries = int(rowptr[-1]) - G.groot_plan_query(plan, "nnz_hd")
                     weights = 4 if explicit else 0
