@@ -435,13 +435,14 @@ def stress_bench(args, G, torch, np, wl, name, props):
         ms_ld = timed_phase(G.GROOT_PHASE_LD)
         ms_hd = timed_phase(G.GROOT_PHASE_HD) if pv["n_hd"] else 0.0
         ms_fin = timed_phase(G.GROOT_PHASE_FINISH) if pv["n_hd"] else 0.0
-        nnz_hd = G.groot_plan_query(plan, "nnz_hd")
+        nnz_hd, dense_rows = G.groot_plan_query(plan, "nnz_hd"), G.groot_plan_query(plan, "dense_rows")
         csr_bytes = G.groot_plan_query(plan, "csr_bytes")
         item = {"degree_threshold": T, "n_hd_rows": pv["n_hd"], "nnz_hd": nnz_hd, "ms_per_step": round(ms, 3),
                 "gflops": round(flops / (ms * 1e-3) / 1e9, 1),
                 "gather_demand_gbps": round(gather_bytes / (ms * 1e-3) / 1e9, 1),
                 "ld_ms": round(ms_ld, 3), "hd_ms": round(ms_hd, 3), "finish_ms": round(ms_fin, 3),
-                "hd_gather_gbps": round(4.0 * F * nnz_hd / (ms_hd * 1e-3) / 1e9, 1) if ms_hd else None,
+                "hd_gather_gbps": round(4.0 * F * nnz_hd / (ms_hd * 1e-3) / 1e9, 1) if ms_hd and not dense_rows else None,
+                "dense_rows": dense_rows,                    # computed without gathers
                 "hd_pieces": G.groot_plan_query(plan, "hd_pieces"), "csr_bytes": csr_bytes,
                 "weight_mode": G.groot_plan_query(plan, "weight_mode")}
         sweep.append(item)

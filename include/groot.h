@@ -489,7 +489,8 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
  * computed from a list), "csr_compressed" (1 when the plan holds 4-byte row pointers and
  * 2-byte column codes, which the pipelined kernel reads instead of the 8- and 4-byte arrays
  * where X has 192 MiB or more, 1 GiB with more than 5 gather slots; a plan holds them where
- * a matrix of max_F columns, or of 256 if that is less, has as much), "hd_pieces" (launch size of the HD kernel),
+ * a matrix of max_F columns, or of 256 if that is less, has as much), "hd_pieces" (pieces of all
+ * high-degree rows: the launch size of the HD kernel where there are no dense rows),
  * "dense_rows" (high-degree rows with so many entries that groot_spmm_execute computes
  * them as a dense product instead of by their pieces, where their entries times F
  * come to 2^25 or more and F is 8 or more),
@@ -498,7 +499,8 @@ groot_status groot_feature_placement(const groot_plan *plan, void *arena_dev, si
  * from the row pointer, 2 read from the weight array), "nnz_hd" (stored entries
  * of the high-degree rows), "csr_bytes" (bytes of the graph's device arrays
  * that one execute at max_F reads: row pointers, column indices, the weights only when
- * the kernels read them, the high-degree pieces' descriptors; "csr_bytes_ld" /
+ * the kernels read them, the high-degree pieces' descriptors; where a dense product
+ * is computed its rows' one bit per column in place of their entries and pieces; "csr_bytes_ld" /
  * "csr_bytes_hd" its split over the low-degree and the high-degree kernel).
  * Errors: EINVAL (NULL, unknown name, plan not uploaded). */
 groot_status groot_plan_query(const groot_plan *plan, const char *what, int64_t *value);

@@ -1591,7 +1591,10 @@ extern "C" groot_status groot_plan_query(const groot_plan *plan, const char *wha
         const bool compact = d.ld_pipelined && ld_reads_compact(d, plan->max_F);
         const int64_t ld = compact ? 4 * (d.n + 1) + (2 + w_bytes) * (d.nnz - d.nnz_hd)
                                    : 8 * (d.n + 1) + per_entry * (d.nnz - d.nnz_hd);
-        const int64_t hd = per_entry * d.nnz_hd + (int64_t)sizeof(HdChunk) * d.n_chunks;
+        int64_t hd = per_entry * d.nnz_hd + (int64_t)sizeof(HdChunk) * d.n_chunks;
+        if (hd_dense_serves(d, plan->max_F))                 // one bit per column of the dense rows in place of their entries
+            hd = per_entry * (d.nnz_hd - d.dense_entries) + (int64_t)sizeof(HdChunk) * (d.n_other_chunks + d.n_dense_rows) +
+                 4 * (int64_t)dense_mask_words(d);
         *value = k == "csr_bytes_ld" ? ld : k == "csr_bytes_hd" ? hd : ld + hd;
     }
     else return fail(GROOT_EINVAL, "groot_plan_query: unknown name '" + k + "'");

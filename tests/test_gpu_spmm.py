@@ -1314,6 +1314,25 @@ def test_high_degree_rows_as_a_dense_product(torch_cuda, n, n_dense, want, width
         assert_close_to_oracle(Y, Y64, S, f"dense rows n={n} {n_dense} F={F}")
 
 
+@pytest.mark.parametrize("n_dense,max_F,said,served", [(500, 12, 500, True), (500, 4, 0, False), (16, 64, 16, False)])
+def test_bytes_that_are_said_to_be_read_with_dense_rows(torch_cuda, n_dense, max_F, said, served):
+    """"csr_bytes_hd" of a plan whose widest call computes the dense rows from one bit per column, and of one whose calls
+    gather them."""
+    n = 50020
+    rowptr, col, val, dense = _dense_rows_graph(n, n_dense, 0.25, np.random.default_rng(3))
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, max_F)
+    assert G.groot_plan_query(plan, "dense_rows") == said
+    length = np.diff(rowptr)
+    others = np.count_nonzero(length == 40)                  # one piece each
+    pieces, nnz_hd = G.groot_plan_query(plan, "hd_pieces"), G.groot_plan_query(plan, "nnz_hd")
+    assert pieces == others + n_dense * -(-int(0.25 * n) // 512) and nnz_hd == length[length >= 32].sum()
+    mask = -(-(-(-n // 32)) // 4) * 512 * 4 * 4              # 128 columns of a row in 16 bytes, rows in tiles of 64
+    read = 4 * 40 * others + 24 * (others + n_dense) + mask if served else 4 * nnz_hd + 24 * pieces
+    assert G.groot_plan_query(plan, "csr_bytes_hd") == read
+    assert G.groot_plan_query(plan, "csr_bytes") == read + G.groot_plan_query(plan, "csr_bytes_ld")
+
+
 def test_dense_product_with_numbers_that_are_not_finite(torch_cuda):
     """An infinity or a NaN in X reaches the rows that have its column and no others."""
     n, F = 30020, 100
