@@ -627,11 +627,9 @@ bool upload_dense_rows(groot_plan *pl, int32_t max_F)
     d.n_dense_rows = 0;
     return err == 0;
 }
-}  // namespace
 
-extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
+groot_status upload(groot_plan *plan, int32_t max_F)
 {
-    if (!plan) return fail(GROOT_EINVAL, "groot_plan_upload: NULL plan");
     if (max_F < 4 || max_F > 512 || max_F % 4) return fail(GROOT_EINVAL, "groot_plan_upload: max_F must be a multiple of 4 in [4,512]");
     if (!plan->g) {
         if (max_F <= plan->max_F) return GROOT_OK;
@@ -745,6 +743,18 @@ extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
     plan->max_F = max_F;
     plan->resident = true;
     return GROOT_OK;
+}
+}  // namespace
+
+extern "C" groot_status groot_plan_upload(groot_plan *plan, int32_t max_F)
+{
+    if (!plan) return fail(GROOT_EINVAL, "groot_plan_upload: NULL plan");
+    try {
+        return upload(plan, max_F);
+    } catch (const std::bad_alloc &) {
+        release_device(plan);
+        return fail(GROOT_ENOMEM, "groot_plan_upload: out of host memory");
+    }
 }
 
 namespace {

@@ -4,6 +4,7 @@ exported symbol table."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -25,6 +26,46 @@ def test_library_exports_every_declared_symbol():
     lib = ctypes.CDLL(G.LIB_PATH)
     for name in declared:
         assert hasattr(lib, name), name
+
+
+def test_upload_without_host_memory_is_an_error_and_no_exception(tmp_path):
+    """The first allocation of host memory inside groot_plan_upload fails: GROOT_ENOMEM, no exception through the C entry."""
+    source, driver = tmp_path / "driver.cpp", tmp_path / "driver"
+    source.write_text("""
+        #include <cstdio>
+        #include <cstdlib>
+        #include <new>
+        #include "groot.h"
+        static thread_local int fail_next = 0;
+        void *operator new(std::size_t n)
+        {
+            if (fail_next) { fail_next = 0; throw std::bad_alloc(); }
+            if (void *p = std::malloc(n ? n : 1)) return p;
+            throw std::bad_alloc();
+        }
+        void operator delete(void *p) noexcept { std::free(p); }
+        void operator delete(void *p, std::size_t) noexcept { std::free(p); }
+        int main()
+        {
+            const int64_t rowptr[] = {0, 1, 2};
+            const int32_t col[] = {0, 1};
+            const float val[] = {1.f, 1.f};
+            groot_graph *g = nullptr;
+            groot_plan *plan = nullptr;
+            if (groot_graph_from_csr(2, rowptr, col, val, &g) || groot_spmm_plan(g, 32, &plan)) return 1;
+            fail_next = 1;
+            const int st = groot_plan_upload(plan, 64);
+            std::printf("%d %d %s", st, fail_next, groot_last_error());
+            groot_plan_free(plan);
+            groot_graph_free(g);
+            return 0;
+        }
+    """)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-o", str(driver), str(source), G.LIB_PATH,
+                    "-Wl,--allow-shlib-undefined", f"-Wl,-rpath,{os.path.dirname(G.LIB_PATH)}", "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    run = subprocess.run([str(driver)], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, run.stderr[-500:]
+    assert run.stdout == f"{G.GROOT_ENOMEM} 0 groot_plan_upload: out of host memory"
 
 
 @pytest.mark.parametrize("n,batch,flags", [
