@@ -1314,6 +1314,44 @@ def test_high_degree_rows_as_a_dense_product(torch_cuda, n, n_dense, want, width
         assert_close_to_oracle(Y, Y64, S, f"dense rows n={n} {n_dense} F={F}")
 
 
+def test_dense_product_phase_by_phase_and_from_a_hip_graph(torch_cuda):
+    """The phases one by one, and replays of a captured call on new inputs with eager work between them, give the bits of the
+    whole eager call; each phase writes the rows that it is said to."""
+    torch = torch_cuda
+    n, F = 50020, 64
+    rowptr, col, val, dense = _dense_rows_graph(n, 230, 0.25, np.random.default_rng(4))
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == 230 and 230 * (n // 4) * F >= 2 ** 25
+    X = wl.uniform_features(21, 0, n, F, device="cuda")
+    whole, steps = torch.full((n, F), float("nan"), device="cuda"), torch.full((n, F), float("nan"), device="cuda")
+    G.groot_spmm_execute(plan, X, whole, F)
+    low = torch.from_numpy(np.diff(rowptr) < 32).cuda()
+    G.groot_spmm_execute_phases(plan, X, steps, F, G.GROOT_PHASE_LD)
+    assert torch.equal(~torch.isnan(steps).any(dim=1), low)
+    for phase in (G.GROOT_PHASE_HD, G.GROOT_PHASE_FINISH):
+        G.groot_spmm_execute_phases(plan, X, steps, F, phase)
+        assert torch.equal(steps[low], whole[low])
+    assert torch.equal(steps, whole)
+    Y = torch.empty_like(X)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        G.groot_spmm_execute(plan, X, Y, F)
+    for seed in (22, 23, 24):
+        X.copy_(wl.uniform_features(seed, 0, n, F, device="cuda"))
+        if seed == 23:
+            X[n // 2, 3] = float("inf")                      # the other sweeps of the dense product, too
+        Y.fill_(float("nan"))
+        G.groot_spmm_execute(plan, X, whole, F)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, whole), f"replay with seed {seed}"
+    Y64, S = oracle.spmm_f64(rowptr, col, val, X.cpu().numpy())
+    assert_close_to_oracle(Y.cpu().numpy(), Y64, S, "replay")
+
+
 @pytest.mark.parametrize("n_dense,max_F,said,served", [(500, 12, 500, True), (500, 4, 0, False), (16, 64, 16, False)])
 def test_bytes_that_are_said_to_be_read_with_dense_rows(torch_cuda, n_dense, max_F, said, served):
     """"csr_bytes_hd" of a plan whose widest call computes the dense rows from one bit per column, and of one whose calls
