@@ -28,13 +28,6 @@ __device__ __forceinline__ int64_t plan_degree(const int64_t *__restrict__ rowpt
     return d < 0 ? 0 : d;
 }
 
-__device__ __forceinline__ void plan_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // hist[block * cols + c]
 __global__ __launch_bounds__(kBlock) void plan_count(const int64_t *__restrict__ rowptr, int64_t n, int32_t T,
                                                      int32_t cols, int32_t *__restrict__ hist,
@@ -109,7 +102,7 @@ __global__ __launch_bounds__(kBlock) void plan_scatter(const int64_t *__restrict
     const int64_t wbase = (int64_t)blockIdx.x * kPlanRowsPerBlock + (int64_t)wave * kPlanRowsPerWave;
 
     for (int c = lane; c < cols; c += kWave) s_pos[wave][c] = 0;
-    plan_wave_sync();
+    wave_sync();
     // per-wavefront counts of every column
     for (int k = 0; k < kPlanRowsPerWave / kWave; ++k) {
         const int64_t i = wbase + (int64_t)k * kWave + lane;
@@ -141,7 +134,7 @@ __global__ __launch_bounds__(kBlock) void plan_scatter(const int64_t *__restrict
         const uint64_t m_hd = __ballot(hd), m_ld = __ballot(ld);
         if (hd) hd_rows[s_pos[wave][T + 1] + __popcll(m_hd & lt_mask)] = (int32_t)i;
         if (ld) ld_rows[s_pos[wave][T] + __popcll(m_ld & lt_mask)] = (int32_t)i;
-        plan_wave_sync();
+        wave_sync();
         if (lane == 0) { s_pos[wave][T + 1] += __popcll(m_hd); s_pos[wave][T] += __popcll(m_ld); }
         uint64_t remaining = m_ld;
         while (remaining) {                                  // one turn per distinct degree in this chunk
@@ -149,12 +142,12 @@ __global__ __launch_bounds__(kBlock) void plan_scatter(const int64_t *__restrict
             const int dl = (int)__shfl((int)d, leader);
             const uint64_t peers = __ballot(ld && (int)d == dl);
             if (ld && (int)d == dl) by_degree[s_pos[wave][dl] + __popcll(peers & lt_mask)] = (int32_t)i;
-            plan_wave_sync();
+            wave_sync();
             if (lane == leader) s_pos[wave][dl] += __popcll(peers);
-            plan_wave_sync();
+            wave_sync();
             remaining &= ~peers;
         }
-        plan_wave_sync();
+        wave_sync();
     }
 }
 

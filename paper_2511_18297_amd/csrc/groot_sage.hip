@@ -56,13 +56,6 @@ constexpr int kSgSlots = kSgProdRows * kSgD;                        // slots of 
 constexpr int kSgH = (kSgSlots + kWave - 1) / kWave;                // column indices per lane
 static_assert(kSgProdRows + 1 <= kWave, "row pointers of a producer fit one wavefront");
 
-__device__ __forceinline__ void sage_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also fences global memory, which
 // makes every wavefront wait for all of its loads and stores in flight.
 __device__ __forceinline__ void sage_lds_barrier()
@@ -301,7 +294,7 @@ __global__ __launch_bounds__(kSgThreads) __attribute__((amdgpu_waves_per_eu(kSgT
         }
         const int32_t len = __shfl_down(rel, 1) - rel;           // all lanes take part in the exchange
         if (l < kSgProdRows) s_inv[p][l] = row_weight<W>(len);   // lane r: weight of row r
-        sage_wave_sync();
+        wave_sync();
     };
 
     // ---- aggregation of four simple rows (one per lane group) in two halves, a whole tile apart: the

@@ -74,13 +74,6 @@ typedef unsigned int sp_u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int sp_u2 __attribute__((ext_vector_type(2)));
 typedef float sp_f2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ void sp_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // two fp32 values -> their bf16 roundings (nearest even), packed: a in the low half
 __device__ __forceinline__ unsigned sp_pack2(float a, float b)
 {
@@ -212,7 +205,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
         }
         if (W == kMean && l < kSpRows) s_inv[w][l] = row_weight<kMean>(len_a);
         if (SD && l < kSpRows) s_inv[w][l] = (float)len_a;   // exact: a row that the slots serve has few entries
-        sp_wave_sync();
+        wave_sync();
         return fix_a;
     };
 
@@ -378,11 +371,11 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
             }
             if (fix_cur) patch(tile, false);             // the rows that had no live slots, parked again
             if constexpr (kDrain) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-            sp_wave_sync();
+            wave_sync();
             v4f acc[kNb];
             multiply(acc);
             store(H + (tile << C::kORowShift) * kSpRows, acc, kSpRows);
-            sp_wave_sync();                              // the tile in LDS is free for the next round
+            wave_sync();                              // the tile in LDS is free for the next round
             fix_cur = fix_next;
         }
     }
@@ -397,7 +390,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
             sp_park<kSpBRow, kSpPlane, P>(a_tile, lr, F + 4 * f, own);
         }
         patch(tile, true);                               // rows past the end: no entries
-        sp_wave_sync();
+        wave_sync();
         v4f acc[kNb];
         multiply(acc);
         store(H + (tile << C::kORowShift) * kSpRows, acc, (int)(n - tile * kSpRows));

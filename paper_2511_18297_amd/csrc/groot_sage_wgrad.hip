@@ -48,13 +48,6 @@ constexpr bool wg_folds(int FI, int FO) { return FI * FO < 64 * 64; }    // 64 x
 typedef float wg_f2 __attribute__((ext_vector_type(2)));
 typedef double wg_d2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ void wg_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // the value of lane (l + 8) % 16 of the same 16 lanes
 __device__ __forceinline__ float wg_other_half(float x)
 {
@@ -192,7 +185,7 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                 if (s < kSlots) s_slot[w][s] = ((live_a >> h) & 1) ? ((int64_t)cc[h] << kRowShift) : zero_off;
             }
             if (W == kMean && l < kWgRows) s_inv[w][l] = row_weight<kMean>(len_a);
-            wg_wave_sync();
+            wave_sync();
             return fix_a;
         };
         // row (inside the tile) of X that this lane holds a float4 of in sweep grp; of dZ for contraction group p of the sweep
@@ -327,7 +320,7 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
             //      than slots, or high-degree: their sums come from the side buffer), for which the loop above has
             //      added zeros, and all of the ragged tile.  Outside the loop because the registers that hold its rows
             //      in flight are needed here (inside it they were spilled), and so that its loads are all unconditional.
-            wg_wave_sync();
+            wave_sync();
             static_assert(kWgPending <= kWgFold, "the noted tiles fit between two folds");
             if constexpr (kFold) {
                 if (pending > until_fold) fold_now();
