@@ -136,7 +136,7 @@ __device__ __forceinline__ v4f row_sum_ahead(int64_t s, int64_t e, const int32_t
 // 37,634 pieces F = 128 453 / 420, the offsets no longer computed lane by lane.
 // Rows of 33 and 65 entries take what they took.  Entries meet in the order that
 // they had (by lane group, four at a time, then the tree), so results have the
-// same bits.
+// same bits (at F = 4 for pieces of up to 768 entries: no four of a lane group's).
 // ---------------------------------------------------------------------------
 // gathers of a lane group in flight: no more than a usual piece of 512 entries has for it (F = 4, 18 M entries: with 8 it
 // was 119 us, now 69)

@@ -2,7 +2,7 @@
 //
 // A gather of a feature row for every stored entry reads a row of X as often as high-degree rows name it: on the
 // polarized graph of 262,144 rows 70 times, 9.5 GB at F = 128, and the vector memory units return no more than 23 TB/s
-// (hd_kernel 380 us).  261 of its rows hold 22 % of all columns each, 83 % of the entries of the high-degree rows.  With
+// (hd_kernel 380 us).  Its 320 longest rows hold 20 % of all columns each, 92 % of the entries of the high-degree rows.  With
 // row-uniform weights the sum of such a row is a product of a row of zeros and ones with X: 16, 32 or 64 rows at a time,
 // v_mfma_f32_16x16x4_f32, the zeros and ones expanded from one bit per column, X read once per 64 rows straight into the
 // instruction's operand layout.  Products with 1 are exact and the sums are fp32, as they were.
@@ -382,9 +382,10 @@ size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F)
 }
 
 // A launch and the finishing kernel more than with the gathers: polarized graphs, whole step, us, gathers / dense product, by
-// entries of the dense rows x F: 8 M (16,384 rows, F = 64) 12.5 / 18.7, 15 M (F = 128) 18.1 / 22.0; 24 M (32,768 rows, F = 64)
-// 20.4 / 22.0; 37 M (65,536 rows, F = 32) 29.0 / 27.3, 48 M (32,768 rows, F = 128) 31.1 / 27.3, 74 M (65,536 rows, F = 64) 39.5 / 38.6;
-// 2.1 G (17 M entries, 262,144 rows): F = 8 108 / 80, F = 32 132 / 88, F = 64 223 / 143, F = 128 414 / 260.
+// entries of the dense rows x F: 16,384 rows 7.4 M (F = 64) 12.4 / 18.3, 15 M (128) 17.6 / 21.4, 23 M (200) 24.5 / 26.1; 32,768 rows
+// 22 M (64) 20.0 / 22.6, 43 M (128) 30.9 / 28.6, 68 M (200) 48.2 / 38.8; 65,536 rows 29 M (32) 28.8 / 27.3, 59 M (64) 38.7 / 38.4, 117 M
+// (128) 54.2 / 51.5; 131,072 rows 35 M (8) 38.0 / 38.5, 141 M (32) 54.8 / 47.2, 566 M (128) 134 / 102; 262,144 rows 134 M (8) 90 / 85,
+// 534 M (32) 128 / 92, 1.07 G (64) 220 / 145, 2.1 G (128) 423 / 273.
 bool hd_dense_serves(const DevicePlan &dp, int32_t F)
 {
     return dp.n_dense_rows > 0 && dp.n_cols == dp.n && F >= kDenseMinF && dp.dense_entries * F >= (int64_t)1 << 25;

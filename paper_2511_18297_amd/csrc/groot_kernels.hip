@@ -191,11 +191,14 @@ static bool ld_pipelined(const DevicePlan &dp, int32_t F4, const RowOut *out)
 }
 
 // Whether the pieces of the high-degree rows join the low-degree rows' launch.  In the same launch / in one of their own, us:
-// 374 pieces (polarized degrees) F = 32 15.4 / 19.7, F = 64 13.8 / 18.5; 512 (256-bit multiplier) F = 32 42.2 / 42.7, F = 64
-// 54.3 / 60.2, F = 100 89.5 / 88.5; 512 (4-LUT shape) F = 32 17.6 / 22.2; 771 (Booth) F = 32 50.0 / 48.0, F = 64 61.6 / 69.0;
-// F = 136 183 / 209; 949 (polarized) F = 32 30.3 / 26.1, F = 64 32.2 / 34.0, F = 128 45.0 / 48.4, F = 100 61.1 / 46.9, F = 200
-// 63.7 / 60.2; 1,024 (shape mapped to cells) F = 136 78 / 94; 2,905 (polarized) F = 64 62.2 / 51.5, F = 128 94.8 / 68.1.  (With pieces
-// whose indices were not staged; they are up to a quarter faster since, in either place.)
+//   F = 32: 374 pieces (polarized) 13.6 / 17.4, 512 (256-bit multiplier) 32.2 / 33.6, 646 (Booth) 24.8 / 25.9, 757 (polarized)
+//     18.8 / 18.5, 949 (polarized) 19.4 / 17.8, 1,024 (multiplier) 34.7 / 33.0, (4-LUT shape) 26.7 / 23.3
+//   F = 64: 757 20.8 / 26.5, 949 20.0 / 25.0, 1,024 (multiplier) 48.8 / 52.6, (4-LUT shape, one copy) 33.2 / 31.6, (four) 30.8 / 33.1;
+//     2,048 (4-LUT shape) 56.3 / 53.1, (mapped to cells) 70.8 / 66.7, 2,099 (polarized) 36.9 / 41.0
+//   F = 100: 512 73.8 / 77.2, 646 48.7 / 56.0, 757 27.3 / 32.5, 1,024 (4-LUT shape) 46.3 / 46.4, (mapped to cells) 57.5 / 59.9: the
+//     pieces would gain up to 1,024 here, too; the line is from pieces whose indices were not staged (949 61.1 / 46.9)
+//   F = 128, 200: 771 (Booth) 137 / 149, 238 / 250; 1,024 (4-LUT shape) 48.3 / 49.8, 72.8 / 75.0; more than 1,024 (polarized, beside
+//     dense rows) 55.3 / 51.6, 92.4 / 81.5
 bool ld_takes_hd(const DevicePlan &dp, int32_t F, const RowOut *out)
 {
     const int64_t few = F == 64 || F >= 128 ? 1024 : 512;
@@ -231,12 +234,11 @@ int launch_hd(const DevicePlan &dp, const float *X, float *Y, int32_t F, void *s
     const int64_t n_out = out ? out->n_out : dp.n;
     if (!weights_ok(dp) || !dp.zero_row) return (int)hipErrorInvalidValue;
     hipStream_t st = (hipStream_t)stream;
-    // Runs of 64 pieces from F = 64 on, where a stretch of X is large beside an L2 (polarized graphs, every row of X gathered
-    // 70 times: 65,536 rows F = 128 90 -> 64 us, 262,144 rows F = 128 571 -> 550, F = 256 1,517 -> 1,030; multipliers, whose rows
-    // are gathered once or twice, the same; runs of 16: 566 and 1,335, of 1,024: 582 and 1,073; cutting rows into slices by XCD:
-    // 594 and 1,181).  At F = 32 it costs 2 %.  At the line: 2,048 pieces of a 512-bit multiplier 245 us either way, 2,067 of a
-    // polarized graph 61 with runs and 78 without (F = 128).  Polarized graphs gain below it too (949 pieces 43.5 and 48.7, 374
-    // 25.6 and 30.9), but up to 1,024 pieces ride in the low-degree rows' launch there.
+    // Runs of 64 pieces from F = 64 on, where a stretch of X is large beside an L2.  Whole step, us, with runs / without: polarized
+    // graphs, every row of X gathered 40 to 70 times, explicit weights (with others most such pieces are dense rows): 2,905 pieces
+    // F = 64 40.9 / 44.8, F = 128 56.3 / 76.3, F = 256 106 / 157; 37,634 pieces F = 128 479 / 485, F = 256 992 / 1,097.  Multipliers,
+    // whose rows are gathered once or twice, the same (2,048 pieces, F = 64 235.6 / 235.7); 6,329 pieces of shorter rows F = 128
+    // 194 / 189.  Below the line one or the other: 757 pieces F = 128 41.3 / 33.2, 374 20.3 / 23.2.
     const int32_t run = F4 >= 16 && dp.n_chunks >= 2048 ? 64 : 1;
     const int64_t grid = run > 1 ? (dp.n_chunks + kXcds * run - 1) / (kXcds * run) * (kXcds * run) : dp.n_chunks;
     if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;

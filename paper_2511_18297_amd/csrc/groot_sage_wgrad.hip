@@ -19,8 +19,8 @@
 // sweep has 8 rows (8 lanes to a row): neighbouring rows 2 k and 2 k + 1 sit in the two halves of 16 lanes, which swap
 // half of their float4 (DPP row rotation by 8), giving operands of row 2 k (p = 0) and of row 2 k + 1 (p = 1).
 //
-// What bounds it: at 64 x 64 the fp32 matrix instructions, 128 of 32 cycles per 16 rows and SIMD (2.1 M cycles of the
-// 2.9 M that 8.4 M rows take, at the 2.0 GHz that the chip grants dense fp32 matrix work), on the other widths the memory
+// What bounds it: at 64 x 64 the fp32 matrix instructions, 128 of 32 cycles per 16 rows and SIMD (2.09 M cycles of
+// the 3.15 M counted at 8.4 M rows, at the 2.05 GHz that the chip grants dense fp32 matrix work), on the other widths the memory
 // traffic.  The form before this one passed the operands transposed through LDS, cut into three bf16 pieces, six piece
 // products on v_mfma_f32_16x16x16_bf16, whose inner sums truncate: at 8.4 M rows, carry-save multipliers, whole call,
 // 64 x 64 2,030 us and 1.3e-5 from the 64-bit result, now 1,431 us and 1.1e-6; on the Booth shape, 4.3 M rows, 64 x 32:
