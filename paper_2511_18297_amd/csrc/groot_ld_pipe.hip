@@ -578,6 +578,9 @@ static int64_t rows_beside_sweep(int depth, int32_t F4, int64_t n_rows)
 //   6 and 7 slots: 134 MB (4-LUT, F = 32) 104.8 / 94.4; 271 MB (cells, F = 32) 172.7 / 166.0, (4-LUT, F = 64) 212.2 / 215.4; 424 MB
 //     (4-LUT, F = 100) 369.8 / 364.2; 540 MB (F = 64) 423.9 / 423.6, (cells) 317.5 / 316.4; 844 MB 710.1 / 710.8; 1.1 GB (4-LUT, F = 32)
 //     803 / 811, (cells) 628 / 640
+// (All from the second pass on.  On inputs that no cache holds 5 slots are even at 67 MB and 1.5 to 3 % faster with the compact matrix
+// at 134 MB, 84.9 / 86.1 (F = 64) and 94.6 / 97.0 (F = 32), 4 to 6 % slower at 140 and 167 MB, 105.5 / 99.6 and 109.9 / 105.9; 6 to 8 slots
+// 1 to 2 % slower up to 424 MB.)
 bool compact_pays(const DevicePlan &dp, int32_t F)
 {
     const int64_t line = dp.pipe_depth <= 5 ? (int64_t)192 << 20 : (int64_t)1 << 30;
