@@ -85,13 +85,15 @@ __device__ __forceinline__ float dense_decode(float sum)
 //
 // A wavefront sums a run of kDenseRun units at most, then the four of them meet in LDS, every one adds up a quarter of the tile,
 // (0 + 2) + (1 + 3), and the row's weight times that goes to the quarter's sums, in LDS too (registers for them would cost the third
-// workgroup of a CU, where the pieces of the other rows run: 286 us instead of 273).  So chains of additions stay short, and no sum
-// of more columns than a piece has entries is formed without the weight.
+// workgroup of a CU, where the pieces of the other rows run: 286 us instead of 273).  So chains of additions stay short.
+// With mean weights the ones are 1 / 64 and the weights 64 times as large, both exact: a sum of many columns that the weight will
+// make small does not overflow before (the gathers apply the weight to the few entries of a lane group, up to 128).
 template <int MB, int NV, int W>
 __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const char *__restrict__ X, int32_t F, int64_t n_cols,
                                            int32_t row_tile, int32_t f0, int32_t k_part)
 {
     typedef float vN __attribute__((ext_vector_type(NV)));
+    constexpr float kOne = W == kMean ? 0x1p-6f : 1.f;
     constexpr int kHalves = MB * NV > 8 ? 2 : 1, kNh = NV / kHalves;              // components exchanged at a time: kNh of a row block
     constexpr int kOwn = MB * kNh > kWavesPerBlock ? MB * kNh / kWavesPerBlock : 1;   // of these a wavefront adds up
     typedef float vOwn __attribute__((ext_vector_type(kHalves * kOwn)));
@@ -103,7 +105,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
     const int f = f0 + NV * m;
     if (threadIdx.x < 16 * MB) {
         const int32_t r = row0 + (int32_t)threadIdx.x;
-        s_weight[threadIdx.x] = r < d.n_rows ? row_weight<W>(d.rows[r].row_nnz) : 0.f;
+        s_weight[threadIdx.x] = r < d.n_rows ? row_weight<W>(d.rows[r].row_nnz) / kOne : 0.f;
     }
     const int64_t first = d.n_units * k_part / d.k_parts, behind = d.n_units * (k_part + 1) / d.k_parts;
     const int64_t share = (behind - first + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -128,7 +130,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
         for (int j = 0; j < 8; ++j) {
             float a[MB];
 #pragma unroll
-            for (int b = 0; b < MB; ++b) a[b] = __builtin_bit_cast(float, __builtin_amdgcn_sbfe(w[b], j, 1) & 0x3f800000);
+            for (int b = 0; b < MB; ++b) a[b] = __builtin_bit_cast(float, __builtin_amdgcn_sbfe(w[b], j, 1) & __builtin_bit_cast(int, kOne));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int b = 0; b < MB; ++b)
@@ -197,7 +199,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
 #pragma unroll
                         for (int v = 0; v < NV; ++v)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) acc[b][v][r] = dense_decode(acc[b][v][r]);
+                            for (int r = 0; r < 4; ++r) acc[b][v][r] = dense_decode(acc[b][v][r] / kOne);
                     finite = all_finite();
                 }
             }

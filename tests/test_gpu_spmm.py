@@ -1539,6 +1539,29 @@ def test_dense_product_is_no_less_precise_than_the_gathers(torch_cuda, n, n_dens
     assert off[0] <= off[1], off
 
 
+@pytest.mark.parametrize("F,scale", [(64, 8e36), (12, 3e37), (64, 1e-41)])
+def test_dense_product_of_very_large_and_very_small_numbers(torch_cuda, F, scale):
+    """Rows whose plain sums overflow and whose weighted sums, like the gathers', do not; and numbers below the least normal one,
+    where every weighted sum of a few entries is rounded to 2^-149: no further off than the gathers."""
+    n, n_dense = 50020, 300
+    rowptr, col, val, dense = _dense_rows_graph(n, n_dense, 0.25, np.random.default_rng(6))
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == n_dense and n_dense * (n // 4) * F >= 2 ** 25
+    X = (np.random.default_rng(7).uniform(0.5, 1, (n, F)) * scale).astype(np.float32)
+    Xd = torch_cuda.from_numpy(X).cuda()
+    want, _ = oracle.spmm_f64(*_dense_rows_of(rowptr, col, val, dense), X)
+    off = []
+    for call in (lambda Y: G.groot_spmm_execute(plan, Xd, Y, F), lambda Y: G.groot_spmm_execute_rows(plan, Xd, Y, F, n)):
+        Y = torch_cuda.empty_like(Xd)
+        call(Y)
+        off.append(np.abs(Y.cpu().numpy()[dense].astype(np.float64) - want))
+    if scale > 1:
+        assert all((x <= 1e-5 * want).all() for x in off)
+    else:
+        assert off[0].max() <= off[1].max() and off[0].mean() <= off[1].mean()
+
+
 @pytest.mark.parametrize("how", ["one", "a hundredth", "a stretch", "all"])
 @pytest.mark.parametrize("ones", [False, True])
 def test_dense_product_gives_infinities_and_nan_like_the_gathers(torch_cuda, how, ones):
