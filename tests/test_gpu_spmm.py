@@ -1607,7 +1607,7 @@ def test_dense_product_gives_infinities_and_nan_like_the_gathers(torch_cuda, how
 
 def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torch_cuda):
     """Only the stretch of columns that holds it is summed again (a row that was gathered again by a single workgroup took 3.4
-    times as long); the allowance is for the box."""
+    times as long); the rest is allowance for the clock."""
     n, F = 131072, 128
     rng = np.random.default_rng(13)
     rowptr, col, val, _ = _dense_rows_graph(n, 320, 0.25, rng)
