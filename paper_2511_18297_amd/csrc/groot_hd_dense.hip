@@ -2,270 +2,375 @@
 //
 // A gather of a feature row for every stored entry reads a row of X as often as high-degree rows name it: on the
 // polarized graph of 262,144 rows 70 times, 9.5 GB at F = 128, and the vector memory units return no more than 23 TB/s
-// (hd_kernel 380 us).  Its 320 longest rows hold 20 % of all columns each, 92 % of the entries of the high-degree rows.  With
-// row-uniform weights the sum of such a row is a product of a row of zeros and ones with X: 16, 32 or 64 rows at a time,
-// v_mfma_f32_16x16x4_f32, the zeros and ones expanded from one bit per column, X read once per 64 rows straight into the
-// instruction's operand layout.  Products with 1 are exact and the sums are fp32, as they were.
+// (hd_kernel 380 us).  Its 384 longest rows hold 15 % of all columns each, 95 % of the entries of the high-degree rows.  With
+// row-uniform weights the sum of such a row is a product of a row of zeros and ones with X.
 //
-// The fp32 matrix instruction does 16 rows x 16 features x 4 columns in 32 cycles, the gathers 41 bytes per cycle and CU:
-// a row is cheaper here from about 7 % of the columns on (choose_dense_rows).  One workgroup per CU multiplies, which keeps its
-// matrix cores busy; the other high-degree rows' pieces, in the same launch, take the memory system beside it (220 us together at
-// F = 128, 156 of them matrix instructions; as two launches 155 + 96; with two workgroups per CU, which leave the pieces no
-// room, 252; these times in one chain per wavefront, see dense_args).
+// The product runs on v_mfma_f32_16x16x32_bf16 and is more precise than fp32 sums.  A number of X is cut into three bf16 pieces by
+// truncation, x = hi + mid + lo, exactly: three times 8 significant bits (bf16 has the exponents of fp32).  Products with 1 are
+// exact.  The sums of the hi pieces and those of mid and lo have accumulators of their own: what is added to an accumulator of
+// 24 bits then has 8 bits (or 16), so next to nothing is rounded, and the two meet in one fp32 addition per run of columns.
+// v_mfma_f32_16x16x4_f32 on X as it is, one bit expanded per operand, does 16 rows x 16 features x 32 columns in 256 cycles, the
+// three pieces take 48: polarized graph, F = 128, 320 rows in 155 us that way, 384 in 65 now.
 //
-// 0 x infinity is not 0: where X holds a number that is not finite, rows without that column would get NaN.  So a run of columns
-// whose sums do not all come out finite is swept again (DensePass).  Polarized graph, 262,144 rows, F = 128, whole step, gathers / here:
-// one NaN in X 453 / 364 us, nothing but NaN 453 / 499 (a row gathered again by one workgroup of the finishing kernel: 893);
-// F = 512 2,805 / 1,570 and 2,817 / 2,344; 65,536 rows, F = 64: 46 / 43 and 46 / 44.
+// One workgroup of eight wavefronts per CU takes a stretch of the columns, 64 features and up to 512 rows, so that X is read
+// once and cut once: 128 columns at a time, every wavefront loads and cuts an eighth (32 columns x 32 features; eight columns of a
+// lane are the eight k of an operand, so nothing is transposed) and puts the operands to LDS, from where the wavefronts of a
+// feature half multiply them with the bits of their rows.  One barrier per 128 columns, loads stay in flight across it.
+//
+// What bounds it: the matrix instructions, 1.3 PFLOP/s in the loop where nothing but these instructions on the same data reach 1.9
+// (the clock falls to 1.95 GHz) and 1.5 with the three vector instructions beside each that a wavefront has here.  Without the cut
+// 4 us of 65 less, without the expansion of the bits 3, without the loads none; cutting in one half of the wavefronts before, in the
+// other after the multiplication 3 us more; operands of the next 32 columns read ahead of the matrix instructions, no difference.
+//
+// 0 x infinity is not 0, and below 2^-110 three pieces do not hold a number: the cut checks itself.  Where 128 columns hold a number
+// that it does not reproduce, it is left out there and these columns' exceptions are multiplied once more (`special`).
 #include <algorithm>
 
 #include "groot_device.h"
 
 namespace groot {
 
-constexpr int kDenseUnit = 32;               // columns per step of the loop: eight instructions a row block and feature block
+constexpr int kDenseUnit = 32;               // columns of a matrix instruction
+constexpr int kDenseStep = 128;              // columns between two barriers: the columns of a mask word and its three neighbours
 constexpr int kDenseTile = 64;               // features of a workgroup
-constexpr int kDenseRun = 16;                // units that a wavefront sums in one chain, at most
-// LDS: what the wavefronts exchange (at most eight of a tile's 4 x MB instruction results at a time), the tile's sums, the weights
-template <int MB> constexpr int kDensePartBytes = kWavesPerBlock * (MB > 1 ? 8 : 4) * kWave * 16;
-template <int MB> constexpr int kDenseOwnBytes = MB * 4 * kWave * 16;
-template <int MB> constexpr int kDenseSmemBytes = kDensePartBytes<MB> + kDenseOwnBytes<MB> + 16 * MB * 4;
+constexpr int kDenseWaves = 8;               // wavefronts per workgroup, one workgroup per CU
+constexpr int kDenseRun = 16;                // steps that one chain of matrix instructions sums, at most
+constexpr int kDenseGroup = 16;              // runs that meet in one fp32 partial sum, at most
+constexpr int kDenseMaxBlocks = 8;           // row blocks of 16 per wavefront, at most
+typedef unsigned int dense_u4 __attribute__((ext_vector_type(4)));
+typedef __bf16 dense_b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 dense_b2 __attribute__((ext_vector_type(2)));
 
 struct DenseArgs {
     const HdChunk *rows;                     // [n_rows] the whole row as one piece, slot -1
-    const uint32_t *mask;                    // [unit / 4][padded row][k < 4]: bit 8 (unit % 4) + j is the unit's column 4 j + k
-    float *partials;                         // [k_part and group][padded rows][F]
+    const uint32_t *mask;                    // [step][padded row][kq < 4]: bit 4 u + i is column 32 u + 8 kq + 2 i of the step, bit 16 + 4 u + i the one behind it
+    float *partials;                         // [k_part, unit share and group][padded rows][F]
     int32_t n_rows, tile_rows, padded;       // padded: n_rows in whole tiles
+    int32_t blocks;                          // row blocks of 16 of a wavefront
     int32_t row_tiles, f_tiles, k_parts;
-    int32_t runs, group;                     // a wavefront's stretch in runs, one chain each; runs that meet in one partial sum
-    int32_t n_partials;                      // of a row: k_parts x groups
-    int64_t n_units;                         // columns in units of kDenseUnit
+    int32_t runs, groups;                    // of a workgroup's stretch of columns, one chain each; and the partial sums they meet in
+    int32_t n_partials;                      // of a row
+    int64_t n_steps;                         // columns in units of kDenseStep
     int64_t n_wg;                            // row_tiles x f_tiles x k_parts
 };
 
-// First column of a unit: the last one is moved back to end with the last column (there are kDenseUnit columns or more) and
-// has bits for those only that the unit before has not.
-__device__ __forceinline__ int64_t dense_first_column(int64_t u, int64_t n_units, int64_t n_cols)
+// The ones of the product are 1 / 64, exact: a sum of many columns that the weight will make small does not overflow before (the
+// gathers apply the weight to the few entries of a lane group, up to 128).
+constexpr uint32_t kDenseOneBits = 0x3C80;
+constexpr double kDenseOne = 0x1p-6;
+constexpr float kDenseUp = 0x1p100f, kDenseDown = 0x1p-100f;   // numbers that the cut does not reproduce, below 2^-109, are cut this much larger
+
+// (a, b) -> packed bf16 pieces, a in the low halves.  What is left of each after the third piece is zero, or has its bits in the
+// low half: that part of r is or-ed to `low`; NaN and infinity make z NaN.  a - hi by v_dot2_f32_bf16 with (-1, 0), one instruction
+// instead of an unpacking and a subtraction; a neighbour that is not finite makes NaN of it, too, and that is seen.
+__device__ __forceinline__ void dense_cut(float a, float b, unsigned &hi, unsigned &mid, unsigned &lo, unsigned &low, float &z)
 {
-    return u == n_units - 1 ? n_cols - kDenseUnit : u * kDenseUnit;
+    unsigned pick_a = 0x0000bf80u, pick_b = 0xbf800000u;
+    asm("" : "+s"(pick_a), "+s"(pick_b));                // in registers: as a literal operand 0x0000bf80 came out as (-1, -1)
+    const dense_b2 first = __builtin_bit_cast(dense_b2, pick_a), second = __builtin_bit_cast(dense_b2, pick_b);
+    auto upper = [](float x, float y) {
+        return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, y), __builtin_bit_cast(unsigned, x), 0x07060302u);
+    };
+    hi = upper(a, b);
+    float ra = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dense_b2, hi), first, a, false);
+    float rb = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dense_b2, hi), second, b, false);
+    mid = upper(ra, rb);
+    ra = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dense_b2, mid), first, ra, false);
+    rb = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dense_b2, mid), second, rb, false);
+    lo = upper(ra, rb);
+    low |= __builtin_bit_cast(unsigned, ra) | __builtin_bit_cast(unsigned, rb);
+    z += ra;
+    z += rb;
 }
 
-// What the second and the third sweep over a run of columns multiply, where the first, of X as it is, did not come out finite.
-// Codes: in the place of what is not finite in X a number that counts its kind in a field of its own; their sums become the
-// infinity or NaN that the accumulators start the last sweep with, over what is finite.
-enum DensePass { kDenseCodes, kDenseFinite };
-constexpr float kDenseInf = 1.f, kDenseNegInf = 1024.f, kDenseNaN = 1048576.f;
-static_assert(kDenseRun * kDenseUnit < 1024, "the count of a run fits its field");
-
-// no branches here: 32 values of a lane each
-__device__ __forceinline__ float dense_operand(float x, int pass)
+// whether the cut reproduces x
+__device__ __forceinline__ bool dense_exact(float x)
 {
-    const bool finite = isfinite(x);
-    float code = x > 0.f ? kDenseInf : kDenseNegInf;
-    code = x != x ? kDenseNaN : code;
-    const float where_finite = pass == kDenseFinite ? x : 0.f, elsewhere = pass == kDenseFinite ? 0.f : code;
-    return finite ? where_finite : elsewhere;
+    unsigned hi, mid, lo, low = 0;
+    float z = 0.f;
+    dense_cut(x, 0.f, hi, mid, lo, low, z);
+    return z == z && (low & 0xffff) == 0;
 }
 
-__device__ __forceinline__ float dense_decode(float sum)
+// What is multiplied in place of x: all that the cut reproduces; then, where a step holds anything else, the infinities and NaN (a one
+// in the first piece for +infinity and NaN, in the second for -infinity and NaN), and the very small numbers.
+enum DensePass { kDenseMain, kDenseCodes, kDenseTiny };
+
+// Orders LDS accesses of the workgroup; loads from global memory stay in flight.
+__device__ __forceinline__ void dense_barrier()
 {
-    const uint32_t n = (uint32_t)sum, pos = n % 1024, neg = n / 1024;
-    float inf = pos ? __builtin_inff() : -__builtin_inff();
-    inf = (sum >= kDenseNaN) | ((pos != 0) & (neg != 0)) ? __builtin_nanf("") : inf;
-    return n ? inf : 0.f;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// One workgroup's tile of 16 MB rows x 16 NV features: the columns of a k_part, a quarter for each wavefront.
-// Lane layout of the instruction: A row and B column are lane % 16, k is lane / 16; D rows are 4 (lane / 16) + r.  Component
-// v of the lane's NV features is the operand whose column m is feature NV m + v, so a lane's load of consecutive features
-// serves NV instructions as it is.  fp32 matrix and vector instructions of a SIMD do not overlap and changing between them costs
-// cycles, so the loop has next to no address arithmetic (scalar bases and constant offsets) and expands the bits of MB
-// instructions' rows, then issues their MB NV instructions: with
-// addresses per lane and the bits expanded as the compiler placed them the polarized graph took 195 us, now 155.
-//
-// A wavefront sums a run of kDenseRun units at most, then the four of them meet in LDS, every one adds up a quarter of the tile,
-// (0 + 2) + (1 + 3), and the row's weight times that goes to the quarter's sums, in LDS too (registers for them would cost the third
-// workgroup of a CU, where the pieces of the other rows run: 286 us instead of 273).  So chains of additions stay short.
-// With mean weights the ones are 1 / 64 and the weights 64 times as large, both exact: a sum of many columns that the weight will
-// make small does not overflow before (the gathers apply the weight to the few entries of a lane group, up to 128).
-template <int MB, int NV, int W>
+// One workgroup's tile of 16 MB RG rows x 32 NV features over a stretch of the columns.  Matrix instruction: A row and B column are
+// lane % 16, k = 8 (lane / 16) + e; D rows are 4 (lane / 16) + r.  B column m of half h and component v is feature
+// 32 h NV / 2 + NV m + v.  RG: wavefronts that share the rows; the 4 / RG groups of wavefronts share a step's units of 32 columns.
+template <int MB, int RG, int NV>
 __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const char *__restrict__ X, int32_t F, int64_t n_cols,
                                            int32_t row_tile, int32_t f0, int32_t k_part)
 {
     typedef float vN __attribute__((ext_vector_type(NV)));
-    constexpr float kOne = W == kMean ? 0x1p-6f : 1.f;
-    constexpr int kHalves = MB * NV > 8 ? 2 : 1, kNh = NV / kHalves;              // components exchanged at a time: kNh of a row block
-    constexpr int kOwn = MB * kNh > kWavesPerBlock ? MB * kNh / kWavesPerBlock : 1;   // of these a wavefront adds up
-    typedef float vOwn __attribute__((ext_vector_type(kHalves * kOwn)));
-    v4f *const s_part = (v4f *)smem;                                              // [wavefront][block and component][lane]
-    v4f *const s_own = (v4f *)(smem + kDensePartBytes<MB>);                       // [wavefront][half][own][lane]
-    float *const s_weight = (float *)(smem + kDensePartBytes<MB> + kDenseOwnBytes<MB>);   // [row]
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, m = lane % 16, k4 = lane / 16;
-    const int32_t row0 = row_tile * d.tile_rows;
-    const int f = f0 + NV * m;
-    if (threadIdx.x < 16 * MB) {
-        const int32_t r = row0 + (int32_t)threadIdx.x;
-        s_weight[threadIdx.x] = r < d.n_rows ? row_weight<W>(d.rows[r].row_nnz) / kOne : 0.f;
-    }
-    const int64_t first = d.n_units * k_part / d.k_parts, behind = d.n_units * (k_part + 1) / d.k_parts;
-    const int64_t share = (behind - first + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int64_t u0 = first + wave * share, u1 = u0 + share < behind ? u0 + share : behind;
-    const int64_t run = (share + d.runs - 1) / d.runs;
-
+    constexpr int kUnits = kDenseStep / kDenseUnit, kShares = 4 / RG;
+    dense_u4 (*const s_b)[kUnits][2][NV][3][kWave] = (dense_u4(*)[kUnits][2][NV][3][kWave])smem;    // [2]: two steps
+    __shared__ int32_t s_special[2];                                              // which passes the step needs beside the main one
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, m = lane % 16, kq = lane / 16;
+    const int half = wave % 2, cut_unit = wave / 2, rg = wave / 2 % RG, share = wave / 2 / RG;
+    const int f = f0 + (half * 16 + m) * NV;                                      // first feature of the lane, cutting and storing
     const int64_t row_bytes = (int64_t)F * 4;
-    const uint32_t x_at = (uint32_t)(k4 * (int)row_bytes + 4 * (f < F - NV ? f : F - NV));
-    const uint32_t bits_at = (uint32_t)((row0 + m) * 16 + k4 * 4);
-    auto load = [&](int64_t u, vN (&x)[8], uint32_t (&w)[MB]) {
-        u = u < d.n_units ? u : d.n_units - 1;
-        const char *const base = X + dense_first_column(u, d.n_units, n_cols) * row_bytes;
-        const uint8_t *const bits = (const uint8_t *)d.mask + (u / 4) * d.padded * 16 + u % 4;
+    const uint32_t x_at = (uint32_t)(8 * kq * (int)row_bytes + 4 * (f < F - NV ? f : F - NV));
+    const uint32_t w_at = (uint32_t)(16 * m + 4 * kq), p_at = (uint32_t)(4 * (4 * kq * F + f));
+    const int64_t s0 = d.n_steps * k_part / d.k_parts, s1 = d.n_steps * (k_part + 1) / d.k_parts;
+    const int32_t n_blocks = d.padded / 16, block0 = (row_tile * RG + rg) * MB;   // the last tile may have blocks past the end
+
+    auto load = [&](int64_t s, vN (&x)[8]) {
+        const int64_t col = s * kDenseStep + cut_unit * kDenseUnit;
+        if (col + kDenseUnit <= n_cols) {
+            const char *const base = X + col * row_bytes;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = *(const vN *)((base + 4 * j * row_bytes) + x_at);
+            for (int e = 0; e < 8; ++e) x[e] = *(const vN *)((base + e * row_bytes) + x_at);
+        } else {                                         // past the end: the last column again, there are no bits for it
 #pragma unroll
-        for (int b = 0; b < MB; ++b) w[b] = (bits + bits_at)[256 * b];
-    };
-    v4f acc[MB][NV];
-    auto multiply = [&](const vN (&x)[8], const uint32_t (&w)[MB]) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            float a[MB];
-#pragma unroll
-            for (int b = 0; b < MB; ++b) a[b] = __builtin_bit_cast(float, __builtin_amdgcn_sbfe(w[b], j, 1) & __builtin_bit_cast(int, kOne));
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int b = 0; b < MB; ++b)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) acc[b][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b], x[j][v], acc[b][v], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 8; ++e) {
+                const int64_t c = col + 8 * kq + e < n_cols ? col + 8 * kq + e : n_cols - 1;
+                x[e] = *(const vN *)(X + c * row_bytes + 4 * (f < F - NV ? f : F - NV));
+            }
         }
     };
+    auto load_mask = [&](int64_t s, uint32_t (&w)[MB]) {
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+            const int32_t block = block0 + b < n_blocks ? block0 + b : n_blocks - 1;
+            w[b] = *(const uint32_t *)((const char *)d.mask + (s * d.padded + 16 * block) * 16 + w_at);
+        }
+    };
+    auto put = [&](int buf, int v, const dense_u4 (&op)[3]) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s_b[buf][cut_unit][half][v][q][lane] = op[q];
+    };
+    auto cut = [&](int buf, const vN (&x)[8]) {
+        unsigned low = 0;
+        float z = 0.f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            dense_u4 op[3];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                unsigned q0, q1, q2;
+                dense_cut(x[2 * p][v], x[2 * p + 1][v], q0, q1, q2, low, z);
+                op[0][p] = q0;
+                op[1][p] = q1;
+                op[2][p] = q2;
+            }
+            put(buf, v, op);
+        }
+        if (__ballot(z != z || (low & 0xffff))) {        // put again, without what is not reproduced
+            int32_t kinds = 0;
+#pragma unroll 1
+            for (int v = 0; v < NV; ++v) {
+                dense_u4 op[3];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const float a = v ? x[2 * p][NV - 1] : x[2 * p][0], b = v ? x[2 * p + 1][NV - 1] : x[2 * p + 1][0];
+                    const bool a_ok = dense_exact(a), b_ok = dense_exact(b);
+                    if (__ballot(!isfinite(a) || !isfinite(b))) kinds |= 1 << kDenseCodes;
+                    if (__ballot((!a_ok && isfinite(a)) || (!b_ok && isfinite(b)))) kinds |= 1 << kDenseTiny;
+                    unsigned q0, q1, q2;
+                    dense_cut(a_ok ? a : 0.f, b_ok ? b : 0.f, q0, q1, q2, low, z);
+                    op[0][p] = q0;
+                    op[1][p] = q1;
+                    op[2][p] = q2;
+                }
+                put(buf, v, op);
+            }
+            if (lane == 0) atomicOr(&s_special[buf], kinds);
+        }
+    };
+    // unit u's bits of a row -> the eight ones and zeros of an operand
+    auto ones = [&](uint32_t w, int u) -> dense_b8 {
+        const uint32_t t = w >> (4 * u);
+        dense_u4 a;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = __umul24(t & (0x00010001u << i), kDenseOneBits >> i);
+        return __builtin_bit_cast(dense_b8, a);
+    };
+    v4f hi[MB][NV], rest[MB][NV];
     auto clear = [&]() {
 #pragma unroll
         for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int v = 0; v < NV; ++v) acc[b][v] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int v = 0; v < NV; ++v) hi[b][v] = rest[b][v] = v4f{0.f, 0.f, 0.f, 0.f};
     };
-    auto all_finite = [&]() {
-        float zero = 0.f;
-#pragma unroll
-        for (int b = 0; b < MB; ++b)
+    auto multiply = [&](int buf, const uint32_t (&w)[MB]) {
+        constexpr int kMine = kUnits / kShares;
+        dense_b8 x[2][NV][3];
+        auto read = [&](int k) {
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) zero = __builtin_fmaf(acc[b][v][r], 0.f, zero);
-        return __ballot(zero != 0.f) == 0;               // otherwise NaN
+                for (int q = 0; q < 3; ++q) x[k & 1][v][q] = __builtin_bit_cast(dense_b8, s_b[buf][k * kShares + share][half][v][q][lane]);
+        };
+        read(0);
+        dense_b8 a = ones(w[0], share);
+#pragma unroll
+        for (int k = 0; k < kMine; ++k) {
+            if (k + 1 < kMine) read(k + 1);
+            __builtin_amdgcn_sched_barrier(0);           // the reads stay ahead of this unit's matrix instructions
+#pragma unroll
+            for (int b = 0; b < MB; ++b) {               // the next block's ones beside this one's matrix instructions
+                const int to = b + 1 < MB ? k : k + 1 < kMine ? k + 1 : k;
+                const dense_b8 next = ones(w[b + 1 < MB ? b + 1 : 0], to * kShares + share);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) hi[b][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k & 1][v][0], hi[b][v], 0, 0, 0);
+#pragma unroll
+                for (int q = 1; q < 3; ++q)
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) rest[b][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k & 1][v][q], rest[b][v], 0, 0, 0);
+                a = next;
+                __builtin_amdgcn_sched_barrier(0);       // no more of them at a time: registers
+            }
+        }
     };
-    vN xa[8], xb[8];
-    uint32_t wa[MB], wb[MB];
-    load(u0, xa, wa);
-    bool finite = true;                                  // of the run before: if not, this one is not tried as it is
+    int64_t slot = 0;                                    // partial sum that the present run goes to
+    bool started = false;                                // something has been written there
+    auto partial = [&](int64_t at, int b) -> char * { return (char *)d.partials + (at * d.padded + 16 * (block0 + b)) * row_bytes + p_at; };
+    // The step's exceptions, over the operands in LDS, which have been multiplied.  Every wavefront of the workgroup gets here.
+    auto special = [&](int64_t s, int buf, const uint32_t (&w)[MB], int32_t kinds) {
 #pragma unroll 1
-    for (int32_t i = 0, slot = k_part * (d.n_partials / d.k_parts); i < d.runs; ++i) {
-        const int64_t begin = u0 + i * run, to = begin + run < u1 ? begin + run : u1;
-        clear();
-        if (finite) {
-#pragma unroll 1
-            for (int64_t u = begin; u < to; u += 2) {    // one unit is multiplied while the next is on its way
-                load(u + 1 < to ? u + 1 : u, xb, wb);
-                __builtin_amdgcn_sched_barrier(0);       // the compiler would sink the loads to their use
-                multiply(xa, wa);
-                load(u + 2 < to ? u + 2 : to, xa, wa);   // in the end the next run's first
-                __builtin_amdgcn_sched_barrier(0);
-                if (u + 1 < to) multiply(xb, wb);
-            }
-            finite = all_finite();
-            if (!finite) clear();
-        }
-        if (!finite) {
-#pragma unroll 1
-            for (int pass = kDenseCodes; pass <= kDenseFinite; ++pass) {
-#pragma unroll 1
-                for (int64_t u = begin; u < to; ++u) {
-                    uint32_t any = 0;
-                    load(u, xa, wa);
+        for (int pass = kDenseCodes; pass <= kDenseTiny; ++pass) {
+            if (!(kinds >> pass & 1)) continue;
+            dense_barrier();                             // what is there has been read
+            vN x[8];
+            load(s, x);
+            if (threadIdx.x == 0) s_special[buf] = 0;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
+            for (int v = 0; v < NV; ++v) {
+                dense_u4 op[3] = {};
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            const float x = dense_operand(xa[j][v], pass);
-                            any |= __builtin_bit_cast(uint32_t, x);   // (of a vector's component it would be the first one's)
-                            xa[j][v] = x;
-                        }
-                    if (__ballot(any)) multiply(xa, wa);   // usually nothing to code
+                for (int p = 0; p < 4; ++p) {
+                    const float ab[2] = {x[2 * p][v], x[2 * p + 1][v]};
+                    float t[2];
+                    unsigned plus[2], minus[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const bool nan = ab[i] != ab[i], exact = dense_exact(ab[i]);
+                        plus[i] = nan || ab[i] == __builtin_inff() ? 0x3f80u : 0u;
+                        minus[i] = nan || ab[i] == -__builtin_inff() ? 0x3f80u : 0u;
+                        t[i] = exact || plus[i] || minus[i] ? 0.f : ab[i] * kDenseUp;
+                    }
+                    unsigned q0, q1, q2, low = 0;
+                    float z = 0.f;
+                    dense_cut(t[0], t[1], q0, q1, q2, low, z);
+                    op[0][p] = pass == kDenseCodes ? plus[0] | plus[1] << 16 : q0;
+                    op[1][p] = pass == kDenseCodes ? minus[0] | minus[1] << 16 : q1;
+                    op[2][p] = pass == kDenseCodes ? 0u : q2;
                 }
-                if (pass == kDenseCodes) {
-#pragma unroll
-                    for (int b = 0; b < MB; ++b)
-#pragma unroll
-                        for (int v = 0; v < NV; ++v)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) acc[b][v][r] = dense_decode(acc[b][v][r] / kOne);
-                    finite = all_finite();
-                }
+                put(buf, v, op);
             }
-            load(to, xa, wa);
-        }
-        const int b_own = wave % MB, v_own = wave / MB * kOwn;
-#pragma unroll
-        for (int h = 0; h < kHalves; ++h) {
-            __syncthreads();                             // what was there has been read
+            dense_barrier();
 #pragma unroll
             for (int b = 0; b < MB; ++b)
 #pragma unroll
-                for (int v = 0; v < kNh; ++v) s_part[((wave * MB + b) * kNh + v) * kWave + lane] = acc[b][h * kNh + v];
-            __syncthreads();
-            if (v_own < kNh) {
-                const v4f weight = *(const v4f *)(s_weight + 16 * b_own + 4 * k4);
+                for (int v = 0; v < NV; ++v) {
+                    v4f t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
+#pragma unroll 1
+                    for (int k = 0; k < kUnits / kShares; ++k) {
+                        const int u = k * kShares + share;
+                        const dense_b8 a = ones(w[b], u);
+                        const dense_u4 (*const op)[kWave] = s_b[buf][u][half][v];
+                        t0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(dense_b8, op[0][lane]), t0, 0, 0, 0);
+                        t1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(dense_b8, op[1][lane]), t1, 0, 0, 0);
+                        t1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(dense_b8, op[2][lane]), t1, 0, 0, 0);
+                    }
 #pragma unroll
-                for (int v = 0; v < kOwn; ++v) {
-                    const v4f *const p = s_part + (b_own * kNh + v_own + v) * kWave + lane;
-                    constexpr int kNext = MB * kNh * kWave;
-                    v4f *const own = s_own + ((wave * kHalves + h) * kOwn + v) * kWave + lane;
-                    const v4f sum = weight * ((p[0] + p[2 * kNext]) + (p[kNext] + p[3 * kNext]));
-                    *own = i % d.group ? *own + sum : sum;
+                    for (int r = 0; r < 4; ++r) {
+                        const float inf = t0[r] > 0.f ? __builtin_inff() : -__builtin_inff();
+                        const float code = t0[r] > 0.f && t1[r] > 0.f ? __builtin_nanf("") : t0[r] > 0.f || t1[r] > 0.f ? inf : 0.f;
+                        t0[r] = pass == kDenseCodes ? code : (t0[r] + t1[r]) * kDenseDown;
+                    }
+                    int64_t at = slot;
+                    asm("" : "+s"(at));                  // no addresses kept from one pass to the next: registers
+                    if (block0 + b < n_blocks && f < F) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            float *const p = (float *)(partial(at, b) + r * row_bytes) + v;
+                            *p = started ? *p + t0[r] : t0[r];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            }
+            started = true;
         }
-        if ((i + 1) % d.group && i + 1 < d.runs) continue;
-        if (v_own < kNh && f < F) {
+    };
+
+    vN x[8];
+    uint32_t w[MB];
+    if (threadIdx.x < 2) s_special[threadIdx.x] = 0;
+    load(s0, x);
+    load_mask(s0, w);
+    dense_barrier();
+    cut(0, x);
+    if (s0 + 1 < s1) load(s0 + 1, x);
+    dense_barrier();
+    const int64_t run = (s1 - s0 + d.runs - 1) / d.runs;
+    int64_t s = s0;
+#pragma unroll 1
+    for (int32_t i = 0; i < d.runs; ++i) {
+        const int64_t to = s0 + (i + 1) * run < s1 ? s0 + (i + 1) * run : s1;
+        if (i % kDenseGroup == 0) {
+            slot = ((int64_t)k_part * kShares + share) * d.groups + i / kDenseGroup;
+            started = false;
+        }
+        clear();
+#pragma unroll 1
+        for (; s < to; ++s) {
+            const int buf = (int)(s - s0) & 1;
+            const bool more = s + 1 < s1;
+            uint32_t next_w[MB];
+            load_mask(more ? s + 1 : s, next_w);
+            if (more) {
+                cut(buf ^ 1, x);
+                load(s + 2 < s1 ? s + 2 : s, x);
+            }
+            multiply(buf, w);
+            const int32_t kinds = __builtin_amdgcn_readfirstlane(s_special[buf]);
+            if (kinds) special(s, buf, w, kinds);
+#pragma unroll
+            for (int b = 0; b < MB; ++b) w[b] = next_w[b];
+            dense_barrier();
+        }
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+            if (block0 + b >= n_blocks || f >= F) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                vOwn out;
+                vN *const p = (vN *)(partial(slot, b) + r * row_bytes);
+                vN sum;
 #pragma unroll
-                for (int v = 0; v < kHalves * kOwn; ++v) out[v] = ((const float *)(s_own + (wave * kHalves * kOwn + v) * kWave + lane))[r];
-                const int64_t row = (int64_t)slot * d.padded + row0 + 16 * b_own + 4 * k4 + r;
-                *(vOwn *)(d.partials + row * F + f + v_own) = out;
+                for (int v = 0; v < NV; ++v) sum[v] = hi[b][v][r] + rest[b][v][r];
+                *p = started ? *p + sum : sum;
             }
         }
-        ++slot;
+        started = true;
     }
 }
 
-// Workgroups [0, d.n_wg): the dense rows.  The ones behind: the pieces of the other high-degree rows, which the memory system
-// serves meanwhile.
-template <int MB, int L, int W>
-__global__ __launch_bounds__(kBlock, 3) void hd_dense_kernel(const DenseArgs d, const HdChunk *__restrict__ chunks,
-                                                          const int32_t *__restrict__ col, const char *__restrict__ X,
-                                                          int64_t zero_off, v4f *__restrict__ Y, v4f *__restrict__ partials,
-                                                          int32_t F4, int64_t n_cols)
+template <int MB, int RG>
+__global__ __launch_bounds__(kDenseWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void hd_dense_kernel(
+    const DenseArgs d, const char *__restrict__ X, int32_t F4, int64_t n_cols, int64_t wgs_per_xcd, int remap)
 {
-    constexpr int kSums = kDenseSmemBytes<MB>, kPiece = kHdSmemBytes<L>;
-    __shared__ __align__(16) char smem[kSums > kPiece ? kSums : kPiece];
-    if (blockIdx.x >= d.n_wg) {
-        hd_piece<L, W>(smem, chunks[blockIdx.x - d.n_wg], col, nullptr, X, zero_off, Y, partials, F4, nullptr);
-        return;
-    }
-    const int32_t t = (int32_t)blockIdx.x, row_tile = t % d.row_tiles, f_tile = t / d.row_tiles % d.f_tiles;
+    __shared__ __align__(16) char smem[2 * (kDenseStep / kDenseUnit) * 2 * 2 * 3 * kWave * 16];   // 96 KB
+    // the tiles of a stretch of columns on one XCD, whose L2 they share
+    const int32_t t = (int32_t)logical_block(wgs_per_xcd, remap), row_tile = t % d.row_tiles, f_tile = t / d.row_tiles % d.f_tiles;
     const int32_t k_part = t / d.row_tiles / d.f_tiles, F = 4 * F4;
     if (F - f_tile * kDenseTile > kDenseTile / 2)
-        dense_tile<MB, 4, W>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
+        dense_tile<MB, RG, 2>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
     else
-        dense_tile<MB, 2, W>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
+        dense_tile<MB, RG, 1>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
 }
 
-// Workgroups [0, d.n_rows): one dense row each, its partial sums meet in fp64.  The ones behind: the split rows among the others, as
-// in hd_finish_kernel.
-template <int L>
+// Workgroups [0, d.n_rows): one dense row each, its partial sums meet in fp64 and get the row's weight.  The ones behind: the split
+// rows among the others, as in hd_finish_kernel.
+template <int L, int W>
 __global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs d, const HdSplitRow *__restrict__ split,
                                                                  int64_t n_split, const v4f *__restrict__ partials,
                                                                  v4f *__restrict__ Y, int32_t F4)
@@ -281,6 +386,7 @@ __global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs
         return;
     }
     const int64_t row = d.rows[blockIdx.x].row;
+    const double weight = (double)row_weight<W>(d.rows[blockIdx.x].row_nnz) / kDenseOne;
 #pragma unroll 1
     for (int32_t fb = 0; fb < F4; fb += L) {
         const int32_t ff = fb + f;
@@ -301,35 +407,35 @@ __global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs
             if (g < stride) s_red[threadIdx.x] += s_red[threadIdx.x + stride * L];
             __syncthreads();
         }
-        if (g == 0 && live) Y[row * F4 + ff] = __builtin_convertvector(s_red[f], v4f);
+        if (g == 0 && live) Y[row * F4 + ff] = __builtin_convertvector(s_red[f] * weight, v4f);
         __syncthreads();
     }
 }
 
-// the four mask words of row r and units 4 b .. 4 b + 3, one thread each; padding rows get zeros
+// the four mask words of row r and step b, one thread each; padding rows get zeros
 __global__ __launch_bounds__(kBlock) void dense_mask_kernel(const HdChunk *__restrict__ rows, int32_t n_rows, int32_t padded,
-                                                            const int32_t *__restrict__ col, int64_t n_cols, int64_t n_units,
+                                                            const int32_t *__restrict__ col, int64_t n_steps,
                                                             uint4 *__restrict__ mask)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t b = i / padded;
     const int32_t r = (int32_t)(i % padded);
-    if (4 * b >= n_units) return;
+    if (b >= n_steps) return;
     uint32_t w[4] = {0, 0, 0, 0};
     if (r < n_rows) {
         const HdChunk row = rows[r];
         const int32_t *const c = col + row.begin;
-        const int64_t first = b * 4 * kDenseUnit;
+        const int64_t first = b * kDenseStep;
         int32_t lo = 0, hi = row.len;                    // first entry with a column >= first
         while (lo < hi) {
             const int32_t mid = lo + (hi - lo) / 2;
             if (c[mid] < first) lo = mid + 1; else hi = mid;
         }
-        for (; lo < row.len && c[lo] < first + 4 * kDenseUnit; ++lo) {
-            const int64_t u = c[lo] / kDenseUnit;
-            const int at = (int)(c[lo] - dense_first_column(u, n_units, n_cols));
+        for (; lo < row.len && c[lo] < first + kDenseStep; ++lo) {
+            const int at = (int)(c[lo] - first), e = at % 8;
+            const uint32_t bit = 1u << (4 * (at / kDenseUnit) + e / 2 + 16 * (e % 2));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) w[k] |= at % 4 == k ? 1u << (at / 4 + 8 * (int)(u % 4)) : 0u;
+            for (int k = 0; k < 4; ++k) w[k] |= at / 8 % 4 == k ? bit : 0u;
         }
     }
     mask[i] = uint4{w[0], w[1], w[2], w[3]};
@@ -346,29 +452,22 @@ static DenseArgs dense_args(const DevicePlan &dp, int32_t F)
     d.partials = dp.dense_partials;
     d.n_rows = dp.n_dense_rows;
     d.tile_rows = dp.dense_tile_rows;
-    d.row_tiles = (dp.n_dense_rows + dp.dense_tile_rows - 1) / dp.dense_tile_rows;
-    d.padded = d.row_tiles * dp.dense_tile_rows;
+    const int32_t tiles = (dp.n_dense_rows + dp.dense_tile_rows - 1) / dp.dense_tile_rows;   // a wavefront has a row block of each
+    d.padded = tiles * dp.dense_tile_rows;
+    const int32_t most = dp.dense_tile_rows == 64 ? kDenseMaxBlocks : 1;
+    d.row_tiles = (tiles + most - 1) / most;
+    d.blocks = (tiles + d.row_tiles - 1) / d.row_tiles;
     d.f_tiles = (F + kDenseTile - 1) / kDenseTile;
-    d.n_units = (dp.n_cols + kDenseUnit - 1) / kDenseUnit;
-    // one workgroup per CU while a wavefront has two units or more to sum
-    const int64_t tiles = (int64_t)d.row_tiles * d.f_tiles;
-    int64_t k = kDenseMaxWorkgroups / tiles;
-    const int64_t most = (d.n_units + 2 * kWavesPerBlock - 1) / (2 * kWavesPerBlock);
-    if (k > most) k = most;
+    d.n_steps = (dp.n_cols + kDenseStep - 1) / kDenseStep;
+    const int64_t wgs = (int64_t)d.row_tiles * d.f_tiles;
+    int64_t k = kDenseMaxWorkgroups / wgs;               // one workgroup per CU while it has a step or more
+    if (k > d.n_steps) k = d.n_steps;
     d.k_parts = (int32_t)(k < 1 ? 1 : k);
-    // How long a run is, and how many meet in fp32, so that the error is no larger than that of the gathers, which grows with a
-    // row's pieces.  Error of the dense rows in the 2-norm, U(-1, 1), here / gathers, 1e-7, F = 128: polarized graphs of 32,768 rows
-    // 0.74 / 1.12, 65,536 1.11 / 1.42, 131,072 1.31 / 1.51, 262,144 1.77 / 2.01 (F = 512 1.96 / 2.11); 64 rows of half of 65,536
-    // columns 1.64 / 1.83; 1,024 rows of a twelfth of them 1.10 / 1.20, of a quarter of 20,000 1.06 / 1.22.  In one chain per
-    // wavefront the 262,144 rows were at 4.1 (F = 512: 8.2).  A run costs 2 us: 260 us a step in one chain, 272 in six (F = 128).
-    const double length = (double)dp.dense_entries / dp.n_dense_rows, pieces = length / 512, per_unit = length / d.n_units;
-    const double run = (14 + 1.1 * pieces) / (1 + per_unit);
-    const int64_t share = ((d.n_units + d.k_parts - 1) / d.k_parts + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int64_t units = run < 2 ? 2 : run > kDenseRun ? kDenseRun : (int64_t)run;
-    d.runs = (int32_t)((share + units - 1) / units);
-    d.group = 4 + (int32_t)(pieces < 1024 ? pieces / 8 : 128);
-    d.n_partials = d.k_parts * ((d.runs + d.group - 1) / d.group);
-    d.n_wg = tiles * d.k_parts;
+    const int64_t share = (d.n_steps + d.k_parts - 1) / d.k_parts;
+    d.runs = (int32_t)((share + kDenseRun - 1) / kDenseRun);
+    d.groups = (d.runs + kDenseGroup - 1) / kDenseGroup;
+    d.n_partials = d.k_parts * (64 / dp.dense_tile_rows) * d.groups;
+    d.n_wg = wgs * d.k_parts;
     return d;
 }
 
@@ -384,29 +483,29 @@ size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F)
 }
 
 // A launch and the finishing kernel more than with the gathers: polarized graphs, whole step, us, gathers / dense product, by
-// entries of the dense rows x F: 16,384 rows 7.4 M (F = 64) 12.4 / 18.3, 15 M (128) 17.6 / 21.4, 23 M (200) 24.5 / 26.1; 32,768 rows
-// 22 M (64) 20.0 / 22.6, 43 M (128) 30.9 / 28.6, 68 M (200) 48.2 / 38.8; 65,536 rows 29 M (32) 28.8 / 27.3, 59 M (64) 38.7 / 38.4, 117 M
-// (128) 54.2 / 51.5; 131,072 rows 35 M (8) 38.0 / 38.5, 141 M (32) 54.8 / 47.2, 566 M (128) 134 / 102; 262,144 rows 134 M (8) 90 / 85,
-// 534 M (32) 128 / 92, 1.07 G (64) 220 / 145, 2.1 G (128) 423 / 273.
+// entries of the dense rows x F: 16,384 rows 7.7 M (F = 64) 13.0 / 15.6, 15 M (128) 18.0 / 19.2, 24 M (200) 25.2 / 24.0; 32,768 rows
+// 11 M (32) 17.8 / 15.8, 22 M (64) 20.8 / 20.2, 43 M (128) 31.0 / 26.2, 67 M (200) 48.5 / 33.5; 65,536 rows 9.5 M (8) 20.0 / 21.5, 19 M
+// (16) 29.3 / 24, 38 M (32) 29.4 / 24.0, 76 M (64) 40.8 / 30.0; 131,072 rows 37 M (8) 38.3 / 32.2, 147 M (32) 56 / 41; 262,144 rows
+// 139 M (8) 92 / 59, 557 M (32) 136 / 66.
 bool hd_dense_serves(const DevicePlan &dp, int32_t F)
 {
-    return dp.n_dense_rows > 0 && dp.n_cols == dp.n && F >= kDenseMinF && dp.dense_entries * F >= (int64_t)1 << 25;
+    return dp.n_dense_rows > 0 && dp.n_cols == dp.n && F >= kDenseMinF && dp.dense_entries * F >= (int64_t)1 << 24;
 }
 
 size_t dense_mask_words(const DevicePlan &dp)
 {
     const size_t padded = (size_t)(dp.n_dense_rows + dp.dense_tile_rows - 1) / dp.dense_tile_rows * dp.dense_tile_rows;
-    const size_t units = (size_t)(dp.n_cols + kDenseUnit - 1) / kDenseUnit;
-    return (units + 3) / 4 * padded * 4;
+    const size_t steps = (size_t)(dp.n_cols + kDenseStep - 1) / kDenseStep;
+    return steps * padded * 4;
 }
 
 int launch_dense_mask(const DevicePlan &dp, void *stream)
 {
     const DenseArgs d = dense_args(dp, 4);
-    const int64_t grid = ((d.n_units + 3) / 4 * d.padded + kBlock - 1) / kBlock;
-    if (!grid_ok(grid) || dp.n_cols < kDenseUnit) return (int)hipErrorInvalidConfiguration;
-    dense_mask_kernel<<<dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream>>>(d.rows, d.n_rows, d.padded, dp.col, dp.n_cols,
-                                                                                      d.n_units, (uint4 *)dp.dense_mask);
+    const int64_t grid = (d.n_steps * d.padded + kBlock - 1) / kBlock;
+    if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
+    dense_mask_kernel<<<dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream>>>(d.rows, d.n_rows, d.padded, dp.col, d.n_steps,
+                                                                                      (uint4 *)dp.dense_mask);
     return (int)hipGetLastError();
 }
 
@@ -425,27 +524,29 @@ static int dense_lanes(int32_t F4)
     return L;
 }
 
-// The dense rows, and the pieces of dp (of the other rows) in the same launch.
-int launch_hd_dense(const DevicePlan &dp, const float *X, float *Y, int32_t F, int64_t n_chunks, void *stream)
+int launch_hd_dense(const DevicePlan &dp, const float *X, int32_t F, void *stream)
 {
-    if (dp.weight_mode == kExplicit || !dp.zero_row) return (int)hipErrorInvalidValue;
+    if (dp.weight_mode == kExplicit) return (int)hipErrorInvalidValue;
     const DenseArgs d = dense_args(dp, F);
-    if (!grid_ok(d.n_wg + n_chunks)) return (int)hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)(d.n_wg + n_chunks));
-    hipStream_t st = (hipStream_t)stream;
-    auto launch = [&](auto mb) {
-        constexpr int MB = decltype(mb)::value;
-        auto go = [&](auto kernel) {
-            kernel<<<grid, dim3(kBlock), 0, st>>>(d, dp.chunks, dp.col, (const char *)X, byte_distance(X, dp.zero_row), (v4f *)Y,
-                                                  (v4f *)dp.partials, F / 4, dp.n_cols);
-        };
-        if (dp.weight_mode == kMean) { GROOT_DENSE_L(dense_lanes(F / 4), (go(hd_dense_kernel<MB, kL, kMean>))) }
-        else { GROOT_DENSE_L(dense_lanes(F / 4), (go(hd_dense_kernel<MB, kL, kOnes>))) }
+    if (!grid_ok(d.n_wg)) return (int)hipErrorInvalidConfiguration;
+    const int remap = dp.xcd_remap && d.n_wg % kXcds == 0;
+    auto launch = [&](auto kernel) {
+        kernel<<<dim3((unsigned)d.n_wg), dim3(kDenseWaves * kWave), 0, (hipStream_t)stream>>>(d, (const char *)X, F / 4, dp.n_cols,
+                                                                                              d.n_wg / kXcds, remap);
     };
-    if (dp.dense_tile_rows == 64) launch(std::integral_constant<int, 4>());
-    else if (dp.dense_tile_rows == 32) launch(std::integral_constant<int, 2>());
-    else if (dp.dense_tile_rows == 16) launch(std::integral_constant<int, 1>());
-    else return (int)hipErrorInvalidValue;
+    if (dp.dense_tile_rows == 16) launch(hd_dense_kernel<1, 1>);
+    else if (dp.dense_tile_rows == 32) launch(hd_dense_kernel<1, 2>);
+    else if (dp.dense_tile_rows != 64) return (int)hipErrorInvalidValue;
+    else switch (d.blocks) {
+    case 1: launch(hd_dense_kernel<1, 4>); break;
+    case 2: launch(hd_dense_kernel<2, 4>); break;
+    case 3: launch(hd_dense_kernel<3, 4>); break;
+    case 4: launch(hd_dense_kernel<4, 4>); break;
+    case 5: launch(hd_dense_kernel<5, 4>); break;
+    case 6: launch(hd_dense_kernel<6, 4>); break;
+    case 7: launch(hd_dense_kernel<7, 4>); break;
+    default: launch(hd_dense_kernel<8, 4>); break;
+    }
     return (int)hipGetLastError();
 }
 
@@ -455,8 +556,12 @@ int launch_hd_dense_finish(const DevicePlan &dp, float *Y, int32_t F, void *stre
     const int L = dense_lanes(F / 4);
     const int64_t n_wg = d.n_rows + (dp.n_split_rows + kBlock / L - 1) / (kBlock / L);
     if (!grid_ok(n_wg)) return (int)hipErrorInvalidConfiguration;
-    GROOT_DENSE_L(L, (hd_dense_finish_kernel<kL><<<dim3((unsigned)n_wg), dim3(kBlock), 0, (hipStream_t)stream>>>(
-                         d, dp.split_rows, dp.n_split_rows, (const v4f *)dp.partials, (v4f *)Y, F / 4)));
+    auto launch = [&](auto kernel) {
+        kernel<<<dim3((unsigned)n_wg), dim3(kBlock), 0, (hipStream_t)stream>>>(d, dp.split_rows, dp.n_split_rows,
+                                                                               (const v4f *)dp.partials, (v4f *)Y, F / 4);
+    };
+    if (dp.weight_mode == kMean) { GROOT_DENSE_L(L, (launch(hd_dense_finish_kernel<kL, kMean>))) }
+    else { GROOT_DENSE_L(L, (launch(hd_dense_finish_kernel<kL, kOnes>))) }
     return (int)hipGetLastError();
 }
 

@@ -551,8 +551,12 @@ groot_status upload_layer_hd_side(groot_plan *pl, const int32_t *hd_rows_host, i
 namespace {
 // The high-degree rows that are cheaper as a dense product than by gathers, longest first, and how many are multiplied at a
 // time.  A tile of rows costs what its padded rows times all columns cost, whatever they hold; a gather costs its entry: a tile
-// pays when its rows together hold one in kDenseShare of the columns each, on average.
-constexpr int64_t kDenseShare = 14;
+// pays when its rows together hold one in kDenseShare of the columns each, on average.  64 rows of 262,144 columns at F = 128 are 10 us
+// of matrix instructions; that many gathers of 512 bytes are 1 % of the columns where the last-level cache serves them (7 TB/s) and
+// 2.6 % where the L2s do (up to 23 TB/s, rows that share their columns).  Whole step, us, for shares of 30 / 60 / 100: 262,144 rows, F =
+// 128 (384, 448 and 512 dense rows) 184 / 182 / 176, F = 200 - / 317 / 307, F = 32 68 / 67.5 / 65.6; 131,072 rows, F = 128 (192, 256, 256) 82 /
+// 79 / 79.  A last tile that is less than half full is left to the gathers.
+constexpr int64_t kDenseShare = 50;
 constexpr int64_t kDenseMinEntries = 32768;  // below, the launches are what a call takes
 
 std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<int32_t> &hd_rows, int32_t &tile_rows)
@@ -571,11 +575,11 @@ std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<i
             const size_t end = std::min(rows.size(), first + (size_t)tile_rows);
             int64_t in_tile = 0;
             for (size_t k = first; k < end; ++k) in_tile += rows[k].len;
-            if (in_tile * kDenseShare < g->n * tile_rows) break;
+            if (in_tile * kDenseShare < g->n * tile_rows || (end - first) * 2 < (size_t)tile_rows) break;
             keep = end;
             entries += in_tile;
         }
-        if (keep && entries >= kDenseMinEntries) {
+        if (keep && entries >= kDenseMinEntries && entries >= g->n) {   // fewer: reading X once is more than they read
             rows.resize(keep);
             while (tile_rows > 16 && rows.size() * 2 <= (size_t)tile_rows) tile_rows /= 2;
             return rows;
@@ -790,8 +794,8 @@ extern "C" groot_status groot_spmm_execute_phases(const groot_plan *plan, const 
     }
     const bool together = (phases & GROOT_PHASE_LD) && (phases & GROOT_PHASE_HD) && ld_takes_hd(dp, F);
     if (!err && (phases & GROOT_PHASE_LD)) err = launch_ld(dp, X_dev, Y_dev, F, hip_stream, nullptr, together);
-    if (!err && dense && (phases & GROOT_PHASE_HD)) err = launch_hd_dense(dp, X_dev, Y_dev, F, together ? 0 : dp.n_chunks, hip_stream);
-    if (!err && !dense && !together && (phases & GROOT_PHASE_HD) && dp.n_chunks) err = launch_hd(dp, X_dev, Y_dev, F, hip_stream);
+    if (!err && !together && (phases & GROOT_PHASE_HD) && dp.n_chunks) err = launch_hd(dp, X_dev, Y_dev, F, hip_stream);
+    if (!err && dense && (phases & GROOT_PHASE_HD)) err = launch_hd_dense(dp, X_dev, F, hip_stream);
     if (!err && dense && (phases & GROOT_PHASE_FINISH)) err = launch_hd_dense_finish(dp, Y_dev, F, hip_stream);
     if (!err && !dense && (phases & GROOT_PHASE_FINISH) && dp.n_split_rows) err = launch_hd_finish(dp, Y_dev, F, hip_stream);
     if (err) return fail(GROOT_EHIP, std::string("groot_spmm_execute: launch failed: ") + hip_error_text(err));

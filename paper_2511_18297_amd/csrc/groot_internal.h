@@ -187,7 +187,7 @@ bool hd_dense_serves(const DevicePlan &dp, int32_t F);
 size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F);
 size_t dense_mask_words(const DevicePlan &dp);
 int launch_dense_mask(const DevicePlan &dp, void *stream);
-int launch_hd_dense(const DevicePlan &dp, const float *X, float *Y, int32_t F, int64_t n_chunks, void *stream);
+int launch_hd_dense(const DevicePlan &dp, const float *X, int32_t F, void *stream);
 int launch_hd_dense_finish(const DevicePlan &dp, float *Y, int32_t F, void *stream);
 // col[p] = ids[col[p]] for p < nnz, in place (a part's local columns -> rows of the whole graph's feature matrix)
 int launch_col_map(int32_t *col, int64_t nnz, const int64_t *ids, void *stream);

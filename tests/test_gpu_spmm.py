@@ -1619,3 +1619,46 @@ def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torc
     finite = _best_time(torch_cuda, run)
     X[n // 3, 5] = float("nan")
     assert _best_time(torch_cuda, run) < 1.7 * finite
+
+
+@pytest.mark.parametrize("n,n_dense,share,F", [(16384, 64, 0.3, 60), (16385, 100, 0.3, 68), (16511, 192, 0.2, 100), (16512, 256, 0.2, 32),
+                                               (20000, 320, 0.2, 96), (20001, 384, 0.2, 64), (20033, 448, 0.1, 128), (9999, 512, 0.2, 160),
+                                               (12345, 576, 0.2, 64), (30001, 1100, 0.05, 132), (200001, 32, 0.2, 300),
+                                               (200001, 16, 0.2, 512), (540000, 1024, 0.021, 512)])
+def test_dense_product_in_tiles_of_every_height(torch_cuda, n, n_dense, share, F):
+    """16 to 512 rows to a workgroup and several workgroups' worth, columns that end anywhere in a step of 128, stretches of one step
+    and of several runs, one and two partial sums per stretch, feature tiles of both kinds; features of very small numbers and of
+    numbers that three bf16 pieces do not hold among the others.  Against fp64: the pieces are exact and what their accumulators
+    round away is below 2^-24 of the running sum per matrix instruction, so 2^-21 of the absolute sum is ample; 2^-148 where the
+    result itself is rounded to multiples of 2^-149."""
+    torch = torch_cuda
+    rng = np.random.default_rng(n)
+    length = np.ones(n, np.int64)
+    dense = np.sort(rng.choice(n, n_dense, replace=False))
+    length[dense] = int(share * n)
+    rowptr = np.concatenate([[0], np.cumsum(length)])
+    col = np.repeat(np.arange(n, dtype=np.int32), length)
+    for r in dense:
+        first = np.sort(rng.choice(n - 1, min(64, length[r]), replace=False))   # a step of the columns apart, from a random place on
+        step = max(1, (n - 1) // length[r])
+        c = np.unique((first[0] + np.arange(length[r]) * step + rng.integers(0, step, length[r])) % n) if step > 1 else None
+        if c is None or c.size != length[r]:
+            c = np.sort(rng.permutation(n)[:length[r]])
+        col[rowptr[r]:rowptr[r + 1]] = c
+    val = np.repeat(np.float32(1) / length.astype(np.float32), length)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    served = G.groot_plan_query(plan, "dense_rows")
+    assert served in (n_dense, n_dense // 64 * 64) and served * int(share * n) * F >= 2 ** 24
+    X = torch.empty((n, F), device="cuda").uniform_(-1, 1, generator=torch.Generator(device="cuda").manual_seed(n))
+    X[:, 1] *= 2.0 ** -112
+    X[:, F - 3] *= 2.0 ** -135
+    X[::97, F - 1] *= 2.0 ** -130
+    Y = torch.full((n, F), float("nan"), device="cuda")
+    G.groot_spmm_execute(plan, X, Y, F)
+    assert torch.isfinite(Y).all()
+    for r in rng.choice(dense, 40):
+        x = X[torch.from_numpy(col[rowptr[r]:rowptr[r + 1]].astype(np.int64)).cuda()].double()
+        w = float(val[rowptr[r]])
+        err = (Y[r].double() - x.sum(0) * w).abs()
+        assert (err <= 2.0 ** -21 * w * x.abs().sum(0) + 2.0 ** -148).all(), (r, err.max().item())
