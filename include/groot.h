@@ -410,8 +410,9 @@ void groot_parts_free(groot_parts *parts);
  * The result owns its device arrays (groot_dev_part_view; layout of the
  * sub-graph: rowptr int64 [n_owned + n_halo + 1], col int32 [nnz] local ids,
  * val float [nnz] or NULL when the graph's weights are row-uniform,
- * global_id int64 [n_owned + n_halo]).  Allocates device memory (4 bytes per
- * node of the whole graph as scratch, freed before it returns) and
+ * global_id int64 [n_owned + n_halo]).  Allocates device memory (as scratch,
+ * freed before it returns: 1.25 bytes per node of the whole graph,
+ * 1.5 with part_of_dev, and 8 per node of the part) and
  * synchronises hip_stream.
  * Errors: EINVAL (NULL, plan not resident, P < 1, P > N, p or a part_of entry
  *   outside [0,P), unknown flags); ENOMEM (host or device); EHIP.

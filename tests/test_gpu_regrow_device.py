@@ -50,7 +50,7 @@ def _check_part(torch, plan, rowptr, col, val, part_of, P, p, flags, weight_mode
     return part, want
 
 
-@pytest.mark.parametrize("n,batch,P", [(2, 1, 2), (8, 1, 5), (16, 2, 16), (32, 3, 4), (64, 1, 3)])
+@pytest.mark.parametrize("n,batch,P", [(2, 1, 2), (8, 1, 5), (16, 2, 16), (32, 3, 4), (64, 1, 3), (55, 1, 7), (63, 1, 4), (71, 2, 3)])
 @pytest.mark.parametrize("flags", [G.GROOT_REGROW, 0])
 def test_multiplier_default_rule(torch_cuda, n, batch, P, flags):
     """The built-in rule (p-th contiguous slice of every copy) on carry-save multipliers; the 32-bit x 3 and
@@ -101,6 +101,32 @@ def test_user_parts_weight_modes_and_directed_graph(torch_cuda):
     # the only part is the whole graph
     part, want = _check_part(torch_cuda, plan, s.rowptr, s.col, w, part_of, 1, 0, G.GROOT_REGROW, 2, False, "one part")
     assert want["n_halo"] == 0 and np.array_equal(want["rowptr"], s.rowptr)
+
+
+def test_more_copies_than_a_grid_has_rows_and_more_rows_than_one_scan_step(torch_cuda):
+    """Node sets as bits: 70,000 copies (the built-in rule, which then needs the bits of the part as well; 39 workgroups of
+    32,768 nodes) and parts of more than 4.2 M rows, whose row pointers take a scan of their own.  A part that is the whole graph
+    is the graph."""
+    aig = wl.csa_multiplier_aig(2)
+    copies = 70000
+    rowptr, col, val, _ = oracle.csr_build(aig.type, aig.fanin0, aig.fanin1, copies)
+    plan = _resident_plan(G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, copies))
+    part_of = oracle.part_of_default(len(rowptr) - 1, aig.num_nodes, 3)
+    for p in (0, 2):
+        _check_part(torch_cuda, plan, rowptr, col, val, part_of, 3, p, G.GROOT_REGROW, 1, True, "70,000 copies")
+    aig = wl.csa_multiplier_aig(512)
+    rowptr, col, val, _ = oracle.csr_build(aig.type, aig.fanin0, aig.fanin1, 1)     # rows of 513 entries are searched, not walked
+    plan = _resident_plan(G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 1))
+    part_of = oracle.part_of_default(len(rowptr) - 1, aig.num_nodes, 3)
+    for p in range(3):
+        _check_part(torch_cuda, plan, rowptr, col, val, part_of, 3, p, G.GROOT_REGROW, 1, True, "csa512")
+    g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 3)
+    view, plan = G.groot_graph_view(g), _resident_plan(g)
+    for part_of in (None, torch_cuda.zeros(view["n"], dtype=torch_cuda.int32, device="cuda")):
+        print("device regrow: the whole of 512 bits x 3", flush=True)
+        got = G.groot_dev_part_download(G.groot_partition_regrow_device(plan, 1, 0, part_of))
+        assert np.array_equal(got["rowptr"], view["rowptr"]) and np.array_equal(got["col"], view["col"])
+        assert np.array_equal(got["global_id"], np.arange(view["n"]))
 
 
 @pytest.mark.parametrize("P", [1, 2, 7])
