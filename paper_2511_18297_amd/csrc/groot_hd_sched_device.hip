@@ -4,6 +4,7 @@
 // partial-sum slots, and the pieces run in the order of their first column (pieces of different rows that read
 // the same stretch of feature rows then run close together).  Integer work; the arrays are bit-identical to what
 // the host builds from the same rows (groot_spmm_plan): pieces in row order, then a stable sort by first column.
+#include <algorithm>
 #include <cstring>
 
 #include <hip/hip_runtime.h>
@@ -22,24 +23,10 @@ __device__ __forceinline__ int64_t hs_pieces(int64_t d, int64_t chunk)
     return p < 1 ? 1 : p;
 }
 
-// per high-degree row k: number of pieces, of partial-sum slots (0 for a single piece), 1 if it is split
-__global__ __launch_bounds__(kBlock) void hs_count(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ hd_rows,
-                                                   const int64_t *__restrict__ n_hd, int64_t chunk, int64_t *__restrict__ pieces,
-                                                   int64_t *__restrict__ slots, int64_t *__restrict__ split)
-{
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= *n_hd) return;
-    const int64_t r = hd_rows[k], d = rowptr[r + 1] - rowptr[r];
-    const int64_t p = hs_pieces(d < 0 ? 0 : d, chunk);
-    pieces[k] = p;
-    slots[k] = p > 1 ? p : 0;
-    split[k] = p > 1 ? 1 : 0;
-}
-
-// Exclusive prefix sums of the three arrays in place (one workgroup walks them in runs of its size), the totals and
-// the number of entries of all high-degree rows.
+// Before every high-degree row: pieces, partial-sum slots (none for a row of a single piece) and split rows (one workgroup walks
+// the rows in runs of its size); the totals and the number of entries of all high-degree rows.
 __global__ __launch_bounds__(1024) void hs_scan(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ hd_rows,
-                                                const int64_t *__restrict__ n_hd_dev, int64_t *__restrict__ pieces,
+                                                const int64_t *__restrict__ n_hd_dev, int64_t chunk, int64_t *__restrict__ pieces,
                                                 int64_t *__restrict__ slots, int64_t *__restrict__ split,
                                                 HdTotals *__restrict__ totals)
 {
@@ -50,13 +37,19 @@ __global__ __launch_bounds__(1024) void hs_scan(const int64_t *__restrict__ rowp
     if (threadIdx.x < 4) s_carry[threadIdx.x] = 0;
     __syncthreads();
     int64_t nnz = 0;
+    auto row_of = [&](int64_t k) -> int64_t { return k < n_hd ? hd_rows[k] : 0; };
+    int64_t row = row_of(threadIdx.x);
     for (int64_t base = 0; base < n_hd; base += 1024) {
         const int64_t k = base + threadIdx.x;
+        const int64_t r = row;
+        row = row_of(k + 1024);                          // of the next run, beside this run's row pointers
         int64_t v[3] = {0, 0, 0};
         if (k < n_hd) {
-            v[0] = pieces[k]; v[1] = slots[k]; v[2] = split[k];
-            const int64_t r = hd_rows[k];
-            nnz += rowptr[r + 1] - rowptr[r];
+            const int64_t d = rowptr[r + 1] - rowptr[r];
+            v[0] = hs_pieces(d < 0 ? 0 : d, chunk);
+            v[1] = v[0] > 1 ? v[0] : 0;
+            v[2] = v[0] > 1 ? 1 : 0;
+            nnz += d;
         }
         int64_t incl[3];
 #pragma unroll
@@ -106,7 +99,7 @@ __global__ __launch_bounds__(1024) void hs_scan(const int64_t *__restrict__ rowp
 }
 
 // One thread per high-degree row writes its pieces (in row order), its split-row record, the sort keys and the
-// identity permutation; the *_rank arrays name the row by its place k in hd_rows instead of its id.
+// identity permutation (order may be NULL); the *_rank arrays name the row by its place k in hd_rows instead of its id.
 __global__ __launch_bounds__(kBlock) void hs_fill(const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                                   const int32_t *__restrict__ hd_rows, int64_t n_hd, int64_t chunk,
                                                   const int64_t *__restrict__ piece_off, const int64_t *__restrict__ slot_off,
@@ -139,7 +132,7 @@ __global__ __launch_bounds__(kBlock) void hs_fill(const int64_t *__restrict__ ro
         ch.row = (int32_t)k;
         chunks_rank[o + c] = ch;
         keys[o + c] = ch.len > 0 ? col[ch.begin] : 0x7fffffff;
-        order[o + c] = (int32_t)(o + c);
+        if (order) order[o + c] = (int32_t)(o + c);
     }
 }
 
@@ -151,6 +144,43 @@ __global__ __launch_bounds__(kBlock) void hs_permute(const HdChunk *__restrict__
     if (c >= n) return;
     out[c] = in[order[c]];
     out_rank[c] = in_rank[order[c]];
+}
+
+// hs_permute for few pieces, which finds their order as well: a piece's place is the number of pieces with a smaller key, or
+// the same key and before it.  A wavefront counts for kRankPieces pieces at a time, 64 keys per comparison, kRankAhead loads in
+// flight.
+constexpr int kRankPieces = 4, kRankAhead = 8;
+__global__ __launch_bounds__(kBlock) void hs_rank(const HdChunk *__restrict__ in, const HdChunk *__restrict__ in_rank,
+                                                  const int32_t *__restrict__ keys, int32_t n,
+                                                  HdChunk *__restrict__ out, HdChunk *__restrict__ out_rank)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int32_t first = (blockIdx.x * kWavesPerBlock + wave) * kRankPieces;
+    if (first >= n) return;
+    int32_t mine[kRankPieces], place[kRankPieces];
+#pragma unroll
+    for (int i = 0; i < kRankPieces; ++i) {
+        mine[i] = keys[first + i < n ? first + i : n - 1];
+        place[i] = 0;
+    }
+    for (int32_t j0 = 0; j0 < n; j0 += kRankAhead * kWave) {
+        int32_t key[kRankAhead];
+#pragma unroll
+        for (int a = 0; a < kRankAhead; ++a) key[a] = keys[j0 + a * kWave + lane < n ? j0 + a * kWave + lane : n - 1];
+#pragma unroll
+        for (int a = 0; a < kRankAhead; ++a) {
+            const int32_t j = j0 + a * kWave + lane;
+#pragma unroll
+            for (int i = 0; i < kRankPieces; ++i)
+                place[i] += __popcll(__ballot(j < n && (key[a] < mine[i] || (key[a] == mine[i] && j < first + i))));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kRankPieces; ++i)
+        if (lane == i && first + i < n) {
+            out[place[i]] = in[first + i];
+            out_rank[place[i]] = in_rank[first + i];
+        }
 }
 
 struct Tmp {                                             // device memory freed on scope exit
@@ -168,7 +198,24 @@ struct Tmp {                                             // device memory freed 
     }
 };
 
+__global__ __launch_bounds__(kBlock) void plan_finish(float *__restrict__ zero_row, int32_t *__restrict__ dst,
+                                                      const int32_t *__restrict__ src, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n || i < kZeroRowFloats + kTrashFloats;
+         i += (int64_t)gridDim.x * kBlock) {
+        if (i < kZeroRowFloats + kTrashFloats) zero_row[i] = 0.f;
+        if (i < n) dst[i] = src[i];
+    }
+}
+
 }  // namespace
+
+int launch_plan_finish(float *zero_row, int32_t *dst, const int32_t *src, int64_t n, void *stream)
+{
+    const int64_t most = std::max<int64_t>(n, kZeroRowFloats + kTrashFloats), grid = (most + kBlock - 1) / kBlock;
+    plan_finish<<<dim3((unsigned)std::min<int64_t>(grid, 4096)), dim3(kBlock), 0, (hipStream_t)stream>>>(zero_row, dst, src, n);
+    return (int)hipGetLastError();
+}
 
 void free_device_hd_schedule(DeviceHdSchedule &s)
 {
@@ -194,11 +241,8 @@ int launch_hd_schedule_count(const int64_t *rowptr_dev, const int32_t *hd_rows_d
         free_hd_counts(c);
         return kErrOutOfDeviceMemory;
     }
-    if (most > 0)
-        hs_count<<<dim3((unsigned)((most + kBlock - 1) / kBlock)), dim3(kBlock), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd_dev,
-                                                                                       hd_chunk < 64 ? 64 : hd_chunk, c.pieces, c.slots,
-                                                                                       c.split);
-    hs_scan<<<dim3(1), dim3(1024), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd_dev, c.pieces, c.slots, c.split, totals_dev);
+    hs_scan<<<dim3(1), dim3(1024), 0, st>>>(rowptr_dev, hd_rows_dev, n_hd_dev, hd_chunk < 64 ? 64 : hd_chunk, c.pieces, c.slots, c.split,
+                                            totals_dev);
     *out = c;
     return (int)hipGetLastError();
 }
@@ -223,8 +267,12 @@ int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev,
     HdChunk *raw = nullptr, *raw_rank = nullptr;
     int32_t *keys = nullptr, *keys_sorted = nullptr, *order = nullptr, *order_sorted = nullptr;
     DeviceHdSchedule s;
+    // Up to 5,120 pieces their order is counted out, n^2 / 64 comparisons in one launch (100 pieces 3.4 us, about 4,200 13.5,
+    // 8,200 38), above it is sorted, three or four launches and hs_permute (100 pieces 11.5 us, 4,200 23)
+    const bool count_out = n_chunks <= 5120;
     if (!tmp.get(&raw, (size_t)n_chunks) || !tmp.get(&raw_rank, (size_t)n_chunks) || !tmp.get(&keys, (size_t)n_chunks) ||
-        !tmp.get(&keys_sorted, (size_t)n_chunks) || !tmp.get(&order, (size_t)n_chunks) || !tmp.get(&order_sorted, (size_t)n_chunks))
+        (!count_out && (!tmp.get(&keys_sorted, (size_t)n_chunks) || !tmp.get(&order, (size_t)n_chunks) ||
+                        !tmp.get(&order_sorted, (size_t)n_chunks))))
         return kErrOutOfDeviceMemory;
     auto own = [&](auto **p, size_t count) {
         return dev_alloc((void **)p, (count ? count : 1) * sizeof(**p)) == 0;
@@ -238,18 +286,24 @@ int launch_hd_schedule_device(const int64_t *rowptr_dev, const int32_t *col_dev,
     hs_fill<<<dim3(grid_rows), dim3(kBlock), 0, st>>>(rowptr_dev, col_dev, hd_rows_dev, n_hd, chunk, pieces, slots, split, raw,
                                                       raw_rank, keys, order, s.split_rows, s.split_rows_rank);
     e = hipGetLastError();
+    if (e == hipSuccess && count_out) {
+        constexpr int kPer = kWavesPerBlock * kRankPieces;
+        hs_rank<<<dim3((unsigned)((n_chunks + kPer - 1) / kPer)), dim3(kBlock), 0, st>>>(raw, raw_rank, keys, (int32_t)n_chunks, s.chunks,
+                                                                                      s.chunks_rank);
+        e = hipGetLastError();
+    }
     // stable sort of the pieces by their first column: radix sort of (key, position) pairs
     size_t sort_bytes = 0;
     void *sort_tmp = nullptr;
-    if (e == hipSuccess)
+    if (e == hipSuccess && !count_out)
         e = rocprim::radix_sort_pairs(nullptr, sort_bytes, keys, keys_sorted, order, order_sorted, (size_t)n_chunks, 0, 32, st);
-    if (e == hipSuccess && !tmp.get((char **)&sort_tmp, sort_bytes)) {
+    if (e == hipSuccess && !count_out && !tmp.get((char **)&sort_tmp, sort_bytes)) {
         free_device_hd_schedule(s);
         return kErrOutOfDeviceMemory;
     }
-    if (e == hipSuccess)
+    if (e == hipSuccess && !count_out)
         e = rocprim::radix_sort_pairs(sort_tmp, sort_bytes, keys, keys_sorted, order, order_sorted, (size_t)n_chunks, 0, 32, st);
-    if (e == hipSuccess) {
+    if (e == hipSuccess && !count_out) {
         hs_permute<<<dim3((unsigned)((n_chunks + kBlock - 1) / kBlock)), dim3(kBlock), 0, st>>>(raw, raw_rank, order_sorted,
                                                                                             n_chunks, s.chunks, s.chunks_rank);
         e = hipGetLastError();

@@ -1394,22 +1394,23 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         std::unique_ptr<groot_plan> pl(new groot_plan);
         // lists on the device; only the high-degree rows and the degree offsets are needed here
         // sizes: the two counts, the T + 1 degree offsets, the totals of the HD schedule, the rows that the compact matrix cannot code
-        DevBuf row_class, hd_rows, ld_rows, by_degree, sizes;
-        constexpr int32_t kTotals = (int32_t)(sizeof(HdTotals) / 8);
+        // of the lists only the high-degree rows are needed, and of those by degree the ones too long for the pipelined kernel
+        DevBuf hd_rows, by_degree, sizes;
+        constexpr int32_t kTotals = (int32_t)(sizeof(HdTotals) / 8), kLonger = kPipeMinDepth + 1;
         struct Counts {
             HdCounts c;
             ~Counts() { free_hd_counts(c); }
         } counts;
-        if (row_class.alloc((size_t)n) || hd_rows.alloc((size_t)n * 4) || ld_rows.alloc((size_t)n * 4) ||
-            by_degree.alloc((size_t)n * 4) || sizes.alloc((size_t)(T + 3 + kTotals + 1) * 8))
+        const int64_t most_hd = std::min(n, part->d.nnz / T), most_longer = std::min(n, part->d.nnz / kLonger);
+        if (hd_rows.alloc((size_t)most_hd * 4) || by_degree.alloc((size_t)most_longer * 4) ||
+            sizes.alloc((size_t)(T + 3 + kTotals + 1) * 8))
             return fail(GROOT_ENOMEM, std::string(who) + "device allocation of the plan lists failed");
-        int err = launch_plan_device(part->d.rowptr, n, T, row_class.as<uint8_t>(), hd_rows.as<int32_t>(),
-                                     ld_rows.as<int32_t>(), by_degree.as<int32_t>(), sizes.as<int64_t>() + 2,
-                                     sizes.as<int64_t>(), hip_stream, false);
+        int err = launch_plan_device(part->d.rowptr, n, T, nullptr, hd_rows.as<int32_t>(), nullptr, by_degree.as<int32_t>(),
+                                     sizes.as<int64_t>() + 2, sizes.as<int64_t>(), hip_stream, false, kLonger);
         if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, std::string(who) + "scratch allocation failed");
         if (err) return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
         HdTotals *const totals_dev = (HdTotals *)(sizes.as<int64_t>() + T + 3);
-        err = launch_hd_schedule_count(part->d.rowptr, hd_rows.as<int32_t>(), sizes.as<int64_t>(), std::min(n, part->d.nnz / T),
+        err = launch_hd_schedule_count(part->d.rowptr, hd_rows.as<int32_t>(), sizes.as<int64_t>(), most_hd,
                                        tuning().hd_chunk, hip_stream, totals_dev, &counts.c);
         if (err == kErrOutOfDeviceMemory) return fail(GROOT_ENOMEM, std::string(who) + "device allocation of the HD schedule failed");
         if (err) return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
@@ -1437,18 +1438,13 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         groot_status st;
         if ((st = to_device<float>(&d.zero_row, nullptr, kZeroRowFloats + kTrashFloats, "zero row")) != GROOT_OK ||
             (st = to_device<float>(&d.partials, nullptr, (size_t)sched.n_partials * max_F, "HD partial sums")) != GROOT_OK ||
-            (st = to_device<float>(&d.hd_agg, nullptr, (size_t)n_hd * max_F, "high-degree sums of the fused layer")) != GROOT_OK ||
-            (st = to_device<int32_t>(&d.hd_rows, nullptr, (size_t)n_hd, "high-degree row list")) != GROOT_OK) {
+            (st = to_device<float>(&d.hd_agg, nullptr, (size_t)n_hd * max_F, "high-degree sums of the fused layer")) != GROOT_OK) {
             std::string keep = groot_last_error();
             release_device(pl.get());
             set_error(keep);
             return st;
         }
-        if ((err = device_zero(d.zero_row, (kZeroRowFloats + kTrashFloats) * sizeof(float), hip_stream)) ||
-            (n_hd && (err = device_copy(d.hd_rows, hd_rows.p, (size_t)n_hd * 4, hip_stream)))) {
-            release_device(pl.get());
-            return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
-        }
+        d.hd_rows = (int32_t *)hd_rows.release();
         bool compress = false;
         d.n_hd_rows = n_hd;
         d.n = d.n_cols = n;
@@ -1475,14 +1471,16 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
             d.compact_always = knob == 2;
             compress = ld_builds_compact(d, max_F, knob);
             const size_t room = (size_t)d.n_mid_rows + (compress ? csr_bad_capacity(n) : 0);
-            if (room) {
-                if ((st = to_device<int32_t>(&d.mid_rows, nullptr, room, "long low-degree rows")) != GROOT_OK ||
-                    (err = device_copy(d.mid_rows, by_degree.as<int32_t>() + first_mid, (size_t)d.n_mid_rows * 4, hip_stream))) {
-                    std::string keep = err ? std::string(who) + hip_error_text(err) : std::string(groot_last_error());
-                    release_device(pl.get());
-                    set_error(keep);
-                    return err ? GROOT_EHIP : st;
-                }
+            if (room && (st = to_device<int32_t>(&d.mid_rows, nullptr, room, "long low-degree rows")) != GROOT_OK) {
+                std::string keep = groot_last_error();
+                release_device(pl.get());
+                set_error(keep);
+                return st;
+            }
+            const int64_t skipped = d.n_mid_rows ? first_mid - at_most(kPipeMinDepth) : 0;     // not longer than the slots after all
+            if ((err = launch_plan_finish(d.zero_row, d.mid_rows, by_degree.as<int32_t>() + skipped, d.n_mid_rows, hip_stream))) {
+                release_device(pl.get());
+                return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
             }
         }
         // the sub-graph moves into the plan
@@ -1496,7 +1494,7 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         bool begun = false;
         int32_t *const n_bad_dev = (int32_t *)(sizes.as<int64_t>() + T + 3 + kTotals);
         int32_t h_bad = -1;
-        if (compress) err = csr_compress_begin(d, hd_rows.as<int32_t>(), n_hd, d.mid_rows + d.n_mid_rows, n_bad_dev, hip_stream, &begun);
+        if (compress) err = csr_compress_begin(d, d.hd_rows, n_hd, d.mid_rows + d.n_mid_rows, n_bad_dev, hip_stream, &begun);
         if (!err && begun) err = pipe_compact_prepare();
         // either way waits for the stream: the plan may be used on any from here on
         if (!err) err = begun ? device_download(&h_bad, n_bad_dev, sizeof h_bad, hip_stream) : device_wait(hip_stream);

@@ -161,7 +161,7 @@ constexpr int kErrTooManyPieces = -3;
 struct HdTotals {
     unsigned long long n_chunks, n_slots, n_split, nnz_hd;
 };
-struct HdCounts {                            // per high-degree row, on the device
+struct HdCounts {                            // pieces, slots and split rows before every high-degree row, on the device
     int64_t *pieces = nullptr, *slots = nullptr, *split = nullptr;
 };
 void free_hd_counts(HdCounts &c);
@@ -199,7 +199,7 @@ constexpr int kPlanDeviceMaxThreshold = 1024;
 constexpr int kErrOutOfDeviceMemory = 2;   // hipErrorOutOfMemory
 int launch_plan_device(const int64_t *rowptr_dev, int64_t n, int32_t T, uint8_t *row_class, int32_t *hd_rows,
                        int32_t *ld_rows, int32_t *by_degree, int64_t *deg_offsets, int64_t *counts, void *stream,
-                       bool wait = true);
+                       bool wait = true, int32_t from = 0);   // row_class, ld_rows: or NULL; by_degree: the rows of at least `from`
 // The same lists with the block table in a fixed array inside the library instead of allocated memory: no
 // allocation, no synchronisation; hipErrorInvalidValue when plan_static_scratch_needed exceeds the array.
 constexpr size_t kPlanStaticScratchBytes = (size_t)8 << 20;
@@ -225,9 +225,9 @@ void free_device_part(DevicePart &part);
 // Small synchronous device reads and copies (sizes and lists of a plan built from device arrays).
 int device_time_ms(void *stream, int reps, int (*fn)(void *ctx), void *ctx, float *ms);
 int device_download(void *dst_host, const void *src_dev, size_t bytes, void *stream);
-int device_copy(void *dst_dev, const void *src_dev, size_t bytes, void *stream);   // device to device, in stream order
-int device_zero(void *dst_dev, size_t bytes, void *stream);                        // in stream order; bytes a multiple of 4
 int device_wait(void *stream);
+// the row of zeros and the area behind it cleared and n ints copied, in stream order
+int launch_plan_finish(float *zero_row, int32_t *dst, const int32_t *src, int64_t n, void *stream);
 const char *hip_error_text(int err);
 
 // Device memory of the library (groot_pool.hip): every allocation that it makes.  dev_alloc returns a hipError_t as int and

@@ -745,20 +745,6 @@ int device_download(void *dst_host, const void *src_dev, size_t bytes, void *str
     return (int)(err != hipSuccess ? err : err2);
 }
 
-int device_copy(void *dst_dev, const void *src_dev, size_t bytes, void *stream)
-{
-    if (!bytes) return 0;
-    hipStream_t st = (hipStream_t)stream;
-    return (int)hipMemcpyAsync(dst_dev, src_dev, bytes, hipMemcpyDeviceToDevice, st);
-}
-
-int device_zero(void *dst_dev, size_t bytes, void *stream)
-{
-    const int64_t n = (int64_t)(bytes / 4);
-    if (n) rg_fill_i32<<<dim3(rg_grid(n, kBlock)), dim3(kBlock), 0, (hipStream_t)stream>>>((int32_t *)dst_dev, n, 0);
-    return (int)hipGetLastError();
-}
-
 int device_wait(void *stream) { return (int)hipStreamSynchronize((hipStream_t)stream); }
 
 }  // namespace groot

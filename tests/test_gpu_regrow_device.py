@@ -149,7 +149,7 @@ def test_rows_of_every_length_of_a_directed_graph(torch_cuda, P, rule):
             _check_part(torch_cuda, plan, rowptr, col, w, part_of, P, p, flags, 2, rule, "row lengths")
 
 
-@pytest.mark.parametrize("n,batch,P,T,F", [(32, 2, 4, 32, 64), (48, 1, 5, 8, 32), (24, 3, 2, 200, 20)])
+@pytest.mark.parametrize("n,batch,P,T,F", [(32, 2, 4, 32, 64), (48, 1, 5, 8, 32), (24, 3, 2, 200, 20), (40, 1, 3, 4, 32)])
 def test_device_built_plans_fill_the_full_result(torch_cuda, n, batch, P, T, F):
     """Partitioned mode with nothing built on the host: every part re-grown on the device, its plan made from
     the device arrays, its owned rows computed into place.  Every element against the oracle on the full
@@ -342,6 +342,37 @@ def test_device_built_schedule_of_high_degree_rows_is_the_host_plans(torch_cuda,
     err = np.abs(H.cpu().numpy().astype(np.float64) - ref_H)
     tol = layer_tolerance(S, scale, a64(Wn))
     assert np.isfinite(err).all() and (err <= tol).all(), float(np.max(err / tol))
+
+
+@pytest.mark.parametrize("n_hd,lengths", [(5120, (2, 6)), (5121, (6, 9)), (1, (8, 12)), (0, (5, 6))])
+def test_device_built_plans_at_the_edges_of_their_rules(torch_cuda, n_hd, lengths):
+    """As many pieces as are put in order by counting, one more (sorted), one, and none; and low-degree rows around the number of
+    gather slots, so that the list of longer rows begins behind rows of 6 entries that are not on it, or is empty."""
+    torch = torch_cuda
+    rng = np.random.default_rng(n_hd)
+    n, T, F = 9000, 32, 32
+    length = rng.integers(lengths[0], lengths[1] + 1, n)
+    length[rng.choice(n, n // 100, replace=False)] = lengths[1] + 2
+    length[rng.choice(n, n_hd, replace=False)] = 33
+    col = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in length]).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(length)]).astype(np.int64)
+    w = rng.random(col.size).astype(np.float32)
+    g = G.groot_graph_from_csr(rowptr, col, w)
+    print(f"device plan: {n_hd} pieces, rows of {lengths}", flush=True)
+    plan = G.groot_dev_part_plan(G.groot_partition_regrow_device(_resident_plan(g), 1, 0), T, F)
+    host = _resident_plan(g, T, F)
+    got, ref = G.groot_plan_hd_pieces(plan), G.groot_plan_hd_pieces(host)
+    assert len(got["row"]) == n_hd
+    for k in ("begin", "len", "row", "slot"):
+        assert np.array_equal(got[k], ref[k]), k
+    for k in ("mid_rows", "pipe_depth", "ld_pipelined", "hd_pieces"):
+        assert G.groot_plan_query(plan, k) == G.groot_plan_query(host, k), k
+    X = wl.uniform_features(3, 0, n, F, device="cuda")
+    Y = torch.full_like(X, float("nan"))
+    G.groot_spmm_execute(plan, X, Y, F)
+    torch.cuda.synchronize()
+    Y64, S = oracle.spmm_f64(rowptr, col, w, X.cpu().numpy())
+    assert_close_to_oracle(Y.cpu().numpy(), Y64, S, f"{n_hd} pieces")
 
 
 def test_error_paths(torch_cuda):
