@@ -96,21 +96,27 @@ __device__ __forceinline__ int32_t hd_place(const int32_t *__restrict__ hd_rows,
 }
 
 // Sum of one row for one float4 slice with row-uniform weights, in CSR order, eight gathers in flight without a branch between
-// them (an entry past the row's end reads the row of zeros).  Xf: the lane's slice of row 0; zero_off: byte distance to its
+// them (an entry past the row's end reads the row of zeros), the next eight columns beside them: a row of 31 entries is five
+// latencies, with its columns fetched when they were needed eight.  Xf: the lane's slice of row 0; zero_off: byte distance to its
 // slice of the row of zeros.
 template <int W>
 __device__ __forceinline__ v4f row_sum_ahead(int64_t s, int64_t e, const int32_t *__restrict__ cols, const char *__restrict__ Xf,
                                              int row_shift, int64_t zero_off)
 {
     v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int64_t p = s; p < e; p += 8) {
-        int64_t c[8];
-        v4f x[8];
+    if (s >= e) return acc;
+    int32_t c[8];
+    auto fetch = [&](int64_t p) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) c[k] = cols[p + k < e ? p + k : e - 1];
+    };
+    fetch(s);
+#pragma unroll 1
+    for (int64_t p = s; p < e; p += 8) {
+        v4f x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = *(const v4f *)(Xf + (p + k < e ? c[k] << row_shift : zero_off));
+        for (int k = 0; k < 8; ++k) x[k] = *(const v4f *)(Xf + (p + k < e ? (int64_t)c[k] << row_shift : zero_off));
+        if (p + 8 < e) fetch(p + 8);
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc += x[k];
     }
