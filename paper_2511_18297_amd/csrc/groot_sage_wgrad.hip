@@ -188,9 +188,6 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
             wave_sync();
             return fix_a;
         };
-        // row (inside the tile) of X that this lane holds a float4 of in sweep grp; of dZ for contraction group p of the sweep
-        auto x_row = [&](int grp) -> int { return grp * kRpg + g; };
-        auto z_row = [&](int grp, int p) -> int { return grp * kRpg + kq * kP + p; };
         // ---- one sweep: kRpg rows, one per lane group: the row's D slots, its own features; and the rows of dZ
         struct Regs {
             v4f xs[D], self;
@@ -206,7 +203,7 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
             return __builtin_nontemporal_load((const ZVec *)(dZ + (tile << kZShift) * kWgRows + z_lane + ((grp * kRpg + p) << kZShift)));
         };
         auto issue = [&](Regs &q, int64_t tile, int grp) {   // the tile whose slots are staged
-            const int lr = x_row(grp);
+            const int lr = grp * kRpg + g;               // row (inside the tile) that this lane holds a float4 of X of
             if (W == kMean) q.inv = s_inv[w][lr];
 #pragma unroll
             for (int k = 0; k < D; ++k) q.xs[k] = *(const v4f *)(Xf + s_slot[w][lr * D + k]);
@@ -331,26 +328,50 @@ __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_e
                 const bool ragged = t >= n_full;
                 const int64_t rp = load_rp(t);           // rows past the end: no entries
                 const int64_t next_rp = __shfl_down(rp, 1);
-                const uint64_t redo = __ballot(l < kWgRows && (ragged || next_rp - rp > D || next_rp - rp >= T));
+                const bool here = t * kWgRows + l < n;
+                // rows past the end of the matrix are in no sum
+                uint32_t redo = (uint32_t)__ballot(l < kWgRows && here && (ragged || next_rp - rp > D || next_rp - rp >= T));
                 const uint32_t hd = (uint32_t)__ballot(l < kWgRows && next_rp - rp >= T);
                 const int32_t place = hd ? hd_place(hd_rows, n_hd, t * kWgRows) : 0;   // of the tile's first high-degree row
+                // kRpg rows at a time, whichever they are: lane group g holds the g-th of what is left.  (By sweeps, whose rows
+                // stand side by side, a tile with one such row in every sweep took kG turns: 79 thousand rows of a multiplier, 32 x 64,
+                // whole call 28.8 us, now 27.7; Booth shape, 10 thousand rows, 64 x 64 32.8, now 31.1.)
 #pragma unroll 1
-                for (int grp = 0; grp < kG; ++grp) {
-                    if ((redo >> (grp * kRpg) & ((1u << kRpg) - 1)) == 0) continue;
-                    const int lr = x_row(grp);
-                    const int64_t row = t * kWgRows + lr, s = __shfl(rp, lr), e = __shfl(rp, lr + 1);
+                while (redo) {
+                    int lr[kRpg];                        // scalars: the turn's rows, -1 past the last
+#pragma unroll
+                    for (int i = 0; i < kRpg; ++i) {
+                        lr[i] = redo ? __builtin_ctz(redo) : -1;
+                        redo &= redo - 1;
+                    }
+                    int mine = lr[0], of_z[kP];          // of the lane's float4 of X, of its values of dZ
+#pragma unroll
+                    for (int p = 0; p < kP; ++p) of_z[p] = lr[p];
+#pragma unroll
+                    for (int i = 1; i < kRpg; ++i) {
+                        if (g == i) mine = lr[i];
+#pragma unroll
+                        for (int p = 0; p < kP; ++p)
+                            if (kq * kP + p == i) of_z[p] = lr[i];
+                    }
                     const v4f zero = {0.f, 0.f, 0.f, 0.f};
-                    v4f a = zero;
-                    if ((hd >> lr) & 1)
-                        a = *(const v4f *)(hd_agg + ((int64_t)(place + __popc(hd & ((1u << lr) - 1))) << kRowShift) + 16 * f);
-                    else if (ragged || e - s > D)
-                        a = row_sum_ahead<W>(s, e, col, Xf, kRowShift, zero_off);
                     ZVec z[kP];
 #pragma unroll
                     for (int p = 0; p < kP; ++p)
-                        z[p] = t * kWgRows + z_row(grp, p) < n ? load_z(t, grp, p) : (ZVec)(0.f);
+                        z[p] = of_z[p] >= 0 ? __builtin_nontemporal_load((const ZVec *)(dZ + ((t * kWgRows + of_z[p]) << kZShift) + 4 * kNb * jl))
+                                            : (ZVec)(0.f);
+                    const int row = mine >= 0 ? mine : 0;
+                    const int64_t s = __shfl(rp, row), e = __shfl(rp, row + 1);
+                    v4f a = zero, own = zero;
+                    if (mine >= 0) {
+                        if (ragged) own = *(const v4f *)(Xf + ((t * kWgRows + mine) << kRowShift));
+                        if ((hd >> mine) & 1)
+                            a = *(const v4f *)(hd_agg + ((int64_t)(place + __popc(hd & ((1u << mine) - 1))) << kRowShift) + 16 * f);
+                        else if (ragged || e - s > D)
+                            a = row_sum_ahead<W>(s, e, col, Xf, kRowShift, zero_off);
+                    }
                     multiply(0, a, z);
-                    if (ragged) multiply(kMc, row < n ? load_self(t, grp) : zero, z);
+                    if (ragged) multiply(kMc, own, z);
                 }
             }
             if constexpr (kFold) {
