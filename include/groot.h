@@ -419,8 +419,8 @@ void groot_parts_free(groot_parts *parts);
  *
  * groot_dev_part_plan -- an executable plan for the part's sub-graph, built
  * from the device arrays (degree classes and counting sort as in
- * groot_plan_lists_device; the schedule of the high-degree rows is made on
- * the host from those rows' extents only).  The sub-graph's arrays MOVE into
+ * groot_plan_lists_device, the schedule of the high-degree rows likewise; only
+ * sizes come back to the host).  The sub-graph's arrays MOVE into
  * the plan: afterwards groot_dev_part_view gives NULL for rowptr/col/val, the
  * part keeps its counts and global_id, and a second call gives EINVAL.  The
  * plan is resident (groot_plan_upload on it is a no-op for max_F' <= max_F and
