@@ -6,8 +6,8 @@
 // row-uniform weights the sum of such a row is a product of a row of zeros and ones with X.
 //
 // The product runs on v_mfma_f32_16x16x32_bf16 and is more precise than fp32 sums.  A number of X is cut into three bf16 pieces by
-// truncation, x = hi + mid + lo, exactly: three times 8 significant bits (bf16 has the exponents of fp32).  Products with 1 are
-// exact.  The sums of the hi pieces and those of mid and lo have accumulators of their own: what is added to an accumulator of
+// truncation, x = hi + mid + lo, exactly: three times 8 significant bits (bf16 has the exponents of fp32).  Products with a power of two
+// are exact.  The sums of the hi pieces and those of mid and lo have accumulators of their own: what is added to an accumulator of
 // 24 bits then has 8 bits (or 16), so next to nothing is rounded, and the two meet in one fp32 addition per run of columns.
 // v_mfma_f32_16x16x4_f32 on X as it is, one bit expanded per operand, does 16 rows x 16 features x 32 columns in 256 cycles, the
 // three pieces take 48: polarized graph, F = 128, 320 rows in 155 us that way, 384 in 65 now.
@@ -22,9 +22,10 @@
 // 4 us of 65 less, without the expansion of the bits 3, without the loads none; cutting in one half of the wavefronts before, in the
 // other after the multiplication 3 us more; operands of the next 32 columns read ahead of the matrix instructions, no difference.
 //
-// 0 x infinity is not 0, and below 2^-110 three pieces do not hold a number: the cut checks itself.  Where 128 columns hold a number
-// that it does not reproduce, it is left out there and these columns' exceptions are multiplied once more (`special`).
+// 0 x infinity is not 0, and numbers from 2^104 on are too large for the scale of the cut, which checks itself.  Where 128 columns hold
+// such a number, it is left out there and these columns' exceptions are multiplied once more (`special`).
 #include <algorithm>
+#include <cmath>
 
 #include "groot_device.h"
 
@@ -52,18 +53,25 @@ struct DenseArgs {
     int32_t n_partials;                      // of a row
     int64_t n_steps;                         // columns in units of kDenseStep
     int64_t n_wg;                            // row_tiles x f_tiles x k_parts
+    uint32_t one_bits;                       // the product's ones, one part in the columns of a partial sum or less, as bf16
+    float down, up;                          // from sums of numbers that were cut 2^24 times and 2^-24 times as large to partial sums
+    double weight_scale;                     // the finishing kernel's, times the row's weight
 };
 
-// The ones of the product are 1 / 64, exact: a sum of many columns that the weight will make small does not overflow before (the
-// gathers apply the weight to the few entries of a lane group, up to 128).
-constexpr uint32_t kDenseOneBits = 0x3C80;
-constexpr double kDenseOne = 0x1p-6;
-constexpr float kDenseUp = 0x1p100f, kDenseDown = 0x1p-100f;   // numbers that the cut does not reproduce, below 2^-109, are cut this much larger
+// Numbers are cut 2^24 times as large: all bits of a subnormal number, too, are then in three pieces that are normal numbers.  What
+// becomes infinite by that, from 2^104 on, is an exception and is cut 2^-24 times as large, in a pass of its own.  The product's ones are
+// one part in the columns that meet in a partial sum, exact, so no sum of numbers below 2^104 overflows.
+constexpr float kDenseUp = 0x1p24f, kDenseDown = 0x1p-24f;
+constexpr int kDenseScaleExp = 24;
+// With mean weights partial sums are stored as one part in 64 or less: the sum of unweighted numbers, which the weight will make small,
+// overflows where they are 1 / 32 of the largest float in every column, or later, however many columns meet in it (the gathers apply the
+// weight to the few entries of a lane group, up to 128 of them).  With smaller parts subnormal results would be rounded more coarsely.
+constexpr int kDenseStoreExp = 6, kDenseHeadExp = 5;
 
-// (a, b) -> packed bf16 pieces, a in the low halves.  What is left of each after the third piece is zero, or has its bits in the
-// low half: that part of r is or-ed to `low`; NaN and infinity make z NaN.  a - hi by v_dot2_f32_bf16 with (-1, 0), one instruction
-// instead of an unpacking and a subtraction; a neighbour that is not finite makes NaN of it, too, and that is seen.
-__device__ __forceinline__ void dense_cut(float a, float b, unsigned &hi, unsigned &mid, unsigned &lo, unsigned &low, float &z)
+// (a, b) -> packed bf16 pieces, a in the low halves, of finite numbers exactly; NaN and infinity make z NaN.  a - hi by
+// v_dot2_f32_bf16 with (-1, 0), one instruction instead of an unpacking and a subtraction; a neighbour that is not finite makes NaN of
+// it, too, and that is seen.
+__device__ __forceinline__ void dense_cut(float a, float b, unsigned &hi, unsigned &mid, unsigned &lo, float &z)
 {
     unsigned pick_a = 0x0000bf80u, pick_b = 0xbf800000u;
     asm("" : "+s"(pick_a), "+s"(pick_b));                // in registers: as a literal operand 0x0000bf80 came out as (-1, -1)
@@ -78,23 +86,13 @@ __device__ __forceinline__ void dense_cut(float a, float b, unsigned &hi, unsign
     ra = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dense_b2, mid), first, ra, false);
     rb = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(dense_b2, mid), second, rb, false);
     lo = upper(ra, rb);
-    low |= __builtin_bit_cast(unsigned, ra) | __builtin_bit_cast(unsigned, rb);
     z += ra;
     z += rb;
 }
 
-// whether the cut reproduces x
-__device__ __forceinline__ bool dense_exact(float x)
-{
-    unsigned hi, mid, lo, low = 0;
-    float z = 0.f;
-    dense_cut(x, 0.f, hi, mid, lo, low, z);
-    return z == z && (low & 0xffff) == 0;
-}
-
-// What is multiplied in place of x: all that the cut reproduces; then, where a step holds anything else, the infinities and NaN (a one
-// in the first piece for +infinity and NaN, in the second for -infinity and NaN), and the very small numbers.
-enum DensePass { kDenseMain, kDenseCodes, kDenseTiny };
+// What is multiplied in place of x: all that is finite 2^24 times as large; then, where a step holds anything else, the infinities and
+// NaN (a one in the first piece for +infinity and NaN, in the second for -infinity and NaN), and the very large numbers.
+enum DensePass { kDenseMain, kDenseCodes, kDenseLarge };
 
 // Orders LDS accesses of the workgroup; loads from global memory stay in flight.
 __device__ __forceinline__ void dense_barrier()
@@ -148,7 +146,6 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
         for (int q = 0; q < 3; ++q) s_b[buf][cut_unit][half][v][q][lane] = op[q];
     };
     auto cut = [&](int buf, const vN (&x)[8]) {
-        unsigned low = 0;
         float z = 0.f;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
@@ -156,14 +153,14 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
                 unsigned q0, q1, q2;
-                dense_cut(x[2 * p][v], x[2 * p + 1][v], q0, q1, q2, low, z);
+                dense_cut(x[2 * p][v] * kDenseUp, x[2 * p + 1][v] * kDenseUp, q0, q1, q2, z);
                 op[0][p] = q0;
                 op[1][p] = q1;
                 op[2][p] = q2;
             }
             put(buf, v, op);
         }
-        if (__ballot(z != z || (low & 0xffff))) {        // put again, without what is not reproduced
+        if (__ballot(z != z)) {                          // put again, without the exceptions
             int32_t kinds = 0;
 #pragma unroll 1
             for (int v = 0; v < NV; ++v) {
@@ -171,11 +168,11 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     const float a = v ? x[2 * p][NV - 1] : x[2 * p][0], b = v ? x[2 * p + 1][NV - 1] : x[2 * p + 1][0];
-                    const bool a_ok = dense_exact(a), b_ok = dense_exact(b);
+                    const bool a_ok = isfinite(a * kDenseUp), b_ok = isfinite(b * kDenseUp);
                     if (__ballot(!isfinite(a) || !isfinite(b))) kinds |= 1 << kDenseCodes;
-                    if (__ballot((!a_ok && isfinite(a)) || (!b_ok && isfinite(b)))) kinds |= 1 << kDenseTiny;
+                    if (__ballot((!a_ok && isfinite(a)) || (!b_ok && isfinite(b)))) kinds |= 1 << kDenseLarge;
                     unsigned q0, q1, q2;
-                    dense_cut(a_ok ? a : 0.f, b_ok ? b : 0.f, q0, q1, q2, low, z);
+                    dense_cut(a_ok ? a * kDenseUp : 0.f, b_ok ? b * kDenseUp : 0.f, q0, q1, q2, z);
                     op[0][p] = q0;
                     op[1][p] = q1;
                     op[2][p] = q2;
@@ -190,7 +187,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
         const uint32_t t = w >> (4 * u);
         dense_u4 a;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = __umul24(t & (0x00010001u << i), kDenseOneBits >> i);
+        for (int i = 0; i < 4; ++i) a[i] = __umul24(t & (0x00010001u << i), d.one_bits >> i);
         return __builtin_bit_cast(dense_b8, a);
     };
     v4f hi[MB][NV], rest[MB][NV];
@@ -236,7 +233,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
     // The step's exceptions, over the operands in LDS, which have been multiplied.  Every wavefront of the workgroup gets here.
     auto special = [&](int64_t s, int buf, const uint32_t (&w)[MB], int32_t kinds) {
 #pragma unroll 1
-        for (int pass = kDenseCodes; pass <= kDenseTiny; ++pass) {
+        for (int pass = kDenseCodes; pass <= kDenseLarge; ++pass) {
             if (!(kinds >> pass & 1)) continue;
             dense_barrier();                             // what is there has been read
             vN x[8];
@@ -252,14 +249,14 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
                     unsigned plus[2], minus[2];
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
-                        const bool nan = ab[i] != ab[i], exact = dense_exact(ab[i]);
+                        const bool nan = ab[i] != ab[i], in_main = isfinite(ab[i] * kDenseUp);
                         plus[i] = nan || ab[i] == __builtin_inff() ? 0x3f80u : 0u;
                         minus[i] = nan || ab[i] == -__builtin_inff() ? 0x3f80u : 0u;
-                        t[i] = exact || plus[i] || minus[i] ? 0.f : ab[i] * kDenseUp;
+                        t[i] = in_main || plus[i] || minus[i] ? 0.f : ab[i] * kDenseDown;
                     }
-                    unsigned q0, q1, q2, low = 0;
+                    unsigned q0, q1, q2;
                     float z = 0.f;
-                    dense_cut(t[0], t[1], q0, q1, q2, low, z);
+                    dense_cut(t[0], t[1], q0, q1, q2, z);
                     op[0][p] = pass == kDenseCodes ? plus[0] | plus[1] << 16 : q0;
                     op[1][p] = pass == kDenseCodes ? minus[0] | minus[1] << 16 : q1;
                     op[2][p] = pass == kDenseCodes ? 0u : q2;
@@ -285,7 +282,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
                     for (int r = 0; r < 4; ++r) {
                         const float inf = t0[r] > 0.f ? __builtin_inff() : -__builtin_inff();
                         const float code = t0[r] > 0.f && t1[r] > 0.f ? __builtin_nanf("") : t0[r] > 0.f || t1[r] > 0.f ? inf : 0.f;
-                        t0[r] = pass == kDenseCodes ? code : (t0[r] + t1[r]) * kDenseDown;
+                        t0[r] = pass == kDenseCodes ? code : (t0[r] + t1[r]) * d.up;
                     }
                     int64_t at = slot;
                     asm("" : "+s"(at));                  // no addresses kept from one pass to the next: registers
@@ -346,7 +343,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
                 vN *const p = (vN *)(partial(slot, b) + r * row_bytes);
                 vN sum;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) sum[v] = hi[b][v][r] + rest[b][v][r];
+                for (int v = 0; v < NV; ++v) sum[v] = (hi[b][v][r] + rest[b][v][r]) * d.down;
                 *p = started ? *p + sum : sum;
             }
         }
@@ -386,7 +383,7 @@ __global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs
         return;
     }
     const int64_t row = d.rows[blockIdx.x].row;
-    const double weight = (double)row_weight<W>(d.rows[blockIdx.x].row_nnz) / kDenseOne;
+    const double weight = (double)row_weight<W>(d.rows[blockIdx.x].row_nnz) * d.weight_scale;
 #pragma unroll 1
     for (int32_t fb = 0; fb < F4; fb += L) {
         const int32_t ff = fb + f;
@@ -468,6 +465,15 @@ static DenseArgs dense_args(const DevicePlan &dp, int32_t F)
     d.groups = (d.runs + kDenseGroup - 1) / kDenseGroup;
     d.n_partials = d.k_parts * (64 / dp.dense_tile_rows) * d.groups;
     d.n_wg = wgs * d.k_parts;
+    const int64_t run = (share + d.runs - 1) / d.runs, columns = std::min(share, run * kDenseGroup) * kDenseStep / (64 / dp.dense_tile_rows);
+    int one = 0, store = kDenseStoreExp;                 // exponents: parts in 2^one and 2^store
+    while ((int64_t)1 << one < columns) ++one;
+    while ((int64_t)1 << (store + kDenseHeadExp) < columns) ++store;
+    if (dp.weight_mode != kMean) store = 0;
+    d.one_bits = (uint32_t)(127 - one) << 7;
+    d.down = (float)std::ldexp(1., one - store - kDenseScaleExp);
+    d.up = (float)std::ldexp(1., one - store + kDenseScaleExp);
+    d.weight_scale = std::ldexp(1., store);
     return d;
 }
 

@@ -1562,6 +1562,77 @@ def test_dense_product_of_very_large_and_very_small_numbers(torch_cuda, F, scale
         assert off[0].max() <= off[1].max() and off[0].mean() <= off[1].mean()
 
 
+def _spread_dense_rows_graph(n, dense, length, rng):
+    """The rows `dense` with `length` columns each all over the matrix, one in every stretch of n / length columns; the others with
+    their diagonal alone; weights 1 / row length"""
+    lengths = np.ones(n, np.int64)
+    lengths[dense] = length
+    rowptr = np.concatenate([[0], np.cumsum(lengths)])
+    col = np.repeat(np.arange(n, dtype=np.int32), lengths)
+    first = np.arange(length, dtype=np.int64) * n // length
+    room = np.diff(np.append(first, n))
+    for r in dense:
+        col[rowptr[r]:rowptr[r + 1]] = first + (rng.random(length) * room).astype(np.int64)
+    return rowptr, col, np.repeat(np.float32(1) / lengths.astype(np.float32), lengths)
+
+
+@pytest.mark.parametrize("n,share,F", [(262144, 0.5, 512), (1200000, 0.25, 512)])
+def test_dense_product_of_very_large_numbers_over_long_stretches(torch_cuda, n, share, F):
+    """8,192 and 37,504 columns that a workgroup sums (in one and in two partial sums): their mean is finite, and so is every partial sum of
+    theirs: numbers up to 2 / 32 of the largest float pass in rows of half of the columns, up to 4 / 32 in rows of a quarter."""
+    rng = np.random.default_rng(n)
+    dense = np.sort(rng.choice(n, 64, replace=False))
+    graph = _spread_dense_rows_graph(n, dense, int(share * n), rng)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(*graph), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == 64
+    X = torch_cuda.empty((n, F), device="cuda").uniform_(1e37, 2e37)
+    Y = torch_cuda.empty_like(X)
+    G.groot_spmm_execute(plan, X, Y, F)
+    for r in dense[::7]:
+        of_row = torch_cuda.from_numpy(graph[1][graph[0][r]:graph[0][r + 1]].astype(np.int64)).cuda()
+        want = X[of_row].double().mean(0)
+        assert ((Y[r].double() - want).abs() <= 1e-6 * want).all(), r
+
+
+@pytest.mark.parametrize("n,n_dense,F", [(30011, 96, 68), (300011, 16, 512)])
+def test_dense_product_of_subnormal_numbers_with_unit_weights(torch_cuda, n, n_dense, F):
+    """Sums of numbers of a few multiples of 2^-149 are exact, from single ones to numbers that are normal again, in workgroups of
+    256 and of 9,472 columns."""
+    rng = np.random.default_rng(n)
+    dense = np.sort(rng.choice(n, n_dense, replace=False))
+    rowptr, col, val = _spread_dense_rows_graph(n, dense, n // 4, rng)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, np.ones_like(val)), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == n_dense and G.groot_plan_query(plan, "weight_mode") == 0
+    times = torch_cuda.from_numpy(rng.integers(-3, 4, (n, F))).cuda()
+    for exp in (-149, -140, -133, -127, -110):
+        X = (times.double() * 2.0 ** exp).float()
+        Y = torch_cuda.empty_like(X)
+        G.groot_spmm_execute(plan, X, Y, F)
+        for r in dense[::5]:
+            want = times[torch_cuda.from_numpy(col[rowptr[r]:rowptr[r + 1]].astype(np.int64)).cuda()].sum(0)
+            assert torch_cuda.equal(Y[r].double() * 2.0 ** 149, want.double() * 2.0 ** (exp + 149)), (exp, r)
+
+
+@pytest.mark.parametrize("exp", [-118, -110, -107, -104, -96, 102, 104, 106])
+def test_dense_product_is_as_precise_at_the_ends_of_the_range(torch_cuda, exp):
+    """Numbers whose third piece would be subnormal, and numbers that are partly too large for the scale of the cut: the same sums as of
+    numbers around 1, as far as these are not rounded to multiples of 2^-149, or no further off than the gathers."""
+    n, F = 20011, 128
+    rowptr, col, val, dense = _dense_rows_graph(n, 128, 0.25, np.random.default_rng(15))
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == 128
+    X = torch_cuda.from_numpy(wl.uniform_features_numpy(5, 0, n, F)).cuda()
+    want = oracle.spmm_f64(*_dense_rows_of(rowptr, col, val, dense), X.cpu().numpy())[0]
+    out = [torch_cuda.empty_like(X) for _ in range(3)]
+    for Y, scale, call in zip(out, (0, exp, exp), (G.groot_spmm_execute, G.groot_spmm_execute, G.groot_spmm_execute_rows)):
+        call(plan, X * 2.0 ** scale, Y, F, *([n] if call is G.groot_spmm_execute_rows else []))
+    off = [np.linalg.norm(np.ldexp(Y.cpu().numpy()[dense].astype(np.float64), -s) - want) for Y, s in zip(out, (0, exp, exp))]
+    assert off[1] <= (1.001 * off[0] if -112 < exp < 104 else off[2]), off
+
+
 @pytest.mark.parametrize("how", ["one", "a hundredth", "a stretch", "all"])
 @pytest.mark.parametrize("ones", [False, True])
 def test_dense_product_gives_infinities_and_nan_like_the_gathers(torch_cuda, how, ones):
@@ -1619,6 +1690,20 @@ def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torc
     finite = _best_time(torch_cuda, run)
     X[n // 3, 5] = float("nan")
     assert _best_time(torch_cuda, run) < 1.7 * finite
+
+
+def test_very_small_numbers_do_not_slow_the_dense_product_down(torch_cuda):
+    """They are summed as all others (as exceptions, in a pass of their own, they took twice as long)."""
+    n, F = 131072, 128
+    rowptr, col, val, _ = _dense_rows_graph(n, 320, 0.25, np.random.default_rng(13))
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, val), 32)
+    G.groot_plan_upload(plan, F)
+    X = torch_cuda.empty((n, F), device="cuda").uniform_(-1, 1)
+    Y = torch_cuda.empty_like(X)
+    run = lambda: G.groot_spmm_execute(plan, X, Y, F)
+    usual = _best_time(torch_cuda, run)
+    X *= 2.0 ** -120
+    assert _best_time(torch_cuda, run) < 1.3 * usual
 
 
 @pytest.mark.parametrize("n,n_dense,share,F", [(16384, 64, 0.3, 60), (16385, 100, 0.3, 68), (16511, 192, 0.2, 100), (16512, 256, 0.2, 32),
