@@ -2,25 +2,29 @@
 //
 // A gather of a feature row for every stored entry reads a row of X as often as high-degree rows name it: on the
 // polarized graph of 262,144 rows 70 times, 9.5 GB at F = 128, and the vector memory units return no more than 23 TB/s
-// (hd_kernel 380 us).  Its 384 longest rows hold 15 % of all columns each, 95 % of the entries of the high-degree rows.  With
+// (hd_kernel 380 us).  Its 448 longest rows hold 15 % of all columns each, 97 % of the entries of the high-degree rows.  With
 // row-uniform weights the sum of such a row is a product of a row of zeros and ones with X.
 //
-// The product runs on v_mfma_f32_16x16x32_bf16 and is more precise than fp32 sums.  A number of X is cut into three bf16 pieces by
-// truncation, x = hi + mid + lo, exactly: three times 8 significant bits (bf16 has the exponents of fp32).  Products with a power of two
-// are exact.  The sums of the hi pieces and those of mid and lo have accumulators of their own: what is added to an accumulator of
-// 24 bits then has 8 bits (or 16), so next to nothing is rounded, and the two meet in one fp32 addition per run of columns.
+// The product runs on v_mfma_f32_16x16x32_bf16.  A number of X is cut into three bf16 pieces by truncation, x = hi + mid + lo, exactly:
+// three times 8 significant bits (bf16 has the exponents of fp32).  Products with a power of two are exact.  What the instruction adds up
+// is truncated to the 24 bits of the accumulator, so the hi pieces, of 8 bits, have one of their own, and next to nothing is cut off
+// where the numbers of 128 columns are of similar size.  Where they are not, the small ones lose bits at every instruction: four of
+// them, 128 columns, are one chain, which a vector addition, rounded to nearest, puts to the sum.  mid and lo, 2^-8 of it, stay in one
+// chain.  Error of the dense rows in the 2-norm, 1e-8, gathers / fp32 instructions / here (131,072 rows, 448 dense, F = 128; 65,536, 64, 512):
+// U(-1, 1) 15.7 / 14.7 / 3.6, 19.3 / 16.4 / 4.1; exp(4 N) 13.7 / 10.9 / 9.0, 11.7 / 10.0 / 10.4; 2^U(-40, 0) 9.7 / 3.9 / 3.5, 12.3 / 4.6 / 4.1.  (In
+// chains of 2,048 columns exp(4 N) 21.8 and 32.7.)  In 20,011 rows, one step or two per workgroup, exp(4 N) 9.5 / 7.9 / 11.1.
 // v_mfma_f32_16x16x4_f32 on X as it is, one bit expanded per operand, does 16 rows x 16 features x 32 columns in 256 cycles, the
-// three pieces take 48: polarized graph, F = 128, 320 rows in 155 us that way, 384 in 65 now.
+// three pieces take 48.
 //
-// One workgroup of eight wavefronts per CU takes a stretch of the columns, 64 features and up to 512 rows, so that X is read
+// One workgroup of eight wavefronts per CU takes a stretch of the columns, 64 features and up to 448 rows, so that X is read
 // once and cut once: 128 columns at a time, every wavefront loads and cuts an eighth (32 columns x 32 features; eight columns of a
 // lane are the eight k of an operand, so nothing is transposed) and puts the operands to LDS, from where the wavefronts of a
 // feature half multiply them with the bits of their rows.  One barrier per 128 columns, loads stay in flight across it.
 //
-// What bounds it: the matrix instructions, 1.3 PFLOP/s in the loop where nothing but these instructions on the same data reach 1.9
-// (the clock falls to 1.95 GHz) and 1.5 with the three vector instructions beside each that a wavefront has here.  Without the cut
-// 4 us of 65 less, without the expansion of the bits 3, without the loads none; cutting in one half of the wavefronts before, in the
-// other after the multiplication 3 us more; operands of the next 32 columns read ahead of the matrix instructions, no difference.
+// Polarized graph, F = 128, 448 rows: 86 us, 1.04 PFLOP/s of the pieces' products.  Counters: matrix units busy 43 % of the cycles (of 2.4 GHz),
+// vector instructions issued in 31 %, three beside each matrix instruction (bits to operands, cut, sums), no bank conflicts.  Neither
+// is at its end: two wavefronts per SIMD, all that the accumulators leave room for, wait for each other at every barrier and for operands.
+// Operands of the next unit read ahead, where registers allow it, make no difference.
 //
 // 0 x infinity is not 0, and numbers from 2^104 on are too large for the scale of the cut, which checks itself.  Where 128 columns hold
 // such a number, it is left out there and these columns' exceptions are multiplied once more (`special`).
@@ -35,12 +39,18 @@ constexpr int kDenseUnit = 32;               // columns of a matrix instruction
 constexpr int kDenseStep = 128;              // columns between two barriers: the columns of a mask word and its three neighbours
 constexpr int kDenseTile = 64;               // features of a workgroup
 constexpr int kDenseWaves = 8;               // wavefronts per workgroup, one workgroup per CU
-constexpr int kDenseRun = 16;                // steps that one chain of matrix instructions sums, at most
-constexpr int kDenseGroup = 16;              // runs that meet in one fp32 partial sum, at most
-constexpr int kDenseMaxBlocks = 8;           // row blocks of 16 per wavefront, at most
+constexpr int kDenseGroup = 256;             // steps that meet in one partial sum, at most
+constexpr int kDenseMaxBlocks = 7;           // row blocks of 16 per wavefront, at most: three sets of 8 registers each
 typedef unsigned int dense_u4 __attribute__((ext_vector_type(4)));
 typedef __bf16 dense_b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 dense_b2 __attribute__((ext_vector_type(2)));
+
+constexpr int kDenseOperandBytes = 2 * (kDenseStep / kDenseUnit) * 2 * 2 * 3 * kWave * 16;   // LDS, 96 KB: two steps' operands
+constexpr int kDenseBlockSumBytes = kDenseWaves * 2 * kWave * 16;                            // 16 KB: a row block of every wavefront
+
+// Row blocks of a wavefront whose sums are in LDS: with those of all seven in registers, of which there are 256, others spill in the loop, and
+// a reload waits for the loads of X, too (polarized graph, F = 128, whole call 198 us; with three blocks' in LDS 175)
+constexpr int dense_lds_blocks(int MB) { return MB == kDenseMaxBlocks ? 3 : 0; }
 
 struct DenseArgs {
     const HdChunk *rows;                     // [n_rows] the whole row as one piece, slot -1
@@ -49,7 +59,7 @@ struct DenseArgs {
     int32_t n_rows, tile_rows, padded;       // padded: n_rows in whole tiles
     int32_t blocks;                          // row blocks of 16 of a wavefront
     int32_t row_tiles, f_tiles, k_parts;
-    int32_t runs, groups;                    // of a workgroup's stretch of columns, one chain each; and the partial sums they meet in
+    int32_t groups, group;                   // partial sums of a workgroup's stretch of columns, and the steps that meet in one
     int32_t n_partials;                      // of a row
     int64_t n_steps;                         // columns in units of kDenseStep
     int64_t n_wg;                            // row_tiles x f_tiles x k_parts
@@ -134,12 +144,9 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
             }
         }
     };
-    auto load_mask = [&](int64_t s, uint32_t (&w)[MB]) {
-#pragma unroll
-        for (int b = 0; b < MB; ++b) {
-            const int32_t block = block0 + b < n_blocks ? block0 + b : n_blocks - 1;
-            w[b] = *(const uint32_t *)((const char *)d.mask + (s * d.padded + 16 * block) * 16 + w_at);
-        }
+    auto mask_of = [&](int64_t s, int b) -> uint32_t {
+        const int32_t block = block0 + b < n_blocks ? block0 + b : n_blocks - 1;
+        return *(const uint32_t *)((const char *)d.mask + (s * d.padded + 16 * block) * 16 + w_at);
     };
     auto put = [&](int buf, int v, const dense_u4 (&op)[3]) {
 #pragma unroll
@@ -190,48 +197,66 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
         for (int i = 0; i < 4; ++i) a[i] = __umul24(t & (0x00010001u << i), d.one_bits >> i);
         return __builtin_bit_cast(dense_b8, a);
     };
-    v4f hi[MB][NV], rest[MB][NV];
-    auto clear = [&]() {
-#pragma unroll
-        for (int b = 0; b < MB; ++b)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) hi[b][v] = rest[b][v] = v4f{0.f, 0.f, 0.f, 0.f};
+    // sums of one step's leading pieces, of the others, of all steps' leading pieces; the last in LDS where registers end
+    constexpr int kLdsBlocks = dense_lds_blocks(MB), kRegBlocks = MB - kLdsBlocks;
+    v4f hi[MB][NV], rest[MB][NV], sum[kRegBlocks][NV];
+    v4f *const s_sum = (v4f *)(smem + kDenseOperandBytes);
+    const v4f zero = {0.f, 0.f, 0.f, 0.f};
+    auto at_sum = [&](int b, int v) -> v4f * { return s_sum + ((wave * kLdsBlocks + b - kRegBlocks) * NV + v) * kWave + lane; };
+    auto add = [&](int b, int v) {
+        if (b < kRegBlocks) sum[b][v] += hi[b][v];
+        else *at_sum(b, v) += hi[b][v];
     };
-    auto multiply = [&](int buf, const uint32_t (&w)[MB]) {
+    uint32_t w[MB];                                      // bits of the step that is multiplied next
+    auto multiply = [&](int buf) {
         constexpr int kMine = kUnits / kShares;
-        dense_b8 x[2][NV][3];
+        // while there are registers, a unit's operands are read and a block's ones expanded ahead
+        constexpr int kAhead = MB < 6 && kMine > 1 ? 2 : 1;
+        constexpr bool kRoom = MB < kDenseMaxBlocks;
+        dense_b8 x[kAhead][NV][3];
         auto read = [&](int k) {
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int q = 0; q < 3; ++q) x[k & 1][v][q] = __builtin_bit_cast(dense_b8, s_b[buf][k * kShares + share][half][v][q][lane]);
+                for (int q = 0; q < 3; ++q) x[k % kAhead][v][q] = __builtin_bit_cast(dense_b8, s_b[buf][k * kShares + share][half][v][q][lane]);
         };
         read(0);
-        dense_b8 a = ones(w[0], share);
+        dense_b8 a = {};
+        if (kRoom) a = ones(w[0], share);
 #pragma unroll
         for (int k = 0; k < kMine; ++k) {
-            if (k + 1 < kMine) read(k + 1);
+            if (kAhead == 2 && k + 1 < kMine) read(k + 1);
             __builtin_amdgcn_sched_barrier(0);           // the reads stay ahead of this unit's matrix instructions
 #pragma unroll
-            for (int b = 0; b < MB; ++b) {               // the next block's ones beside this one's matrix instructions
+            for (int b = 0; b < MB; ++b) {
+                dense_b8 next = a;
                 const int to = b + 1 < MB ? k : k + 1 < kMine ? k + 1 : k;
-                const dense_b8 next = ones(w[b + 1 < MB ? b + 1 : 0], to * kShares + share);
+                if (kRoom) next = ones(w[b + 1 < MB ? b + 1 : 0], to * kShares + share);
+                else a = ones(w[b], k * kShares + share);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) hi[b][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k & 1][v][0], hi[b][v], 0, 0, 0);
+                for (int v = 0; v < NV; ++v)
+                    hi[b][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k % kAhead][v][0], k ? hi[b][v] : zero, 0, 0, 0);
 #pragma unroll
                 for (int q = 1; q < 3; ++q)
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) rest[b][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k & 1][v][q], rest[b][v], 0, 0, 0);
+                    for (int v = 0; v < NV; ++v)
+                        rest[b][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, x[k % kAhead][v][q], rest[b][v], 0, 0, 0);
+                if (b > 0 && k == kMine - 1)             // of the block before: its instructions have ended
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) add(b - 1, v);
                 a = next;
                 __builtin_amdgcn_sched_barrier(0);       // no more of them at a time: registers
             }
+            if (kAhead == 1 && k + 1 < kMine) read(k + 1);
         }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) add(MB - 1, v);
     };
     int64_t slot = 0;                                    // partial sum that the present run goes to
     bool started = false;                                // something has been written there
     auto partial = [&](int64_t at, int b) -> char * { return (char *)d.partials + (at * d.padded + 16 * (block0 + b)) * row_bytes + p_at; };
     // The step's exceptions, over the operands in LDS, which have been multiplied.  Every wavefront of the workgroup gets here.
-    auto special = [&](int64_t s, int buf, const uint32_t (&w)[MB], int32_t kinds) {
+    auto special = [&](int64_t s, int buf, int32_t kinds) {
 #pragma unroll 1
         for (int pass = kDenseCodes; pass <= kDenseLarge; ++pass) {
             if (!(kinds >> pass & 1)) continue;
@@ -268,11 +293,12 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
             for (int b = 0; b < MB; ++b)
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    v4f t0 = {0.f, 0.f, 0.f, 0.f}, t1 = t0;
+                    v4f t0 = zero, t1 = zero;
+                    const uint32_t bits = mask_of(s, b);
 #pragma unroll 1
                     for (int k = 0; k < kUnits / kShares; ++k) {
                         const int u = k * kShares + share;
-                        const dense_b8 a = ones(w[b], u);
+                        const dense_b8 a = ones(bits, u);
                         const dense_u4 (*const op)[kWave] = s_b[buf][u][half][v];
                         t0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(dense_b8, op[0][lane]), t0, 0, 0, 0);
                         t1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(dense_b8, op[1][lane]), t1, 0, 0, 0);
@@ -300,37 +326,42 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
     };
 
     vN x[8];
-    uint32_t w[MB];
     if (threadIdx.x < 2) s_special[threadIdx.x] = 0;
     load(s0, x);
-    load_mask(s0, w);
+#pragma unroll
+    for (int b = 0; b < MB; ++b) w[b] = mask_of(s0, b);
     dense_barrier();
     cut(0, x);
     if (s0 + 1 < s1) load(s0 + 1, x);
     dense_barrier();
-    const int64_t run = (s1 - s0 + d.runs - 1) / d.runs;
     int64_t s = s0;
 #pragma unroll 1
-    for (int32_t i = 0; i < d.runs; ++i) {
-        const int64_t to = s0 + (i + 1) * run < s1 ? s0 + (i + 1) * run : s1;
-        if (i % kDenseGroup == 0) {
-            slot = ((int64_t)k_part * kShares + share) * d.groups + i / kDenseGroup;
-            started = false;
-        }
-        clear();
+    for (int32_t i = 0; i < d.groups; ++i) {
+        const int64_t to = s0 + (i + 1) * (int64_t)d.group < s1 ? s0 + (i + 1) * (int64_t)d.group : s1;
+        slot = ((int64_t)k_part * kShares + share) * d.groups + i;
+        started = false;
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                rest[b][v] = zero;
+                if (b < kRegBlocks) sum[b][v] = zero;
+                else *at_sum(b, v) = zero;
+            }
 #pragma unroll 1
         for (; s < to; ++s) {
             const int buf = (int)(s - s0) & 1;
             const bool more = s + 1 < s1;
             uint32_t next_w[MB];
-            load_mask(more ? s + 1 : s, next_w);
+#pragma unroll
+            for (int b = 0; b < MB; ++b) next_w[b] = mask_of(more ? s + 1 : s, b);
             if (more) {
                 cut(buf ^ 1, x);
                 load(s + 2 < s1 ? s + 2 : s, x);
             }
-            multiply(buf, w);
+            multiply(buf);
             const int32_t kinds = __builtin_amdgcn_readfirstlane(s_special[buf]);
-            if (kinds) special(s, buf, w, kinds);
+            if (kinds) special(s, buf, kinds);
 #pragma unroll
             for (int b = 0; b < MB; ++b) w[b] = next_w[b];
             dense_barrier();
@@ -341,13 +372,12 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 vN *const p = (vN *)(partial(slot, b) + r * row_bytes);
-                vN sum;
+                vN out;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) sum[v] = (hi[b][v][r] + rest[b][v][r]) * d.down;
-                *p = started ? *p + sum : sum;
+                for (int v = 0; v < NV; ++v) out[v] = ((b < kRegBlocks ? sum[b < kRegBlocks ? b : 0][v] : *at_sum(b, v))[r] + rest[b][v][r]) * d.down;
+                *p = started ? *p + out : out;
             }
         }
-        started = true;
     }
 }
 
@@ -355,7 +385,7 @@ template <int MB, int RG>
 __global__ __launch_bounds__(kDenseWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void hd_dense_kernel(
     const DenseArgs d, const char *__restrict__ X, int32_t F4, int64_t n_cols, int64_t wgs_per_xcd, int remap)
 {
-    __shared__ __align__(16) char smem[2 * (kDenseStep / kDenseUnit) * 2 * 2 * 3 * kWave * 16];   // 96 KB
+    __shared__ __align__(16) char smem[kDenseOperandBytes + dense_lds_blocks(MB) * kDenseBlockSumBytes];
     // the tiles of a stretch of columns on one XCD, whose L2 they share
     const int32_t t = (int32_t)logical_block(wgs_per_xcd, remap), row_tile = t % d.row_tiles, f_tile = t / d.row_tiles % d.f_tiles;
     const int32_t k_part = t / d.row_tiles / d.f_tiles, F = 4 * F4;
@@ -451,9 +481,15 @@ static DenseArgs dense_args(const DevicePlan &dp, int32_t F)
     d.tile_rows = dp.dense_tile_rows;
     const int32_t tiles = (dp.n_dense_rows + dp.dense_tile_rows - 1) / dp.dense_tile_rows;   // a wavefront has a row block of each
     d.padded = tiles * dp.dense_tile_rows;
-    const int32_t most = dp.dense_tile_rows == 64 ? kDenseMaxBlocks : 1;
-    d.row_tiles = (tiles + most - 1) / most;
-    d.blocks = (tiles + d.row_tiles - 1) / d.row_tiles;
+    // Row blocks of a wavefront and workgroups beside each other, as few blocks in all as may be, those past the last row among them; what
+    // every workgroup does for itself, the cut above all, is half a block's work.
+    const int32_t most = dp.dense_tile_rows == 64 ? kDenseMaxBlocks : 1, least = (tiles + most - 1) / most;
+    for (int32_t t = least; t < 2 * least + 1; ++t) {
+        const int32_t blocks = (tiles + t - 1) / t;
+        if (t > least && t * (2 * blocks + 1) >= d.row_tiles * (2 * d.blocks + 1)) continue;
+        d.row_tiles = t;
+        d.blocks = blocks;
+    }
     d.f_tiles = (F + kDenseTile - 1) / kDenseTile;
     d.n_steps = (dp.n_cols + kDenseStep - 1) / kDenseStep;
     const int64_t wgs = (int64_t)d.row_tiles * d.f_tiles;
@@ -461,11 +497,11 @@ static DenseArgs dense_args(const DevicePlan &dp, int32_t F)
     if (k > d.n_steps) k = d.n_steps;
     d.k_parts = (int32_t)(k < 1 ? 1 : k);
     const int64_t share = (d.n_steps + d.k_parts - 1) / d.k_parts;
-    d.runs = (int32_t)((share + kDenseRun - 1) / kDenseRun);
-    d.groups = (d.runs + kDenseGroup - 1) / kDenseGroup;
+    d.groups = (int32_t)((share + kDenseGroup - 1) / kDenseGroup);
+    d.group = (int32_t)((share + d.groups - 1) / d.groups);
     d.n_partials = d.k_parts * (64 / dp.dense_tile_rows) * d.groups;
     d.n_wg = wgs * d.k_parts;
-    const int64_t run = (share + d.runs - 1) / d.runs, columns = std::min(share, run * kDenseGroup) * kDenseStep / (64 / dp.dense_tile_rows);
+    const int64_t columns = (int64_t)d.group * kDenseStep / (64 / dp.dense_tile_rows);
     int one = 0, store = kDenseStoreExp;                 // exponents: parts in 2^one and 2^store
     while ((int64_t)1 << one < columns) ++one;
     while ((int64_t)1 << (store + kDenseHeadExp) < columns) ++store;
@@ -550,8 +586,7 @@ int launch_hd_dense(const DevicePlan &dp, const float *X, int32_t F, void *strea
     case 4: launch(hd_dense_kernel<4, 4>); break;
     case 5: launch(hd_dense_kernel<5, 4>); break;
     case 6: launch(hd_dense_kernel<6, 4>); break;
-    case 7: launch(hd_dense_kernel<7, 4>); break;
-    default: launch(hd_dense_kernel<8, 4>); break;
+    default: launch(hd_dense_kernel<7, 4>); break;
     }
     return (int)hipGetLastError();
 }

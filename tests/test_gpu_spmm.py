@@ -1539,6 +1539,39 @@ def test_dense_product_is_no_less_precise_than_the_gathers(torch_cuda, n, n_dens
     assert off[0] <= off[1], off
 
 
+@pytest.mark.parametrize("n,n_dense,share,F", [(20011, 512, 0.25, 128), (65536, 64, 0.5, 512), (100003, 448, 0.08, 128)])
+@pytest.mark.parametrize("kind", ["exp(4 N)", "2^U(-20, 0)", "2^U(-40, 0)", "one in a thousand", "one in a stretch"])
+def test_dense_product_of_positive_numbers_over_many_binades(torch_cuda, n, n_dense, share, F, kind):
+    """Features of one sign and of very different size, small ones of which lose bits beside large ones in a truncating chain of matrix
+    instructions, always to the same side: in the 2-norm no further off than the gathers, or than a unit in the last place where a workgroup
+    sums 128 or 256 columns, so that there are no long chains."""
+    torch = torch_cuda
+    rng = np.random.default_rng(n + F)
+    dense = np.sort(rng.choice(n, n_dense, replace=False))
+    graph = _spread_dense_rows_graph(n, dense, int(share * n), rng)
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(*graph), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == n_dense and n_dense * int(share * n) * F >= 2 ** 25
+    X = torch.empty((n, F), device="cuda").uniform_(0, 1, generator=torch.Generator(device="cuda").manual_seed(n))
+    if kind == "exp(4 N)":
+        X = torch.exp(4 * torch.erfinv((2 * X.double() - 1).clamp(-1 + 1e-9, 1 - 1e-9)) * 2 ** 0.5).float()
+    elif kind.startswith("2^"):
+        X = torch.exp2(X * (-20 if "20" in kind else -40))
+    elif kind == "one in a thousand":
+        X = (X + 1) * 2.0 ** -15
+        X[5::997] = 1
+        X[3] = 4
+    else:
+        X = (X + 1) * 2.0 ** -17
+        X[::2048] = 1
+    want = torch.stack([X[torch.from_numpy(graph[1][graph[0][r]:graph[0][r + 1]].astype(np.int64)).cuda()].double().mean(0) for r in dense])
+    rows, Y, off = torch.from_numpy(dense).cuda(), torch.empty_like(X), []
+    for call in (lambda: G.groot_spmm_execute(plan, X, Y, F), lambda: G.groot_spmm_execute_rows(plan, X, Y, F, n)):
+        call()
+        off.append(((Y[rows].double() - want).norm() / want.norm()).item())
+    assert off[0] <= max(off[1], 2.0 ** -23 if n < 2 ** 15 else 0), off
+
+
 @pytest.mark.parametrize("F,scale", [(64, 8e36), (12, 3e37), (64, 1e-41)])
 def test_dense_product_of_very_large_and_very_small_numbers(torch_cuda, F, scale):
     """Rows whose plain sums overflow and whose weighted sums, like the gathers', do not; and numbers below the least normal one,
@@ -1711,11 +1744,11 @@ def test_very_small_numbers_do_not_slow_the_dense_product_down(torch_cuda):
                                                (12345, 576, 0.2, 64), (30001, 1100, 0.05, 132), (200001, 32, 0.2, 300),
                                                (200001, 16, 0.2, 512), (540000, 1024, 0.021, 512)])
 def test_dense_product_in_tiles_of_every_height(torch_cuda, n, n_dense, share, F):
-    """16 to 512 rows to a workgroup and several workgroups' worth, columns that end anywhere in a step of 128, stretches of one step
-    and of several runs, one and two partial sums per stretch, feature tiles of both kinds; features of very small numbers and of
-    numbers that three bf16 pieces do not hold among the others.  Against fp64: the pieces are exact and what their accumulators
-    round away is below 2^-24 of the running sum per matrix instruction, so 2^-21 of the absolute sum is ample; 2^-148 where the
-    result itself is rounded to multiples of 2^-149."""
+    """16 to 448 rows to a workgroup and several workgroups' worth, columns that end anywhere in a step of 128, stretches of one step
+    and of many, one and two partial sums per stretch, feature tiles of both kinds; features of very small and of subnormal numbers among
+    the others.  Against fp64: the pieces are exact, and a chain of four matrix instructions truncates four times, by 2^-23 of its own sum
+    each at most, so by 2^-21 of the absolute sum at most; the additions of chains round by 2^-24 of a running sum that cancels.  2^-148
+    where the result itself is rounded to multiples of 2^-149."""
     torch = torch_cuda
     rng = np.random.default_rng(n)
     length = np.ones(n, np.int64)
