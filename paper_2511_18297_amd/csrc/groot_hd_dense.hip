@@ -21,7 +21,7 @@
 // lane are the eight k of an operand, so nothing is transposed) and puts the operands to LDS, from where the wavefronts of a
 // feature half multiply them with the bits of their rows.  One barrier per 128 columns, loads stay in flight across it.
 //
-// Polarized graph, F = 128, 448 rows: 86 us, 1.04 PFLOP/s of the pieces' products.  Counters: matrix units busy 43 % of the cycles (of 2.4 GHz),
+// Polarized graph, F = 128, 448 rows: 86 us (24 with 16 rows or fewer, which is X at 5.5 TB/s), 1.04 PFLOP/s of the pieces' products.  Counters: matrix units busy 43 % of the cycles (of 2.4 GHz),
 // vector instructions issued in 31 %, three beside each matrix instruction (bits to operands, cut, sums), no bank conflicts.  Neither
 // is at its end: two wavefronts per SIMD, all that the accumulators leave room for, wait for each other at every barrier and for operands.
 // Operands of the next unit read ahead, where registers allow it, make no difference.
@@ -30,6 +30,7 @@
 // such a number, it is left out there and these columns' exceptions are multiplied once more (`special`).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "groot_device.h"
 
@@ -54,7 +55,7 @@ constexpr int dense_lds_blocks(int MB) { return MB == kDenseMaxBlocks ? 3 : 0; }
 
 struct DenseArgs {
     const HdChunk *rows;                     // [n_rows] the whole row as one piece, slot -1
-    const uint32_t *mask;                    // [step][padded row][kq < 4]: bit 4 u + i is column 32 u + 8 kq + 2 i of the step, bit 16 + 4 u + i the one behind it
+    const uint32_t *mask;                    // [step][padded row][kq < 4]: bit 4 u + i is column 8 kq + 2 i of unit u, bit 16 + 4 u + i the one behind it
     float *partials;                         // [k_part, unit share and group][padded rows][F]
     int32_t n_rows, tile_rows, padded;       // padded: n_rows in whole tiles
     int32_t blocks;                          // row blocks of 16 of a wavefront
@@ -104,6 +105,13 @@ __device__ __forceinline__ void dense_cut(float a, float b, unsigned &hi, unsign
 // NaN (a one in the first piece for +infinity and NaN, in the second for -infinity and NaN), and the very large numbers.
 enum DensePass { kDenseMain, kDenseCodes, kDenseLarge };
 
+// First column that the unit at `column` loads: a unit that would end behind the last column is moved back to end with it, and has bits only
+// for columns from `column` on (there are kDenseUnit columns or more).
+__device__ __forceinline__ int64_t dense_first_column(int64_t column, int64_t n_cols)
+{
+    return column < n_cols - kDenseUnit ? column : n_cols - kDenseUnit;
+}
+
 // Orders LDS accesses of the workgroup; loads from global memory stay in flight.
 __device__ __forceinline__ void dense_barrier()
 {
@@ -130,19 +138,10 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
     const int64_t s0 = d.n_steps * k_part / d.k_parts, s1 = d.n_steps * (k_part + 1) / d.k_parts;
     const int32_t n_blocks = d.padded / 16, block0 = (row_tile * RG + rg) * MB;   // the last tile may have blocks past the end
 
-    auto load = [&](int64_t s, vN (&x)[8]) {
-        const int64_t col = s * kDenseStep + cut_unit * kDenseUnit;
-        if (col + kDenseUnit <= n_cols) {
-            const char *const base = X + col * row_bytes;
+    auto load = [&](int64_t s, vN (&x)[8]) {             // without a branch, see the loop
+        const char *const base = X + dense_first_column(s * kDenseStep + cut_unit * kDenseUnit, n_cols) * row_bytes;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = *(const vN *)((base + e * row_bytes) + x_at);
-        } else {                                         // past the end: the last column again, there are no bits for it
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int64_t c = col + 8 * kq + e < n_cols ? col + 8 * kq + e : n_cols - 1;
-                x[e] = *(const vN *)(X + c * row_bytes + 4 * (f < F - NV ? f : F - NV));
-            }
-        }
+        for (int e = 0; e < 8; ++e) x[e] = *(const vN *)((base + e * row_bytes) + x_at);
     };
     auto mask_of = [&](int64_t s, int b) -> uint32_t {
         const int32_t block = block0 + b < n_blocks ? block0 + b : n_blocks - 1;
@@ -332,7 +331,7 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
     for (int b = 0; b < MB; ++b) w[b] = mask_of(s0, b);
     dense_barrier();
     cut(0, x);
-    if (s0 + 1 < s1) load(s0 + 1, x);
+    load(s0 + 1 < s1 ? s0 + 1 : s0, x);
     dense_barrier();
     int64_t s = s0;
 #pragma unroll 1
@@ -351,14 +350,14 @@ __device__ __forceinline__ void dense_tile(char *smem, const DenseArgs &d, const
 #pragma unroll 1
         for (; s < to; ++s) {
             const int buf = (int)(s - s0) & 1;
-            const bool more = s + 1 < s1;
+            // The last step, too, cuts and loads for one that does not come: where there are paths with and without loads, the compiler
+            // counts on the fewest and has the bits and the next step wait for the loads of X that were issued last (12 rows of half of
+            // 262,144 columns, this kernel, F = 128 and 512: 30.4 and 132 us, now 24.2 and 96).
             uint32_t next_w[MB];
 #pragma unroll
-            for (int b = 0; b < MB; ++b) next_w[b] = mask_of(more ? s + 1 : s, b);
-            if (more) {
-                cut(buf ^ 1, x);
-                load(s + 2 < s1 ? s + 2 : s, x);
-            }
+            for (int b = 0; b < MB; ++b) next_w[b] = mask_of(s + 1 < s1 ? s + 1 : s, b);
+            cut(buf ^ 1, x);
+            load(s + 2 < s1 ? s + 2 : s, x);
             multiply(buf);
             const int32_t kinds = __builtin_amdgcn_readfirstlane(s_special[buf]);
             if (kinds) special(s, buf, kinds);
@@ -395,53 +394,58 @@ __global__ __launch_bounds__(kDenseWaves * kWave) __attribute__((amdgpu_waves_pe
         dense_tile<MB, RG, 1>(smem, d, X, F, n_cols, row_tile, f_tile * kDenseTile, k_part);
 }
 
-// Workgroups [0, d.n_rows): one dense row each, its partial sums meet in fp64 and get the row's weight.  The ones behind: the split
-// rows among the others, as in hd_finish_kernel.
+// Workgroups [0, n_dense): kDenseFinishLanes x 4 features of a dense row each, whose partial sums meet in fp64 and get the row's weight.
+// The ones behind: the split rows among the others, as in hd_finish_kernel.  A few dense rows are a few workgroups, and what one takes is
+// latencies: 32 lane groups share a row's partial sums (up to 1,024 as a rule), 4 or 16 of each in flight.  12 rows of 512 partial sums, F = 128,
+// and of 128, F = 512, 4.8 and 5.0 us; with a workgroup per row 8.8 and 8.7.
+constexpr int kDenseFinishLanes = 8;
 template <int L, int W>
-__global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs d, const HdSplitRow *__restrict__ split,
+__global__ __launch_bounds__(kBlock) void hd_dense_finish_kernel(const DenseArgs d, int32_t n_dense, const HdSplitRow *__restrict__ split,
                                                                  int64_t n_split, const v4f *__restrict__ partials,
                                                                  v4f *__restrict__ Y, int32_t F4)
 {
-    constexpr int G = kBlock / L;
+    constexpr int G = kBlock / kDenseFinishLanes;
     typedef double v4d __attribute__((ext_vector_type(4)));
     auto wide = [](v4f x) { return __builtin_convertvector(x, v4d); };
-    __shared__ v4d s_red[kBlock];                        // [G][L]
-    const int g = threadIdx.x / L, f = threadIdx.x % L;
-    if (blockIdx.x >= d.n_rows) {
-        const int64_t k = (int64_t)(blockIdx.x - d.n_rows) * G + g;
-        if (k < n_split) hd_finish_row<L>(split[k], partials, Y, F4, nullptr, f);
+    __shared__ v4d s_red[kBlock];                        // [G][kDenseFinishLanes]
+    if ((int32_t)blockIdx.x >= n_dense) {
+        const int64_t k = (int64_t)((int32_t)blockIdx.x - n_dense) * (kBlock / L) + threadIdx.x / L;
+        if (k < n_split) hd_finish_row<L>(split[k], partials, Y, F4, nullptr, threadIdx.x % L);
         return;
     }
-    const int64_t row = d.rows[blockIdx.x].row;
-    const double weight = (double)row_weight<W>(d.rows[blockIdx.x].row_nnz) * d.weight_scale;
-#pragma unroll 1
-    for (int32_t fb = 0; fb < F4; fb += L) {
-        const int32_t ff = fb + f;
-        const bool live = ff < F4;
-        v4d acc = {0., 0., 0., 0.};
-        const v4f *p = (const v4f *)d.partials + (int64_t)blockIdx.x * F4 + (live ? ff : 0);
-        const int64_t step = (int64_t)d.padded * F4;
-        int32_t k = g;
-        for (; k + 3 * G < d.n_partials; k += 4 * G) {
-            const v4f x0 = p[k * step], x1 = p[(k + G) * step], x2 = p[(k + 2 * G) * step], x3 = p[(k + 3 * G) * step];
-            acc += (wide(x0) + wide(x1)) + (wide(x2) + wide(x3));
-        }
-        for (; k < d.n_partials; k += G) acc += wide(p[k * step]);
-        s_red[threadIdx.x] = acc;
-        __syncthreads();
+    const int g = threadIdx.x / kDenseFinishLanes, f_blocks = (F4 + kDenseFinishLanes - 1) / kDenseFinishLanes;
+    const int32_t r = (int32_t)blockIdx.x / f_blocks, f = (int32_t)blockIdx.x % f_blocks * kDenseFinishLanes + threadIdx.x % kDenseFinishLanes;
+    const HdChunk row = d.rows[r];
+    v4d acc = {0., 0., 0., 0.};
+    const v4f *p = (const v4f *)d.partials + (int64_t)r * F4 + (f < F4 ? f : 0);
+    const int64_t step = (int64_t)d.padded * F4;
+    int32_t k = g;
+    auto take = [&](auto ahead) {
+        constexpr int kAhead = decltype(ahead)::value;
+        v4f x[kAhead];
 #pragma unroll
-        for (int stride = G / 2; stride > 0; stride /= 2) {
-            if (g < stride) s_red[threadIdx.x] += s_red[threadIdx.x + stride * L];
-            __syncthreads();
-        }
-        if (g == 0 && live) Y[row * F4 + ff] = __builtin_convertvector(s_red[f] * weight, v4f);
+        for (int i = 0; i < kAhead; ++i) x[i] = p[(k + i * G < d.n_partials ? k + i * G : k) * step];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if (k + i * G < d.n_partials) acc += wide(x[i]);
+        k += kAhead * G;
+    };
+    while (k + 4 * G < d.n_partials) take(std::integral_constant<int, 16>());
+    if (k < d.n_partials) take(std::integral_constant<int, 4>());
+    s_red[threadIdx.x] = acc;
+    __syncthreads();
+#pragma unroll
+    for (int stride = G / 2; stride > 0; stride /= 2) {
+        if (g < stride) s_red[threadIdx.x] += s_red[threadIdx.x + stride * kDenseFinishLanes];
         __syncthreads();
     }
+    const double weight = (double)row_weight<W>(row.row_nnz) * d.weight_scale;
+    if (g == 0 && f < F4) Y[(int64_t)row.row * F4 + f] = __builtin_convertvector(s_red[threadIdx.x] * weight, v4f);
 }
 
 // the four mask words of row r and step b, one thread each; padding rows get zeros
 __global__ __launch_bounds__(kBlock) void dense_mask_kernel(const HdChunk *__restrict__ rows, int32_t n_rows, int32_t padded,
-                                                            const int32_t *__restrict__ col, int64_t n_steps,
+                                                            const int32_t *__restrict__ col, int64_t n_cols, int64_t n_steps,
                                                             uint4 *__restrict__ mask)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -459,10 +463,11 @@ __global__ __launch_bounds__(kBlock) void dense_mask_kernel(const HdChunk *__res
             if (c[mid] < first) lo = mid + 1; else hi = mid;
         }
         for (; lo < row.len && c[lo] < first + kDenseStep; ++lo) {
-            const int at = (int)(c[lo] - first), e = at % 8;
-            const uint32_t bit = 1u << (4 * (at / kDenseUnit) + e / 2 + 16 * (e % 2));
+            const int unit = (int)(c[lo] - first) / kDenseUnit;
+            const int at = (int)(c[lo] - dense_first_column(first + unit * kDenseUnit, n_cols)), e = at % 8;
+            const uint32_t bit = 1u << (4 * unit + e / 2 + 16 * (e % 2));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) w[k] |= at / 8 % 4 == k ? bit : 0u;
+            for (int k = 0; k < 4; ++k) w[k] |= at / 8 == k ? bit : 0u;
         }
     }
     mask[i] = uint4{w[0], w[1], w[2], w[3]};
@@ -545,8 +550,8 @@ int launch_dense_mask(const DevicePlan &dp, void *stream)
 {
     const DenseArgs d = dense_args(dp, 4);
     const int64_t grid = (d.n_steps * d.padded + kBlock - 1) / kBlock;
-    if (!grid_ok(grid)) return (int)hipErrorInvalidConfiguration;
-    dense_mask_kernel<<<dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream>>>(d.rows, d.n_rows, d.padded, dp.col, d.n_steps,
+    if (!grid_ok(grid) || dp.n_cols < kDenseUnit) return (int)hipErrorInvalidConfiguration;
+    dense_mask_kernel<<<dim3((unsigned)grid), dim3(kBlock), 0, (hipStream_t)stream>>>(d.rows, d.n_rows, d.padded, dp.col, dp.n_cols, d.n_steps,
                                                                                       (uint4 *)dp.dense_mask);
     return (int)hipGetLastError();
 }
@@ -595,10 +600,11 @@ int launch_hd_dense_finish(const DevicePlan &dp, float *Y, int32_t F, void *stre
 {
     const DenseArgs d = dense_args(dp, F);
     const int L = dense_lanes(F / 4);
-    const int64_t n_wg = d.n_rows + (dp.n_split_rows + kBlock / L - 1) / (kBlock / L);
+    const int64_t n_dense = (int64_t)d.n_rows * ((F / 4 + kDenseFinishLanes - 1) / kDenseFinishLanes);
+    const int64_t n_wg = n_dense + (dp.n_split_rows + kBlock / L - 1) / (kBlock / L);
     if (!grid_ok(n_wg)) return (int)hipErrorInvalidConfiguration;
     auto launch = [&](auto kernel) {
-        kernel<<<dim3((unsigned)n_wg), dim3(kBlock), 0, (hipStream_t)stream>>>(d, dp.split_rows, dp.n_split_rows,
+        kernel<<<dim3((unsigned)n_wg), dim3(kBlock), 0, (hipStream_t)stream>>>(d, (int32_t)n_dense, dp.split_rows, dp.n_split_rows,
                                                                                (const v4f *)dp.partials, (v4f *)Y, F / 4);
     };
     if (dp.weight_mode == kMean) { GROOT_DENSE_L(L, (launch(hd_dense_finish_kernel<kL, kMean>))) }

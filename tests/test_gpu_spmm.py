@@ -1725,6 +1725,31 @@ def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torc
     assert _best_time(torch_cuda, run) < 1.7 * finite
 
 
+@pytest.mark.parametrize("n,n_dense,F", [(8192, 17, 512), (8193, 17, 512), (8223, 30, 260), (262149, 12, 32), (300015, 40, 100)])
+def test_last_columns_and_partial_sums_of_a_few_dense_rows(torch_cuda, n, n_dense, F):
+    """A few rows, 128 to 1,024 partial sums each, whose last columns are in a unit of the matrix instruction that ends with or behind the last
+    column; X is infinite in the columns before them, which such a unit loads, too, and the rows do not name."""
+    dense = np.arange(1, n, n // n_dense)[:n_dense]
+    first = n - (n % 32 or 7)
+    cols = np.concatenate([np.arange(n // 2, dtype=np.int32), np.arange(first, n, dtype=np.int32)])
+    length = np.ones(n, np.int64)
+    length[dense] = cols.size
+    rowptr = np.concatenate([[0], np.cumsum(length)])
+    col = np.repeat(np.arange(n, dtype=np.int32), length)
+    for r in dense:
+        col[rowptr[r]:rowptr[r + 1]] = cols
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, np.repeat(np.float32(1) / length.astype(np.float32), length)), 32)
+    G.groot_plan_upload(plan, F)
+    assert G.groot_plan_query(plan, "dense_rows") == n_dense and n_dense * cols.size * F >= 2 ** 25
+    X = torch_cuda.empty((n, F), device="cuda").uniform_(-1, 1)
+    X[n - 50:first] = float("inf")
+    Y = torch_cuda.empty_like(X)
+    G.groot_spmm_execute(plan, X, Y, F)
+    want = X[torch_cuda.from_numpy(cols.astype(np.int64)).cuda()].double()
+    err = (Y[torch_cuda.from_numpy(dense).cuda()].double() - want.mean(0)).abs()
+    assert (err <= 2.0 ** -21 * want.abs().mean(0)).all(), err.max()
+
+
 def test_very_small_numbers_do_not_slow_the_dense_product_down(torch_cuda):
     """They are summed as all others (as exceptions, in a pass of their own, they took twice as long)."""
     n, F = 131072, 128
