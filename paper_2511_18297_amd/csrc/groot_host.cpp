@@ -555,8 +555,11 @@ namespace {
 // of matrix instructions; that many gathers of 512 bytes are 1 % of the columns where the last-level cache serves them (7 TB/s) and
 // 2.6 % where the L2s do (up to 23 TB/s, rows that share their columns).  Whole step, us, for shares of 30 / 60 / 100: 262,144 rows, F =
 // 128 (384, 448 and 512 dense rows) 184 / 182 / 176, F = 200 - / 317 / 307, F = 32 68 / 67.5 / 65.6; 131,072 rows, F = 128 (192, 256, 256) 82 /
-// 79 / 79.  A last tile that is less than half full is left to the gathers.
-constexpr int64_t kDenseShare = 50;
+// 79 / 79.  A last tile that is not full adds a row block of 64 all the same and pays if its rows hold that many entries; it is taken from two
+// columns' worth of the matrix on (64 rows / 31).  Whole call, us, F = 32 / 128 / 512, 262,144 rows, last tile by gathers / in the product: 31
+// rows of a quarter of the columns 66 / 145 / 710, 37 / 100 / 443; 31 of a tenth 52 / 152 / 679, 37 / 101 / 442; below the line 6 of a quarter
+// 38 / 104 / 488, 37 / 100 / 442.  4 rows of half of the columns, all there are, 43 / 107 / 487, 35 / 90 / 390, 7 49 / 139 / 594, 34 / 89 / 393.
+constexpr int64_t kDenseShare = 50, kDenseLastShare = 31;
 constexpr int64_t kDenseMinEntries = 32768;  // below, the launches are what a call takes
 
 std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<int32_t> &hd_rows, int32_t &tile_rows)
@@ -575,7 +578,7 @@ std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<i
             const size_t end = std::min(rows.size(), first + (size_t)tile_rows);
             int64_t in_tile = 0;
             for (size_t k = first; k < end; ++k) in_tile += rows[k].len;
-            if (in_tile * kDenseShare < g->n * tile_rows || (end - first) * 2 < (size_t)tile_rows) break;
+            if (in_tile * (end - first == (size_t)tile_rows ? kDenseShare : kDenseLastShare) < g->n * tile_rows) break;
             keep = end;
             entries += in_tile;
         }

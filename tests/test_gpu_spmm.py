@@ -1725,6 +1725,25 @@ def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torc
     assert _best_time(torch_cuda, run) < 1.7 * finite
 
 
+@pytest.mark.parametrize("n,rows,want", [(30016, [(95, 0.25)], 95), (30016, [(95, 0.1)], 95), (30016, [(159, 0.25)], 159),
+                                         (30016, [(70, 0.5)], 70), (30016, [(70, 0.1)], 64), (70000, [(4, 0.5)], 4), (70000, [(7, 0.5)], 7),
+                                         (70000, [(2, 0.9)], 2), (70000, [(16, 0.25), (60, 0.02)], 64)])
+def test_rows_that_are_computed_as_a_dense_product(torch_cuda, n, rows, want):
+    """A last tile of rows is taken by the entries that it holds, however few its rows are; so are the only rows."""
+    rng = np.random.default_rng(n)
+    lengths = np.concatenate([np.full(k, int(share * n)) for k, share in rows])
+    dense = np.sort(rng.choice(n, lengths.size, replace=False))
+    length = np.ones(n, np.int64)
+    length[dense] = lengths
+    rowptr = np.concatenate([[0], np.cumsum(length)])
+    col = np.repeat(np.arange(n, dtype=np.int32), length)
+    for r in dense:
+        col[rowptr[r]:rowptr[r + 1]] = np.arange(length[r])
+    plan = G.groot_spmm_plan(G.groot_graph_from_csr(rowptr, col, np.repeat(np.float32(1) / length.astype(np.float32), length)), 32)
+    G.groot_plan_upload(plan, 128)
+    assert G.groot_plan_query(plan, "dense_rows") == want
+
+
 @pytest.mark.parametrize("n,n_dense,F", [(8192, 17, 512), (8193, 17, 512), (8223, 30, 300), (262149, 12, 32), (300015, 40, 100)])
 def test_last_columns_and_partial_sums_of_a_few_dense_rows(torch_cuda, n, n_dense, F):
     """A few rows, 128 to 1,024 partial sums each, whose last columns are in a unit of the matrix instruction that ends with or behind the last
