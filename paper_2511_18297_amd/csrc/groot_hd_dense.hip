@@ -529,14 +529,17 @@ size_t dense_partials_floats(const DevicePlan &dp, int32_t max_F)
     return most;
 }
 
-// A launch and the finishing kernel more than with the gathers: polarized graphs, whole step, us, gathers / dense product, by
-// entries of the dense rows x F: 16,384 rows 7.7 M (F = 64) 13.0 / 15.6, 15 M (128) 18.0 / 19.2, 24 M (200) 25.2 / 24.0; 32,768 rows
-// 11 M (32) 17.8 / 15.8, 22 M (64) 20.8 / 20.2, 43 M (128) 31.0 / 26.2, 67 M (200) 48.5 / 33.5; 65,536 rows 9.5 M (8) 20.0 / 21.5, 19 M
-// (16) 29.3 / 24, 38 M (32) 29.4 / 24.0, 76 M (64) 40.8 / 30.0; 131,072 rows 37 M (8) 38.3 / 32.2, 147 M (32) 56 / 41; 262,144 rows
-// 139 M (8) 92 / 59, 557 M (32) 136 / 66.
+// Where the product takes less than the gathers of the same rows, in femtoseconds: a gather 300 per entry and feature; the product 4 us of launches, 150 per
+// column and feature to read and cut X, 4.7 per padded row, column and feature.  Whole calls, us, gathers / product, polarized graphs: 16,384
+// rows (64 dense), F = 64 12.2 / 15.8, 128 17.6 / 19.0, 200 24.2 / 22.9; 32,768 rows (64) F = 32 17.2 / 16.2, 64 20.0 / 20.2, 128 30.4 / 24.4; 65,536
+// rows (128) F = 8 19.3 / 21.4, 12 25.9 / 25.2, 16 28.6 / 23.7, 128 54.1 / 35.4; 131,072 rows (256) F = 8 37.8 / 31.2; 262,144 rows F = 8 89.8 / 56.0.  Rows of one
+// length: 64 of 5 % of 262,144 columns F = 8 23.4 / 25.2, 16 33.0 / 30.9, 128 118 / 93; 16 of 10 % F = 32 34.0 / 34.0, 48 51.5 / 50.0, 128 93.8 / 90.5; of 65,536
+// columns 64 of 5 % F = 64 21.9 / 27.3, 128 32.6 / 31.9, 200 49.4 / 46.3; 300 of 3 % F = 32 22.5 / 26.7, 64 33.7 / 36.6, 128 51.1 / 44.5; 16 of 10 % F = 200 40.4 / 44.9.
 bool hd_dense_serves(const DevicePlan &dp, int32_t F)
 {
-    return dp.n_dense_rows > 0 && dp.n_cols == dp.n && F >= kDenseMinF && dp.dense_entries * F >= (int64_t)1 << 24;
+    if (dp.n_dense_rows < 1 || dp.n_cols != dp.n || F < kDenseMinF) return false;
+    const int64_t padded = (dp.n_dense_rows + dp.dense_tile_rows - 1) / dp.dense_tile_rows * dp.dense_tile_rows;
+    return 300. * dp.dense_entries * F >= 4e9 + (150 + 4.7 * padded) * dp.n_cols * F;
 }
 
 size_t dense_mask_words(const DevicePlan &dp)

@@ -550,16 +550,17 @@ groot_status upload_layer_hd_side(groot_plan *pl, const int32_t *hd_rows_host, i
 
 namespace {
 // The high-degree rows that are cheaper as a dense product than by gathers, longest first, and how many are multiplied at a
-// time.  A tile of rows costs what its padded rows times all columns cost, whatever they hold; a gather costs its entry: a tile
-// pays when its rows together hold one in kDenseShare of the columns each, on average.  64 rows of 262,144 columns at F = 128 are 10 us
-// of matrix instructions; that many gathers of 512 bytes are 1 % of the columns where the last-level cache serves them (7 TB/s) and
-// 2.6 % where the L2s do (up to 23 TB/s, rows that share their columns).  Whole step, us, for shares of 30 / 60 / 100: 262,144 rows, F =
-// 128 (384, 448 and 512 dense rows) 184 / 182 / 176, F = 200 - / 317 / 307, F = 32 68 / 67.5 / 65.6; 131,072 rows, F = 128 (192, 256, 256) 82 /
-// 79 / 79.  A last tile that is not full adds a row block of 64 all the same and pays if its rows hold that many entries; it is taken from two
+// time.  A tile of rows costs what its padded rows times all columns cost, 4.7 fs per feature of X, whatever they hold; a gather costs its
+// entry, 300 fs (groot_hd_dense.hip): a tile pays when its rows together hold one in kDenseShare of the columns each, on average.  Where X is small
+// gathers cost less, where it is in no cache more.  Whole call, us, for shares of 14 / 30 / 50 / 80 / 120, polarized graphs: 262,144 rows, F = 128 (320,
+// 384, 448, 448 and 512 dense rows) 204 / 179 / 176 / 177 / 174, F = 200 357 / 311 / 308 / 307 / 300, F = 32 72 / 67 / 67 / 67 / 65; 131,072 rows, F =
+// 128 (192, 192, 256, 256, 256) 81 / 81 / 76 / 76 / 75; 65,536 rows (64, then 128) 56 / 36.  256 rows of 1.5 % of the columns, gathers / product: 262,144
+// columns, F = 32 / 128 / 512 38.7 / 120 / 552, 42.3 / 116 / 509; 65,536 columns, F = 32 / 128 16.8 / 32.2, 25.4 / 41.7.
+// A last tile that is not full adds a row block of 64 all the same and pays if its rows hold that many entries; it is taken from two
 // columns' worth of the matrix on (64 rows / 31).  Whole call, us, F = 32 / 128 / 512, 262,144 rows, last tile by gathers / in the product: 31
 // rows of a quarter of the columns 66 / 145 / 710, 37 / 100 / 443; 31 of a tenth 52 / 152 / 679, 37 / 101 / 442; below the line 6 of a quarter
 // 38 / 104 / 488, 37 / 100 / 442.  4 rows of half of the columns, all there are, 43 / 107 / 487, 35 / 90 / 390, 7 49 / 139 / 594, 34 / 89 / 393.
-constexpr int64_t kDenseShare = 50, kDenseLastShare = 31;
+constexpr int64_t kDenseShare = 64, kDenseLastShare = 31;
 constexpr int64_t kDenseMinEntries = 32768;  // below, the launches are what a call takes
 
 std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<int32_t> &hd_rows, int32_t &tile_rows)
