@@ -212,22 +212,25 @@ struct Tmp {                                             // device memory freed 
     }
 };
 
-__global__ __launch_bounds__(kBlock) void plan_finish(float *__restrict__ zero_row, int32_t *__restrict__ dst,
-                                                      const int32_t *__restrict__ src, int64_t n)
+__global__ __launch_bounds__(kBlock) void plan_finish(float *__restrict__ zero_row, int32_t *__restrict__ mid, const int32_t *__restrict__ mid_src,
+                                                      int64_t n_mid, int32_t *__restrict__ hd, const int32_t *__restrict__ hd_src, int64_t n_hd)
 {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n || i < kZeroRowFloats + kTrashFloats;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n_mid || i < n_hd || i < kZeroRowFloats + kTrashFloats;
          i += (int64_t)gridDim.x * kBlock) {
         if (i < kZeroRowFloats + kTrashFloats) zero_row[i] = 0.f;
-        if (i < n) dst[i] = src[i];
+        if (i < n_mid) mid[i] = mid_src[i];
+        if (i < n_hd) hd[i] = hd_src[i];
     }
 }
 
 }  // namespace
 
-int launch_plan_finish(float *zero_row, int32_t *dst, const int32_t *src, int64_t n, void *stream)
+int launch_plan_finish(float *zero_row, int32_t *mid, const int32_t *mid_src, int64_t n_mid, int32_t *hd, const int32_t *hd_src,
+                       int64_t n_hd, void *stream)
 {
-    const int64_t most = std::max<int64_t>(n, kZeroRowFloats + kTrashFloats), grid = (most + kBlock - 1) / kBlock;
-    plan_finish<<<dim3((unsigned)std::min<int64_t>(grid, 4096)), dim3(kBlock), 0, (hipStream_t)stream>>>(zero_row, dst, src, n);
+    const int64_t most = std::max<int64_t>({n_mid, n_hd, kZeroRowFloats + kTrashFloats}), grid = (most + kBlock - 1) / kBlock;
+    plan_finish<<<dim3((unsigned)std::min<int64_t>(grid, 4096)), dim3(kBlock), 0, (hipStream_t)stream>>>(zero_row, mid, mid_src, n_mid, hd,
+                                                                                                          hd_src, n_hd);
     return (int)hipGetLastError();
 }
 

@@ -1377,7 +1377,6 @@ struct DevBuf {
     ~DevBuf() { dev_free(p); }
     int alloc(size_t bytes) { return dev_alloc(&p, bytes ? bytes : 1); }
     template <class T> T *as() const { return (T *)p; }
-    void *release() { void *q = p; p = nullptr; return q; }
 };
 }  // namespace
 
@@ -1442,13 +1441,13 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
         groot_status st;
         if ((st = to_device<float>(&d.zero_row, nullptr, kZeroRowFloats + kTrashFloats, "zero row")) != GROOT_OK ||
             (st = to_device<float>(&d.partials, nullptr, (size_t)sched.n_partials * max_F, "HD partial sums")) != GROOT_OK ||
-            (st = to_device<float>(&d.hd_agg, nullptr, (size_t)n_hd * max_F, "high-degree sums of the fused layer")) != GROOT_OK) {
+            (st = to_device<float>(&d.hd_agg, nullptr, (size_t)n_hd * max_F, "high-degree sums of the fused layer")) != GROOT_OK ||
+            (st = to_device<int32_t>(&d.hd_rows, nullptr, (size_t)n_hd, "high-degree row list")) != GROOT_OK) {   // hd_rows has room for most_hd
             std::string keep = groot_last_error();
             release_device(pl.get());
             set_error(keep);
             return st;
         }
-        d.hd_rows = (int32_t *)hd_rows.release();
         bool compress = false;
         d.n_hd_rows = n_hd;
         d.n = d.n_cols = n;
@@ -1482,7 +1481,8 @@ extern "C" groot_status groot_dev_part_plan(groot_dev_part *part, int32_t degree
                 return st;
             }
             const int64_t skipped = d.n_mid_rows ? first_mid - at_most(kPipeMinDepth) : 0;     // not longer than the slots after all
-            if ((err = launch_plan_finish(d.zero_row, d.mid_rows, by_degree.as<int32_t>() + skipped, d.n_mid_rows, hip_stream))) {
+            if ((err = launch_plan_finish(d.zero_row, d.mid_rows, by_degree.as<int32_t>() + skipped, d.n_mid_rows, d.hd_rows,
+                                          hd_rows.as<int32_t>(), n_hd, hip_stream))) {
                 release_device(pl.get());
                 return fail(GROOT_EHIP, std::string(who) + hip_error_text(err));
             }

@@ -226,8 +226,9 @@ void free_device_part(DevicePart &part);
 int device_time_ms(void *stream, int reps, int (*fn)(void *ctx), void *ctx, float *ms);
 int device_download(void *dst_host, const void *src_dev, size_t bytes, void *stream);
 int device_wait(void *stream);
-// the row of zeros and the area behind it cleared and n ints copied, in stream order
-int launch_plan_finish(float *zero_row, int32_t *dst, const int32_t *src, int64_t n, void *stream);
+// the row of zeros and the area behind it cleared and two lists copied, in stream order
+int launch_plan_finish(float *zero_row, int32_t *mid, const int32_t *mid_src, int64_t n_mid, int32_t *hd, const int32_t *hd_src,
+                       int64_t n_hd, void *stream);
 const char *hip_error_text(int err);
 
 // Device memory of the library (groot_pool.hip): every allocation that it makes.  dev_alloc returns a hipError_t as int and

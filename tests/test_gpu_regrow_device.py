@@ -375,6 +375,21 @@ def test_device_built_plans_at_the_edges_of_their_rules(torch_cuda, n_hd, length
     assert_close_to_oracle(Y.cpu().numpy(), Y64, S, f"{n_hd} pieces")
 
 
+def test_a_part_plan_keeps_no_more_rows_than_it_has_high_degree_ones(torch_cuda):
+    """The list of the high-degree rows is made with room for every row that could be one (nnz / threshold); a plan that kept it as it
+    is would hold 2.6 MB more with a threshold of 8 than with one of 1,024, on a graph with some hundred such rows."""
+    aig = wl.csa_multiplier_aig(256)
+    per_plan = []
+    for T in (8, 1024):                                      # with the last object of each, all memory goes back
+        whole = _resident_plan(G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 2))
+        plans = [G.groot_dev_part_plan(G.groot_partition_regrow_device(whole, 1, 0), T, 32) for _ in range(4)]
+        before = torch_cuda.cuda.mem_get_info()[0]
+        plans += [G.groot_dev_part_plan(G.groot_partition_regrow_device(whole, 1, 0), T, 32) for _ in range(24)]
+        per_plan.append((before - torch_cuda.cuda.mem_get_info()[0]) / 24)
+        del plans, whole
+    assert per_plan[1] > 1e7 and per_plan[0] - per_plan[1] < 1e6, per_plan
+
+
 def test_error_paths(torch_cuda):
     torch = torch_cuda
     aig = wl.csa_multiplier_aig(8)
