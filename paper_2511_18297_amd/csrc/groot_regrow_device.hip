@@ -27,6 +27,7 @@ constexpr int kRgWords = 4;                                        // words of a
 constexpr int kRgBlockWords = kBlock * kRgWords;                   // ... per workgroup: 32,768 nodes
 constexpr int kRgLenBlock = 1024;                                  // rows per workgroup of the length kernels
 constexpr int kRgFusedSums = 4096;                                 // up to so many of them every workgroup adds up those before it
+constexpr int kRgFusedCounts = 1024;                               // ... so many workgroups of words, 33 M nodes, of which all would read them
 constexpr int kRgMark = 8;                                         // entries in flight per thread of rg_mark_slices
 constexpr int kRgShort = 16;                                       // longest row that one lane walks alone
 constexpr int kRgUnroll = 4;                                       // 64-entry chunks of a long row in flight
@@ -246,9 +247,27 @@ __device__ __forceinline__ int64_t rg_block_prefix(int64_t x)
     return run;
 }
 
-// Set bits before every word and the ids of the set, ascending; grid as rg_count.  A workgroup adds up the counts of those before
-// it by itself (at most a few thousand of them, one per 32,768 nodes).
-__global__ __launch_bounds__(kBlock) void rg_place(RgGraph g, const int32_t *__restrict__ cnt, int64_t *__restrict__ global_id,
+// One workgroup per array of n_sums numbers: they become the sums of those before them, which T holds.
+template <class T>
+__global__ __launch_bounds__(kRgLenBlock) void rg_scan_sums(T *__restrict__ sums, int64_t n_sums)
+{
+    sums += blockIdx.x * n_sums;
+    const int64_t seg = (n_sums + kRgLenBlock - 1) / kRgLenBlock;
+    const int64_t b0 = (int64_t)threadIdx.x * seg < n_sums ? (int64_t)threadIdx.x * seg : n_sums;
+    const int64_t b1 = b0 + seg < n_sums ? b0 + seg : n_sums;
+    int64_t sum = 0;
+    for (int64_t b = b0; b < b1; ++b) sum += (int64_t)sums[b];
+    int64_t run = rg_block_prefix<kRgLenBlock / kWave>(sum);
+    for (int64_t b = b0; b < b1; ++b) {
+        const int64_t v = (int64_t)sums[b];
+        sums[b] = (T)run;
+        run += v;
+    }
+}
+
+// Set bits before every word and the ids of the set, ascending; grid as rg_count.  scanned: cnt holds prefixes already; else a workgroup adds
+// up the counts of those before it by itself, up to kRgFusedCounts of them, one per 32,768 nodes.
+__global__ __launch_bounds__(kBlock) void rg_place(RgGraph g, const int32_t *__restrict__ cnt, bool scanned, int64_t *__restrict__ global_id,
                                                    unsigned long long *__restrict__ sums, int64_t n_sums)
 {
     if (blockIdx.y == 0)                                 // rg_row_len adds to them
@@ -257,8 +276,12 @@ __global__ __launch_bounds__(kBlock) void rg_place(RgGraph g, const int32_t *__r
     const uint32_t *const bits = own ? g.own : g.halo;
     cnt += (int64_t)blockIdx.y * gridDim.x;
     int64_t before = 0;
-    for (int64_t b = threadIdx.x; b < blockIdx.x; b += kBlock) before += cnt[b];
-    before = rg_block_sum<kWavesPerBlock>(before);
+    if (scanned) {
+        before = cnt[blockIdx.x];
+    } else {
+        for (int64_t b = threadIdx.x; b < blockIdx.x; b += kBlock) before += cnt[b];
+        before = rg_block_sum<kWavesPerBlock>(before);
+    }
     const int64_t at = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const uint4 w4 = ((const uint4 *)bits)[at];
     const uint32_t w[kRgWords] = {w4.x, w4.y, w4.z, w4.w};
@@ -414,22 +437,6 @@ __global__ __launch_bounds__(kBlock) void rg_row_len_long(RgGraph g, const int64
     if (threadIdx.x == 0) {
         rg_add(totals + kRgNnz, nnz);
         rg_add(totals + kRgCross, cross);
-    }
-}
-
-// One workgroup: sums -> exclusive prefix
-__global__ __launch_bounds__(kRgLenBlock) void rg_scan_sums(unsigned long long *__restrict__ sums, int64_t n_sums)
-{
-    const int64_t seg = (n_sums + kRgLenBlock - 1) / kRgLenBlock;
-    const int64_t b0 = (int64_t)threadIdx.x * seg < n_sums ? (int64_t)threadIdx.x * seg : n_sums;
-    const int64_t b1 = b0 + seg < n_sums ? b0 + seg : n_sums;
-    int64_t sum = 0;
-    for (int64_t b = b0; b < b1; ++b) sum += (int64_t)sums[b];
-    int64_t run = rg_block_prefix<kRgLenBlock / kWave>(sum);
-    for (int64_t b = b0; b < b1; ++b) {
-        const int64_t v = (int64_t)sums[b];
-        sums[b] = (unsigned long long)run;
-        run += v;
     }
 }
 
@@ -685,7 +692,9 @@ int launch_regrow_device(const DevicePlan &dp, int64_t n1, int32_t P, const int3
         return done(kErrOutOfDeviceMemory);
 
     if (n_loc) {
-        rg_place<<<dim3((unsigned)blocks, sets), dim3(kBlock), 0, st>>>(g, cnt, part.global_id, sums, n_sums);
+        const bool scanned = blocks > kRgFusedCounts;
+        if (scanned) rg_scan_sums<<<dim3(sets), dim3(kRgLenBlock), 0, st>>>(cnt, blocks);
+        rg_place<<<dim3((unsigned)blocks, sets), dim3(kBlock), 0, st>>>(g, cnt, scanned, part.global_id, sums, n_sums);
         rg_row_len<<<dim3(rg_grid(n_loc, kBlock)), dim3(kBlock), 0, st>>>(g, part.global_id, n_loc, len, sums, totals, long_list,
                                                                           n_long);
         if (!rg_long_by_search(g))

@@ -129,6 +129,30 @@ def test_more_copies_than_a_grid_has_rows_and_more_rows_than_one_scan_step(torch
         assert np.array_equal(got["global_id"], np.arange(view["n"]))
 
 
+def test_node_sets_whose_counts_take_a_scan_of_their_own(torch_cuda):
+    """42 M nodes, 1,280 workgroups of words: the whole graph as one part, by the built-in rule and by the caller's, and a part whose boundary
+    lies in other workgroups, against the sets computed here."""
+    torch = torch_cuda
+    aig = wl.csa_multiplier_aig(1024)
+    g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 5)
+    view, plan = G.groot_graph_view(g), _resident_plan(g)
+    n = view["n"]
+    part_of = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for rule in (None, part_of):
+        print("device regrow: the whole of 1,024 bits x 5", flush=True)
+        got = G.groot_dev_part_download(G.groot_partition_regrow_device(plan, 1, 0, rule))
+        assert np.array_equal(got["global_id"], np.arange(n))
+        assert np.array_equal(got["rowptr"], view["rowptr"]) and np.array_equal(got["col"], view["col"])
+    part_of[n // 2 - 1000:] = 1                              # in the middle of the third copy
+    owned = np.arange(n // 2 - 1000, n)
+    of_owned = view["col"][view["rowptr"][owned[0]]:]
+    halo = np.unique(of_owned[of_owned < owned[0]])
+    print("device regrow: half of 1,024 bits x 5", flush=True)
+    got = G.groot_dev_part_download(G.groot_partition_regrow_device(plan, 2, 1, part_of))
+    assert halo.size and np.array_equal(got["global_id"], np.concatenate([owned, halo]))
+    assert np.array_equal(got["rowptr"][:owned.size + 1], view["rowptr"][owned[0]:] - view["rowptr"][owned[0]])
+
+
 @pytest.mark.parametrize("P", [1, 2, 7])
 @pytest.mark.parametrize("rule", [True, False])
 def test_rows_of_every_length_of_a_directed_graph(torch_cuda, P, rule):
