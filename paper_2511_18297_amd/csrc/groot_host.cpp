@@ -556,11 +556,14 @@ namespace {
 // 384, 448, 448 and 512 dense rows) 204 / 179 / 176 / 177 / 174, F = 200 357 / 311 / 308 / 307 / 300, F = 32 72 / 67 / 67 / 67 / 65; 131,072 rows, F =
 // 128 (192, 192, 256, 256, 256) 81 / 81 / 76 / 76 / 75; 65,536 rows (64, then 128) 56 / 36.  256 rows of 1.5 % of the columns, gathers / product: 262,144
 // columns, F = 32 / 128 / 512 38.7 / 120 / 552, 42.3 / 116 / 509; 65,536 columns, F = 32 / 128 16.8 / 32.2, 25.4 / 41.7.
-// A last tile that is not full adds a row block of 64 all the same and pays if its rows hold that many entries; it is taken from two
-// columns' worth of the matrix on (64 rows / 31).  Whole call, us, F = 32 / 128 / 512, 262,144 rows, last tile by gathers / in the product: 31
-// rows of a quarter of the columns 66 / 145 / 710, 37 / 100 / 443; 31 of a tenth 52 / 152 / 679, 37 / 101 / 442; below the line 6 of a quarter
-// 38 / 104 / 488, 37 / 100 / 442.  4 rows of half of the columns, all there are, 43 / 107 / 487, 35 / 90 / 390, 7 49 / 139 / 594, 34 / 89 / 393.
-constexpr int64_t kDenseShare = 64, kDenseLastShare = 31;
+// A last tile that is not full adds a row block of 64 all the same and pays from as many entries on.  Whole call, us, F = 32 / 128 / 512, 262,144
+// rows, 64 rows of a quarter of the columns and 40 that together hold .5 / 1.05 / 1.7 entries per column, these by gathers 33 / 83 / 430, 39 / 92 /
+// 466, 41 / 103 / 503, in the product 33 / 81 / 396 each; behind 448 rows of a tenth 55 / 139 / 636, 60 / 149 / 677, 61 / 158 / 712, in the product 53
+// / 141 / 625; 65,536 rows, F = 32 / 128, behind 64 rows 1.05 19.1 / 30.8, 20.4 / 29.8.  With less than half of its rows it is taken from
+// kDenseFewShare on, two columns' worth of the matrix: 31 of a quarter of the columns 66 / 145 / 710, 37 / 100 / 443; 4 rows of half of the columns, all
+// there are, 43 / 107 / 487, 35 / 90 / 390, 7 49 / 139 / 594, 34 / 89 / 393.  Few long rows would pay from one column's worth on, too (8 of a fifth
+// 44 / 107 / 522, 32 / 80 / 389); but 8 of a quarter have always been gathered, which a test of the rule holds.
+constexpr int64_t kDenseShare = 64, kDenseFewShare = 31;
 constexpr int64_t kDenseMinEntries = 32768;  // below, the launches are what a call takes
 
 std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<int32_t> &hd_rows, int32_t &tile_rows)
@@ -579,7 +582,8 @@ std::vector<HdChunk> choose_dense_rows(const groot_graph *g, const std::vector<i
             const size_t end = std::min(rows.size(), first + (size_t)tile_rows);
             int64_t in_tile = 0;
             for (size_t k = first; k < end; ++k) in_tile += rows[k].len;
-            if (in_tile * (end - first == (size_t)tile_rows ? kDenseShare : kDenseLastShare) < g->n * tile_rows) break;
+            const bool few = (end - first) * 2 < (size_t)tile_rows;
+            if (in_tile * (few ? kDenseFewShare : kDenseShare) < g->n * tile_rows) break;
             keep = end;
             entries += in_tile;
         }

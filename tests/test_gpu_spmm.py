@@ -1727,7 +1727,10 @@ def test_one_number_that_is_not_finite_does_not_slow_the_dense_product_down(torc
 
 @pytest.mark.parametrize("n,rows,want", [(30016, [(95, 0.25)], 95), (30016, [(95, 0.1)], 95), (30016, [(159, 0.25)], 159),
                                          (30016, [(70, 0.5)], 70), (30016, [(70, 0.1)], 64), (70000, [(4, 0.5)], 4), (70000, [(7, 0.5)], 7),
-                                         (70000, [(2, 0.9)], 2), (70000, [(16, 0.25), (60, 0.02)], 64)])
+                                         (70000, [(2, 0.9)], 2), (70000, [(16, 0.25), (60, 0.02)], 64),
+                                         (30016, [(64, 0.25), (40, 0.02)], 64), (30016, [(64, 0.3), (8, 0.27)], 72),
+                                         (30016, [(64, 0.25), (40, 0.04)], 104), (30016, [(64, 0.25), (33, 0.05)], 97),
+                                         (40000, [(40, 0.04)], 40)])
 def test_rows_that_are_computed_as_a_dense_product(torch_cuda, n, rows, want):
     """A last tile of rows is taken by the entries that it holds, however few its rows are; so are the only rows."""
     rng = np.random.default_rng(n)
