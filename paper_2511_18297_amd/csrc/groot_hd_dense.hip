@@ -13,6 +13,8 @@
 // chain.  Error of the dense rows in the 2-norm, 1e-8, gathers / fp32 instructions / here (131,072 rows, 448 dense, F = 128; 65,536, 64, 512):
 // U(-1, 1) 15.7 / 14.7 / 3.6, 19.3 / 16.4 / 4.1; exp(4 N) 13.7 / 10.9 / 9.0, 11.7 / 10.0 / 10.4; 2^U(-40, 0) 9.7 / 3.9 / 3.5, 12.3 / 4.6 / 4.1.  (In
 // chains of 2,048 columns exp(4 N) 21.8 and 32.7.)  In 20,011 rows, one step or two per workgroup, exp(4 N) 9.5 / 7.9 / 11.1.
+// Chains of two (five other seeds: 7.1 to 9.3 there instead of 7.1 to 10.8, where the gathers have 9.4 to 13.3; the same elsewhere) take 224 us a
+// call on the polarized graph instead of 177.
 // v_mfma_f32_16x16x4_f32 on X as it is, one bit expanded per operand, does 16 rows x 16 features x 32 columns in 256 cycles, the
 // three pieces take 48.
 //
@@ -21,9 +23,9 @@
 // lane are the eight k of an operand, so nothing is transposed) and puts the operands to LDS, from where the wavefronts of a
 // feature half multiply them with the bits of their rows.  One barrier per 128 columns, loads stay in flight across it.
 //
-// Polarized graph, F = 128, 448 rows: 86 us (24 with 16 rows or fewer, which is X at 5.5 TB/s), 1.04 PFLOP/s of the pieces' products.  Counters: matrix units busy 43 % of the cycles (of 2.4 GHz),
-// vector instructions issued in 31 %, three beside each matrix instruction (bits to operands, cut, sums), no bank conflicts.  Neither
-// is at its end: two wavefronts per SIMD, all that the accumulators leave room for, wait for each other at every barrier and for operands.
+// Polarized graph, F = 128, 448 rows: 86 to 89 us (24 with 16 rows or fewer, which is X at 5.5 TB/s), 1.02 to 1.05 PFLOP/s of the pieces'
+// products.  Counters: matrix units busy in 42 % of the cycles (of 2.3 GHz), vector instructions issued in 31 %, three beside each matrix
+// instruction (bits to operands, cut, sums), no bank conflicts.  Neither is at its end: two wavefronts per SIMD, all that the accumulators leave room for, wait for each other at every barrier and for operands.
 // Operands of the next unit read ahead, where registers allow it, make no difference.
 //
 // 0 x infinity is not 0, and numbers from 2^104 on are too large for the scale of the cut, which checks itself.  Where 128 columns hold

@@ -18,7 +18,7 @@
 //                writing its owned columns first and its boundary columns after
 // Seven launches where long rows need no walk.  The parts are small, so launches and the latencies inside them are most of the
 // time: with 14 launches and the int32 numbering a part of 10 thousand rows (109-bit multiplier, 9 parts) took 66 us of kernels,
-// now 32, one of a million rows (512-bit x 4, 8 parts) 191, now 98.
+// now 30, one of a million rows (512-bit x 4, 8 parts) 191, now 95.
 #include "groot_device.h"
 
 namespace groot {

@@ -183,7 +183,8 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW /
 
     // ---- the row pointers of the first tiles, then the weights, then the first tile's columns are on their way, and the weights
     //      are cut while those arrive: three latencies before the first gather is issued instead of six.  On small graphs, one
-    //      tile per wavefront, that is most of the launch (kernel on 32 thousand rows, 32 -> 32: 7.8 us, now 7.1; call on 157 thousand, 64 -> 64: 33.5, now 32.0).
+    //      tile per wavefront, that is most of the launch (kernel on 32 thousand rows, 32 -> 32: 7.8 us, now 7.1; call on 157 thousand, 64 -> 64:
+    //      33.5, now 32.0; a training step on 32 thousand rows is bound by the host and takes what it took).
     rp_a = load_rp(t_first);
     const int64_t rp_second = load_rp(t_first + stride);
     rp_b = load_rp(t_first + 2 * stride);
