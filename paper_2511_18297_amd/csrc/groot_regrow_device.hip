@@ -27,7 +27,9 @@ constexpr int kRgWords = 4;                                        // words of a
 constexpr int kRgBlockWords = kBlock * kRgWords;                   // ... per workgroup: 32,768 nodes
 constexpr int kRgLenBlock = 1024;                                  // rows per workgroup of the length kernels
 constexpr int kRgFusedSums = 4096;                                 // up to so many of them every workgroup adds up those before it
-constexpr int kRgFusedCounts = 1024;                               // ... so many workgroups of words, 33 M nodes, of which all would read them
+// ... so many workgroups of words, 134 M nodes.  Every one adding up those before it is quadratic; rg_place without / with the scan and its time, us:
+// 42 M nodes 14.2 / 16.5, 134 M 19.4 / 20.1 (and the launch); at 2^31 nodes 2 x 10^9 loads, or a scan.
+constexpr int kRgFusedCounts = 4096;
 constexpr int kRgMark = 8;                                         // entries in flight per thread of rg_mark_slices
 constexpr int kRgShort = 16;                                       // longest row that one lane walks alone
 constexpr int kRgUnroll = 4;                                       // 64-entry chunks of a long row in flight

@@ -129,28 +129,36 @@ def test_more_copies_than_a_grid_has_rows_and_more_rows_than_one_scan_step(torch
         assert np.array_equal(got["global_id"], np.arange(view["n"]))
 
 
-def test_node_sets_whose_counts_take_a_scan_of_their_own(torch_cuda):
-    """42 M nodes, 1,280 workgroups of words: the whole graph as one part, by the built-in rule and by the caller's, and a part whose boundary
-    lies in other workgroups, against the sets computed here."""
+@pytest.mark.parametrize("n", [134217728 - 65536, 134217728 + 2])
+def test_node_sets_whose_counts_take_a_scan_of_their_own(torch_cuda, n):
+    """Up to 4,096 workgroups of words, and one more: the second half of a graph of self-loops and, for every 4,099th node of either half, an edge
+    to the node half of the graph away, by the built-in rule and by the caller's, which are the same sets."""
     torch = torch_cuda
-    aig = wl.csa_multiplier_aig(1024)
-    g = G.groot_graph_build(aig.type, aig.fanin0, aig.fanin1, 5)
-    view, plan = G.groot_graph_view(g), _resident_plan(g)
-    n = view["n"]
+    half = n // 2
+    lower = np.arange(17, half, 4099)                        # the boundary of the second half
+    both = np.concatenate([lower, lower + half])
+    length = np.ones(n, np.int64)
+    length[both] = 2
+    rowptr = np.concatenate([[0], np.cumsum(length)])
+    col = np.repeat(np.arange(n, dtype=np.int32), length)
+    col[rowptr[lower] + 1] = lower + half
+    col[rowptr[lower + half]] = lower
+    val = np.repeat(np.float32(1) / length.astype(np.float32), length)
+    plan = _resident_plan(G.groot_graph_from_csr(rowptr, col, val))
     part_of = torch.zeros(n, dtype=torch.int32, device="cuda")
+    part_of[half:] = 1
+    ids = np.concatenate([np.arange(half, n), lower])
+    # a row of the second half names its own node first, then the boundary one; a boundary row its owned neighbour, then itself
+    local_length = np.concatenate([length[half:], np.full(lower.size, 2)])
+    local_rowptr = np.concatenate([[0], np.cumsum(local_length)])
+    local_col = np.repeat(np.arange(ids.size), local_length)
+    local_col[local_rowptr[lower] + 1] = half + np.arange(lower.size)
+    local_col[local_rowptr[half:half + lower.size]] = lower
     for rule in (None, part_of):
-        print("device regrow: the whole of 1,024 bits x 5", flush=True)
-        got = G.groot_dev_part_download(G.groot_partition_regrow_device(plan, 1, 0, rule))
-        assert np.array_equal(got["global_id"], np.arange(n))
-        assert np.array_equal(got["rowptr"], view["rowptr"]) and np.array_equal(got["col"], view["col"])
-    part_of[n // 2 - 1000:] = 1                              # in the middle of the third copy
-    owned = np.arange(n // 2 - 1000, n)
-    of_owned = view["col"][view["rowptr"][owned[0]]:]
-    halo = np.unique(of_owned[of_owned < owned[0]])
-    print("device regrow: half of 1,024 bits x 5", flush=True)
-    got = G.groot_dev_part_download(G.groot_partition_regrow_device(plan, 2, 1, part_of))
-    assert halo.size and np.array_equal(got["global_id"], np.concatenate([owned, halo]))
-    assert np.array_equal(got["rowptr"][:owned.size + 1], view["rowptr"][owned[0]:] - view["rowptr"][owned[0]])
+        print("device regrow: half of", n, flush=True)
+        got = G.groot_dev_part_download(G.groot_partition_regrow_device(plan, 2, 1, rule))
+        assert np.array_equal(got["global_id"], ids)
+        assert np.array_equal(got["rowptr"], local_rowptr) and np.array_equal(got["col"], local_col)
 
 
 @pytest.mark.parametrize("P", [1, 2, 7])
